@@ -111,7 +111,11 @@ enum {
  *            importance step divides the window rows of every 256-key slice over
  *            several workgroups that leave partial column sums there, added in a
  *            fixed order afterwards; with less (or NULL) each slice is summed by
- *            one workgroup.  Both forms are deterministic; they differ from each
+ *            one workgroup.  Prompts whose query tiles leave the GPU unevenly
+ *            busy also take the key-split attention form there: the keys of a
+ *            query tile are divided over several workgroups that leave 32-bit
+ *            partial rows, combined by a second kernel.  All forms are
+ *            deterministic; they differ from each
  *            other in the order of the fp32 additions.  The contents are
  *            scratch before and after the call; concurrent calls need separate
  *            workspaces.
@@ -136,7 +140,10 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * remaining chunk catches up afterwards).  Same formulas as above with
  * delta_b = Nk_b - Nq_b >= 0.  Every chunk query is a window query
  * (desc->window is ignored) when importance is non-NULL.
- * workspace: as for pdd_prefill_attn, with one more form.
+ * workspace: as for pdd_prefill_attn, with one more form.  (The key-split
+ * attention form, which few or short chunks behind a long prefix take, packs the
+ * query heads of a group into its tiles; the importance then comes from the
+ * separate kernel.)
  * Given pdd_workspace_bytes(desc, PDD_CALL_PREFILL_ATTN_CHUNKED) bytes (one
  * float per query head, tile of 128 or 256 queries and key), the importance is
  * taken inside the attention kernel: once a workgroup knows the log-sum-exp of
@@ -159,10 +166,10 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments without the workspace, same results bit for bit as
  * pdd_prefill_attn_chunked called with a workspace of pdd_workspace_bytes(desc,
- * PDD_CALL_PREFILL_ATTN_CHUNKED) bytes.  The scratch is a fixed 16 MiB array
+ * PDD_CALL_PREFILL_ATTN_CHUNKED) bytes, with or without importance.  The scratch is a fixed 16 MiB array
  * inside the library's device image (one copy per GPU, held until the process
- * ends); the call allocates and frees nothing.  A shape whose scratch would
- * exceed 16 MiB is rejected with PDD_ERR_WORKSPACE and nothing is enqueued.
+ * ends); the call allocates and frees nothing.  A shape whose importance scratch
+ * in the plain attention form would exceed 16 MiB is rejected with PDD_ERR_WORKSPACE and nothing is enqueued.
  * All calls on one GPU share that array: calls that overlap in time on the same
  * GPU (different streams or threads) race on it and must be serialised by the
  * caller.  Nothing in it has to be cleared between calls (every partial sum a
@@ -354,9 +361,12 @@ pdd_status pdd_pack_mask(const uint8_t *mask, int32_t n_rows, int32_t batch, int
 
 /*
  * Bytes of DEVICE scratch `which_call` can use for this descriptor (0 when it
- * has no use for any).  At most 8 * n_kv_heads * total_k * 4 bytes, for the
- * chunked call at most ceil(max_seqlen_q / 128) * n_q_heads *
- * total_k * 4 bytes and 256 MiB; never grows with Nq*Nk: the attention weights
+ * has no use for any).  At most the larger of 8 * n_kv_heads * total_k * 4 bytes
+ * (partial importance sums), for the chunked call ceil(max_seqlen_q / 128) *
+ * n_q_heads * total_k * 4 bytes up to 256 MiB (the in-kernel importance), and
+ * for the key-split attention form ceil(max_seqlen_k / 512) * total_q *
+ * n_q_heads * (head_dim + 1) * 4 bytes up to 256 MiB (16 MiB in the chunked
+ * call): the attention weights
  * are not materialised (Section 3.2 "Preliminaries").  The figure depends on
  * the descriptor, on PDD_OPT_ATTN_WAVES and on the number of compute units of
  * the current device only.  A call that is given less runs with a form that

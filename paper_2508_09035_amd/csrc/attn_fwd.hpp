@@ -20,6 +20,15 @@
 //   operand (the contraction index "key" may be permuted freely as long as the
 //   V^T fragments are read with the same permutation).
 //
+// Key-split form (SPLIT)
+//   For launches that would leave most of the chip or of their tiles idle (few tokens behind a
+//   long prefix, long prompts with few heads): a tile's 128 rows are (token, head of the KV group)
+//   pairs, so one read of K and V serves the whole group, and a workgroup walks only `split_tiles`
+//   key tiles; attn_combine_kernel joins the pieces.  V tiles are double instead of triple
+//   buffered, so that two workgroups share a compute unit's LDS.  Bound by HBM with few rows
+//   (8 sequences x 1 token, 97 MB of K and V: 102 -> 20 us, 4.9 TB/s of a copy's 5.1), by the
+//   matrix pipe with many (256 tokens behind 8192 keys, 32/8 heads: 122 -> 42 us, 0.83 PFLOP/s).
+//
 // Data movement and instruction schedule
 //   * K and V tiles (64 keys x 2 D bytes) go from HBM/L2 straight into LDS with
 //     buffer_load ... lds (no staging registers, no ds_write); rows past the
@@ -66,7 +75,20 @@ struct AttnParams {
     // [G * n_qtiles][Hkv][total_k], slice hg * n_qtiles + t written by the workgroup of query
     // head g * G + hg and query tile t (every key of its sequence, zeros included).
     float *imp_part;
+    // Only read by kernels that split the keys (see SPLIT below) and by attn_combine_kernel: key
+    // tiles per workgroup and the most splits of a
+    // sequence, partial outputs [split][total_q][Hq][D] (normalised within their
+    // split), their log2-sum-exp2 [split][total_q][Hq], and ceil(2^32 / G) (0 where G = 1).
+    int32_t split_tiles, n_split;
+    uint32_t g_magic;
+    float *part_o, *part_l;
 };
+
+// x / G for the packed rows of the key-split form, 0 <= x < 2^32 / G
+__device__ __forceinline__ int div_group(int x, uint32_t magic)
+{
+    return magic ? (int)__umulhi((uint32_t)x, magic) : x;
+}
 
 constexpr int kBN = 64;  // keys per LDS tile
 
@@ -96,10 +118,12 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 constexpr int kAttnBufs = 3;             // K and V tiles are triple buffered
 constexpr int kSweepBufs = 6;            // importance sweep: K tiles rotate through six buffers,
 constexpr int kSweepAhead = 5;           //   tile t+5 is requested while tile t is summed
+constexpr int kSplitVBufs = 2;           // key-split form: V tiles are double buffered, two workgroups per compute unit
 template <int D>
 struct AttnSmem {
     static constexpr int TILE = kBN * D * 2;                       // one K or V tile in LDS, bytes
     static constexpr int BYTES = (2 * kAttnBufs + 1) * TILE;     // + the fourth Q slot of an 8-wave workgroup
+    static constexpr int SPLIT_BYTES = (kAttnBufs + kSplitVBufs) * TILE;
     static constexpr int SWEEP_BYTES = (kSweepBufs + 1) * TILE;    // + exchange area
 };
 constexpr float kLazyLog2 = 8.0f;        // a row's softmax reference may lag its running max by a factor 2^8
@@ -154,7 +178,7 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(uint32_t lo, uint32_t hi)
     return __builtin_bit_cast(bf16x8, c);
 }
 
-template <int D, int NWAVES, bool IMP = false>
+template <int D, int NWAVES, bool IMP = false, bool SPLIT = false>
 __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fwd_kernel(const AttnParams p)
 {
@@ -165,12 +189,13 @@ void attn_fwd_kernel(const AttnParams p)
     constexpr int RPI = 1024 / ROWB;            // rows one buffer_load ... lds instruction fills
     constexpr int kTileBytes = AttnSmem<D>::TILE;
     constexpr int BM = NWAVES * 32;
+    constexpr int VBUFS = SPLIT ? kSplitVBufs : kAttnBufs;
     constexpr int NKK = D / 16, NDB = D / 32;
     constexpr int NLD = kBN / RPI / NWAVES;     // buffer_load..lds instructions per tile per wave
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem_attn[];
     uint8_t *Ks = smem_attn;                               // [3][kTileBytes], tile t in buffer t % 3
-    uint8_t *Vs = smem_attn + kAttnBufs * kTileBytes;   // [3][kTileBytes]
+    uint8_t *Vs = smem_attn + kAttnBufs * kTileBytes;   // [VBUFS][kTileBytes], tile t in buffer t % VBUFS
 
     // Workgroups go to the 8 XCDs round robin, each XCD with an L2 of its own.  KV head fastest:
     // where the number of KV heads divides 8 or is a multiple of 8, all workgroups that share the
@@ -178,14 +203,25 @@ void attn_fwd_kernel(const AttnParams p)
     // heads of the group, the sequence, and the query tiles from the last (longest) down.
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
-    const int hg = bid % p.G;   bid /= p.G;
-    const int b = bid % p.B;    bid /= p.B;
-    const int t = p.n_qtiles - 1 - bid;
+    // The key-split form has no query head per workgroup (a tile holds rows of the whole group);
+    // its query tiles come right after one another, because they read the same keys.
+    const int hg = SPLIT ? 0 : bid % p.G;
+    int t, b, split = 0;
+    if constexpr (SPLIT) {
+        t = bid % p.n_qtiles;   bid /= p.n_qtiles;
+        b = bid % p.B;          split = bid / p.B;
+    } else {
+        bid /= p.G;
+        b = bid % p.B;
+        t = p.n_qtiles - 1 - bid / p.B;
+    }
     const int h = g * p.G + hg;
 
     const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
     const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
-    const int nq = qe - qs, nk = ke - ks;
+    const int nk = ke - ks;
+    const int nq = SPLIT ? (qe - qs) * p.G : qe - qs;    // rows: (token, head of the group) pairs, token major, or tokens
+    const auto token_of = [&](int row) { return SPLIT ? div_group(row, p.g_magic) : row; };
     // The sequence's query tiles are aligned to its END: tile t of n_qt holds rows m0 .. m0 + BM - 1
     // with m0 = nq - (n_qt - t) BM, and where nq is not a multiple of BM the rows below 0, which
     // do not exist, fall into tile 0, the workgroup with the fewest keys (aligned to the start,
@@ -201,7 +237,7 @@ void attn_fwd_kernel(const AttnParams p)
             for (int j = tid; j < nk; j += NWAVES * 64) part_row[j] = 0.f;
         return;
     }
-    const int delta = nk - nq;
+    const int delta = nk - (qe - qs);
 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -210,18 +246,29 @@ void attn_fwd_kernel(const AttnParams p)
     const int wave_q0 = m0 + 32 * wave;
     const int qrow = wave_q0 + n;
     const int qrow_c = max(qrow, 0);               // a row that does not exist computes like row 0; nothing of it is stored
-    const int lim = qrow_c + delta;
-    const int wave_lim_max = max(wave_q0 + 31, 0) + delta;
-    const int wave_lim_min = max(wave_q0, 0) + delta;
-    const int kend = min(nk, m0 + BM + delta);
-    const int n_tiles = kend > 0 ? (kend + kBN - 1) / kBN : 0;
+    const int kend = min(nk, token_of(max(m0 + BM - 1, 0)) + 1 + delta);
+    int n_tiles = kend > 0 ? (kend + kBN - 1) / kBN : 0;
+    // Key-split form: everything below works on the keys k0 .. k0 + nk_w - 1 of this workgroup's
+    // tiles as if they were the whole sequence; a row sees them up to its own limit or up to the
+    // last of them, and a row that sees none keeps an empty state (log-sum-exp -inf, output 0).
+    int k0 = 0, nk_w = nk, cap = 0x7fffffff;
+    if constexpr (SPLIT) {
+        if (split * p.split_tiles >= n_tiles) return;
+        k0 = split * p.split_tiles * kBN;
+        n_tiles = min(p.split_tiles, n_tiles - split * p.split_tiles);
+        nk_w = min(nk - k0, n_tiles * kBN);
+        cap = nk_w - 1;
+    }
+    const int lim = min(token_of(qrow_c) + delta - k0, cap);
+    const int wave_lim_max = min(token_of(max(wave_q0 + 31, 0)) + delta - k0, cap);
+    const int wave_lim_min = min(token_of(max(wave_q0, 0)) + delta - k0, cap);
 
     // ---- buffer resources over this sequence's K / V rows of KV head g
-    const uint16_t *kbase = p.k + (int64_t)ks * p.k_st + (int64_t)g * p.k_sh;
-    const uint16_t *vbase = p.v + (int64_t)ks * p.v_st + (int64_t)g * p.v_sh;
+    const uint16_t *kbase = p.k + (int64_t)(ks + k0) * p.k_st + (int64_t)g * p.k_sh;
+    const uint16_t *vbase = p.v + (int64_t)(ks + k0) * p.v_st + (int64_t)g * p.v_sh;
     const uint32_t k_row_bytes = (uint32_t)p.k_st * 2u, v_row_bytes = (uint32_t)p.v_st * 2u;
-    const uint32_t k_span = nk > 0 ? (uint32_t)(nk - 1) * k_row_bytes + (uint32_t)ROWB : 0u;
-    const uint32_t v_span = nk > 0 ? (uint32_t)(nk - 1) * v_row_bytes + (uint32_t)ROWB : 0u;
+    const uint32_t k_span = nk_w > 0 ? (uint32_t)(nk_w - 1) * k_row_bytes + (uint32_t)ROWB : 0u;
+    const uint32_t v_span = nk_w > 0 ? (uint32_t)(nk_w - 1) * v_row_bytes + (uint32_t)ROWB : 0u;
     const uint32_t ks_lds = lds_addr_of(Ks), vs_lds = lds_addr_of(Vs);
 
     // DMA lane mapping: instruction ci of wave w fills the RPI LDS rows RPI q .. RPI q + RPI - 1,
@@ -293,17 +340,25 @@ void attn_fwd_kernel(const AttnParams p)
     bf16x8 qf[NKK];
     auto issue_q = [&]() {
         const int q_first = max(wave_q0, 0);        // the wave's first existing row
-        const uint16_t *qbase = p.q + (int64_t)(qs + q_first) * p.q_st + (int64_t)h * p.q_sh;
+        const int i_first = token_of(q_first);
+        const uint16_t *qbase = p.q + (int64_t)(qs + i_first) * p.q_st + (int64_t)h * p.q_sh;
         const uint32_t q_row_bytes = (uint32_t)p.q_st * 2u;
         const int q_rows = wave_q0 + 32 - q_first;
-        const uint32_t q_span = q_rows > 0 ? (uint32_t)(q_rows - 1) * q_row_bytes + (uint32_t)ROWB : 0u;
+        uint32_t q_span = q_rows > 0 ? (uint32_t)(token_of(q_first + q_rows - 1) - i_first) * q_row_bytes + (uint32_t)ROWB : 0u;
+        if constexpr (SPLIT) q_span += (uint32_t)(p.G - 1) * (uint32_t)p.q_sh * 2u;
         const i32x4 rs = make_rsrc(qbase, q_span);
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) {
             const int r = RPI * i + lane / CH;
             const int c = (lane % CH) ^ swz_row<D>(r);
-            const int r_rel = max(wave_q0 + r - q_first, 0);
-            dma16_to_lds(rs, ks_lds + q_lds_off + 1024 * i, (uint32_t)r_rel * q_row_bytes + (uint32_t)c * 16u);
+            uint32_t r_off;                         // of the row from the first one
+            if constexpr (SPLIT) {
+                const int rr = max(wave_q0 + r, 0), ri = token_of(rr);
+                r_off = (uint32_t)(ri - i_first) * q_row_bytes + (uint32_t)(rr - ri * p.G) * (uint32_t)p.q_sh * 2u;
+            } else {
+                r_off = (uint32_t)max(wave_q0 + r - q_first, 0) * q_row_bytes;
+            }
+            dma16_to_lds(rs, ks_lds + q_lds_off + 1024 * i, r_off + (uint32_t)c * 16u);
         }
     };
 
@@ -387,7 +442,7 @@ void attn_fwd_kernel(const AttnParams p)
             __syncthreads();
             __syncthreads();
             for (int it = 0; it < n_tiles; ++it) {
-                if (it + 1 < n_tiles) issue_v(it + 1, (it + 1) % 3);
+                if (it + 1 < n_tiles) issue_v(it + 1, (it + 1) % VBUFS);
                 if (it + 2 < n_tiles) issue_k(it + 2, (it + 2) % 3);
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();
@@ -424,7 +479,7 @@ void attn_fwd_kernel(const AttnParams p)
     // ---- hot tiles: those that no wave of the workgroup has to mask (fully visible to the
     // workgroup's first existing query: 64 (t+1) - 1 <= max(m0, 0) + delta) and that have a
     // successor tile.
-    const int first_lim = max(m0, 0) + delta;
+    const int first_lim = min(token_of(max(m0, 0)) + delta - k0, cap);
     const int n_hot = max(0, min((first_lim + 1) / kBN, n_tiles - 1));   // tiles 0 .. n_hot-1
 
     // The block `cur` arrives in the log2 domain (see above): the scale-and-shift and the row max
@@ -540,11 +595,11 @@ void attn_fwd_kernel(const AttnParams p)
     };
     auto hot_tile = [&](auto par_c, const int it) {
         constexpr int PAR = decltype(par_c)::value;
-        constexpr int P1 = (PAR + 1) % 3, P2 = (PAR + 2) % 3;
-        issue_v(it + 1, P1);
+        constexpr int P1 = (PAR + 1) % 3, P2 = (PAR + 2) % 3, V0 = PAR % VBUFS, V1 = (PAR + 1) % VBUFS;
+        issue_v(it + 1, V1);
         if (it + 2 < n_tiles) issue_k(it + 2, P2);
-        pipe_half(std::false_type{}, sA, sB, P1 * kTileBytes, PAR * kTileBytes, 0, false);
-        pipe_half(std::false_type{}, sB, sA, P1 * kTileBytes + 32 * ROWB, PAR * kTileBytes + 32 * ROWB, 0, false);
+        pipe_half(std::false_type{}, sA, sB, P1 * kTileBytes, V0 * kTileBytes, 0, false);
+        pipe_half(std::false_type{}, sB, sA, P1 * kTileBytes + 32 * ROWB, V0 * kTileBytes + 32 * ROWB, 0, false);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     };
@@ -556,14 +611,14 @@ void attn_fwd_kernel(const AttnParams p)
     const int lim4 = lim - 4 * hh;
     auto masked_tile = [&](auto par_c, const int it) {
         constexpr int PAR = decltype(par_c)::value;
-        constexpr int P1 = (PAR + 1) % 3, P2 = (PAR + 2) % 3;
-        if (it + 1 < n_tiles) issue_v(it + 1, P1);
+        constexpr int P1 = (PAR + 1) % 3, P2 = (PAR + 2) % 3, V0 = PAR % VBUFS, V1 = (PAR + 1) % VBUFS;
+        if (it + 1 < n_tiles) issue_v(it + 1, V1);
         if (it + 2 < n_tiles) issue_k(it + 2, P2);
         if (kBN * it <= wave_lim_max) {
             const int l1 = lim4 - (kBN * it + 32);
             const int w1 = wave_lim_min - (kBN * it + 32);      // the same for the wave's first row
-            pipe_half(std::true_type{}, sA, sB, P1 * kTileBytes, PAR * kTileBytes, l1, w1 < 31);
-            pipe_half(std::true_type{}, sB, sA, P1 * kTileBytes + 32 * ROWB, PAR * kTileBytes + 32 * ROWB, l1 - 32, w1 < 63);
+            pipe_half(std::true_type{}, sA, sB, P1 * kTileBytes, V0 * kTileBytes, l1, w1 < 31);
+            pipe_half(std::true_type{}, sB, sA, P1 * kTileBytes + 32 * ROWB, V0 * kTileBytes + 32 * ROWB, l1 - 32, w1 < 63);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -583,23 +638,68 @@ void attn_fwd_kernel(const AttnParams p)
     }
     // Plain tiles: the two blocks a tile computes ahead (its own second and the next tile's
     // first) are visible in full to every row of the workgroup, i.e. all hot tiles but the last.
-    const int n_plain = max(0, n_hot - 1) / 3 * 3;   // whole rounds of the three LDS buffers
-    for (; it < n_plain; it += 3) {
+    // whole rounds of the LDS buffers (three; six where K has three and V two)
+    constexpr int ROUND = VBUFS == 3 ? 3 : 6;
+    const int n_plain = max(0, n_hot - 1) / ROUND * ROUND;
+    for (; it < n_plain; it += ROUND) {
         hot_tile(std::integral_constant<int, 0>{}, it);
         hot_tile(std::integral_constant<int, 1>{}, it + 1);
         hot_tile(std::integral_constant<int, 2>{}, it + 2);
+        if constexpr (ROUND == 6) {
+            hot_tile(std::integral_constant<int, 3>{}, it + 3);
+            hot_tile(std::integral_constant<int, 4>{}, it + 4);
+            hot_tile(std::integral_constant<int, 5>{}, it + 5);
+        }
     }
     // ---- the last hot tiles and the diagonal region
-    for (; it < n_tiles; it += 3) {
+    for (; it < n_tiles; it += ROUND) {
         masked_tile(std::integral_constant<int, 0>{}, it);
         if (it + 1 < n_tiles) masked_tile(std::integral_constant<int, 1>{}, it + 1);
         if (it + 2 < n_tiles) masked_tile(std::integral_constant<int, 2>{}, it + 2);
+        if constexpr (ROUND == 6) {
+            if (it + 3 < n_tiles) masked_tile(std::integral_constant<int, 3>{}, it + 3);
+            if (it + 4 < n_tiles) masked_tile(std::integral_constant<int, 4>{}, it + 4);
+            if (it + 5 < n_tiles) masked_tile(std::integral_constant<int, 5>{}, it + 5);
+        }
     }
 
     // ---- epilogue
     const float l_run = (l_part[0] + l_part[1]) + (l_part[2] + l_part[3]);
     const float l_tot = l_run + xchg_half(l_run);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    // Key-split form: the rows leave as 32-bit values, normalised within their split, with the
+    // split's log2-sum-exp2, whole rows at a time through LDS as below.
+    if constexpr (SPLIT) {
+        constexpr int FCH = D / 4, RPF = 64 / FCH;      // 16-byte chunks per row, rows per store instruction
+        uint8_t *ost = smem_attn + wave * (32 * 2 * ROWB);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int bq = 0; bq < 4; ++bq) {
+                f32x4 x;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = oacc[db][4 * bq + r] * inv;
+                *(f32x4 *)(ost + n * 2 * ROWB + (((8 * db + 2 * bq + hh) ^ (n & (FCH - 1))) * 16)) = x;
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slice is read by other lanes of the wave
+        const int sr = lane / FCH, sc = lane % FCH;
+        const int64_t row0 = (int64_t)split * p.total_q + qs;
+#pragma unroll
+        for (int i = 0; i < 32 / RPF; ++i) {
+            const int row = RPF * i + sr, r_abs = wave_q0 + row;
+            const f32x4 x = *(const f32x4 *)(ost + row * 2 * ROWB + ((sc ^ (row & (FCH - 1))) * 16));
+            if (r_abs >= 0) {
+                const int ri = token_of(r_abs);
+                *(f32x4 *)(p.part_o + ((row0 + ri) * p.Hq + h + (r_abs - ri * p.G)) * D + 4 * sc) = x;
+            }
+        }
+        if (qrow >= 0 && hh == 0) {
+            const int ri = token_of(qrow);
+            p.part_l[(row0 + ri) * p.Hq + h + (qrow - ri * p.G)] =
+                l_tot > 0.f ? __builtin_amdgcn_logf(l_tot) - ref : -INFINITY;
+        }
+        return;
+    }
     // O leaves through LDS (the K and V buffers are free now): each wave lays its 32 rows out row
     // by row in a slice of its own, 16-byte chunk c of row r at position c ^ (r mod CH), and then
     // stores RPI whole rows per instruction, 16 bytes per lane.  (Stored straight from the
@@ -804,6 +904,77 @@ void attn_fwd_kernel(const AttnParams p)
     }
 #else
     (void)p;
+#endif
+}
+
+// Key-split form, second kernel: output and log-sum-exp of every (token, query head) from the
+// partial rows of its splits:
+//   lse2 = log2 sum_s 2^lse2_s,   o = sum_s 2^(lse2_s - lse2) o_s.
+// One wave per row: a lane fetches the log2-sum-exp2 of one split (all of them are in flight at
+// once, 64 at a time) and the wave reads 256 / D partial rows at a time, 16 bytes per lane, four
+// steps in flight.  Bound by latency with few rows (4 us), by HBM with many.
+template <int D>
+__global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p, const int rows_per_wg)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int LPR = D / 4, SPS = 64 / LPR;        // lanes per partial row, splits per step
+    const int lane = threadIdx.x & 63;
+    const int64_t x = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // token * Hq + head
+    if (x >= (int64_t)p.total_q * p.Hq) return;
+    const int tok = (int)(x / p.Hq), h = (int)(x - (int64_t)tok * p.Hq);
+    // the sequence: last b with cu_q[b] <= tok
+    int b = 0, z = p.B - 1;
+    while (b < z) {
+        const int mid = (b + z + 1) >> 1;
+        if (p.cu_q[mid] <= tok) b = mid; else z = mid - 1;
+    }
+    const int qs = p.cu_q[b], qe = min(p.cu_q[b + 1], p.total_q);
+    if (tok < qs || tok >= qe) return;
+    const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
+    const int nk = ke - ks, delta = nk - (qe - qs);
+    // last row of the row's tile, keys that tile reaches, splits that hold them
+    const int n_rows = (qe - qs) * p.G, r = (tok - qs) * p.G + h % p.G;
+    const int last = n_rows - 1 - (n_rows - 1 - r) / rows_per_wg * rows_per_wg;
+    const int kend = min(nk, last / p.G + 1 + delta);
+    const int n_tiles = kend > 0 ? (kend + kBN - 1) / kBN : 0;
+    const int n_split = min((n_tiles + p.split_tiles - 1) / p.split_tiles, p.n_split);
+
+    const int64_t stride = (int64_t)p.total_q * p.Hq;
+    const float *pl = p.part_l + x;
+    float top = -INFINITY;
+    for (int s = lane; s < n_split; s += 64) top = fmaxf(top, pl[s * stride]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off, 64));
+    const float base = top > -INFINITY ? top : 0.f;   // a row that sees no key: every weight is 0
+    const int sub = lane / LPR, c = lane % LPR;
+    const float *po = p.part_o + (sub * stride + x) * D + 4 * c;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float sum = 0.f;
+    for (int s0 = 0; s0 < n_split; s0 += 64) {
+        const float w = s0 + lane < n_split ? fast_exp2(pl[(s0 + lane) * stride] - base) : 0.f;
+        sum += w;
+        const int m = min(64, n_split - s0);
+#pragma unroll 4
+        for (int s = 0; s < m; s += SPS) {
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+            if (s + sub < m) o = *(const f32x4 *)(po + (s0 + s) * stride * D);
+            acc += __shfl(w, s + sub, 64) * o;        // s + sub <= 63; weight 0 past the last split
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+#pragma unroll
+    for (int off = 32; off >= LPR; off >>= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
+    if (sum > 0.f) acc *= 1.f / sum;
+    if (lane < LPR)
+        *(bf16x4 *)(p.o + (int64_t)tok * p.o_st + (int64_t)h * p.o_sh + 4 * c) = __builtin_convertvector(acc, bf16x4);
+    if (lane == 0)
+        p.lse[(int64_t)h * p.total_q + tok] =
+            sum > 0.f ? (top + __builtin_amdgcn_logf(sum)) * 0.6931471805599453f : -INFINITY;
+#else
+    (void)p; (void)rows_per_wg;
 #endif
 }
 

@@ -147,6 +147,23 @@ pdd_status launch_attn_t(const pdd::AttnParams &p, int64_t blocks, hipStream_t s
 
 int compute_units();
 
+constexpr int kSplitRows = 128;          // packed (token, head) rows per workgroup of the key-split form
+constexpr size_t kSplitWorkspaceMax = (size_t)256 << 20;
+struct SplitPlan { int tiles, n_split; size_t bytes; };        // tiles == 0: the form does not apply
+
+template <int D>
+pdd_status launch_attn_split(const pdd::AttnParams &p, int64_t blocks, hipStream_t st)
+{
+    const pdd_status s = launch_attn_kernel(pdd::attn_fwd_kernel<D, kSplitRows / 32, false, true>,
+                                            pdd::AttnSmem<D>::SPLIT_BYTES, 2 * kSplitRows, p, blocks, st);
+    if (s) return s;
+    const int64_t n = ((int64_t)p.total_q * p.Hq + 3) / 4;       // one wave per (token, head)
+    hipLaunchKernelGGL(pdd::attn_combine_kernel<D>, dim3((unsigned)n), dim3(256), 0, st, p, kSplitRows);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(PDD_ERR_HIP, "attention combine launch: %s", hipGetErrorString(e));
+    return PDD_OK;
+}
+
 // Queries per attention workgroup.  8 waves (256 queries, one workgroup per compute unit) halve the
 // K/V traffic into LDS per flop and win wherever the compute units stay evenly busy; 4 waves (128
 // queries: twice as many workgroups of half the rows, which spread more evenly; at head_dim 64
@@ -192,14 +209,96 @@ void launch_importance_reduce(const float *part, float *imp, int64_t n, int n_sp
                        part, imp, n, n_split);
 }
 
+size_t importance_workspace(const pdd_attn_desc *d, int window);
+
+// What keeps the importance kernel from taking this shape (32-bit byte offsets inside one
+// sequence's Q rows and inside the log-sum-exp tensor), or NULL
+const char *importance_limits(const pdd_attn_desc *d)
+{
+    const int64_t span = 2 * ((int64_t)d->max_seqlen_q * d->q_stride_tok + (int64_t)d->n_q_heads * d->q_stride_head);
+    if (span >= (1LL << 32)) return "a sequence's Q span must stay below 4 GiB";
+    if ((int64_t)d->n_q_heads * d->total_q * 4 >= (1LL << 32)) return "the log-sum-exp tensor must stay below 4 GiB";
+    return nullptr;
+}
+
+// Whether and how the keys of a call are split over workgroups (attn_fwd_kernel's SPLIT form).
+// The plain form gives a workgroup all keys of 128 or 256 queries of one head, so a call lasts at
+// least as long as its longest sequence's walk over the key tiles, however few workgroups there
+// are, and a chunk of few tokens leaves most rows of every tile empty.  The split form packs the
+// (token, head) rows of a KV group into its tiles and cuts the walk into pieces of `tiles` key
+// tiles; it pays with 32-bit partial rows, written once and read back by a second kernel.
+// The choice compares two estimates in microseconds, fitted to kernel times on 256 compute units
+// (plain against split, second kernel included): 1 token x 8 sequences behind 500 to 7900 keys,
+// 32/8 heads, 102 -> 25; 5 to 64 tokens x 4 sequences behind 700 to 12345 keys, 148 -> 42; 200
+// tokens behind 16000, 4/2 heads, 215 -> 30; prompts of 2048 tokens x 1 head 31 -> 18 and of 8192
+// x 4/2 heads 117 -> 94; the plain form is better on 128 tokens x 8 behind 4000, 64/8 heads
+// (135 against 153), 256 x 4 behind 8192, 64/8 heads (238 against 291) and prompts that fill the
+// chip (8192 tokens x 8 heads 135 against 165).  One step is one key tile of one workgroup.
+// The scratch of a chunked call stays within the built-in scratch, so that the call without a
+// workspace argument takes the same form.  Depends on the descriptor and the device only.
+SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
+{
+    const SplitPlan none = {0, 0, 0};
+    if (g_attn_waves != 0 || d->total_q <= 0 || d->total_k <= 0 || d->max_seqlen_q <= 0 || d->max_seqlen_k <= 0 ||
+        d->n_q_heads % d->n_kv_heads)
+        return none;
+    const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q;
+    // the kernel divides a row by G with one 32-bit multiplication, addresses 32 rows of Q with
+    // 32-bit byte offsets
+    if (G > 65535 || max_q * G >= (1LL << 31) || max_q * G * G >= (1LL << 32)) return none;
+    if (d->q_stride_tok >= (1LL << 25) || G * d->q_stride_head >= (1LL << 30)) return none;
+    const double cus = (double)compute_units();
+    const int64_t n_qt = (max_q * G + kSplitRows - 1) / kSplitRows;
+    const int64_t tiles_max = (d->max_seqlen_k + pdd::kBN - 1) / pdd::kBN;
+    const double tiles_all = (double)d->total_k / pdd::kBN + 0.5 * B;
+    const double seen = 1.0 - 0.5 * max_q / d->max_seqlen_k;    // share of the keys an average query tile walks
+
+    // Key tiles per workgroup: about one workgroup per compute unit, 8 to 24 tiles (fewer and the
+    // start of a workgroup and the partial rows cost more than they spread; decode of the 8
+    // sequences above: 26 us at 8 tiles, 20 at 12, 21 at 16, 26 at 24), evened out over the
+    // longest sequence, and as many more as the scratch asks for.
+    const double base = (double)(n_qt * Hkv);
+    double T = 24;
+    if (cus > base * B) T = std::ceil(tiles_all * base / (cus - base * B));
+    T = T < 8 ? 8 : T > 24 ? 24 : T;
+    const size_t per_split = (size_t)d->total_q * d->n_q_heads * (d->head_dim + 1) * sizeof(float);
+    const size_t room = (chunked ? (size_t)PDD_STATIC_SCRATCH_BYTES : kSplitWorkspaceMax) / per_split;
+    int64_t n_split = (tiles_max + (int64_t)T - 1) / (int64_t)T;
+    if (n_split > (int64_t)room) n_split = (int64_t)room;
+    if (n_split < 2) return none;
+    const int64_t tiles = (tiles_max + n_split - 1) / n_split;
+    n_split = (tiles_max + tiles - 1) / tiles;
+    if ((double)n_split * base * B >= 2147483647.0) return none;
+    if (chunked) {      // the importance kernel has to be able to follow (the sweep has wider limits)
+        if (importance_workspace(d, -1) > PDD_STATIC_SCRATCH_BYTES) return none;
+        if (importance_limits(d)) return none;
+    }
+
+    const int bm = attn_rows_per_workgroup(d);
+    const int64_t n_qt_plain = (max_q + bm - 1) / bm;
+    const double fill = (double)max_q / (double)(n_qt_plain * bm);      // rows in use of the plain form's tiles
+    const double work = (double)n_qt_plain * d->n_q_heads * tiles_all * seen / cus;
+    const bool d64 = d->head_dim == 64;        // half the bytes and matrix work, the same exponentials
+    const double plain = (d64 ? 0.75 : 1.0) *
+        (bm == 256 ? std::fmax(tiles_max * (0.75 + 0.5 * fill), work * (0.75 + 1.05 * fill))
+                   : std::fmax((double)tiles_max, work) * (0.75 + 0.15 * fill));
+    const double partial = (double)n_split * per_split * seen * 1e-6 / 4.0;     // written and read back, at 4 TB/s each
+    const double split = std::fmax(tiles * 0.8, base * tiles_all * seen / cus * (d64 ? 0.95 : 1.1)) + 8.0 + partial;
+    if (split > 0.9 * plain) return none;
+    return {(int)tiles, (int)n_split, (size_t)n_split * per_split};
+}
+
 // imp_part != NULL: sweep_workspace(d) bytes; the importance sweep runs inside
 // the attention kernel and leaves its partial sums there.
+// split_ws != NULL: the key-split form of `plan`, with plan.bytes of scratch.
 pdd_status launch_attn(const pdd_attn_desc *d, const void *q, const void *k, const void *v, void *o, float *lse,
-                       hipStream_t st, float *imp_part = nullptr)
+                       hipStream_t st, float *imp_part = nullptr, const SplitPlan *plan = nullptr,
+                       void *split_ws = nullptr)
 {
     if (d->total_q == 0) return PDD_OK;
     pdd::AttnParams p;
     p.imp_part = imp_part;
+    p.split_tiles = p.n_split = 0;  p.g_magic = 0;  p.part_o = p.part_l = nullptr;
     p.q = (const uint16_t *)q;  p.k = (const uint16_t *)k;  p.v = (const uint16_t *)v;
     p.o = (uint16_t *)o;  p.lse = lse;
     p.cu_q = d->cu_seqlens_q;  p.cu_k = d->cu_seqlens_k;
@@ -224,6 +323,15 @@ pdd_status launch_attn(const pdd_attn_desc *d, const void *q, const void *k, con
         // and inside the 32 query rows of a wave
         if ((int64_t)d->q_stride_tok * 2 * 32 >= (1LL << 32))
             return fail(PDD_ERR_UNSUPPORTED, "32 rows of Q must span less than 4 GiB");
+    }
+    if (split_ws) {
+        p.split_tiles = plan->tiles;  p.n_split = plan->n_split;
+        p.n_qtiles = (int)(((int64_t)d->max_seqlen_q * p.G + kSplitRows - 1) / kSplitRows);
+        p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
+        p.part_o = (float *)split_ws;
+        p.part_l = p.part_o + (size_t)plan->n_split * d->total_q * d->n_q_heads * d->head_dim;
+        const int64_t n = (int64_t)p.n_qtiles * d->batch * d->n_kv_heads * plan->n_split;
+        return d->head_dim == 128 ? launch_attn_split<128>(p, n, st) : launch_attn_split<64>(p, n, st);
     }
     if (d->head_dim == 128)
         return nw == 8 ? launch_attn_t<128, 8>(p, blocks, st) : launch_attn_t<128, 4>(p, blocks, st);
@@ -297,12 +405,7 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.window = window;
     p.scale_log2 = scale_log2(d);
     p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
-    {   // 32-bit byte offsets inside one sequence's Q rows (buffer addressing)
-        const int64_t span = 2 * ((int64_t)d->max_seqlen_q * d->q_stride_tok + (int64_t)d->n_q_heads * d->q_stride_head);
-        if (span >= (1LL << 32)) return fail(PDD_ERR_UNSUPPORTED, "a sequence's Q span must stay below 4 GiB");
-        if ((int64_t)d->n_q_heads * d->total_q * 4 >= (1LL << 32))
-            return fail(PDD_ERR_UNSUPPORTED, "the log-sum-exp tensor must stay below 4 GiB");
-    }
+    if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
     // the row split needs room for its partial sums; without it the single-pass form runs
     const size_t need = importance_workspace(d, window);
     const bool split = need > 0 && workspace && workspace_bytes >= need;
@@ -341,10 +444,20 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
 
 // What the chunked call can use: room for the in-kernel sweep where that applies, else for the
 // row split of the separate importance kernel.
-size_t chunked_workspace(const pdd_attn_desc *d)
+size_t plain_chunked_workspace(const pdd_attn_desc *d)
 {
     const size_t sweep = sweep_workspace(d);
     return sweep ? sweep : importance_workspace(d, -1);
+}
+
+// The same with the key-split form where that applies: its partial rows, and after them, in the
+// same place, the partial sums of the importance kernel.
+size_t chunked_workspace(const pdd_attn_desc *d)
+{
+    const size_t split = split_plan(d, true).bytes;
+    if (!split) return plain_chunked_workspace(d);
+    const size_t imp = importance_workspace(d, -1);
+    return split > imp ? split : imp;
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device.
@@ -407,7 +520,11 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
         return 0;
     switch (which_call) {
     case PDD_CALL_PREFILL_ATTN:
-        return desc->window > 0 ? importance_workspace(desc, desc->window) : 0;
+    {
+        const size_t imp = desc->window > 0 ? importance_workspace(desc, desc->window) : 0;
+        const size_t split = split_plan(desc, false).bytes;
+        return split > imp ? split : imp;
+    }
     case PDD_CALL_PREFILL_ATTN_CHUNKED:
         return chunked_workspace(desc);
     case PDD_CALL_TOKEN_IMPORTANCE:
@@ -427,7 +544,11 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
     if (s) return s;
     if (desc->window > 0 && !importance)
         return fail(PDD_ERR_INVALID_ARG, "window > 0 needs an importance buffer");
-    s = launch_attn(desc, q, k, v, o, lse, (hipStream_t)stream);
+    const SplitPlan plan = split_plan(desc, false);
+    if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace))
+        s = launch_attn(desc, q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+    else
+        s = launch_attn(desc, q, k, v, o, lse, (hipStream_t)stream);
     if (s) return s;
     if (importance && desc->window > 0)
         return launch_importance(desc, q, k, lse, importance, desc->window, workspace, workspace_bytes,
@@ -443,6 +564,13 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     if (s) return s;
     s = check_ptrs(q_chunk, k_all, v_all, o, lse);
     if (s) return s;
+    const SplitPlan plan = split_plan(desc, true);
+    if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace)) {
+        s = launch_attn(desc, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+        if (s || !importance) return s;
+        return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,
+                                 (hipStream_t)stream);
+    }
     const size_t sweep = importance ? sweep_workspace(desc) : 0;
     if (sweep && workspace && workspace_bytes >= sweep) {
         if (reinterpret_cast<uintptr_t>(workspace) & 15u)
@@ -471,10 +599,13 @@ pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const voi
 {
     pdd_status s = check_desc(desc, MODE_CHUNKED);
     if (s) return s;
-    const size_t need = importance ? chunked_workspace(desc) : 0;
-    if (need > PDD_STATIC_SCRATCH_BYTES)
+    const size_t plain = importance ? plain_chunked_workspace(desc) : 0;
+    if (plain > PDD_STATIC_SCRATCH_BYTES)
         return fail(PDD_ERR_WORKSPACE, "this shape wants %zu bytes of scratch, the built-in scratch holds %u "
-                    "(use pdd_prefill_attn_chunked with a workspace)", need, (unsigned)PDD_STATIC_SCRATCH_BYTES);
+                    "(use pdd_prefill_attn_chunked with a workspace)", plain, (unsigned)PDD_STATIC_SCRATCH_BYTES);
+    // (the key-split form never wants more than the built-in scratch)
+    const size_t split = split_plan(desc, true).bytes;
+    const size_t need = importance ? chunked_workspace(desc) : split;
     void *ws = nullptr;
     if (need > 0) {
         s = static_scratch(&ws);

@@ -156,6 +156,44 @@ def test_random_chunks_with_long_prefix(seed):
                     label=f"chunk {seed}: q={lens_q} k={lens_k} heads={hq}/{hkv} d={d}")
 
 
+_SPLIT_SHAPES = {       # (new tokens, keys or None for prefill, query heads, KV heads, window)
+    # groups of 3 heads (rows divide by a number that is no power of two); no queries at all; a key count that
+    # is a whole number of tiles; a chunk without prefix
+    "group-3": ([1, 0, 33, 127, 3], [5001, 300, 4096, 127, 4], 6, 2, 0),
+    "group-16": ([5, 9], [9005, 1033], 16, 1, 0),               # all heads of a token in half a wave
+    "mha": ([129, 128, 1], [2629, 6128, 65], 8, 8, 0),         # one row past a row tile and exactly one
+    "one-head": ([300], [1500], 1, 1, 0),
+    "prefill": ([3000, 1, 700], None, 2, 1, 40),                # splits that end at the diagonal
+}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", list(_SPLIT_SHAPES))
+def test_keys_split_over_workgroups(name, d):
+    """The attention form that cuts the keys into pieces and packs the heads of a group into its
+    tiles, against the oracle on every row; its scratch is filled with NaN patterns before."""
+    lens_q, lens_k, hq, hkv, window = _SPLIT_SHAPES[name]
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, d, window, "1/4", seed=700 + d, chunked=lens_k is not None)
+    dev = DeviceWorkload(wl)
+    assert dev.workspace_bytes >= 2 * wl.total_q * hq * (d + 1) * 4, "this shape is one that splits its keys"
+    dev.poison()
+    dev.workspace.fill_(0xFF)
+    dev.attn(True)
+    torch.cuda.synchronize()
+    O, lse, imp = dev.results()[:3]
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale)
+    oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, window or -1)
+    assert np.abs(O - oO).max() <= O_ATOL
+    rel_close(lse, oL, "lse")
+    rel_close(imp, oI, "importance")
+    assert (dev.workspace.view(torch.int32) != -1).any(), "the scratch was not used"
+    bits = [x.clone() for x in (dev.o, dev.lse, dev.imp)]
+    dev.poison()
+    dev.attn(True)                                              # the same bits again
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(bits, (dev.o, dev.lse, dev.imp)))
+
+
 def test_empty_sequence_in_batch_and_no_host_copies():
     wl = W.make_custom("t", [40, 0, 129], None, 2, 1, 64, 16, "1/2", seed=9)
     dev = DeviceWorkload(wl)
