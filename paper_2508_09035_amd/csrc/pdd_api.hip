@@ -741,12 +741,18 @@ pdd_status pdd_aggregate_scores(const float *scores, int32_t n_layers, int32_t n
     p.scores = scores;  p.weights = layer_weights;  p.out = out;  p.layer_stride = layer_stride;
     p.n_layers = n_layers;  p.n_heads = n_heads;  p.total_k = total_k;
     p.reduce_heads = reduce_heads ? 1 : 0;  p.accumulate = accumulate ? 1 : 0;
-    const bool vec = total_k % 4 == 0 && layer_stride % 4 == 0 && ((uintptr_t)scores % 16) == 0 &&
-                     ((uintptr_t)out % 16) == 0;
-    const int per_block = 256 * (vec ? 4 : 1);
-    const dim3 grid((unsigned)((total_k + per_block - 1) / per_block), (unsigned)(reduce_heads ? 1 : n_heads));
-    if (vec) hipLaunchKernelGGL(pdd::aggregate_scores_kernel<4>, grid, dim3(256), 0, (hipStream_t)stream, p);
-    else     hipLaunchKernelGGL(pdd::aggregate_scores_kernel<1>, grid, dim3(256), 0, (hipStream_t)stream, p);
+    // Four tokens per lane, fewer where a row is too short to occupy every compute unit that way;
+    // then waves that share the layers until there are 16 per compute unit (32 layers x 8 heads x
+    // 32768 tokens into one row: 256 workgroups of 2 tokens per lane and 16 waves).
+    const int64_t rows = reduce_heads ? 1 : n_heads, cus = compute_units();
+    auto groups = [&](int v) { return ((total_k + 64LL * v - 1) / (64 * v)) * rows; };
+    const int vec = groups(4) >= cus ? 4 : groups(2) >= cus ? 2 : 1;
+    int waves = 1;
+    while (2 * waves <= pdd::kAggMaxWaves && 2 * waves <= n_layers && groups(vec) * waves < 16 * cus) waves *= 2;
+    const dim3 grid((unsigned)((total_k + 64LL * vec - 1) / (64 * vec)), (unsigned)rows), block(64 * waves);
+    if (vec == 4)      hipLaunchKernelGGL(pdd::aggregate_scores_kernel<4>, grid, block, 0, (hipStream_t)stream, p);
+    else if (vec == 2) hipLaunchKernelGGL(pdd::aggregate_scores_kernel<2>, grid, block, 0, (hipStream_t)stream, p);
+    else               hipLaunchKernelGGL(pdd::aggregate_scores_kernel<1>, grid, block, 0, (hipStream_t)stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(PDD_ERR_HIP, "aggregate launch: %s", hipGetErrorString(e));
     return PDD_OK;
