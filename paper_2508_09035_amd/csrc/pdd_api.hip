@@ -716,8 +716,10 @@ pdd_status pdd_select_sentences(const float *scores, int32_t n_heads, int32_t ba
     p.n_heads = n_heads;  p.B = batch;  p.total_k = total_k;  p.total_sent = total_sent;
     p.s_cap = max_sent_per_seq > 0 ? ((max_sent_per_seq + 3) & ~3) : 4;
     p.mode = agg_mode == PDD_SENT_MEAN ? pdd::kSentMean : pdd::kSentSum;
-    const int smem = p.s_cap * 16;
-    s = raise_lds_limit(reinterpret_cast<const void *>(pdd::select_sentences_kernel), pdd::kSentMax * 16);
+    const int step = 4 * pdd::kSelThreads;
+    p.seg = max_seqlen_k >= pdd::kSentSeg ? pdd::kSentSeg : (max_seqlen_k / step + 1) * step;
+    const int smem = p.seg * (int)sizeof(float);
+    s = raise_lds_limit(reinterpret_cast<const void *>(pdd::select_sentences_kernel), pdd::kSentSeg * (int)sizeof(float));
     if (s) return s;
     hipError_t e;
     hipLaunchKernelGGL(pdd::select_sentences_kernel, dim3((unsigned)batch, (unsigned)n_heads),

@@ -10,18 +10,28 @@
 // fits the budget is kept.  Outputs: keep flag per sentence, 0/1 mask per
 // token, number of kept tokens.
 //
-// One 1024-thread workgroup per row.  Sentence sums are serial fp32 loops in
-// token order (deterministic); ranks come from counting in LDS (S^2 / 1024
-// compares per thread, S <= 8192 sentences); the kept prefix from a block
-// scan of the lengths in rank order; the token mask from a binary search of
-// the sentence ends.
+// One 1024-thread workgroup per row; a thread owns up to eight consecutive
+// sentences, whose bounds, scores and lengths stay in registers.
+//   * The row's scores come through LDS in pieces of up to 16384 (whole-row loads,
+//     the next piece requested while one is summed); a sentence is summed by its
+//     owner in token order, one fp32 chain.  (Read by the owner straight from
+//     memory, one score after the other, the longest sentence alone cost 60 us.)
+//   * No ranks are formed: the kept prefix of the ranking is every sentence above a
+//     threshold key and the first of those that tie with it, and the threshold
+//     is found like the k-th score of a token row (see next_probe), with the
+//     lengths as weights: one barrier per probe, until 64 sentences are left.
+//   * The token mask: kept sentences flip a bit at their start and at their end,
+//     and a prefix parity over the bits gives the mask 32768 tokens at a time.
+// Bound by the latency of its steps on the one compute unit the row runs on:
+// 1 row of 32768 tokens in 1362 sentences 149 -> 21 us (serial reads, S^2 ranks and
+// a binary search per token before).
 #pragma once
 #include "select_topk.hpp"
 
 namespace pdd {
 
 enum { kSentSum = 0, kSentMean = 1 };
-constexpr int kSentMax = 8192;    // sentences per sequence held in LDS
+constexpr int kSentMax = 8192;    // sentences per sequence
 
 struct SentParams {
     const float *scores;
@@ -30,17 +40,52 @@ struct SentParams {
     int32_t *kept_tokens;
     float *sent_scores;
     int32_t n_heads, B, total_k, total_sent, s_cap, mode;
+    int32_t seg;              // scores in LDS at a time, a multiple of 4 * kSelThreads up to kSentSeg
 };
+
+constexpr int kSentOwn = kSentMax / kSelThreads;     // sentences per thread at most
+constexpr int kSentSeg = 16 * kSelThreads;            // scores in LDS at a time, at most
+constexpr int kSentChunk = 32 * kSelThreads;          // mask tokens at a time: one 32-bit word per thread
+// a probe either cuts the tokens inside the bracket to a quarter (at most 16 times), or is
+// followed by one that halves the bracket (at most 32 pairs)
+constexpr int kSentMaxProbes = 96;
+constexpr int kSentFinish = 64;                       // sentences left in the bracket that are compared directly
+
+typedef float sent_f32x4 __attribute__((ext_vector_type(4), aligned(4)));    // four scores at any score's address
+
+// Exclusive scan over the workgroup's 1024 values in thread order; `sh` is used by one call only.
+template <typename Op>
+__device__ __forceinline__ int block_excl_scan(int x, int init, Op op, int32_t *sh, int lane, int wave, int *total)
+{
+    int incl = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl = op(incl, o);
+    }
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    int pre = init, all = init;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        if (w < wave) pre = op(pre, sh[w]);
+        all = op(all, sh[w]);
+    }
+    *total = all;
+    const int up = __shfl_up(incl, 1, 64);
+    return lane == 0 ? pre : op(pre, up);
+}
 
 __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const SentParams p)
 {
-    extern __shared__ __attribute__((aligned(16))) int32_t sent_smem[];
-    int32_t *send = sent_smem;                       // [s_cap] clamped sentence ends
-    uint32_t *skey = (uint32_t *)(send + p.s_cap);   // [s_cap] order keys, later keep flags
-    int32_t *slen = (int32_t *)(skey + p.s_cap);     // [s_cap] token counts
-    int32_t *lenr = slen + p.s_cap;                  // [s_cap] lengths in rank order -> inclusive scan
-    __shared__ int32_t wsum[kSelWaves];
-    __shared__ int32_t sh_m;
+    extern __shared__ __attribute__((aligned(16))) uint8_t sent_smem[];    // p.seg scores, later mask words
+    float *const stage = (float *)sent_smem;
+    uint32_t *const bits = (uint32_t *)sent_smem;
+    __shared__ int32_t sh_end[kSelWaves], sh_tie[kSelWaves];
+    __shared__ uint32_t wave_min[kSelWaves], wave_max[kSelWaves], wave_par[kSelWaves];
+    __shared__ unsigned long long probe_tot[kSentMaxProbes];       // tokens | sentences << 32 at or above a probe
+    __shared__ uint32_t fin_key[kSentFinish], fin_len[kSentFinish];
+    __shared__ uint32_t fin_count, fin_T, fin_above, sh_kept;
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -51,127 +96,224 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     const int s1 = min(max(p.cu_sent[b + 1], s0), p.total_sent);
     const int S = min(s1 - s0, p.s_cap);
     const int c0 = min(max(p.cand_b ? p.cand_b[b] : 0, 0), nk);
-    const int budget = max(p.budget[b], 0);
+    const uint32_t budget = (uint32_t)max(p.budget[b], 0);
     const float *seq = p.scores + (int64_t)g * p.total_k + ks;
     uint8_t *mrow = p.mask ? p.mask + (int64_t)g * p.total_k + ks : nullptr;
 
-    // sentence ends, forced into [c0, nk] and non-decreasing (serial fix-up by one thread is
-    // avoided: an end smaller than its predecessor is raised by a running maximum below)
-    for (int s = tid; s < S; s += kSelThreads) send[s] = min(max(p.sent_end[s0 + s], c0), nk);
-    __syncthreads();
-    // running maximum over at most a few thousand entries: wave 0, 64 lanes, chunked
-    if (wave == 0) {
-        const int ch = (S + 63) / 64;
-        const int lo = lane * ch, hi = min(lo + ch, S);
-        int mx = c0;
-        for (int s = lo; s < hi; ++s) mx = max(mx, send[s]);
-        int run = mx;                                  // inclusive max over lanes <= lane
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(run, off, 64);
-            if (lane >= off) run = max(run, o);
-        }
-        int prev = __shfl_up(run, 1, 64);
-        if (lane == 0) prev = c0;
-        for (int s = lo; s < hi; ++s) { prev = max(prev, send[s]); send[s] = prev; }
-    }
-    __syncthreads();
-    const int content_end = S > 0 ? send[S - 1] : c0;
+    if (tid < kSentMaxProbes) probe_tot[tid] = 0;
+    if (tid == 0) { fin_count = 0; sh_kept = 0; }
 
-    // sentence scores
-    for (int s = tid; s < S; s += kSelThreads) {
-        const int st = s == 0 ? c0 : send[s - 1], en = send[s];
-        float acc = 0.f;
-        for (int x = st; x < en; ++x) acc += seq[x];
-        const int len = en - st;
-        const float sc = (p.mode == kSentMean) ? acc / (float)max(len, 1) : acc;
-        skey[s] = order_key(sc);
-        slen[s] = len;
-        if (p.sent_scores) p.sent_scores[(int64_t)g * p.total_sent + s0 + s] = sc;
-    }
-    __syncthreads();
-
-    // ranks by counting; lengths scattered into rank order
-    constexpr int OWN = kSentMax / kSelThreads;        // sentences per thread at most
-    int my_rank[OWN];
+    // ---- sentence bounds: ends forced into [c0, nk] and non-decreasing (running maximum)
+    const int ch = (S + kSelThreads - 1) / kSelThreads;          // sentences per thread, <= kSentOwn
+    const int s_lo = tid * ch;
+    int end[kSentOwn];
+    int mx = c0;
 #pragma unroll
-    for (int i = 0; i < OWN; ++i) {
-        const int s = i * kSelThreads + tid;
-        my_rank[i] = 0;
-        if (s < S) {
-            const uint32_t ksv = skey[s];
-            int beats = 0;
-            for (int t = 0; t < S; ++t) {
-                const uint32_t kt = skey[t];
-                beats += (kt > ksv || (kt == ksv && t < s)) ? 1 : 0;
+    for (int i = 0; i < kSentOwn; ++i) {
+        if (i < ch && s_lo + i < S) mx = max(mx, min(max(p.sent_end[s0 + s_lo + i], c0), nk));
+        end[i] = mx;
+    }
+    int content_end;
+    const int begin = block_excl_scan(mx, c0, [](int x, int y) { return max(x, y); }, sh_end, lane, wave, &content_end);
+#pragma unroll
+    for (int i = 0; i < kSentOwn; ++i) end[i] = max(end[i], begin);
+
+    // ---- sentence scores.  Sentence i covers [start of i, end[i]), start = end of the one before
+    float acc[kSentOwn];
+#pragma unroll
+    for (int i = 0; i < kSentOwn; ++i) acc[i] = 0.f;
+    constexpr int QUADS = kSentSeg / (4 * kSelThreads);
+    sent_f32x4 pre[QUADS];
+    auto request = [&](int at) {
+#pragma unroll
+        for (int q = 0; q < QUADS; ++q) {
+            const int o = 4 * (q * kSelThreads + tid), x = at + o;
+            if (o < p.seg) {
+                if (x + 4 <= content_end) pre[q] = *(const sent_f32x4 *)(seq + x);
+                else
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) pre[q][j] = x + j < content_end ? seq[x + j] : 0.f;
             }
-            my_rank[i] = beats;
-            lenr[beats] = slen[s];
         }
-    }
-    __syncthreads();
-
-    // inclusive scan of lenr[0..S): contiguous chunk per thread
-    const int ch = (S + kSelThreads - 1) / kSelThreads;
-    const int lo = min(tid * ch, S), hi = min(lo + ch, S);
-    int local = 0;
-    for (int r = lo; r < hi; ++r) local += lenr[r];
-    int incl = local;
+    };
+    request(c0);
+    for (int seg0 = c0; seg0 < content_end; seg0 += p.seg) {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    int base = incl - local;
-    for (int w = 0; w < wave; ++w) base += wsum[w];
-    int cnt_fit = 0;
-    for (int r = lo; r < hi; ++r) {
-        base += lenr[r];
-        lenr[r] = base;                                  // cumulative token count of ranks 0..r
-        cnt_fit += base <= budget ? 1 : 0;
-    }
-    // m = number of leading ranks that fit (the cumulative counts are non-decreasing)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) cnt_fit += __shfl_xor(cnt_fit, off, 64);
-    __syncthreads();
-    if (lane == 0) wsum[wave] = cnt_fit;
-    __syncthreads();
-    if (tid == 0) {
-        int m = 0;
-        for (int w = 0; w < kSelWaves; ++w) m += wsum[w];
-        sh_m = m;
-        if (p.kept_tokens) p.kept_tokens[(int64_t)g * p.B + b] = m > 0 ? lenr[m - 1] : 0;
-    }
-    __syncthreads();
-    const int m = sh_m;
-
-    // keep flags
-#pragma unroll
-    for (int i = 0; i < OWN; ++i) {
-        const int s = i * kSelThreads + tid;
-        if (s < S) {
-            const uint32_t kept = my_rank[i] < m ? 1u : 0u;
-            skey[s] = kept;
-            if (p.sent_keep) p.sent_keep[(int64_t)g * p.total_sent + s0 + s] = (uint8_t)kept;
+        for (int q = 0; q < QUADS; ++q) {
+            const int o = 4 * (q * kSelThreads + tid);
+            if (o < p.seg) *(float4 *)(stage + o) = make_float4(pre[q][0], pre[q][1], pre[q][2], pre[q][3]);
         }
-    }
-    __syncthreads();
-
-    // token mask: token x of the content belongs to the first sentence whose end is > x
-    if (mrow) {
-        for (int x = tid; x < nk; x += kSelThreads) {
-            uint8_t v = 0;
-            if (x >= c0 && x < content_end) {
-                int a = 0, z = S - 1;                    // send[z] > x holds for z = S - 1
-                while (a < z) {
-                    const int mid = (a + z) >> 1;
-                    if (send[mid] > x) z = mid; else a = mid + 1;
+        __syncthreads();
+        if (seg0 + p.seg < content_end) request(seg0 + p.seg);
+#pragma unroll
+        for (int i = 0; i < kSentOwn; ++i) {
+            if (i < ch) {
+                int x = max(i == 0 ? begin : end[i - 1], seg0) - seg0;
+                const int z = min(end[i] - seg0, p.seg);
+                float a = acc[i];
+                for (; x + 8 <= z; x += 8) {          // eight reads in flight, added in token order
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[j] = stage[x + j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) a += v[j];
                 }
-                v = (uint8_t)skey[a];
+                for (; x < z; ++x) a += stage[x];
+                acc[i] = a;
             }
-            mrow[x] = v;
+        }
+        __syncthreads();
+    }
+    // slots without a sentence: key 0, length 0
+    uint32_t key[kSentOwn], len[kSentOwn];
+    uint32_t kmin = 0xffffffffu, kmax = 0;
+#pragma unroll
+    for (int i = 0; i < kSentOwn; ++i) {
+        key[i] = len[i] = 0;
+        if (i < ch && s_lo + i < S) {
+            const int n = end[i] - (i == 0 ? begin : end[i - 1]);
+            const float sc = (p.mode == kSentMean) ? acc[i] / (float)max(n, 1) : acc[i];
+            key[i] = order_key(sc);
+            len[i] = (uint32_t)n;
+            kmin = min(kmin, key[i]);
+            kmax = max(kmax, key[i]);
+            if (p.sent_scores) p.sent_scores[(int64_t)g * p.total_sent + s0 + s_lo + i] = sc;
+        }
+    }
+
+    // ---- threshold: the largest T whose sentences (key >= T) hold more tokens than the budget.  The
+    // ranking then keeps every sentence above T and, in index order, those at T that still fit.
+    const uint32_t total = (uint32_t)(content_end - c0);
+    uint32_t T = 0, above = 0;                                   // above = tokens of the sentences > T
+    const bool all = total <= budget;                            // the same in every thread
+    if (!all) {
+        wave_min_max(kmin, kmax);
+        if (lane == 63) { wave_min[wave] = kmin; wave_max[wave] = kmax; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) {
+            kmin = w == 0 ? wave_min[0] : min(kmin, wave_min[w]);
+            kmax = w == 0 ? wave_max[0] : max(kmax, wave_max[w]);
+        }
+        const uint32_t need = budget + 1u;
+        uint32_t lo = kmin, hi = kmax, w_lo = total, n_lo = (uint32_t)S, n_above = 0;
+        bool interp = true;
+        for (int probe = 0; lo < hi && n_lo - n_above > (uint32_t)kSentFinish; ++probe) {
+            const uint32_t inside = w_lo - above;
+            const uint32_t mid = next_probe(lo, hi, inside, need - above, interp);
+            uint32_t w = 0, n = 0;
+#pragma unroll
+            for (int i = 0; i < kSentOwn; ++i) {                  // mid > lo >= kmin: empty slots never count
+                w += key[i] >= mid ? len[i] : 0u;
+                n += key[i] >= mid ? 1u : 0u;
+            }
+            uint32_t sc[2] = {w, n};
+            wave_incl_scan_n(sc);
+            if (lane == 63) atomicAdd(&probe_tot[probe], (unsigned long long)sc[0] | (unsigned long long)sc[1] << 32);
+            __syncthreads();
+            const unsigned long long t = probe_tot[probe];
+            if ((uint32_t)t >= need) { lo = mid; w_lo = (uint32_t)t; n_lo = (uint32_t)(t >> 32); }
+            else { hi = mid - 1u; above = (uint32_t)t; n_above = (uint32_t)(t >> 32); }
+            interp = !interp || 4u * (w_lo - above) <= inside;
+        }
+        T = lo;
+        if (lo < hi) {
+            // at most kSentFinish sentences lie in [lo, hi]
+#pragma unroll
+            for (int i = 0; i < kSentOwn; ++i)
+                if (i < ch && s_lo + i < S && key[i] - lo <= hi - lo) {
+                    const uint32_t at = atomicAdd(&fin_count, 1u);
+                    fin_key[at] = key[i];
+                    fin_len[at] = len[i];
+                }
+            __syncthreads();
+            if (wave == 0) {
+                const int m = (int)fin_count;
+                const uint32_t mine = lane < m ? fin_key[lane] : 0u;
+                uint32_t gt = above, ge = above;
+                for (int j = 0; j < m; ++j) {
+                    const uint32_t k = fin_key[j], l = fin_len[j];
+                    gt += k > mine ? l : 0u;
+                    ge += k >= mine ? l : 0u;
+                }
+                if (lane < m && gt < need && ge >= need) { fin_T = mine; fin_above = gt; }   // one key at most
+            }
+            __syncthreads();
+            T = fin_T;
+            above = fin_above;
+        }
+    }
+
+    // ---- keep flags
+    uint32_t kept = 0;
+    {
+        uint32_t tie = 0;
+#pragma unroll
+        for (int i = 0; i < kSentOwn; ++i) tie += (i < ch && s_lo + i < S && key[i] == T) ? len[i] : 0u;
+        int tie_all;
+        uint32_t run = (uint32_t)block_excl_scan((int)tie, 0, [](int x, int y) { return x + y; }, sh_tie, lane, wave, &tie_all);
+        uint32_t tokens = 0;
+#pragma unroll
+        for (int i = 0; i < kSentOwn; ++i) {
+            if (i < ch && s_lo + i < S) {
+                bool k = all || key[i] > T;
+                if (!all && key[i] == T) {
+                    run += len[i];
+                    k = run <= budget - above;
+                }
+                kept |= k ? 1u << i : 0u;
+                tokens += k ? len[i] : 0u;
+                if (p.sent_keep) p.sent_keep[(int64_t)g * p.total_sent + s0 + s_lo + i] = k ? 1 : 0;
+            }
+        }
+        if (p.kept_tokens) {
+            tokens = wave_incl_scan(tokens);
+            if (lane == 63) atomicAdd(&sh_kept, tokens);
+            __syncthreads();
+            if (tid == 0) p.kept_tokens[(int64_t)g * p.B + b] = (int32_t)sh_kept;
+        }
+    }
+
+    // ---- token mask
+    if (mrow) {
+        uint32_t carry = 0;                                       // parity of the flips before the chunk
+        const bool dwords = ((uint32_t)(uintptr_t)mrow & 3u) == 0;
+        for (int x0 = 0; x0 < nk; x0 += kSentChunk) {
+            __syncthreads();
+            bits[tid] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kSentOwn; ++i) {
+                if (kept >> i & 1u) {
+                    const uint32_t a = (uint32_t)((i == 0 ? begin : end[i - 1]) - x0), z = (uint32_t)(end[i] - x0);
+                    if (a < (uint32_t)kSentChunk) atomicXor(&bits[a >> 5], 1u << (a & 31u));
+                    if (z < (uint32_t)kSentChunk) atomicXor(&bits[z >> 5], 1u << (z & 31u));
+                }
+            }
+            __syncthreads();
+            uint32_t v = bits[tid];
+#pragma unroll
+            for (int off = 1; off < 32; off <<= 1) v ^= v << off;
+            const uint64_t par = __ballot(v >> 31);
+            if (lane == 0) wave_par[wave] = (uint32_t)__popcll(par) & 1u;
+            __syncthreads();
+            uint32_t odd = carry ^ ((uint32_t)__popcll(par & ((1ull << lane) - 1ull)) & 1u);
+#pragma unroll
+            for (int w = 0; w < kSelWaves; ++w) {
+                odd ^= w < wave ? wave_par[w] : 0u;
+                carry ^= wave_par[w];
+            }
+            bits[tid] = v ^ (0u - odd);
+            __syncthreads();
+            for (int o = 4 * tid; o < kSentChunk && x0 + o < nk; o += 4 * kSelThreads) {
+                const uint32_t nib = bits[o >> 5] >> (o & 31) & 15u;
+                const uint32_t v4 = nib * 0x00204081u & 0x01010101u;     // bit j of the nibble to byte j
+                uint8_t *mp = mrow + x0 + o;
+                if (dwords && x0 + o + 4 <= nk) *(uint32_t *)mp = v4;
+                else
+                    for (int j = 0; j < 4; ++j)
+                        if (x0 + o + j < nk) mp[j] = (uint8_t)(v4 >> (8 * j));
+            }
         }
     }
 }

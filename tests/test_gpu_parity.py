@@ -852,7 +852,65 @@ def test_select_sentences(mode, exact_scores):
             assert np.min(np.abs(others - want_sc[g, s])) <= 4e-6 * max(abs(want_sc[g, s]), 1e-30), (g, s)
 
 
+@pytest.mark.parametrize("mean_len,levels", [(24.0, 8), (1.0, 1), (9.0, 64), (400.0, 3)])
+def test_select_sentences_with_ties(mean_len, levels):
+    """Sentences that tie in score (few score levels, down to one for the whole row, where the index
+    alone decides), 1 to 8192 of them, budgets from nothing to everything, rows of more than 32768
+    tokens and rows that start at any byte of the mask: exact, because every score is a small integer."""
+    rng = np.random.default_rng(int(mean_len) + levels)
+    lens = [70001, 1025, 3, 64, 33000, 8191, 500]
+    counts = [min(8192, max(1, int(n / mean_len))) for n in lens]
+    cb = [0, 1, 0, 0, 7, 0, 499]
+    ends, cu_sent = [], [0]
+    for n, c, lo in zip(lens, counts, cb):
+        ends.append(np.sort(rng.integers(lo, n + 1, size=c)))      # empty sentences among them
+        cu_sent.append(cu_sent[-1] + c)
+    ends = np.concatenate(ends).astype(np.int32)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_sent = np.array(cu_sent, dtype=np.int32)
+    cb = np.array(cb, dtype=np.int32)
+    # one score per sentence on its first token: the sum is that score
+    heads = 2
+    tok = np.zeros((heads, int(cu[-1])), dtype=np.float32)
+    for b in range(len(lens)):
+        start = int(cb[b])
+        for s in range(cu_sent[b], cu_sent[b + 1]):
+            if ends[s] > start:
+                tok[:, cu[b] + start] = rng.integers(0, levels, size=heads) - levels // 2
+            start = int(ends[s])
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for share in (0.0, 0.001, 0.3, 0.9, 1.0):
+        budget = np.array([int(share * n) for n in lens], dtype=np.int32)
+        skeep = torch.full((heads, len(ends)), 7, dtype=torch.uint8, device="cuda")
+        mask = torch.full((heads, int(cu[-1])), 7, dtype=torch.uint8, device="cuda")
+        kept = torch.full((heads, len(lens)), -1, dtype=torch.int32, device="cuda")
+        pdd.select_sentences(d(tok), d(cu), max(lens), d(cu_sent), d(ends), max(counts), d(budget), pdd.SENT_SUM,
+                             d(cb), None, skeep, mask, kept, cu)
+        torch.cuda.synchronize()
+        _, w_keep, w_mask, w_kept = oracle.select_sentences(tok.astype(np.float64), cu, cu_sent, ends, budget, "sum", cb)
+        assert np.array_equal(skeep.cpu().numpy(), w_keep), share
+        assert np.array_equal(mask.cpu().numpy(), w_mask), share
+        assert np.array_equal(kept.cpu().numpy(), w_kept), share
+
+
 # --------------------------------------------------- cross-layer aggregation
+@pytest.mark.parametrize("layers,heads,total_k", [(33, 3, 130), (1, 9, 4099), (40, 1, 16385), (7, 17, 63), (5, 2, 70001)])
+@pytest.mark.parametrize("reduce_heads", [False, True])
+def test_aggregate_scores_shapes(layers, heads, total_k, reduce_heads):
+    """Layers shared by 1 to 16 waves, 1 to 4 tokens per lane, rows that start at any 4-byte address.
+    Positive terms: an fp32 sum of n of them, weighted, is within (n + 2) 2^-24 of its value."""
+    rng = np.random.default_rng(layers)
+    s32 = rng.random((layers, heads, total_k)).astype(np.float32)
+    w32 = (rng.random(layers) + 0.5).astype(np.float32)
+    out = torch.full((1 if reduce_heads else heads, total_k), 2.0, dtype=torch.float32, device="cuda")
+    for accumulate in (False, True):
+        pdd.aggregate_scores(torch.from_numpy(s32).cuda(), out, torch.from_numpy(w32).cuda(), reduce_heads, accumulate)
+        torch.cuda.synchronize()
+        want = oracle.aggregate_scores(s32, w32, reduce_heads) * (2 if accumulate else 1)
+        n = 2 * layers * (heads if reduce_heads else 1) + 2
+        np.testing.assert_allclose(out.cpu().numpy().astype(np.float64), want, rtol=n * 2.0 ** -24)
+
+
 @pytest.mark.parametrize("total_k,reduce_heads", [(32768, False), (32768, True), (1003, False), (1003, True)])
 def test_aggregate_scores(total_k, reduce_heads):
     rng = np.random.default_rng(17)
