@@ -215,6 +215,11 @@ pdd_status pdd_token_importance(const pdd_attn_desc *desc, const void *q, const 
  * slots are filled with -1 (callers that want the error check k_b on their side,
  * where they computed it).
  * -0.0 ranks equal to +0.0.
+ *   workspace    DEVICE scratch, 16-byte aligned, or NULL.  With at least
+ *                pdd_workspace_bytes(desc, PDD_CALL_SELECT_TOPK) bytes (desc:
+ *                batch, n_kv_heads = n_heads and max_seqlen_k are read) rows of
+ *                more than 32768 keys are divided over workgroups; the outputs
+ *                are the same without it.
  */
 pdd_status pdd_select_topk(const float *scores, int32_t n_heads, int32_t batch,
                            int32_t total_k, const int32_t *cu_seqlens_k,
@@ -366,7 +371,7 @@ pdd_status pdd_pack_mask(const uint8_t *mask, int32_t n_rows, int32_t batch, int
  * n_q_heads * total_k * 4 bytes up to 256 MiB (the in-kernel importance), and
  * for the key-split attention form ceil(max_seqlen_k / 512) * total_q *
  * n_q_heads * (head_dim + 1) * 4 bytes up to 256 MiB (16 MiB in the chunked
- * call): the attention weights
+ * call), for the selection 8720 bytes per 4096 keys up to 69 MiB: the attention weights
  * are not materialised (Section 3.2 "Preliminaries").  The figure depends on
  * the descriptor, on PDD_OPT_ATTN_WAVES and on the number of compute units of
  * the current device only.  A call that is given less runs with a form that

@@ -13,6 +13,7 @@
 #include "attn_fwd.hpp"
 #include "importance.hpp"
 #include "select_topk.hpp"
+#include "select_split.hpp"
 #include "pack_mask.hpp"
 #include "select_sentences.hpp"
 #include "aggregate.hpp"
@@ -347,6 +348,41 @@ void launch_select_reg(const pdd::SelParams &p, dim3 grid, hipStream_t st)
         hipLaunchKernelGGL((pdd::select_topk_reg_kernel<QPT, true>), grid, dim3(pdd::kSelThreads), 0, st, p);
 }
 
+// Chunks of the longest sequence where a selection divides its rows over workgroups, 0 where a row
+// stays in one.  Rows of up to 32768 candidates fit one workgroup's registers: 17.8 us divided against
+// 18.1 in one at 8 x 32768, 17.0 against 14.0 at 8 x 16384, 134 against 40 at 512 x 32768.  Longer
+// ones are read again in every pass of the one workgroup: 65536 19.1 against 117, 131072 20.9 against
+// 225 (8 rows), 153 against 367 (128 rows).  Beyond 8192 workgroups the four launches lose by their
+// total work (0.037 us each; 512 rows x 131072 would take about 610 against 497); beyond 512 chunks
+// the sums over them would.
+int select_chunks(int64_t n_heads, int64_t batch, int64_t max_seqlen_k)
+{
+    const int64_t chunks = (max_seqlen_k + pdd::kSplitSelChunk - 1) / pdd::kSplitSelChunk;
+    if (max_seqlen_k <= pdd::kSelRegCap || chunks > 512 || batch > 8192 || n_heads > 8192) return 0;
+    return n_heads * batch * chunks <= 8192 ? (int)chunks : 0;
+}
+
+pdd_status launch_select_split(const pdd::SelParams &s, int chunks, void *workspace, hipStream_t st)
+{
+    pdd::SplitSelParams p;
+    const int64_t slots = (int64_t)s.n_heads * s.B * chunks;
+    p.s = s;
+    p.n_chunks = chunks;
+    p.state = (pdd::SplitSelState *)workspace;
+    p.hist[0] = (uint32_t *)(p.state + slots);
+    p.hist[1] = p.hist[0] + slots * (pdd::kSplitSelBins / 2);
+    p.group[0] = p.hist[1] + slots * (pdd::kSplitSelBins / 2);
+    p.group[1] = p.group[0] + slots * pdd::kSplitSelGroups;
+    const dim3 grid((unsigned)chunks, (unsigned)s.B, (unsigned)s.n_heads), block(pdd::kSelThreads);
+    hipLaunchKernelGGL(pdd::select_level_kernel<0>, grid, block, 0, st, p);
+    hipLaunchKernelGGL(pdd::select_level_kernel<1>, grid, block, 0, st, p);
+    hipLaunchKernelGGL(pdd::select_level_kernel<2>, grid, block, 0, st, p);
+    hipLaunchKernelGGL(pdd::select_finish_kernel, grid, block, 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(PDD_ERR_HIP, "select launch: %s", hipGetErrorString(e));
+    return PDD_OK;
+}
+
 int compute_units()
 {
     static std::atomic<int> cached{0};
@@ -529,8 +565,11 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
         return chunked_workspace(desc);
     case PDD_CALL_TOKEN_IMPORTANCE:
         return desc->window != 0 ? importance_workspace(desc, desc->window) : 0;
+    case PDD_CALL_SELECT_TOPK:
+        return (size_t)desc->n_kv_heads * desc->batch *
+               select_chunks(desc->n_kv_heads, desc->batch, desc->max_seqlen_k) * pdd::kSplitSelChunkBytes;
     default:
-        return 0;  // the selection keeps its intermediates in registers / LDS
+        return 0;
     }
 }
 
@@ -633,8 +672,6 @@ pdd_status pdd_select_topk_pooled(const float *scores, int32_t n_heads, int32_t 
                                   int32_t *out_indices, uint8_t *out_mask, void *workspace,
                                   size_t workspace_bytes, pdd_stream stream)
 {
-    (void)workspace;
-    (void)workspace_bytes;
     if (!scores || !cu_seqlens_k || !k_per_seq || !cu_keep) return fail(PDD_ERR_INVALID_ARG, "NULL pointer");
     if (n_heads < 1 || batch < 1) return fail(PDD_ERR_INVALID_ARG, "n_heads and batch must be >= 1");
     if (total_k < 0 || total_keep < 0 || max_seqlen_k < 0 || max_seqlen_k > total_k)
@@ -662,6 +699,10 @@ pdd_status pdd_select_topk_pooled(const float *scores, int32_t n_heads, int32_t 
     p.pooled_out = pooled_out;
     const dim3 grid((unsigned)batch, (unsigned)n_heads);
     hipStream_t st = (hipStream_t)stream;
+    const int chunks = p.pool_r == 0 ? select_chunks(n_heads, batch, max_seqlen_k) : 0;
+    if (chunks && workspace && aligned16(workspace) &&
+        workspace_bytes >= (size_t)n_heads * batch * chunks * pdd::kSplitSelChunkBytes)
+        return launch_select_split(p, chunks, workspace, st);
     // rows of up to 32768 candidates stay in registers (4096 per step and 1024 threads)
     if (max_seqlen_k <= 4 * pdd::kSelThreads)
         launch_select_reg<1>(p, grid, st);

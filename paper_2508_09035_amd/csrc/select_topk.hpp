@@ -14,7 +14,8 @@
 //    at ~30 cycles per wave instruction, they dominated the radix variant)
 //    and no re-reading of the row.  The kept indices are written in ascending
 //    order from ballot prefix counts, with a 16*EPT-entry scan across waves.
-//  * select_topk_kernel (longer rows): most-significant-first radix select,
+//  * select_topk_kernel (longer rows without a workspace, pooled, or very many of them;
+//    see select_split.hpp for the others): most-significant-first radix select,
 //    8 bits per pass, digits taken from (key - min key) scaled to the row's
 //    range, LDS histograms; the row is re-read from L2 in every pass.
 //
@@ -145,6 +146,27 @@ __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx)
     PDD_MINMAX_STEP(0x142, 0xa)
     PDD_MINMAX_STEP(0x143, 0xc)
 #undef PDD_MINMAX_STEP
+}
+
+// The r-th largest (1 <= r <= m) of m <= kSelFinish keys in LDS, slots m .. kSelFinish + 3 zero, by
+// the lanes of one wave: true in the one lane that then holds it and the number of larger keys.
+__device__ __forceinline__ bool rank_in_wave(const uint32_t *keys, int m, uint32_t r, int lane, uint32_t &key, uint32_t &gt)
+{
+    key = lane < m ? keys[lane] : 0u;
+    gt = 0;
+    uint32_t ge = 0;
+    for (int j0 = 0; j0 < m; j0 += 4) {                           // slots past m hold 0: below every key
+        const uint4 o4 = *(const uint4 *)(keys + j0);
+        const uint32_t o[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            gt += o[x] > key ? 1u : 0u;
+            ge += o[x] >= key ? 1u : 0u;
+        }
+    }
+    const bool hit = lane < m && gt < r && r <= ge;               // every hit lane holds the same key
+    const uint64_t hb = __ballot(hit);
+    return hb != 0 && lane == (int)__builtin_ctzll(hb);
 }
 
 // At most 64 vector registers, so that two workgroups (8 waves per SIMD) share a compute unit: the
@@ -296,22 +318,11 @@ void select_topk_reg_kernel(const SelParams p)
                 if (key[i][j] - lo <= width) fin_keys[atomicAdd(&fin_count, 1u)] = key[i][j];
         __syncthreads();
         if (wave == 0) {
-            const int m = (int)fin_count;                                 // <= kSelFinish = 64
-            const uint32_t mine_k = lane < m ? fin_keys[lane] : 0u;
-            uint32_t gt = 0, ge = 0;
-            for (int j0 = 0; j0 < m; j0 += 4) {                           // slots past m hold 0: below every key
-                const uint4 o4 = *(const uint4 *)(fin_keys + j0);
-                const uint32_t o[4] = {o4.x, o4.y, o4.z, o4.w};
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    gt += o[x] > mine_k ? 1u : 0u;
-                    ge += o[x] >= mine_k ? 1u : 0u;
-                }
+            uint32_t key_T, gt;
+            if (rank_in_wave(fin_keys, (int)fin_count, (uint32_t)kk - c_above, lane, key_T, gt)) {
+                fin_T = key_T;
+                fin_above = c_above + gt;
             }
-            const uint32_t r = (uint32_t)kk - c_above;                    // 1 <= r <= m
-            const bool hit = lane < m && gt < r && r <= ge;               // every hit lane holds the same key
-            const uint64_t hb = __ballot(hit);
-            if (hb != 0 && lane == (int)__builtin_ctzll(hb)) { fin_T = mine_k; fin_above = c_above + gt; }
         }
         __syncthreads();
         lo = fin_T;

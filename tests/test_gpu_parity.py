@@ -452,6 +452,48 @@ def test_select_long_rows_beyond_lds_staging():
     _select_case(s, lens, [1, 33000])
 
 
+@pytest.mark.parametrize("dist", ["spread", "equal", "low_bits", "signs", "infinities"])
+@pytest.mark.parametrize("lens", [[32769], [36864, 5, 0, 4097, 4096], [131071, 40000]])
+def test_select_rows_divided_over_workgroups(lens, dist):
+    """Rows of more than 32768 candidates with a workspace: chunks of 4096 that end on a remainder, sequences
+    shorter than a chunk and empty ones, candidate ranges, k = 0 and k beyond the candidates, at odd
+    addresses; scores that differ only in their last digit, ties across chunks.  Exact."""
+    rng = np.random.default_rng(sum(lens))
+    heads, cu = 2, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    shape = (heads, sum(lens))
+    scores = {"spread": rng.random(shape) ** 6, "equal": np.full(shape, 0.25), "signs": rng.normal(size=shape),
+              "low_bits": np.float32(1.0) + rng.integers(0, 900, shape) * 2.0 ** -23,
+              "infinities": np.where(rng.random(shape) < 0.6, -np.inf, rng.choice([np.inf, 1.0, -0.0, 0.0], shape))}
+    s32 = scores[dist].astype(np.float32)
+    n = np.array(lens, dtype=np.int32)
+    for begin, end, k in ((n * 0, n, n // 3), (n // 7, n - n // 9, n // 2), (n // 7, n - n // 9, n * 0), (n // 2, n, n)):
+        cand_b, cand_e = begin.astype(np.int32), end.astype(np.int32)
+        k_keep = np.minimum(k, n).astype(np.int32)
+        cu_keep = np.concatenate([[0], np.cumsum(k_keep)]).astype(np.int32)
+        desc = pdd.AttnDesc()
+        desc.batch, desc.n_q_heads, desc.n_kv_heads, desc.head_dim = len(lens), heads, heads, 128
+        desc.total_q = desc.total_k = int(cu[-1])
+        desc.max_seqlen_q = desc.max_seqlen_k = max(lens)
+        need = pdd.workspace_bytes(desc, pdd.CALL_SELECT_TOPK)
+        assert need > 0
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        sc = torch.from_numpy(np.concatenate([[9.0], s32.ravel()]).astype(np.float32)).cuda()[1:].view(shape)   # 4-byte aligned
+        idx = torch.full((heads, int(cu_keep[-1])), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full((s32.size + 3,), 9, dtype=torch.uint8, device="cuda")[3:].view(shape)
+        dev = lambda a: torch.from_numpy(a).cuda()
+        pdd.select_topk(sc, dev(cu), max(lens), dev(k_keep), dev(cu_keep), int(cu_keep[-1]), idx, mask, dev(cand_b),
+                        dev(cand_e), cu, workspace=ws)
+        taken = np.minimum(k_keep, cand_e - cand_b)
+        want_idx, want_mask = oracle.select_topk(s32.astype(np.float64), cu, taken, cand_b, cand_e)
+        got, cu_want = idx.cpu().numpy(), np.concatenate([[0], np.cumsum(taken)])
+        for b in range(len(lens)):
+            row = got[:, cu_keep[b]:cu_keep[b + 1]]
+            assert np.array_equal(row[:, :taken[b]], want_idx[:, cu_want[b]:cu_want[b + 1]])
+            assert (row[:, taken[b]:] == -1).all()
+        assert np.array_equal(mask.cpu().numpy(), want_mask)
+        assert (ws != 0xFF).any() or not taken.any(), "the scratch was not used"
+
+
 @pytest.mark.parametrize("name", ["c1", "c2", "c3", "c5", "c4"])
 def test_gate_a_oracle_scores_of_every_configuration(name):
     """The oracle's importance of each benchmark configuration, rounded to fp32, through the GPU
