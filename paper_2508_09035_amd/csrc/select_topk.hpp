@@ -75,7 +75,7 @@ __device__ __forceinline__ uint32_t order_key(float x)
 // row's part that starts at a 16-byte boundary of the score tensor (the up to three candidates
 // before it sit one each in the first lanes of wave 0): 16-byte loads, the mask written four
 // bytes at a time where the mask tensor's alignment allows it.
-// POOL = true ranks the 1-D pooled scores (evaluated while loading; no 16-byte loads then);
+// POOL = true ranks the 1-D pooled scores (see PoolStage);
 // the instantiation for unpooled scores carries none of the pooling code.
 // ---------------------------------------------------------------------------
 constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 32 probes (see next_probe)
@@ -147,6 +147,88 @@ __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx)
     PDD_MINMAX_STEP(0x143, 0xc)
 #undef PDD_MINMAX_STEP
 }
+
+// Pooled scores of kSelPoolStep consecutive keys at a time, four per thread.  The scores of a step
+// and the pool_r on either side of it pass through LDS once, 16 bytes per lane (the scores outside
+// the sequence as the neutral element), those of the next step requested meanwhile; a window is
+// added up (or its maximum taken) in key order, the four windows of a thread from shared reads.
+// (Read from memory by every window on its own, 2 r + 1 loads per key, the four prompts of 2360 to 12001
+// keys x 8 heads took 34 us with r = 3 and 2480 us with r = 512; 20 and 87 us like this.)
+constexpr int kSelPoolStep = 4 * kSelThreads;
+constexpr int kSelPoolMax = 512;        // largest radius
+typedef float pool_f32x4 __attribute__((ext_vector_type(4), aligned(4)));       // four scores at any score's address
+
+struct PoolStage {
+    const int r;
+    const bool is_max;
+    const float none, scale;            // neutral element; what the sum is multiplied with
+    pool_f32x4 next[2];
+    __device__ explicit PoolStage(const SelParams &p)
+        : r(p.pool_r), is_max(p.pool_mode == kPoolMax), none(is_max ? -INFINITY : 0.f), scale(is_max ? 1.f : p.pool_inv) {}
+
+    // scores first - r + 4 tid .. + 3 and, where they belong to the step, the same kSelPoolStep further
+    __device__ __forceinline__ void request(const float *seq, int nk, int first, int tid)
+    {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int at = q * kSelPoolStep + 4 * tid, x = first - r + at;
+            if (at < kSelPoolStep + 2 * r) {
+                if (x >= 0 && x + 4 <= nk) next[q] = *(const pool_f32x4 *)(seq + x);
+                else
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) next[q][j] = x + j >= 0 && x + j < nk ? seq[x + j] : none;
+            }
+        }
+    }
+
+    // the thread's four pooled scores of keys first + 4 tid .. + 3
+    __device__ __forceinline__ void step(const float *seq, int nk, int first, bool is_first, bool more, int tid, float (&out)[4])
+    {
+        __shared__ __attribute__((aligned(16))) float stage[kSelPoolStep + 2 * kSelPoolMax];
+        if (is_first) request(seq, nk, first, tid);
+        else __syncthreads();                                    // the last step's reads are done
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int at = q * kSelPoolStep + 4 * tid;
+            if (at < kSelPoolStep + 2 * r) *(float4 *)(stage + at) = make_float4(next[q][0], next[q][1], next[q][2], next[q][3]);
+        }
+        __syncthreads();
+        if (more) request(seq, nk, first + kSelPoolStep, tid);
+        const float4 *quads = (const float4 *)stage + tid;
+        if (is_max) windows(quads, out, [](float a, float x) { return fmaxf(a, x); });
+        else windows(quads, out, [](float a, float x) { return a + x; });
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] *= scale;
+    }
+
+    // window j = elements j .. j + 2 r from the first quad on
+    template <typename Op>
+    __device__ __forceinline__ void windows(const float4 *quads, float (&out)[4], Op op)
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] = none;
+        auto edge = [&](int q) {
+            const float4 t = quads[q];
+            const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * q + e >= j && 4 * q + e <= j + 2 * r) out[j] = op(out[j], v[e]);
+        };
+        edge(0);
+        int q = 1;
+        for (; 4 * q + 3 <= 2 * r; ++q) {                        // in all four windows
+            const float4 t = quads[q];
+            const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) out[j] = op(out[j], v[e]);
+        }
+        for (; 4 * q <= 2 * r + 3; ++q) edge(q);
+    }
+};
 
 // The r-th largest (1 <= r <= m) of m <= kSelFinish keys in LDS, slots m .. kSelFinish + 3 zero, by
 // the lanes of one wave: true in the one lane that then holds it and the number of larger keys.
@@ -231,15 +313,20 @@ void select_topk_reg_kernel(const SelParams p)
     const float *qbase = seq + c0 + nhead;                       // 16-byte aligned (unpooled)
     uint32_t key[QPT][4];
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    PoolStage pool(p);
 #pragma unroll
     for (int i = 0; i < QPT; ++i) {
         const int xw = 4 * (i * kSelThreads + 64 * wave_u);      // the wave's first index of this step
         if constexpr (POOL) {
-            const int x0 = xw + 4 * lane;
+            if (i * kSelPoolStep < n) {                          // the same in every thread
+                float pooled[4];
+                pool.step(seq, nk, c0 + i * kSelPoolStep, i == 0, (i + 1) * kSelPoolStep < n, tid, pooled);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                key[i][j] = (x0 + j < nq_el)
-                    ? order_key(pooled_score(seq, nk, c0 + x0 + j, p.pool_r, p.pool_mode, p.pool_inv)) : 0u;
+                for (int j = 0; j < 4; ++j) key[i][j] = (xw + 4 * lane + j < n) ? order_key(pooled[j]) : 0u;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) key[i][j] = 0u;
+            }
         } else if (xw + 255 < nq_el) {                           // all of its 64 quads lie inside the row
             const float4 t = *(const float4 *)(qbase + xw + 4 * lane);
             key[i][0] = order_key(t.x);  key[i][1] = order_key(t.y);

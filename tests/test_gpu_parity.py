@@ -803,6 +803,33 @@ def test_pooled_selection(case, mode, kernel):
     check_selection(want_pooled, dev.idx.cpu().numpy(), dev.mask.cpu().numpy(), wl, 1e-6, "pooled fp64")
 
 
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("kernel", [3, 129, 1025])
+@pytest.mark.parametrize("lens", [[1, 3, 4096, 300], [4097, 8193], [32768]])
+def test_pooled_selection_windows(lens, kernel, mode):
+    """Windows of the smallest and the largest size around the edges of a step of 4096 keys, wider than the
+    sequence, and reaching keys outside the candidate range; negative scores.  Same checks as above."""
+    rng = np.random.default_rng(kernel)
+    wl = W.make_custom("t", lens, None, 1, 1, 64, 0, seed=0)
+    wl.n_kv_heads = 2
+    s32 = rng.normal(size=(2, sum(lens))).astype(np.float32)
+    n = np.array(lens, dtype=np.int32)
+    wl.cand_begin, wl.cand_end = n // 5, n - n // 6
+    wl.k_keep = ((wl.cand_end - wl.cand_begin + 2) // 3).astype(np.int32)
+    want = oracle.pool_scores(s32.astype(np.float64), wl.cu_seqlens_k, kernel, mode)
+    dev = DeviceWorkload(wl)
+    dev.poison()
+    pooled = torch.full(s32.shape, float("nan"), dtype=torch.float32, device="cuda")
+    pdd.select_topk_pooled(torch.from_numpy(s32).cuda(), dev.cu_k, dev.max_k, dev.k_keep, dev.cu_keep, dev.total_keep,
+                           dev.idx, dev.mask, kernel, pdd.POOL_MAX if mode == "max" else pdd.POOL_AVG, pooled,
+                           dev.cand_b, dev.cand_e, wl.cu_seqlens_k)
+    got = pooled.cpu().numpy().astype(np.float64)
+    # one fp32 chain of up to 1025 additions of values of size 1, times 1 / kernel (itself rounded)
+    atol = 0 if mode == "max" else kernel * 2.0 ** -24 * np.abs(s32).max() * 2
+    np.testing.assert_allclose(got, want, rtol=0, atol=atol)
+    check_selection(got, dev.idx.cpu().numpy(), dev.mask.cpu().numpy(), wl, -1, "pooled")
+
+
 # ------------------------------------------------- sentence-level selection
 def _sentence_split(rng, lo, hi, mean_len, with_empty):
     """Ends of sentences tiling [lo, hi): geometric lengths, optionally a few empty ones."""
