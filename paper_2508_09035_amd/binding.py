@@ -7,6 +7,9 @@ import ctypes
 import os
 from typing import Optional
 
+import numpy as np
+import torch
+
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG_DIR, "libpdd.so")
 _lib = None
@@ -113,17 +116,21 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The calls below spend about as long on the host as the smallest of them on the GPU, so the
+# marshalling takes the short ways: the current stream's handle without a Stream object (1.5 -> 0.3
+# us), a host array's address without numpy's ctypes view (1.2 -> 0.3 us), a descriptor filled by its
+# constructor (8 -> 3 us).
 def _stream() -> Optional[int]:
-    import torch
-    return torch.cuda.current_stream().cuda_stream or None
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
 
 
 def _host_i32(a):
     """Keep a contiguous int32 host array alive and return (array, address)."""
-    import numpy as np
     if a is None:
         return None, None
     arr = np.ascontiguousarray(a, dtype=np.int32)
+    if arr.flags.writeable and arr.size:
+        return arr, ctypes.addressof(ctypes.c_int32.from_buffer(arr))
     return arr, arr.ctypes.data
 
 
@@ -134,21 +141,13 @@ def make_desc(q, k, v, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q: int, max_seq
     the importance-only call).  Returns (desc, keepalive)."""
     qh, qh_addr = _host_i32(cu_seqlens_q_host)
     kh, kh_addr = _host_i32(cu_seqlens_k_host)
-    d = AttnDesc()
-    d.batch = cu_seqlens_q.numel() - 1
-    d.n_q_heads, d.n_kv_heads, d.head_dim = q.shape[1], k.shape[1], q.shape[2]
-    d.total_q, d.total_k = q.shape[0], k.shape[0]
-    d.max_seqlen_q, d.max_seqlen_k = int(max_seqlen_q), int(max_seqlen_k)
-    d.cu_seqlens_q, d.cu_seqlens_k = cu_seqlens_q.data_ptr(), cu_seqlens_k.data_ptr()
-    d.cu_seqlens_q_host, d.cu_seqlens_k_host = qh_addr, kh_addr
-    d.q_stride_tok, d.q_stride_head = q.stride(0), q.stride(1)
-    d.k_stride_tok, d.k_stride_head = k.stride(0), k.stride(1)
-    if v is not None:
-        d.v_stride_tok, d.v_stride_head = v.stride(0), v.stride(1)
-    if o is not None:
-        d.o_stride_tok, d.o_stride_head = o.stride(0), o.stride(1)
-    d.softmax_scale = float(softmax_scale)
-    d.window = int(window)
+    total_q, n_q_heads, head_dim = q.shape[:3]
+    total_k, n_kv_heads = k.shape[:2]
+    d = AttnDesc(cu_seqlens_q.numel() - 1, n_q_heads, n_kv_heads, head_dim, total_q, total_k,
+                 int(max_seqlen_q), int(max_seqlen_k), cu_seqlens_q.data_ptr(), cu_seqlens_k.data_ptr(),
+                 qh_addr, kh_addr, *q.stride()[:2], *k.stride()[:2],
+                 *((0, 0) if v is None else v.stride()[:2]), *((0, 0) if o is None else o.stride()[:2]),
+                 float(softmax_scale), int(window))
     return d, (qh, kh)
 
 
@@ -295,7 +294,6 @@ def choose_r_L(l, k_c, k_d, delta, xi_scene, tpot_c, tpot_d, tau, delta_cloud=0.
 def pack_mask_layout(cu_seqlens_k_host):
     """pdd_pack_mask_layout (host only): int32 numpy prefix sums of the per-sequence byte
     counts of the bit stream, and the bytes per row."""
-    import numpy as np
     cu = np.ascontiguousarray(cu_seqlens_k_host, dtype=np.int32)
     out = np.zeros(len(cu), dtype=np.int32)
     total = load_library().pdd_pack_mask_layout(len(cu) - 1, cu.ctypes.data, out.ctypes.data)
