@@ -6,14 +6,20 @@
 // One workgroup of 1024 threads per (sequence, head) row; scores become
 // order-preserving uint32 keys.  Two kernels:
 //
-//  * select_topk_reg_kernel<EPT> (rows of up to 1024*EPT <= 32768 candidates):
-//    every thread keeps its EPT keys in registers for the whole kernel.  The
-//    k-th largest key is found by bisection on the key value inside the row's
-//    [min, max] range: one step = EPT compares per lane, wave ballots counted
-//    on the scalar unit, one 16-entry LDS exchange.  No LDS atomics (measured
-//    at ~30 cycles per wave instruction, they dominated the radix variant)
-//    and no re-reading of the row.  The kept indices are written in ascending
-//    order from ballot prefix counts, with a 16*EPT-entry scan across waves.
+//  * select_topk_reg_kernel<QPT> (rows of up to 4096 * QPT <= 32768 candidates):
+//    every thread keeps its 4 QPT keys in registers for the whole kernel.  The k-th
+//    largest key is found in a few rounds of two probes on the key value: one round = two
+//    compares per key, wave ballots counted on the scalar unit and lane counts on the
+//    vector unit, one LDS counter.  A histogram (of a sample, where the row is long)
+//    places the first bracket, and the keys left in it move to LDS early, because a
+//    round costs by its instructions: 16 cycles each with four waves per SIMD.  The row is
+//    not read again.  The kept indices are written in ascending order from
+//    prefix counts, with a 16 * QPT-entry scan across waves.
+//    By single interpolated or bisecting probes from the row's range on (8 to 11, 27 with many
+//    ties) 8 rows took, scores spread over octaves / log-normal: 4096 9.5 / 10.5 us, 16384 13.6 / 16.2,
+//    32768 20.0 / 21.3, 512 rows of 32768 42.1 / 47.4; now 6.5 / 6.3, 11.6 / 11.6, 17.0 / 17.2, 36.7 / 37.0.
+//    Histograms of all keys of long rows were slower: 50 cycles per LDS atomic of a wave.  So
+//    were fewer threads with more keys each (256 x 16: 9.7 us at 4096).
 //  * select_topk_kernel (longer rows without a workspace, pooled, or very many of them;
 //    see select_split.hpp for the others): most-significant-first radix select,
 //    8 bits per pass, digits taken from (key - min key) scaled to the row's
@@ -41,7 +47,9 @@ struct SelParams {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelFinish = 64;    // keys left in the bracket that are ranked directly
+constexpr int kSelFinish = 128;   // keys left in the bracket that are ranked directly
+constexpr int kSelList = 4 * kSelThreads;     // keys left in the bracket that move to four per thread
+constexpr int kSelBins = 1024;    // of the histograms that place the bracket, one bin per thread
 constexpr int kSelRegCap = 32 * 1024;  // rows up to this many candidates stay in registers
 
 // Score of key j after 1-D pooling along the sequence (paper Section 3.2: a pooling step
@@ -78,7 +86,7 @@ __device__ __forceinline__ uint32_t order_key(float x)
 // POOL = true ranks the 1-D pooled scores (see PoolStage);
 // the instantiation for unpooled scores carries none of the pooling code.
 // ---------------------------------------------------------------------------
-constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 32 probes (see next_probe)
+constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 21 rounds by thirds, 8 that cut the keys to a quarter
 
 // inclusive prefix sum over the 64 lanes of a wave (DPP row shifts and row broadcasts)
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
@@ -230,25 +238,55 @@ struct PoolStage {
     }
 };
 
-// The r-th largest (1 <= r <= m) of m <= kSelFinish keys in LDS, slots m .. kSelFinish + 3 zero, by
-// the lanes of one wave: true in the one lane that then holds it and the number of larger keys.
-__device__ __forceinline__ bool rank_in_wave(const uint32_t *keys, int m, uint32_t r, int lane, uint32_t &key, uint32_t &gt)
+// Next pair a <= b of values to probe in the threshold search of select_topk_reg_kernel over the
+// bracket [lo, hi] (lo < hi) that holds `inside` keys, of which the `need` largest (1 <= need <=
+// inside) lie at or above the threshold; both in [lo + 1, hi].  With interpolate set, the keys are taken as
+// evenly spread over the bracket, and the pair encloses the threshold's place by two standard
+// deviations of the number of keys above it and a sixteenth of the keys (scores are evenly spread
+// over no more than an octave); otherwise the bracket is cut into thirds.  (The approximate
+// reciprocal and root only place the probes.)
+__device__ __forceinline__ void next_pair(uint32_t lo, uint32_t hi, uint32_t inside, uint32_t need, bool interpolate,
+                                          uint32_t &a, uint32_t &b)
 {
-    key = lane < m ? keys[lane] : 0u;
-    gt = 0;
-    uint32_t ge = 0;
-    for (int j0 = 0; j0 < m; j0 += 4) {                           // slots past m hold 0: below every key
-        const uint4 o4 = *(const uint4 *)(keys + j0);
-        const uint32_t o[4] = {o4.x, o4.y, o4.z, o4.w};
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            gt += o[x] > key ? 1u : 0u;
-            ge += o[x] >= key ? 1u : 0u;
-        }
+    const uint32_t span = hi - lo;
+    if (!interpolate) {
+        a = lo + 1u + span / 3u;
+        b = hi - span / 3u;
+        return;
     }
-    const bool hit = lane < m && gt < r && r <= ge;               // every hit lane holds the same key
-    const uint64_t hb = __ballot(hit);
-    return hb != 0 && lane == (int)__builtin_ctzll(hb);
+    const float keys = (float)inside, each = __builtin_amdgcn_rcpf(keys), per_key = (float)span * each;
+    const float down = (float)need - 0.5f;                        // keys between hi and the threshold
+    const float dev = 2.f * __builtin_amdgcn_sqrtf(down * fmaxf(1.f - down * each, 0.f)) + 0.0625f * keys + 2.f;
+    a = hi - min((uint32_t)fminf((down + dev) * per_key, 4294967040.f), span - 1u);
+    b = hi - min((uint32_t)fminf(fmaxf(down - dev, 0.f) * per_key, 4294967040.f), hi - a);
+}
+
+// Wave 0's part of a histogram step over kSelBins bins: the bins in which the keys of rank r0 and r1
+// (from the top) lie, the keys above the first of them, and its own.  Untouched where there is no such rank.
+struct SelPlace { int32_t bin[2]; uint32_t above, own; };
+__device__ __forceinline__ uint32_t hist_total(const uint32_t *hist, int lane, uint32_t (&bin)[16], uint32_t &incl)
+{
+    uint32_t sum = 0;                                            // lane: 16 consecutive bins
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint4 t = ((const uint4 *)hist)[4 * lane + q];
+        bin[4 * q] = t.x;  bin[4 * q + 1] = t.y;  bin[4 * q + 2] = t.z;  bin[4 * q + 3] = t.w;
+        sum += (t.x + t.y) + (t.z + t.w);
+    }
+    incl = wave_incl_scan(sum);
+    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+}
+__device__ __forceinline__ void hist_place(const uint32_t (&bin)[16], uint32_t total, uint32_t incl, int lane, int r0, int r1,
+                                           SelPlace *out)
+{
+    int run = (int)(total - incl);
+#pragma unroll
+    for (int e = 15; e >= 0; --e) {
+        const int up = run + (int)bin[e];
+        if (run < r0 && r0 <= up) { out->bin[0] = 16 * lane + e; out->above = (uint32_t)run; out->own = bin[e]; }
+        if (run < r1 && r1 <= up) out->bin[1] = 16 * lane + e;
+        run = up;
+    }
 }
 
 // At most 64 vector registers, so that two workgroups (8 waves per SIMD) share a compute unit: the
@@ -258,11 +296,12 @@ template <int QPT, bool POOL>
 __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void select_topk_reg_kernel(const SelParams p)
 {
-    __shared__ uint32_t wave_min[kSelWaves], wave_max[kSelWaves];
     __shared__ uint32_t cnt[kSelWaves * QPT];          // per (i, wave): gt count | eq count << 16
-    __shared__ uint32_t probe_tot[kSelMaxProbes];      // count of probe number p, summed over the waves
-    __shared__ __attribute__((aligned(16))) uint32_t fin_keys[kSelFinish + 4];
-    __shared__ uint32_t fin_count, fin_T, fin_above, head_tot;
+    __shared__ uint32_t probe_tot[kSelMaxProbes];      // counts of pair number p, summed over the waves
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins], fin_keys[kSelFinish + 4];
+    __shared__ uint32_t list[QPT > 1 ? kSelList : 1];
+    __shared__ uint32_t sh_min, sh_max, list_count, fin_count, fin_T, fin_above, head_tot;
+    __shared__ SelPlace place;
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -287,6 +326,17 @@ void select_topk_reg_kernel(const SelParams p)
     int32_t *out = p.out_idx + (int64_t)g * p.total_keep + keep0;
     uint8_t *mrow = p.out_mask ? p.out_mask + (int64_t)g * p.total_k + ks : nullptr;
 
+    hist[tid] = 0;
+    if (tid < kSelMaxProbes) probe_tot[tid] = 0;
+    if (tid < kSelFinish + 4) fin_keys[tid] = 0;
+    if (tid == 0) {
+        list_count = fin_count = 0;
+        sh_min = 0xffffffffu;
+        sh_max = 0;
+        place.bin[0] = kSelBins - 1;
+        place.bin[1] = 0;
+    }
+    __syncthreads();
     if (p.pooled_out) {
         float *po = p.pooled_out + (int64_t)g * p.total_k + ks;
         if constexpr (POOL) {
@@ -346,71 +396,176 @@ void select_topk_reg_kernel(const SelParams p)
         kmax = max(kmax, max(max(key[i][0], key[i][1]), max(key[i][2], key[i][3])));
     }
     wave_min_max(kmin, kmax);
-    if (lane == 63) { wave_min[wave] = kmin; wave_max[wave] = kmax; }
-    if (tid < kSelMaxProbes) probe_tot[tid] = 0;
-    if (tid < kSelFinish + 4) fin_keys[tid] = 0;
-    if (tid == 0) fin_count = 0;
+    if (lane == 63) { atomicMin(&sh_min, kmin); atomicMax(&sh_max, kmax); }
     __syncthreads();
-    kmin = wave_min[0];  kmax = wave_max[0];
-#pragma unroll
-    for (int w = 1; w < kSelWaves; ++w) { kmin = min(kmin, wave_min[w]); kmax = max(kmax, wave_max[w]); }
-    kmin += 1u;                                                  // back from key - 1 (kk >= 1: the row has a real key)
 
-    // ---- threshold search: largest T in [kmin, kmax] with count(key >= T) >= kk, by probes on the
-    // key value with the bracket [lo, hi] and the two counts c_lo = count(key >= lo) >= kk >
-    // c_above = count(key > hi) (see next_probe).  Every probed value is > lo >= kmin > 0, so empty
-    // slots never count.  The waves' counts of a probe meet in an LDS counter of their own (integer
-    // atomics; one fresh counter per probe, so none is ever cleared), which every thread reads
-    // back after the barrier.  Once at most kSelFinish keys are left inside the bracket they are
-    // collected in LDS (in any order) and one wave ranks them directly.
-    uint32_t lo = kmin, hi = kmax;
-    uint32_t c_lo = (uint32_t)n, c_above = 0;
-    bool interp = true;
-    int probe = 0;
-    while (lo < hi && c_lo - c_above > (uint32_t)kSelFinish) {
+    // ---- threshold search: largest T in the row's range with count(key >= T) >= kk, over the bracket [lo, hi] with
+    // c_lo = count(key >= lo) >= kk > c_above = count(key > hi), in rounds of two probes (see next_pair).
+    // A round costs the workgroup some thousand cycles with few keys per thread, twice that with 32, so
+    //   * rows of up to 4096 candidates count all of them into bins over the row's range and go on in
+    //     the bin that holds the threshold;
+    //   * longer rows do so with about 1024 keys, spread over the row, which gives two bins that enclose
+    //     the threshold but for some three standard deviations of its rank: the first pair of probes;
+    //   * once at most 4096 keys are left inside the bracket, these move to LDS and four to a thread, and
+    //     once at most kSelFinish are left they are ranked directly.
+    // Every probed value is > lo > 0, so empty slots never count.
+    uint32_t lo = sh_min + 1u, hi = sh_max;                      // lo: back from key - 1 (kk >= 1: the row has a real key)
+    uint32_t c_lo = (uint32_t)n, c_above = 0, pa = 0, pb = 0;
+    bool placed = false, interp = true;
+    int round = 0;
+    const int shift = max(32 - __builtin_clz((hi - lo) | 1u) - 10, 0);     // kSelBins = 2^10
+    // One round: `count` adds this wave's keys >= pa to its first argument and those >= pb to the second.
+    // The waves' sums meet in an LDS counter of their own (one fresh counter per round, so none is ever
+    // cleared), two to a word: a count is at most 32768.
+    auto probe = [&](auto &&count) {
         const uint32_t inside = c_lo - c_above;
-        const uint32_t mid = next_probe(lo, hi, inside, (uint32_t)kk - c_above, interp);
-        // Half of the comparisons are counted with a ballot and a scalar population count, half per
-        // lane on the vector unit with one wave sum at the end.  The 16 waves of the workgroup (and
-        // a second workgroup on the same compute unit) share one scalar unit: all on it, the probe
-        // queues there (1.87 TB/s over 512 rows of 32768); all on the vector unit is slower again
-        // (2.17 TB/s); the split reaches 2.29 TB/s.
-        uint32_t c = (uint32_t)__popcll(__ballot(khead >= mid));
-        uint32_t cl[2] = {0u, 0u};
-#pragma unroll
-        for (int i = 0; i < QPT; ++i) {
-            c += (uint32_t)__popcll(__ballot(key[i][0] >= mid));
-            c += (uint32_t)__popcll(__ballot(key[i][1] >= mid));
-            cl[0] += key[i][2] >= mid ? 1u : 0u;
-            cl[1] += key[i][3] >= mid ? 1u : 0u;
-        }
-        c += (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(cl[0] + cl[1]), 63);
-        if (lane == 0) atomicAdd(&probe_tot[probe], c);
+        if (!placed) next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
+        placed = false;
+        uint32_t ca = 0, cb = 0, la = 0, lb = 0;                 // of the wave; of the lane
+        count(ca, cb, la, lb);
+        const uint32_t both = (ca | cb << 16) + (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(la | lb << 16), 63);
+        if (lane == 0) atomicAdd(&probe_tot[round], both);
         __syncthreads();
-        const uint32_t tot = probe_tot[probe];
-        ++probe;
-        if (tot >= (uint32_t)kk) { lo = mid; c_lo = tot; }
-        else { hi = mid - 1u; c_above = tot; }
+        const uint32_t tot = probe_tot[round], tot_a = tot & 0xffffu, tot_b = tot >> 16;
+        ++round;
+        if (tot_b >= (uint32_t)kk) { lo = pb; c_lo = tot_b; }
+        else {
+            c_above = tot_b;
+            hi = pb - 1u;
+            if (tot_a >= (uint32_t)kk) { lo = pa; c_lo = tot_a; }
+            else { hi = pa - 1u; c_above = tot_a; }
+        }
         interp = !interp || 4u * (c_lo - c_above) <= inside;
+    };
+    constexpr int NL = QPT > 1 ? kSelList / kSelThreads : 5;
+    uint32_t lk[NL];                                             // the thread's keys of the second part of the search
+    uint32_t list_above = 0;                                     // keys above all of those
+    if constexpr (QPT > 1) {
+        if (lo < hi && n > kSelList) {
+            uint32_t k = key[0][0];
+#pragma unroll
+            for (int o = 1; o < QPT; ++o) k = (tid & (QPT - 1)) == o ? key[o][0] : k;
+            if (k != 0) atomicAdd(&hist[(k - lo) >> shift], 1u);
+            __syncthreads();
+            if (wave == 0) {
+                uint32_t bin[16], incl;
+                const uint32_t m = hist_total(hist, lane, bin, incl);
+                const float share = (float)kk * __builtin_amdgcn_rcpf((float)n), rank = share * (float)m;
+                const float dev = 3.f * __builtin_amdgcn_sqrtf(rank * fmaxf(1.f - share, 0.f)) + 1.f;
+                hist_place(bin, m, incl, lane, (int)(rank - dev), (int)(rank + dev) + 1, &place);
+            }
+            __syncthreads();
+            // upper edge of the one bin, lower edge of the other; the row's ends where there is none
+            pb = lo + (place.bin[0] == kSelBins - 1 ? hi - lo : min((uint32_t)(place.bin[0] + 1) << shift, hi - lo));
+            pa = min(lo + max((uint32_t)place.bin[1] << shift, 1u), pb);
+            placed = true;
+            // Half of the comparisons are counted with a ballot and a scalar population count, half per
+            // lane on the vector unit with one wave sum at the end.  The 16 waves of the workgroup (and
+            // a second workgroup on the same compute unit) share one scalar unit: all on it, the probes
+            // queue there (512 rows of 32768, single probes: 1.87 TB/s); all on the vector unit is slower
+            // again (2.17 TB/s); the split reaches 2.29 TB/s.
+            while (lo < hi && c_lo - c_above > (uint32_t)kSelList)
+                probe([&](uint32_t &ca, uint32_t &cb, uint32_t &la, uint32_t &lb) {
+                    ca = (uint32_t)__popcll(__ballot(khead >= pa));
+                    cb = (uint32_t)__popcll(__ballot(khead >= pb));
+#pragma unroll
+                    for (int i = 0; i < QPT; ++i) {
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            ca += (uint32_t)__popcll(__ballot(key[i][j] >= pa));
+                            cb += (uint32_t)__popcll(__ballot(key[i][j] >= pb));
+                            la += key[i][j + 2] >= pa ? 1u : 0u;
+                            lb += key[i][j + 2] >= pb ? 1u : 0u;
+                        }
+                    }
+                });
+        }
+        if (lo < hi) {                                           // at most kSelList keys lie in [lo, hi]
+            const uint32_t width = hi - lo;                      // empty slots, key 0 < lo, wrap past it
+            uint32_t c = khead - lo <= width ? 1u : 0u;
+#pragma unroll
+            for (int i = 0; i < QPT; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) c += key[i][j] - lo <= width ? 1u : 0u;
+            const uint32_t incl = wave_incl_scan(c);
+            uint32_t at = 0;
+            if (lane == 63 && incl > 0) at = atomicAdd(&list_count, incl);
+            uint32_t *dst = list + (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - c;
+            if (khead - lo <= width) *dst++ = khead;
+            // compared again against a copy of lo the compiler cannot relate to the first (see Tc below)
+            uint32_t lc = lo;
+            asm volatile("" : "+v"(lc));
+#pragma unroll
+            for (int i = 0; i < QPT; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (key[i][j] - lc <= width) *dst++ = key[i][j];
+            list_above = c_above;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NL; ++q) lk[q] = q * kSelThreads + tid < (int)(c_lo - c_above) ? list[q * kSelThreads + tid] : 0u;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lk[j] = key[0][j];
+        lk[4] = khead;
     }
-    if (lo < hi) {
-        // at most kSelFinish keys lie in [lo, hi] (empty slots, key 0 < lo, fall outside by the
-        // unsigned wrap): the (kk - c_above)-th largest of them is T
-        const uint32_t width = hi - lo;
-        if (khead - lo <= width) fin_keys[atomicAdd(&fin_count, 1u)] = khead;
+    if (lo < hi && n > kSelFinish && n <= kSelList) {            // the row's keys are all in lk
 #pragma unroll
-        for (int i = 0; i < QPT; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (key[i][j] - lo <= width) fin_keys[atomicAdd(&fin_count, 1u)] = key[i][j];
+        for (int q = 0; q < NL; ++q)
+            if (lk[q] != 0) atomicAdd(&hist[(lk[q] - lo) >> shift], 1u);
         __syncthreads();
         if (wave == 0) {
-            uint32_t key_T, gt;
-            if (rank_in_wave(fin_keys, (int)fin_count, (uint32_t)kk - c_above, lane, key_T, gt)) {
-                fin_T = key_T;
-                fin_above = c_above + gt;
+            uint32_t bin[16], incl;
+            const uint32_t m = hist_total(hist, lane, bin, incl);
+            hist_place(bin, m, incl, lane, kk, 0, &place);
+        }
+        __syncthreads();
+        const uint32_t first = (uint32_t)place.bin[0] << shift;
+        hi = lo + min(first + ((1u << shift) - 1u), hi - lo);
+        lo += first;
+        c_above = place.above;
+        c_lo = place.above + place.own;
+    }
+    while (lo < hi && c_lo - c_above > (uint32_t)kSelFinish)
+        probe([&](uint32_t &ca, uint32_t &, uint32_t &la, uint32_t &lb) {
+            // the list has none of the keys above it
+            if (wave == 0) ca = list_above | list_above << 16;
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                la += lk[q] >= pa ? 1u : 0u;
+                lb += lk[q] >= pb ? 1u : 0u;
+            }
+        });
+    if (lo < hi) {
+        // at most kSelFinish keys lie in [lo, hi]: the (kk - c_above)-th largest of them is T
+        const uint32_t width = hi - lo;
+#pragma unroll
+        for (int q = 0; q < NL; ++q)
+            if (lk[q] - lo <= width) fin_keys[atomicAdd(&fin_count, 1u)] = lk[q];
+        __syncthreads();
+        // eight lanes to a key
+        constexpr int PER = kSelThreads / kSelFinish;
+        const int m = (int)(c_lo - c_above);
+        const uint32_t mine = fin_keys[tid / PER];
+        uint32_t above = 0, upto = 0;
+#pragma unroll
+        for (int q = 0; q < kSelFinish / (4 * PER); ++q) {       // slots past m hold 0: below every key
+            const uint4 o4 = *(const uint4 *)(fin_keys + 4 * (q * PER + (tid & (PER - 1))));
+            const uint32_t o[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                above += o[x] > mine ? 1u : 0u;
+                upto += o[x] >= mine ? 1u : 0u;
             }
         }
+        uint32_t both = above | upto << 16;
+#pragma unroll
+        for (int off = 1; off < PER; off <<= 1) both += (uint32_t)__shfl_xor((int)both, off, 64);
+        above = both & 0xffffu;
+        upto = both >> 16;
+        const uint32_t r = (uint32_t)kk - c_above;               // 1 <= r <= m
+        if (tid / PER < m && above < r && r <= upto) { fin_T = mine; fin_above = c_above + above; }      // equal keys only
         __syncthreads();
         lo = fin_T;
         c_above = fin_above;

@@ -452,6 +452,30 @@ def test_select_long_rows_beyond_lds_staging():
     _select_case(s, lens, [1, 33000])
 
 
+@pytest.mark.parametrize("n", [128, 129, 132, 4095, 4096, 4097, 8192, 16384, 32767])
+def test_select_threshold_search_off_its_good_path(n):
+    """Rows whose sample says nothing about them (every fourth score high, the position within a quad
+    that is sampled; the rest of the keys in another range), two values, neighbouring floats, a few values far
+    apart, a heavy tie among spread scores: k from 1 to n.  Exact."""
+    rng = np.random.default_rng(n)
+    x = np.arange(n)
+    u = rng.random(n)
+    rows = np.stack([np.where(x % 4 == 0, 1e6 + x, u), np.where(x % 4 == 0, u * 1e-6, 1.0 + u), np.where(u < 0.3, 2.0, -1.0),
+                     1.0 + rng.integers(0, n, n) * 2.0 ** -23, 10.0 ** rng.integers(-30, 30, n),
+                     np.where(u < 0.5, 0.7, rng.random(n) ** 6)]).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cu = np.array([0, n], dtype=np.int32)
+    scores = dev(rows)
+    for k in sorted({1, 2, n // 10, n // 4, n // 2, 3 * n // 4, n - 1, n}):
+        keep = np.array([k], dtype=np.int32)
+        idx = torch.full((len(rows), k), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full(rows.shape, 9, dtype=torch.uint8, device="cuda")
+        pdd.select_topk(scores, dev(cu), n, dev(keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask, None, None, cu)
+        want_idx, want_mask = oracle.select_topk(rows.astype(np.float64), cu, keep)
+        assert np.array_equal(idx.cpu().numpy(), want_idx), f"k = {k}"
+        assert np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
+
+
 @pytest.mark.parametrize("dist", ["spread", "equal", "low_bits", "signs", "infinities"])
 @pytest.mark.parametrize("lens", [[32769], [36864, 5, 0, 4097, 4096], [131071, 40000]])
 def test_select_rows_divided_over_workgroups(lens, dist):
