@@ -384,7 +384,9 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call);
  *   PDD_OPT_ATTN_WAVES: wavefronts per attention workgroup, 4 (128 queries) or
  *   8 (256 queries); 0 = chosen per problem (default).
  *   PDD_OPT_IMPORTANCE_KEYS: keys per workgroup of the importance kernel, 128
- *   or 256; 0 = chosen per problem (default).  Results do not depend on it.
+ *   or 256: the two give the same bits; 0 = chosen per problem (default), which
+ *   for windows of few rows is a kernel with all of them in LDS, whose sums are
+ *   added in another order.
  */
 enum { PDD_OPT_ATTN_WAVES = 0, PDD_OPT_IMPORTANCE_KEYS = 1 };
 pdd_status pdd_set_option(int option, int value);

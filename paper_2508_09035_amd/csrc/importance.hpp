@@ -40,6 +40,9 @@ struct ImpParams {
     // fixed order r = 0, 1, ...
     int32_t n_split;
     float *part;
+    // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave.
+    uint32_t g_magic;
+    int32_t groups;
 };
 
 constexpr int kImpWaves = 4;
@@ -227,6 +230,124 @@ void importance_kernel(const ImpParams p)
         const float tot = colsum[kg] + xchg_half(colsum[kg]);
         float *dst = p.n_split > 1 ? p.part + (int64_t)split * p.Hkv * p.total_k : p.imp;
         if (hh == 0 && jkey[kg] < nk) dst[(int64_t)g * p.total_k + ks + jkey[kg]] = tot;
+    }
+#else
+    (void)p;
+#endif
+}
+
+// The same sums with all window rows of the workgroup's (sequence, KV head) resident in LDS, for windows
+// of few rows.  Rows are (token, head of the group) pairs, token major, so that a short window
+// fills its 32-row blocks.  The rows and their log-sum-exp are loaded once, behind the one barrier of
+// the kernel; then each wave walks `groups` groups of 32 keys by itself, K fragments of the next
+// group requested while one is summed.  (The kernel above waits at a barrier for every block of 32 rows
+// with some 0.3 us of work between barriers.)  Bound by the exponentials on long launches (32768
+// tokens x 32/8 heads, 128 rows: 600 cycles per block and SIMD, 384 of vector issue; 50 -> 42 us), by the
+// first loads on short ones (4096 tokens, 64 rows: 9.1 -> 7.0 us; 5 to 64 tokens behind 700 to 12345 keys
+// x 4 sequences 40 -> 26; 1 token behind 500 to 7900 keys x 8 sequences 25 -> 15.6).
+template <int D>
+constexpr int importance_rows_block_bytes() { return 32 * 2 * D + 32 * (int)sizeof(float); }
+
+template <int D>
+__global__ __launch_bounds__(1024) void importance_rows_kernel(const ImpParams p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int NKK = D / 16, ROW_BYTES = D * 2, CH = D / 8, QBLK_BYTES = 32 * ROW_BYTES;
+    constexpr int RPI = 1024 / ROW_BYTES;        // rows per DMA instruction
+    extern __shared__ __attribute__((aligned(1024))) uint8_t imp_smem[];     // blocks of rows, then their log-sum-exp
+
+    int bid = blockIdx.x;
+    const int g = bid % p.Hkv;  bid /= p.Hkv;
+    const int b = bid % p.B;
+    const int kt = bid / p.B;
+    const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
+    const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
+    const int nq = qe - qs, nk = ke - ks, delta = nk - nq;
+    const int waves = blockDim.x >> 6;
+    const int j_wg0 = kt * waves * p.groups * 32;
+    if (j_wg0 >= nk) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hh = lane >> 5;
+    const int W = (nq > 0 && delta >= 0) ? ((p.window < 0 || p.window > nq) ? nq : p.window) : 0;
+    const int iw0 = nq - W;                       // first window token
+    const int n_rows = W * p.G, n_blocks = (n_rows + 31) / 32;
+    // first row that sees key j
+    auto row_of = [&](int j) { return min(max(0, j - delta - iw0), W) * p.G; };
+
+    bf16x8 kf[NKK];
+    const uint16_t *const kbase = p.k + (int64_t)ks * p.k_st + (int64_t)g * p.k_sh + 8 * hh;
+    auto load_k = [&](int j0) {
+        const uint16_t *kp = kbase + (int64_t)min(j0 + n, nk - 1) * p.k_st;
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) kf[kk] = *(const bf16x8 *)(kp + 16 * kk);
+    };
+    const int j_first = j_wg0 + 32 * wave;
+    load_k(j_first);
+    const int block0 = row_of(j_wg0) / 32;        // blocks before it see none of the workgroup's keys
+    float *const lse_sh = (float *)(imp_smem + n_blocks * QBLK_BYTES);
+    if (n_rows > 0) {
+        const uint16_t *qbase = p.q + (int64_t)(qs + iw0) * p.q_st + (int64_t)(g * p.G) * p.q_sh;
+        const uint32_t q_row_bytes = (uint32_t)p.q_st * 2u, q_head_bytes = (uint32_t)p.q_sh * 2u;
+        const i32x4 rs = make_rsrc(qbase, (uint32_t)(W - 1) * q_row_bytes + (uint32_t)(p.G - 1) * q_head_bytes + (uint32_t)ROW_BYTES);
+        const uint32_t lds = lds_addr_of(imp_smem);
+        for (int i = block0 * (32 / RPI) + wave; i < n_blocks * (32 / RPI); i += waves) {
+            const int r = RPI * i + lane / CH;
+            const int rr = min(r, n_rows - 1), tok = div_group(rr, p.g_magic);
+            const int pos = lane % CH, c = D == 128 ? (pos ^ swz_row<128>(r & 31)) : (pos ^ ((r >> 1) & 7));
+            dma16_to_lds(rs, lds + 1024 * i, (uint32_t)tok * q_row_bytes + (uint32_t)(rr - tok * p.G) * q_head_bytes + (uint32_t)c * 16u);
+        }
+        for (int r = 32 * block0 + tid; r < 32 * n_blocks; r += blockDim.x) {
+            float l2 = INFINITY;                  // rows past the last one add nothing
+            if (r < n_rows) {
+                const int tok = div_group(r, p.g_magic);
+                l2 = p.lse[(int64_t)(g * p.G + r - tok * p.G) * p.total_q + qs + iw0 + tok] * 1.4426950408889634f;
+            }
+            lse_sh[r] = -l2;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    uint32_t qaddr[NKK];                          // row n, chunk 2 kk + hh of a block
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+        const int c = 2 * kk + hh;
+        qaddr[kk] = (uint32_t)n * ROW_BYTES + (uint32_t)(D == 128 ? (c ^ swz_row<128>(n)) : (c ^ ((n >> 1) & 7))) * 16u;
+    }
+    const float c2 = p.scale_log2;
+    for (int t = 0; t < p.groups; ++t) {
+        const int j0 = j_first + 32 * waves * t;
+        if (j0 >= nk) break;
+        bf16x8 kc[NKK];
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) kc[kk] = kf[kk];
+        if (t + 1 < p.groups) load_k(j0 + 32 * waves);
+        const int key_row = row_of(j0 + n), last_row = row_of(j0 + 31);
+        float colsum = 0.f;
+        for (int rb = row_of(j0) / 32; rb < n_blocks; ++rb) {
+            const uint8_t *qb = imp_smem + rb * QBLK_BYTES;
+            f32x16 sc;
+            const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKK; ++kk)
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qb + qaddr[kk]), kc[kk], kk == 0 ? zero16 : sc, 0, 0, 0);
+            f32x4 nl[4];                          // rows 8 (e / 4) + 4 hh + e % 4
+#pragma unroll
+            for (int bq = 0; bq < 4; ++bq) nl[bq] = *(const f32x4 *)(lse_sh + 32 * rb + 8 * bq + 4 * hh);
+            if (last_row <= 32 * rb) {            // every row sees every key
+#pragma unroll
+                for (int e = 0; e < 16; ++e) colsum += fast_exp2(fmaf(sc[e], c2, nl[e >> 2][e & 3]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float pe = fast_exp2(fmaf(sc[e], c2, nl[e >> 2][e & 3]));
+                    colsum += 32 * rb + 8 * (e >> 2) + 4 * hh + (e & 3) >= key_row ? pe : 0.f;
+                }
+            }
+        }
+        const float tot = colsum + xchg_half(colsum);
+        if (hh == 0 && j0 + n < nk) p.imp[(int64_t)g * p.total_k + ks + j0 + n] = tot;
     }
 #else
     (void)p;

@@ -148,6 +148,7 @@ pdd_status launch_attn_t(const pdd::AttnParams &p, int64_t blocks, hipStream_t s
 
 int compute_units();
 
+constexpr int kLdsBytes = 160 * 1024;    // of a compute unit, and the most one workgroup can have
 constexpr int kSplitRows = 128;          // packed (token, head) rows per workgroup of the key-split form
 constexpr size_t kSplitWorkspaceMax = (size_t)256 << 20;
 struct SplitPlan { int tiles, n_split; size_t bytes; };        // tiles == 0: the form does not apply
@@ -421,10 +422,51 @@ int importance_split(const pdd_attn_desc *d, int window)
     return best;
 }
 
+// Whether the importance takes the form with all window rows in LDS, and its launch shape.
+// The rows have to fit the 160 KB of a compute unit (19 blocks of 32 at head_dim 128).  Above 80 KB one
+// 16-wave workgroup runs per compute unit: only for launches that fill the chip's 4096 wave slots with 32-key
+// groups (64 tokens x 4 behind 8192 keys, 64/8 heads 55 -> 51 us; 200 tokens behind 16000, 4/2
+// heads, would take 17 us against 11.4 of the streaming kernel, which divides the rows).  Below,
+// two or more run per compute unit; four waves each while all of them are resident at once (4096
+// tokens, 64 rows: 7.0 us, 8.7 with eight waves), else eight waves, which load the rows half as often,
+// and two groups per wave from 4096 groups on (8 prompts of 512 to 7900 tokens, 64 rows: 38 us with
+// four waves, 30.0 / 29.4 with eight and one / two groups; 34 with the streaming kernel).
+struct ImpRowsPlan { int waves, groups; size_t lds; };            // waves == 0: the form does not apply
+ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
+{
+    const ImpRowsPlan none = {0, 0, 0};
+    if (g_imp_keys != 0) return none;
+    const int64_t w = (window < 0 || window > d->max_seqlen_q) ? d->max_seqlen_q : window;
+    const int64_t blocks = (w * (d->n_q_heads / d->n_kv_heads) + 31) / 32;
+    const int64_t lds = blocks * (d->head_dim == 128 ? pdd::importance_rows_block_bytes<128>() : pdd::importance_rows_block_bytes<64>());
+    if (lds > kLdsBytes) return none;
+    const int64_t tasks = (int64_t)(d->total_k / 32 + d->batch) * d->n_kv_heads, slots = 16 * (int64_t)compute_units();
+    const int groups = tasks >= slots ? 2 : 1;
+    if (lds > kLdsBytes / 2) return tasks >= slots ? ImpRowsPlan{16, groups, (size_t)lds} : none;
+    const int64_t resident = lds > kLdsBytes / 3 ? 2 : lds > kLdsBytes / 4 ? 3 : 4;     // 4-wave workgroups per compute unit
+    if (tasks <= 4 * resident * compute_units()) return {4, 1, (size_t)lds};
+    return {8, groups, (size_t)lds};
+}
+
 size_t importance_workspace(const pdd_attn_desc *d, int window)
 {
+    if (importance_rows(d, window).waves) return 0;
     const int r = importance_split(d, window);
     return r > 1 ? (size_t)r * d->n_kv_heads * (size_t)d->total_k * sizeof(float) : 0;
+}
+
+template <typename Kern>
+pdd_status launch_importance_rows(Kern kern, const pdd::ImpParams &p, const ImpRowsPlan &rows, int max_k, hipStream_t st)
+{
+    const pdd_status s = raise_lds_limit(reinterpret_cast<const void *>(kern), kLdsBytes);
+    if (s) return s;
+    const int keys = 32 * rows.waves * rows.groups;
+    const int64_t blocks = ((int64_t)max_k + keys - 1) / keys * p.B * p.Hkv;
+    if (blocks > 0x7fffffffLL) return fail(PDD_ERR_INVALID_ARG, "launch grid too large");
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * rows.waves), rows.lds, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(PDD_ERR_HIP, "importance launch: %s", hipGetErrorString(e));
+    return PDD_OK;
 }
 
 pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *k, const float *lse, float *imp,
@@ -442,6 +484,12 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.scale_log2 = scale_log2(d);
     p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
+    if (const ImpRowsPlan rows = importance_rows(d, window); rows.waves) {
+        p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
+        p.groups = rows.groups;
+        return d->head_dim == 128 ? launch_importance_rows(pdd::importance_rows_kernel<128>, p, rows, d->max_seqlen_k, st)
+                                  : launch_importance_rows(pdd::importance_rows_kernel<64>, p, rows, d->max_seqlen_k, st);
+    }
     // the row split needs room for its partial sums; without it the single-pass form runs
     const size_t need = importance_workspace(d, window);
     const bool split = need > 0 && workspace && workspace_bytes >= need;

@@ -362,6 +362,34 @@ def test_importance_with_and_without_scratch(name):
         pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
 
 
+@pytest.mark.parametrize("lens,prefix,hq,hkv,d,window", [
+    ([31, 1, 0, 33, 500], None, 4, 4, 64, 1),                     # one row; sequences of a key and of none
+    ([513, 700], None, 10, 2, 128, 13),                           # 65 rows of 5 heads
+    ([300, 97, 64, 1023], None, 6, 2, 128, 200),                  # windows longer than some of the prompts, 600 rows: 19 blocks
+    ([300, 97, 64, 1023], None, 6, 2, 128, 203),                  # 20 blocks: the streaming kernel
+    ([1000, 1300], None, 8, 2, 64, 300),                          # 1200 rows of head_dim 64: the streaming kernel
+    ([7, 0, 1, 40], [900, 77, 2049, 1500], 6, 2, 128, -1),        # chunks, one without tokens: its keys read zero
+    ([9, 30], [6000, 3100], 16, 16, 64, -1),                      # eight waves, two key groups each
+    ([64], [8161], 128, 16, 128, -1),                             # sixteen waves, two key groups each, 512 rows
+])
+def test_importance_rows_in_lds(lens, prefix, hq, hkv, d, window):
+    """Every launch shape of the importance kernel that holds the window rows in LDS, and the shapes next to
+    its limits, against the oracle; the same bits on a second run."""
+    chunked = prefix is not None
+    klens = [a + b for a, b in zip(lens, prefix)] if chunked else None
+    wl = W.make_custom("t", lens, klens, hq, hkv, d, 0 if chunked else window, "1/4", seed=91, chunked=chunked)
+    dev = DeviceWorkload(wl)
+    got = []
+    for _ in range(2):
+        dev.poison()
+        dev.attn(True)
+        torch.cuda.synchronize()
+        got.append(dev.imp.clone())
+    assert torch.equal(got[0], got[1])
+    oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, window)
+    rel_close(got[0].cpu().numpy().astype(np.float64), oI, "importance")
+
+
 def test_importance_key_widths_give_the_same_bits():
     """The importance kernel with 256 and with 128 keys per workgroup (the library picks by launch
     size): the same column sums bit for bit, on ragged prefill (windows that end inside a key
