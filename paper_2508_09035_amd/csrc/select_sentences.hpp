@@ -12,21 +12,25 @@
 //
 // One 1024-thread workgroup per row; a thread owns up to eight consecutive
 // sentences, whose bounds, scores and lengths stay in registers.
-//   * The row's scores come through LDS in pieces of up to 16384 (whole-row loads,
+//   * The row's scores come through LDS in pieces of up to 32768 (whole-row loads,
 //     the next piece requested while one is summed); a sentence is summed by its
 //     owner in token order, one fp32 chain.  (Read by the owner straight from
 //     memory, one score after the other, the longest sentence alone cost 60 us.)
 //   * No ranks are formed: the kept prefix of the ranking is every sentence above a
 //     threshold key and the first of those that tie with it, and the threshold
-//     is found like the k-th score of a token row (see next_probe), with the
-//     lengths as weights: one barrier per probe, until 64 sentences are left.
+//     is found like the k-th score of a short token row, with the lengths as weights:
+//     a histogram over the row's range, probes (see next_probe) where its bin holds
+//     more than 64 sentences.
 //   * The token mask: kept sentences flip a bit at their start and at their end,
 //     and a prefix parity over the bits gives the mask 32768 tokens at a time.
 // Bound by the latency of its steps on the one compute unit the row runs on:
-// 1 row of 32768 tokens in 1362 sentences 149 -> 21 us (serial reads, S^2 ranks and
-// a binary search per token before).
+// 1 row of 32768 tokens in 1362 sentences 149 -> 15.5 us (serial reads, S^2 ranks and
+// a binary search per token before; 21 with the scores in two pieces and five to seven probes
+// instead of the histogram), a third of it the sums, whose LDS reads of 64 sentences
+// at a time conflict.
 #pragma once
 #include "select_topk.hpp"
+#include <type_traits>
 
 namespace pdd {
 
@@ -44,7 +48,7 @@ struct SentParams {
 };
 
 constexpr int kSentOwn = kSentMax / kSelThreads;     // sentences per thread at most
-constexpr int kSentSeg = 16 * kSelThreads;            // scores in LDS at a time, at most
+constexpr int kSentSeg = 32 * kSelThreads;            // scores in LDS at a time, at most
 constexpr int kSentChunk = 32 * kSelThreads;          // mask tokens at a time: one 32-bit word per thread
 // a probe either cuts the tokens inside the bracket to a quarter (at most 16 times), or is
 // followed by one that halves the bracket (at most 32 pairs)
@@ -53,27 +57,16 @@ constexpr int kSentFinish = 64;                       // sentences left in the b
 
 typedef float sent_f32x4 __attribute__((ext_vector_type(4), aligned(4)));    // four scores at any score's address
 
-// Exclusive scan over the workgroup's 1024 values in thread order; `sh` is used by one call only.
-template <typename Op>
-__device__ __forceinline__ int block_excl_scan(int x, int init, Op op, int32_t *sh, int lane, int wave, int *total)
+// inclusive prefix maximum of values >= 0 over the 64 lanes of a wave (see wave_incl_scan)
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t x)
 {
-    int incl = x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl = op(incl, o);
-    }
-    if (lane == 63) sh[wave] = incl;
-    __syncthreads();
-    int pre = init, all = init;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        if (w < wave) pre = op(pre, sh[w]);
-        all = op(all, sh[w]);
-    }
-    *total = all;
-    const int up = __shfl_up(incl, 1, 64);
-    return lane == 0 ? pre : op(pre, up);
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+    return x;
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const SentParams p)
@@ -81,10 +74,13 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     extern __shared__ __attribute__((aligned(16))) uint8_t sent_smem[];    // p.seg scores, later mask words
     float *const stage = (float *)sent_smem;
     uint32_t *const bits = (uint32_t *)sent_smem;
-    __shared__ int32_t sh_end[kSelWaves], sh_tie[kSelWaves];
+    __shared__ int32_t sh_end[kSelWaves];
+    __shared__ uint32_t sh_tie[kSelWaves];
     __shared__ uint32_t wave_min[kSelWaves], wave_max[kSelWaves], wave_par[kSelWaves];
     __shared__ unsigned long long probe_tot[kSentMaxProbes];       // tokens | sentences << 32 at or above a probe
-    __shared__ uint32_t fin_key[kSentFinish], fin_len[kSentFinish];
+    __shared__ __attribute__((aligned(16))) unsigned long long hist[kSelBins];     // tokens | sentences << 32 of a bin
+    __shared__ __attribute__((aligned(16))) uint2 fin[kSentFinish];              // key, length
+    __shared__ struct { uint32_t bin, tokens, sentences, above, n_above; } place;
     __shared__ uint32_t fin_count, fin_T, fin_above, sh_kept;
 
     const int b = blockIdx.x, g = blockIdx.y;
@@ -101,6 +97,8 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     uint8_t *mrow = p.mask ? p.mask + (int64_t)g * p.total_k + ks : nullptr;
 
     if (tid < kSentMaxProbes) probe_tot[tid] = 0;
+    hist[tid] = 0;
+    if (tid < kSentFinish) fin[tid] = make_uint2(0, 0);
     if (tid == 0) { fin_count = 0; sh_kept = 0; }
 
     // ---- sentence bounds: ends forced into [c0, nk] and non-decreasing (running maximum)
@@ -113,8 +111,19 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
         if (i < ch && s_lo + i < S) mx = max(mx, min(max(p.sent_end[s0 + s_lo + i], c0), nk));
         end[i] = mx;
     }
-    int content_end;
-    const int begin = block_excl_scan(mx, c0, [](int x, int y) { return max(x, y); }, sh_end, lane, wave, &content_end);
+    const int mx_incl = (int)wave_incl_max((uint32_t)mx);
+    if (lane == 63) sh_end[wave] = mx_incl;
+    __syncthreads();
+    int content_end = c0, begin = c0;                             // running maximum of all threads, of those before this one
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        content_end = max(content_end, sh_end[w]);
+        begin = w < wave ? max(begin, sh_end[w]) : begin;
+    }
+    {
+        const int up = __shfl_up(mx_incl, 1, 64);
+        begin = lane > 0 ? max(begin, up) : begin;
+    }
 #pragma unroll
     for (int i = 0; i < kSentOwn; ++i) end[i] = max(end[i], begin);
 
@@ -148,17 +157,25 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
 #pragma unroll
         for (int i = 0; i < kSentOwn; ++i) {
             if (i < ch) {
-                int x = max(i == 0 ? begin : end[i - 1], seg0) - seg0;
+                const int x = max(i == 0 ? begin : end[i - 1], seg0) - seg0;
                 const int z = min(end[i] - seg0, p.seg);
                 float a = acc[i];
-                for (; x + 8 <= z; x += 8) {          // eight reads in flight, added in token order
-                    float v[8];
+                // eight scores from two quads at a time, added in token order; in the first and the last
+                // eight, what lies outside the sentence counts as zero (the masks are what a step costs
+                // most, and the reads stay inside the stage: p.seg is a multiple of 8)
+                auto eight = [&](int y, auto masked) {
+                    const float4 q0 = *(const float4 *)(stage + y), q1 = *(const float4 *)(stage + y + 4);
+                    const float v[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = stage[x + j];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) a += v[j];
+                    for (int j = 0; j < 8; ++j)
+                        a += !decltype(masked)::value || (y + j >= x && y + j < z) ? v[j] : 0.f;
+                };
+                if (x < z) {
+                    int y = x & ~7;
+                    eight(y, std::true_type{});
+                    for (y += 8; y + 8 <= z; y += 8) eight(y, std::false_type{});
+                    if (y < z) eight(y, std::true_type{});
                 }
-                for (; x < z; ++x) a += stage[x];
                 acc[i] = a;
             }
         }
@@ -198,6 +215,40 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
         const uint32_t need = budget + 1u;
         uint32_t lo = kmin, hi = kmax, w_lo = total, n_lo = (uint32_t)S, n_above = 0;
         bool interp = true;
+        if (lo < hi && S > kSentFinish) {
+            // the bin of the row's range that holds T
+            const int shift = max(32 - __builtin_clz(hi - lo) - 10, 0);       // kSelBins = 2^10
+#pragma unroll
+            for (int i = 0; i < kSentOwn; ++i)
+                if (i < ch && s_lo + i < S) atomicAdd(&hist[(key[i] - lo) >> shift], 1ull << 32 | len[i]);
+            __syncthreads();
+            if (wave == 0) {
+                unsigned long long bin[16], sum = 0;              // lane: 16 consecutive bins
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    bin[e] = hist[16 * lane + e];
+                    sum += bin[e];
+                }
+                uint32_t sc[2] = {(uint32_t)sum, (uint32_t)(sum >> 32)};
+                wave_incl_scan_n(sc);
+                uint32_t w = total - sc[0], n = (uint32_t)S - sc[1];
+#pragma unroll
+                for (int e = 15; e >= 0; --e) {
+                    const uint32_t wb = (uint32_t)bin[e], nb = (uint32_t)(bin[e] >> 32);
+                    if (w < need && need <= w + wb) place = {(uint32_t)(16 * lane + e), wb, nb, w, n};
+                    w += wb;
+                    n += nb;
+                }
+            }
+            __syncthreads();
+            const uint32_t first = place.bin << shift;
+            hi = lo + min(first + ((1u << shift) - 1u), hi - lo);
+            lo += first;
+            above = place.above;
+            w_lo = above + place.tokens;
+            n_above = place.n_above;
+            n_lo = n_above + place.sentences;
+        }
         for (int probe = 0; lo < hi && n_lo - n_above > (uint32_t)kSentFinish; ++probe) {
             const uint32_t inside = w_lo - above;
             const uint32_t mid = next_probe(lo, hi, inside, need - above, interp);
@@ -223,18 +274,18 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
             for (int i = 0; i < kSentOwn; ++i)
                 if (i < ch && s_lo + i < S && key[i] - lo <= hi - lo) {
                     const uint32_t at = atomicAdd(&fin_count, 1u);
-                    fin_key[at] = key[i];
-                    fin_len[at] = len[i];
+                    fin[at] = make_uint2(key[i], len[i]);
                 }
             __syncthreads();
             if (wave == 0) {
                 const int m = (int)fin_count;
-                const uint32_t mine = lane < m ? fin_key[lane] : 0u;
+                const uint32_t mine = fin[lane].x;                // slots past m: key 0, length 0
                 uint32_t gt = above, ge = above;
-                for (int j = 0; j < m; ++j) {
-                    const uint32_t k = fin_key[j], l = fin_len[j];
-                    gt += k > mine ? l : 0u;
-                    ge += k >= mine ? l : 0u;
+#pragma unroll 4
+                for (int j = 0; j < m; j += 2) {
+                    const uint4 o = *(const uint4 *)(fin + j);
+                    gt += (o.x > mine ? o.y : 0u) + (o.z > mine ? o.w : 0u);
+                    ge += (o.x >= mine ? o.y : 0u) + (o.z >= mine ? o.w : 0u);
                 }
                 if (lane < m && gt < need && ge >= need) { fin_T = mine; fin_above = gt; }   // one key at most
             }
@@ -250,8 +301,12 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
         uint32_t tie = 0;
 #pragma unroll
         for (int i = 0; i < kSentOwn; ++i) tie += (i < ch && s_lo + i < S && key[i] == T) ? len[i] : 0u;
-        int tie_all;
-        uint32_t run = (uint32_t)block_excl_scan((int)tie, 0, [](int x, int y) { return x + y; }, sh_tie, lane, wave, &tie_all);
+        const uint32_t tie_incl = wave_incl_scan(tie);
+        if (lane == 63) sh_tie[wave] = tie_incl;
+        __syncthreads();
+        uint32_t run = tie_incl - tie;
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) run += w < wave ? sh_tie[w] : 0u;
         uint32_t tokens = 0;
 #pragma unroll
         for (int i = 0; i < kSentOwn; ++i) {
