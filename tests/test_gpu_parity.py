@@ -162,7 +162,7 @@ _SPLIT_SHAPES = {       # (new tokens, keys or None for prefill, query heads, KV
     "group-3": ([1, 0, 33, 127, 3], [5001, 300, 4096, 127, 4], 6, 2, 0),
     "group-16": ([5, 9], [9005, 1033], 16, 1, 0),               # all heads of a token in half a wave
     "mha": ([129, 128, 1], [2629, 6128, 65], 8, 8, 0),         # one row past a row tile and exactly one
-    "one-head": ([300], [1500], 1, 1, 0),
+    "one-head": ([300], [2500], 1, 1, 0),                       # (at 1500 keys and head_dim 64 the plain form is chosen)
     "prefill": ([3000, 1, 700], None, 2, 1, 40),                # splits that end at the diagonal
 }
 
