@@ -71,9 +71,10 @@ __device__ __forceinline__ float pooled_score(const float *seq, int nk, int j, i
 
 __device__ __forceinline__ uint32_t order_key(float x)
 {
-    // monotone map fp32 -> uint32 (larger float <=> larger key); -0.0 == +0.0
+    // monotone map fp32 -> uint32 (larger float <=> larger key); -0.0 == +0.0.  Never 0, which stands
+    // for a slot without a candidate: the NaN of all ones would be, and would miss in every count
     const uint32_t u = __float_as_uint(x + 0.0f);
-    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);    // negative: all bits flipped; else the sign bit set
+    return max(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u), 1u);    // negative: all bits flipped; else the sign bit set
 }
 
 

@@ -504,6 +504,28 @@ def test_select_threshold_search_off_its_good_path(n):
         assert np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
 
 
+@pytest.mark.parametrize("n", [5, 128, 300, 4097, 32768])
+def test_select_key_of_the_lowest_nan(n):
+    """A score whose bits are all ones (a buffer filled with 0xFF bytes) ranks below every other value
+    and is still a candidate: it takes its slot when everything is kept, and none before."""
+    rng = np.random.default_rng(n)
+    bits = rng.standard_normal((2, n)).astype(np.float32).view(np.uint32)
+    low = rng.random((2, n)) < 0.4
+    low[:, :2], bits[1, -1] = (True, False), np.uint32(0xFF800000)            # -infinity
+    low[1, -1] = False
+    bits[low] = 0xFFFFFFFF
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cu, scores = np.array([0, n], dtype=np.int32), dev(bits.view(np.float32))
+    rank = np.where(low, -np.inf, np.maximum(bits.view(np.float32), np.float32(-1e30))).astype(np.float64)
+    for k in sorted({1, n - int(low.sum(1).max()), n - 1, n}):
+        idx = torch.full((2, k), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full((2, n), 9, dtype=torch.uint8, device="cuda")
+        keep = np.array([k], dtype=np.int32)
+        pdd.select_topk(scores, dev(cu), n, dev(keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask, None, None, cu)
+        want_idx, want_mask = oracle.select_topk(rank, cu, keep)
+        assert np.array_equal(idx.cpu().numpy(), want_idx) and np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
+
+
 @pytest.mark.parametrize("dist", ["spread", "equal", "low_bits", "signs", "infinities"])
 @pytest.mark.parametrize("lens", [[32769], [36864, 5, 0, 4097, 4096], [131071, 40000]])
 def test_select_rows_divided_over_workgroups(lens, dist):
