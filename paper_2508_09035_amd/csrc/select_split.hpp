@@ -62,7 +62,7 @@ __device__ __forceinline__ SelRow split_sel_row(const SelParams &p)
     const int c0 = min(max(p.cand_b ? p.cand_b[b] : 0, 0), r.nk);
     const int c1 = min(max(p.cand_e ? p.cand_e[b] : r.nk, c0), r.nk);
     r.c0 = c0;
-    r.n = c1 - c0;
+    r.n = min(c1 - c0, (int)gridDim.x * kSplitSelChunk);         // what the workspace has room for
     r.chunks = (r.n + kSplitSelChunk - 1) / kSplitSelChunk;
     r.keep0 = min(max(p.cu_keep[b], 0), p.total_keep);
     const int keep1 = min(max(p.cu_keep[b + 1], r.keep0), p.total_keep);
