@@ -487,6 +487,8 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     if (const ImpRowsPlan rows = importance_rows(d, window); rows.waves) {
         p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
         p.groups = rows.groups;
+        // the LDS is sized from max_seqlen_q; a longer sequence of the device array keeps to it
+        if (window < 0 || window > d->max_seqlen_q) p.window = d->max_seqlen_q;
         return d->head_dim == 128 ? launch_importance_rows(pdd::importance_rows_kernel<128>, p, rows, d->max_seqlen_k, st)
                                   : launch_importance_rows(pdd::importance_rows_kernel<64>, p, rows, d->max_seqlen_k, st);
     }
