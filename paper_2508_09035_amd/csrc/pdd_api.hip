@@ -602,8 +602,11 @@ pdd_status pdd_set_option(int option, int value)
 
 size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
 {
-    if (!desc || desc->batch < 1 || desc->n_kv_heads < 1 || desc->n_q_heads < desc->n_kv_heads || desc->total_k < 0)
-        return 0;
+    if (!desc || desc->batch < 1 || desc->n_kv_heads < 1) return 0;
+    if (which_call == PDD_CALL_SELECT_TOPK)         // the attention fields are not read
+        return (size_t)desc->n_kv_heads * desc->batch *
+               select_chunks(desc->n_kv_heads, desc->batch, desc->max_seqlen_k) * pdd::kSplitSelChunkBytes;
+    if (desc->n_q_heads < desc->n_kv_heads || desc->total_k < 0) return 0;
     switch (which_call) {
     case PDD_CALL_PREFILL_ATTN:
     {
@@ -615,9 +618,6 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
         return chunked_workspace(desc);
     case PDD_CALL_TOKEN_IMPORTANCE:
         return desc->window != 0 ? importance_workspace(desc, desc->window) : 0;
-    case PDD_CALL_SELECT_TOPK:
-        return (size_t)desc->n_kv_heads * desc->batch *
-               select_chunks(desc->n_kv_heads, desc->batch, desc->max_seqlen_k) * pdd::kSplitSelChunkBytes;
     default:
         return 0;
     }

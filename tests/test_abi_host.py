@@ -242,7 +242,7 @@ def test_workspace_bytes_host_only():
         d.window = -1
         n = lib.pdd_workspace_bytes(ctypes.byref(d), call)
         assert n > 0 and n % plane == 0 and n // plane <= 8
-    assert lib.pdd_workspace_bytes(ctypes.byref(d), 3) == 0          # the selection uses none
+    assert lib.pdd_workspace_bytes(ctypes.byref(d), 3) == 0          # no rows of more than 32768 keys
     assert lib.pdd_workspace_bytes(None, 0) == 0
     # the chunked call asks for the sweep's room: one float per query head, 256-row query tile and key
     assert lib.pdd_workspace_bytes(ctypes.byref(d), 1) == 64 * 1 * 4 * 8448 * 4
@@ -250,6 +250,20 @@ def test_workspace_bytes_host_only():
     d.n_q_heads, d.total_q, d.max_seqlen_q = 128, 4 * 4096, 4096    # 128 heads x 16 query tiles x 33792 keys x 4 B
     n = lib.pdd_workspace_bytes(ctypes.byref(d), 1)
     assert 0 < n <= 8 * plane
+
+
+def test_selection_workspace_reads_its_documented_fields_only():
+    """PDD_CALL_SELECT_TOPK reads batch, n_kv_heads and max_seqlen_k: the figure is the same whatever the
+    attention fields hold, nothing included."""
+    lib = pdd.load_library()
+    d = AttnDesc()
+    d.batch, d.n_kv_heads, d.max_seqlen_k = 1, 8, 131072
+    need = lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK)
+    assert need == 8 * 32 * 8720                                     # 32 chunks of 4096 keys per row
+    d.n_q_heads, d.head_dim, d.total_k, d.max_seqlen_q = 3, -1, -1, -1
+    assert lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK) == need
+    d.max_seqlen_k = 32768
+    assert lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK) == 0
 
 
 def test_noalloc_rejects_shapes_beyond_its_scratch():
