@@ -241,8 +241,9 @@ const char *importance_limits(const pdd_attn_desc *d)
 SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
 {
     const SplitPlan none = {0, 0, 0};
+    // (the scratch query comes here with whatever its caller's descriptor holds)
     if (g_attn_waves != 0 || d->total_q <= 0 || d->total_k <= 0 || d->max_seqlen_q <= 0 || d->max_seqlen_k <= 0 ||
-        d->n_q_heads % d->n_kv_heads)
+        (d->head_dim != 64 && d->head_dim != 128) || d->n_q_heads % d->n_kv_heads)
         return none;
     const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q;
     // the kernel divides a row by G with one 32-bit multiplication, addresses 32 rows of Q with
@@ -263,6 +264,7 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     double T = 24;
     if (cus > base * B) T = std::ceil(tiles_all * base / (cus - base * B));
     T = T < 8 ? 8 : T > 24 ? 24 : T;
+    if ((double)d->total_q * d->n_q_heads > (double)kSplitWorkspaceMax) return none;
     const size_t per_split = (size_t)d->total_q * d->n_q_heads * (d->head_dim + 1) * sizeof(float);
     const size_t room = (chunked ? (size_t)PDD_STATIC_SCRATCH_BYTES : kSplitWorkspaceMax) / per_split;
     int64_t n_split = (tiles_max + (int64_t)T - 1) / (int64_t)T;

@@ -266,6 +266,29 @@ def test_selection_workspace_reads_its_documented_fields_only():
     assert lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK) == 0
 
 
+def test_workspace_query_takes_any_descriptor():
+    """The scratch query validates nothing and must return all the same: head dimensions that no call takes
+    (-1 used to divide by zero), extreme and negative sizes.  In a process of its own, because the
+    failure is a signal."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, itertools, sys
+sys.path.insert(0, sys.argv[1])
+import paper_2508_09035_amd as pdd
+lib, top = pdd.load_library(), 2 ** 31 - 1
+for head_dim, heads, n, kv in itertools.product((-1, 0, 96, 64, 128, top), (1, 8, top), (-1, 0, 1, 4096, top), (1, 8, top)):
+    d = pdd.AttnDesc()
+    d.batch, d.n_q_heads, d.n_kv_heads, d.head_dim, d.window = 1, heads, kv, head_dim, 32
+    d.total_q = d.total_k = d.max_seqlen_q = d.max_seqlen_k = n
+    for call in range(5):
+        lib.pdd_workspace_bytes(ctypes.byref(d), call)
+print("all returned")
+"""
+    r = subprocess.run([sys.executable, "-c", code, ROOT], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "all returned" in r.stdout, (r.returncode, r.stderr[-500:])
+
+
 def test_noalloc_rejects_shapes_beyond_its_scratch():
     """The allocation-free chunked entry point refuses, on the host, a shape whose scratch
     would not fit its built-in 16 MiB array: nothing is launched."""
