@@ -450,9 +450,10 @@ ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
     return {8, groups, (size_t)lds};
 }
 
+// What the streaming kernel can use, also where the form above runs and needs none: the figure must not
+// change with PDD_OPT_IMPORTANCE_KEYS, which a caller may set after sizing the scratch.
 size_t importance_workspace(const pdd_attn_desc *d, int window)
 {
-    if (importance_rows(d, window).waves) return 0;
     const int r = importance_split(d, window);
     return r > 1 ? (size_t)r * d->n_kv_heads * (size_t)d->total_k * sizeof(float) : 0;
 }

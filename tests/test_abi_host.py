@@ -289,6 +289,27 @@ print("all returned")
     assert r.returncode == 0 and "all returned" in r.stdout, (r.returncode, r.stderr[-500:])
 
 
+def test_workspace_figure_does_not_depend_on_the_importance_option():
+    """Scratch sized under one setting of PDD_OPT_IMPORTANCE_KEYS serves a call under another one, for
+    windows that the default setting sums without scratch too."""
+    lib = pdd.load_library()
+    d = good_desc()                                     # 4096 tokens x 32/8 heads, window 128: all rows fit the LDS
+    d.n_q_heads, d.n_kv_heads, d.head_dim, d.window = 32, 8, 64, 128
+    d.total_q = d.total_k = d.max_seqlen_q = d.max_seqlen_k = 4096
+    chunk = good_desc()                                 # 100 new tokens behind 20000, importance over all of them
+    chunk.total_q = chunk.max_seqlen_q = 100
+    chunk.total_k = chunk.max_seqlen_k = 20100
+    try:
+        for desc in (d, chunk):
+            got = []
+            for keys in (0, 128, 256):
+                pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, keys)
+                got.append([lib.pdd_workspace_bytes(ctypes.byref(desc), call) for call in range(4)])
+            assert got[0] == got[1] == got[2] and any(got[0])
+    finally:
+        pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, 0)
+
+
 def test_noalloc_rejects_shapes_beyond_its_scratch():
     """The allocation-free chunked entry point refuses, on the host, a shape whose scratch
     would not fit its built-in 16 MiB array: nothing is launched."""
