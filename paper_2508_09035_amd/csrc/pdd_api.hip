@@ -487,6 +487,11 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.scale_log2 = scale_log2(d);
     p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
+    // the row split needs room for its partial sums; without it the single-pass form runs.  Scratch that
+    // it could not use for its address is refused whichever form runs.
+    const size_t need = importance_workspace(d, window);
+    const bool split = need > 0 && workspace && workspace_bytes >= need;
+    if (split && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
     if (const ImpRowsPlan rows = importance_rows(d, window); rows.waves) {
         p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
         p.groups = rows.groups;
@@ -495,11 +500,6 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
         return d->head_dim == 128 ? launch_importance_rows(pdd::importance_rows_kernel<128>, p, rows, d->max_seqlen_k, st)
                                   : launch_importance_rows(pdd::importance_rows_kernel<64>, p, rows, d->max_seqlen_k, st);
     }
-    // the row split needs room for its partial sums; without it the single-pass form runs
-    const size_t need = importance_workspace(d, window);
-    const bool split = need > 0 && workspace && workspace_bytes >= need;
-    if (split && (reinterpret_cast<uintptr_t>(workspace) & 15u))
-        return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
     p.n_split = split ? importance_split(d, window) : 1;
     p.part = split ? (float *)workspace : nullptr;
     int64_t blocks = (int64_t)p.n_ktiles * d->batch * d->n_kv_heads * p.n_split;

@@ -310,6 +310,21 @@ def test_workspace_figure_does_not_depend_on_the_importance_option():
         pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, 0)
 
 
+def test_misaligned_scratch_is_refused_for_short_windows_too():
+    """Scratch off a 16-byte boundary is refused where the streaming importance kernel would use it, whichever
+    form the window then takes (this one has all its rows in LDS)."""
+    lib = pdd.load_library()
+    d = good_desc()
+    d.n_q_heads, d.n_kv_heads, d.window = 32, 8, 128
+    for f in ("q", "k"):
+        setattr(d, f + "_stride_tok", 32 * 128)
+    d.total_q = d.total_k = d.max_seqlen_q = d.max_seqlen_k = 4096
+    need = lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_TOKEN_IMPORTANCE)
+    assert need > 0
+    rc = lib.pdd_token_importance(ctypes.byref(d), 0x10000, 0x20000, 0x50000, 0x60000, 0x70008, need, None)
+    assert rc == -3 and "aligned" in lib.pdd_last_error().decode()
+
+
 def test_noalloc_rejects_shapes_beyond_its_scratch():
     """The allocation-free chunked entry point refuses, on the host, a shape whose scratch
     would not fit its built-in 16 MiB array: nothing is launched."""
