@@ -315,9 +315,7 @@ def test_misaligned_scratch_is_refused_for_short_windows_too():
     form the window then takes (this one has all its rows in LDS)."""
     lib = pdd.load_library()
     d = good_desc()
-    d.n_q_heads, d.n_kv_heads, d.window = 32, 8, 128
-    for f in ("q", "k"):
-        setattr(d, f + "_stride_tok", 32 * 128)
+    d.n_q_heads, d.n_kv_heads, d.head_dim, d.window = 32, 8, 64, 128
     d.total_q = d.total_k = d.max_seqlen_q = d.max_seqlen_k = 4096
     need = lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_TOKEN_IMPORTANCE)
     assert need > 0
