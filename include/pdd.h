@@ -164,16 +164,20 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
 /*
  * pdd_prefill_attn_chunked for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): same arguments without the workspace, same results bit for bit as
- * pdd_prefill_attn_chunked called with a workspace of pdd_workspace_bytes(desc,
- * PDD_CALL_PREFILL_ATTN_CHUNKED) bytes, with or without importance.  The scratch is a fixed 16 MiB array
+ * hipMalloc): same arguments without the workspace.  With importance, same
+ * results bit for bit as pdd_prefill_attn_chunked called with a workspace of
+ * pdd_workspace_bytes(desc, PDD_CALL_PREFILL_ATTN_CHUNKED) bytes.  The scratch is a fixed 16 MiB array
  * inside the library's device image (one copy per GPU, held until the process
  * ends); the call allocates and frees nothing.  A shape whose importance scratch
  * in the plain attention form would exceed 16 MiB is rejected with PDD_ERR_WORKSPACE and nothing is enqueued.
- * All calls on one GPU share that array: calls that overlap in time on the same
+ * All calls with importance on one GPU share that array: calls that overlap in time on the same
  * GPU (different streams or threads) race on it and must be serialised by the
  * caller.  Nothing in it has to be cleared between calls (every partial sum a
  * call reads it has written itself).
+ * Without importance (NULL) the call uses no scratch and may overlap with any
+ * other; its results are those of pdd_prefill_attn_chunked without a workspace,
+ * bit for bit.  (Few or short chunks behind a long prefix are faster there with
+ * a workspace: the key-split form.)
  */
 pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const void *q_chunk,
                                             const void *k_all, const void *v_all, void *o,

@@ -691,13 +691,14 @@ pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const voi
 {
     pdd_status s = check_desc(desc, MODE_CHUNKED);
     if (s) return s;
-    const size_t plain = importance ? plain_chunked_workspace(desc) : 0;
+    // Attention alone needs no scratch, so it takes none of the shared one: such calls may overlap.
+    if (!importance) return pdd_prefill_attn_chunked(desc, q_chunk, k_all, v_all, o, lse, nullptr, nullptr, 0, stream);
+    const size_t plain = plain_chunked_workspace(desc);
     if (plain > PDD_STATIC_SCRATCH_BYTES)
         return fail(PDD_ERR_WORKSPACE, "this shape wants %zu bytes of scratch, the built-in scratch holds %u "
                     "(use pdd_prefill_attn_chunked with a workspace)", plain, (unsigned)PDD_STATIC_SCRATCH_BYTES);
     // (the key-split form never wants more than the built-in scratch)
-    const size_t split = split_plan(desc, true).bytes;
-    const size_t need = importance ? chunked_workspace(desc) : split;
+    const size_t need = chunked_workspace(desc);
     void *ws = nullptr;
     if (need > 0) {
         s = static_scratch(&ws);

@@ -37,6 +37,35 @@ def test_noalloc_chunked_matches_workspace_call_twice():
                              seed=43, chunked=True))
 
 
+def test_noalloc_without_importance_uses_no_scratch():
+    """Attention alone leaves the shared array alone: on shapes that split their keys when they have scratch
+    the call gives the bits of the ordinary call without a workspace, and two such calls on two streams
+    at once, which would overwrite each other's partial rows there, give them too."""
+    wls = [W.make_custom("t", [1] * 8, n, 32, 8, 128, 0, "1/4", seed=44 + i, chunked=True)
+           for i, n in enumerate(([2361, 1385, 1503, 513, 7899, 4832, 1605, 3660], [6000, 300, 7000, 4100, 900, 2500, 8001, 65]))]
+    devs, want = [DeviceWorkload(wl) for wl in wls], []
+    for dev in devs:
+        dev.attn(False)
+        torch.cuda.synchronize()
+        split = dev.o.clone()
+        dev.poison()
+        dev.attn(False, use_workspace=False)
+        torch.cuda.synchronize()
+        assert not torch.equal(split, dev.o), "this shape is one that splits its keys when it has scratch"
+        want.append((dev.o.clone(), dev.lse.clone()))
+        dev.poison()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]        # default priority
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for wl, dev, st in zip(wls, devs, streams):
+            with torch.cuda.stream(st):
+                pdd.prefill_attn_chunked_noalloc(dev.q, dev.k, dev.v, dev.o, dev.lse, None, dev.cu_q, dev.cu_k,
+                                                 dev.max_q, dev.max_k, wl.scale, wl.cu_seqlens_q, wl.cu_seqlens_k)
+    torch.cuda.synchronize()
+    for dev, (o, lse) in zip(devs, want):
+        assert torch.equal(o, dev.o) and torch.equal(lse, dev.lse)
+
+
 def test_noalloc_chunked_under_graph_capture():
     """What the entry point is for: the chunked call and the selection behind it captured in a HIP
     graph (nothing in them allocates, frees or clears memory) and replayed three times, with eager
