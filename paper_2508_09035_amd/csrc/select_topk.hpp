@@ -159,8 +159,9 @@ __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx)
 
 // Pooled scores of kSelPoolStep consecutive keys at a time, four per thread.  The scores of a step
 // and the pool_r on either side of it pass through LDS once, 16 bytes per lane (the scores outside
-// the sequence as the neutral element), those of the next step requested meanwhile; a window is
-// added up (or its maximum taken) in key order, the four windows of a thread from shared reads.
+// the sequence as zero, or as the nearest one inside it where the maximum is taken), those of the
+// next step requested meanwhile; a window is added up (or its maximum taken) in key order from its first
+// score on, as in pooled_score (a window of NaN stays NaN), the four windows of a thread from shared reads.
 // (Read from memory by every window on its own, 2 r + 1 loads per key, the four prompts of 2360 to 12001
 // keys x 8 heads took 34 us with r = 3 and 2480 us with r = 512; 20 and 87 us like this.)
 constexpr int kSelPoolStep = 4 * kSelThreads;
@@ -170,10 +171,10 @@ typedef float pool_f32x4 __attribute__((ext_vector_type(4), aligned(4)));       
 struct PoolStage {
     const int r;
     const bool is_max;
-    const float none, scale;            // neutral element; what the sum is multiplied with
+    const float scale;                  // what the sum is multiplied with
     pool_f32x4 next[2];
     __device__ explicit PoolStage(const SelParams &p)
-        : r(p.pool_r), is_max(p.pool_mode == kPoolMax), none(is_max ? -INFINITY : 0.f), scale(is_max ? 1.f : p.pool_inv) {}
+        : r(p.pool_r), is_max(p.pool_mode == kPoolMax), scale(is_max ? 1.f : p.pool_inv) {}
 
     // scores first - r + 4 tid .. + 3 and, where they belong to the step, the same kSelPoolStep further
     __device__ __forceinline__ void request(const float *seq, int nk, int first, int tid)
@@ -185,7 +186,10 @@ struct PoolStage {
                 if (x >= 0 && x + 4 <= nk) next[q] = *(const pool_f32x4 *)(seq + x);
                 else
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) next[q][j] = x + j >= 0 && x + j < nk ? seq[x + j] : none;
+                    for (int j = 0; j < 4; ++j) {
+                        const int in = min(max(x + j, 0), nk - 1);
+                        next[q][j] = is_max || in == x + j ? seq[in] : 0.f;
+                    }
             }
         }
     }
@@ -214,8 +218,6 @@ struct PoolStage {
     template <typename Op>
     __device__ __forceinline__ void windows(const float4 *quads, float (&out)[4], Op op)
     {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = none;
         auto edge = [&](int q) {
             const float4 t = quads[q];
             const float v[4] = {t.x, t.y, t.z, t.w};
@@ -223,7 +225,8 @@ struct PoolStage {
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (4 * q + e >= j && 4 * q + e <= j + 2 * r) out[j] = op(out[j], v[e]);
+                    if (4 * q + e == j) out[j] = v[e];
+                    else if (4 * q + e > j && 4 * q + e <= j + 2 * r) out[j] = op(out[j], v[e]);
         };
         edge(0);
         int q = 1;

@@ -904,6 +904,40 @@ def test_pooled_selection_windows(lens, kernel, mode):
     check_selection(got, dev.idx.cpu().numpy(), dev.mask.cpu().numpy(), wl, -1, "pooled")
 
 
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("n", [2, 300, 4097, 20000, 33000])
+def test_pooled_selection_ranks_what_it_returns(n, mode):
+    """The ranking and the pooled scores that the call returns agree where scores are infinite or NaN, in rows
+    that stay in registers and in longer ones: a maximum over NaN alone is NaN (its key lies above
+    +infinity's), at the ends of the row too.  Exact, from the returned scores' bits."""
+    rng, kernel = np.random.default_rng(n), 7
+    s32 = rng.normal(size=(2, n)).astype(np.float32)
+    s32[:, rng.integers(0, n, n // 50)] = -np.inf
+    s32[1, rng.integers(0, n, n // 90)] = np.inf
+    for at in [0, n - 9] + list(rng.integers(0, n, n // 200)):
+        s32[:, max(at, 0):at + int(rng.integers(5, 20))] = np.nan
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cu = np.array([0, n], dtype=np.int32)
+    for k in sorted({1, n // 20 + 1, n // 2, n}):
+        idx = torch.full((2, k), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full((2, n), 9, dtype=torch.uint8, device="cuda")
+        pooled = torch.zeros((2, n), dtype=torch.float32, device="cuda")
+        pdd.select_topk_pooled(dev(s32), dev(cu), n, dev(np.array([k], dtype=np.int32)), dev(np.array([0, k], dtype=np.int32)), k,
+                               idx, mask, kernel, pdd.POOL_MAX if mode == "max" else pdd.POOL_AVG, pooled, None, None, cu)
+        got = pooled.cpu().numpy()
+        pad = np.pad(np.isnan(s32), ((0, 0), (3, 3)), constant_values=mode == "max")
+        all_or_any = np.lib.stride_tricks.sliding_window_view(pad, kernel, axis=1)
+        if mode == "max":
+            assert np.array_equal(np.isnan(got), all_or_any.all(-1))
+        else:                                                    # infinities of both signs make a NaN as well
+            assert np.isnan(got[all_or_any.any(-1)]).all()
+        bits = (got + np.float32(0)).view(np.int32).astype(np.int64)
+        key = np.where(bits < 0, -1 - bits, bits + 2 ** 31)
+        want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+        assert np.array_equal(idx.cpu().numpy(), want), k
+        assert all(np.array_equal(np.flatnonzero(mask[g].cpu().numpy()), want[g]) for g in range(2)), k
+
+
 # ------------------------------------------------- sentence-level selection
 def _sentence_split(rng, lo, hi, mean_len, with_empty):
     """Ends of sentences tiling [lo, hi): geometric lengths, optionally a few empty ones."""
