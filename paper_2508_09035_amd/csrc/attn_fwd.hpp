@@ -695,8 +695,10 @@ void attn_fwd_kernel(const AttnParams p)
         }
         if (qrow >= 0 && hh == 0) {
             const int ri = token_of(qrow);
+            // A NaN sum stays NaN and reaches the joined row's sum, as the plain form's sum holds it (compared
+            // as bits, because the compiler takes float comparisons to be free of NaN).
             p.part_l[(row0 + ri) * p.Hq + h + (qrow - ri * p.G)] =
-                l_tot > 0.f ? __builtin_amdgcn_logf(l_tot) - ref : -INFINITY;
+                __float_as_uint(l_tot) == 0u ? -INFINITY : __builtin_amdgcn_logf(l_tot) - ref;
         }
         return;
     }

@@ -194,6 +194,34 @@ def test_keys_split_over_workgroups(name, d):
     assert all(torch.equal(a, b) for a, b in zip(bits, (dev.o, dev.lse, dev.imp)))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_split_over_workgroups_with_a_nan_key(d):
+    """A key of NaN, which no caller should pass, spoils the same rows in the same way whichever form runs: every
+    row that sees it has NaN outputs and a log-sum-exp of -infinity, and no other row changes."""
+    wl = W.make_custom("t", [40, 3], [6000, 2503], 8, 2, d, 0, "1/4", seed=71, chunked=True)
+    dev = DeviceWorkload(wl)
+    assert dev.workspace_bytes >= 2 * wl.total_q * 8 * (d + 1) * 4, "this shape is one that splits its keys"
+    dev.attn(False)
+    torch.cuda.synchronize()
+    clean = (dev.o.clone(), dev.lse.clone())
+    got = []
+    for at in (700, 5970):                                      # an early piece, every row; the last one, rows from 10 on
+        keep = dev.k[at].clone()
+        dev.k[at] = float("nan")
+        for scratch in (True, False):
+            dev.poison()
+            dev.attn(False, use_workspace=scratch)
+            torch.cuda.synchronize()
+            got.append((dev.o.clone(), dev.lse.clone()))
+        dev.k[at] = keep
+        (so, sl), (po, pl) = got[-2:]
+        first = max(0, at - 5960)
+        assert torch.equal(so[:first], clean[0][:first]) and torch.equal(so[40:], clean[0][40:])
+        assert torch.isnan(so[first:40]).all() and torch.isnan(po[first:40]).all()
+        assert (sl[:, first:40] == -float("inf")).all() and (pl[:, first:40] == -float("inf")).all()
+        assert torch.equal(sl[:, :first], clean[1][:, :first]) and torch.equal(sl[:, 40:], clean[1][:, 40:])
+
+
 def test_empty_sequence_in_batch_and_no_host_copies():
     wl = W.make_custom("t", [40, 0, 129], None, 2, 1, 64, 16, "1/2", seed=9)
     dev = DeviceWorkload(wl)
