@@ -7,9 +7,6 @@ import ctypes
 import os
 from typing import Optional
 
-import numpy as np
-import torch
-
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG_DIR, "libpdd.so")
 _lib = None
@@ -116,18 +113,41 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# torch and numpy load with the first call that needs them: the host-only functions work without torch.
 # The calls below spend about as long on the host as the smallest of them on the GPU, so the
 # marshalling takes the short ways: the current stream's handle without a Stream object (1.5 -> 0.3
-# us), a host array's address without numpy's ctypes view (1.2 -> 0.3 us), a descriptor filled by its
-# constructor (8 -> 3 us).
+# us) where this torch has the function that its own generated code calls for it, a host array's
+# address without numpy's ctypes view (1.2 -> 0.3 us), a descriptor filled by its constructor (8 -> 3 us).
+_np = _current_device = _raw_stream = None
+
+
+def _load_torch() -> None:
+    global _current_device, _raw_stream
+    import torch
+    _current_device = torch.cuda.current_device
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                          lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream() -> Optional[int]:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+    if _raw_stream is None:
+        _load_torch()
+    return _raw_stream(_current_device()) or None
+
+
+def _numpy():
+    global _np
+    if _np is None:
+        import numpy
+        _np = numpy
+    return _np
 
 
 def _host_i32(a):
     """Keep a contiguous int32 host array alive and return (array, address)."""
     if a is None:
         return None, None
+    np = _np or _numpy()
     arr = np.ascontiguousarray(a, dtype=np.int32)
     if arr.flags.writeable and arr.size:
         return arr, ctypes.addressof(ctypes.c_int32.from_buffer(arr))
@@ -294,6 +314,7 @@ def choose_r_L(l, k_c, k_d, delta, xi_scene, tpot_c, tpot_d, tau, delta_cloud=0.
 def pack_mask_layout(cu_seqlens_k_host):
     """pdd_pack_mask_layout (host only): int32 numpy prefix sums of the per-sequence byte
     counts of the bit stream, and the bytes per row."""
+    np = _numpy()
     cu = np.ascontiguousarray(cu_seqlens_k_host, dtype=np.int32)
     out = np.zeros(len(cu), dtype=np.int32)
     total = load_library().pdd_pack_mask_layout(len(cu) - 1, cu.ctypes.data, out.ctypes.data)

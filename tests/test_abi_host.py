@@ -217,6 +217,26 @@ def test_bench_refuses_more_than_one_gpu():
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
 
 
+def test_host_only_functions_work_without_torch():
+    """The package imports, and everything that never touches a GPU runs, where torch is not installed."""
+    import subprocess
+    import sys
+    code = """
+import sys
+sys.modules["torch"] = None                          # importing it raises
+sys.path.insert(0, sys.argv[1])
+import paper_2508_09035_amd as pdd
+assert "gfx950" in pdd.version()
+assert pdd.choose_r_L(8192, 0.02, 0.5, 300, 0.6, 30, 50, 100, delta_cloud=200) == (0.6, 43)
+assert pdd.workspace_bytes(pdd.AttnDesc(), 0) == 0
+pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
+assert pdd.pack_mask_layout([0, 13, 77])[1] == 10
+print("done")
+"""
+    r = subprocess.run([sys.executable, "-c", code, ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "done" in r.stdout, r.stderr[-800:]
+
+
 def test_pack_mask_layout_matches_the_oracle_layout():
     import oracle
     cu = np.array([0, 13, 77, 77, 1077, 1084, 5183], dtype=np.int32)
