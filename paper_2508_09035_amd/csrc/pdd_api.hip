@@ -844,12 +844,22 @@ pdd_status pdd_aggregate_scores(const float *scores, int32_t n_layers, int32_t n
     const int64_t rows = reduce_heads ? 1 : n_heads, cus = compute_units();
     auto groups = [&](int v) { return ((total_k + 64LL * v - 1) / (64 * v)) * rows; };
     const int vec = groups(4) >= cus ? 4 : groups(2) >= cus ? 2 : 1;
-    int waves = 1;
-    while (2 * waves <= pdd::kAggMaxWaves && 2 * waves <= n_layers && groups(vec) * waves < 16 * cus) waves *= 2;
-    const dim3 grid((unsigned)((total_k + 64LL * vec - 1) / (64 * vec)), (unsigned)rows), block(64 * waves);
-    if (vec == 4)      hipLaunchKernelGGL(pdd::aggregate_scores_kernel<4>, grid, block, 0, (hipStream_t)stream, p);
-    else if (vec == 2) hipLaunchKernelGGL(pdd::aggregate_scores_kernel<2>, grid, block, 0, (hipStream_t)stream, p);
-    else               hipLaunchKernelGGL(pdd::aggregate_scores_kernel<1>, grid, block, 0, (hipStream_t)stream, p);
+    p.share_log2 = 0;
+    while ((2 << p.share_log2) <= pdd::kAggMaxWaves && (2 << p.share_log2) <= n_layers && (groups(vec) << p.share_log2) < 16 * cus)
+        ++p.share_log2;
+    const int waves = (1 << p.share_log2) > pdd::kAggMinWaves ? 1 << p.share_log2 : pdd::kAggMinWaves;
+    const int64_t tokens = 64LL * vec * (waves >> p.share_log2);        // of a workgroup
+    const dim3 grid((unsigned)((total_k + tokens - 1) / tokens), (unsigned)rows), block(64 * waves);
+    // Loads in flight: eight per wave where waves are few; where they fill every compute unit by
+    // themselves that queues at the memory: two from 16 waves per compute unit on (32 layers x 8 heads x
+    // 131072, 16 waves: 20.4 us against 25.0 with eight and 22.7 with one; x 1048576 into one row 161 against
+    // 206), one from 64 on (per head x 1048576, 128 waves: 184 against 197 with eight and 207 with two).
+    hipStream_t st = (hipStream_t)stream;
+    if (p.share_log2 == 0 && groups(4) >= 64 * cus)      hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 1>), grid, block, 0, st, p);
+    else if (p.share_log2 == 0 && groups(4) >= 16 * cus) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 2>), grid, block, 0, st, p);
+    else if (vec == 4) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 8>), grid, block, 0, st, p);
+    else if (vec == 2) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<2, 8>), grid, block, 0, st, p);
+    else               hipLaunchKernelGGL((pdd::aggregate_scores_kernel<1, 8>), grid, block, 0, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(PDD_ERR_HIP, "aggregate launch: %s", hipGetErrorString(e));
     return PDD_OK;

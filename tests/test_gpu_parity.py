@@ -1099,10 +1099,12 @@ def test_select_sentences_with_ties(mean_len, levels):
 
 
 # --------------------------------------------------- cross-layer aggregation
-@pytest.mark.parametrize("layers,heads,total_k", [(33, 3, 130), (1, 9, 4099), (40, 1, 16385), (7, 17, 63), (5, 2, 70001)])
+@pytest.mark.parametrize("layers,heads,total_k", [(33, 3, 130), (1, 9, 4099), (40, 1, 16385), (7, 17, 63), (5, 2, 70001),
+                                                  (1, 1, 5), (2, 3, 1027), (3, 1, 70001), (3, 16, 65539), (5, 64, 65541)])
 @pytest.mark.parametrize("reduce_heads", [False, True])
 def test_aggregate_scores_shapes(layers, heads, total_k, reduce_heads):
-    """Layers shared by 1 to 16 waves, 1 to 4 tokens per lane, rows that start at any 4-byte address.
+    """Layers shared by 1 to 16 waves, workgroups of one to four runs of tokens, 1 to 4 tokens per lane, one to
+    eight loads in flight, rows that start at any 4-byte address.
     Positive terms: an fp32 sum of n of them, weighted, is within (n + 2) 2^-24 of its value."""
     rng = np.random.default_rng(layers)
     s32 = rng.random((layers, heads, total_k)).astype(np.float32)
