@@ -355,14 +355,16 @@ void launch_select_reg(const pdd::SelParams &p, dim3 grid, hipStream_t st)
 // stays in one.  Rows of up to 32768 candidates fit one workgroup's registers: 17.8 us divided against
 // 18.1 in one at 8 x 32768, 17.0 against 14.0 at 8 x 16384, 134 against 40 at 512 x 32768.  Longer
 // ones are read again in every pass of the one workgroup: 65536 19.1 against 117, 131072 20.9 against
-// 225 (8 rows), 153 against 367 (128 rows).  Beyond 8192 workgroups the four launches lose by their
-// total work (0.037 us each; 512 rows x 131072 would take about 610 against 497); beyond 512 chunks
-// the sums over them would.
+// 225 (8 rows), 153 against 367 (128 rows).  The four launches cost 0.035 us per chunk and so lose where
+// the rows alone keep the chip busy, two to a compute unit: divided against one workgroup per row, 320 rows of
+// 33000 / 50000 / 65536 109 / 151 / 180 against 112 / 167 / 216, 384 rows 126 / 175 / 212 against 114 / 170 / 219,
+// 512 rows 160 / 225 / 276 against 119 / 176 / 227.  Beyond 512 chunks
+// the sums over them would lose; 8192 chunks bound the scratch to 68 MiB.
 int select_chunks(int64_t n_heads, int64_t batch, int64_t max_seqlen_k)
 {
     const int64_t chunks = (max_seqlen_k + pdd::kSplitSelChunk - 1) / pdd::kSplitSelChunk;
     if (max_seqlen_k <= pdd::kSelRegCap || chunks > 512 || batch > 8192 || n_heads > 8192) return 0;
-    return n_heads * batch * chunks <= 8192 ? (int)chunks : 0;
+    return 4 * n_heads * batch <= 5 * (int64_t)compute_units() && n_heads * batch * chunks <= 8192 ? (int)chunks : 0;
 }
 
 pdd_status launch_select_split(const pdd::SelParams &s, int chunks, void *workspace, hipStream_t st)

@@ -284,6 +284,12 @@ def test_selection_workspace_reads_its_documented_fields_only():
     assert lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK) == need
     d.max_seqlen_k = 32768
     assert lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK) == 0
+    # rows that keep the chip busy by themselves stay in one workgroup each (more than 5/4 per compute unit)
+    d.max_seqlen_k = 33000
+    for batch, divided in ((40, True), (41, False), (64, False)):
+        d.batch = batch
+        need = lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_SELECT_TOPK)
+        assert need == (8 * batch * 9 * 8720 if divided else 0), batch
 
 
 def test_workspace_query_takes_any_descriptor():
