@@ -12,8 +12,7 @@
 // their sums are added in the order of the layers through LDS.  fp32, a fixed
 // order for a given shape: deterministic.  The loads of a wave are contiguous and
 // only as aligned as a score is (gfx950 loads 16 bytes from any 4-byte address),
-// so every row length takes the wide form.  A workgroup has four waves at least, also
-// where they share nothing: the LDS of the sums lets ten workgroups onto a compute unit.
+// so every row length takes the wide form.  A workgroup has four waves at least.
 // 32 layers x 8 heads x 32768 tokens into one row (34 MB, held by the last-level cache):
 // 48 -> 6.6 us (one thread per four tokens walked all 256 scores, 32 workgroups);
 // 32 x 8 x 27090 per head 13.1 -> 8.5 us.  From memory: 1 layer x 8 x 1048576 12.8 us (5.3 TB/s; 22.6 in
@@ -21,6 +20,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace pdd {
 
@@ -42,7 +42,8 @@ __global__ __launch_bounds__(64 * kAggMaxWaves) void aggregate_scores_kernel(con
 {
     typedef float vec __attribute__((ext_vector_type(VEC)));
     typedef float vec_any __attribute__((ext_vector_type(VEC), aligned(4)));
-    __shared__ vec part_sum[kAggMaxWaves][64];
+    extern __shared__ __attribute__((aligned(16))) uint8_t agg_smem[];      // sums of the waves, where they share
+    vec *const part_sum = (vec *)agg_smem;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int share = 1 << p.share_log2, part = wave & (share - 1);          // waves on these tokens, and which of them
     const int64_t group = (int64_t)blockIdx.x * (blockDim.x >> (6 + p.share_log2)) + (wave >> p.share_log2);
@@ -50,59 +51,69 @@ __global__ __launch_bounds__(64 * kAggMaxWaves) void aggregate_scores_kernel(con
     const int row = blockIdx.y;                       // output row
     const int h_lo = p.reduce_heads ? 0 : row, n_h = p.reduce_heads ? p.n_heads : 1;
     const int l_lo = (int)((int64_t)p.n_layers * part >> p.share_log2), l_hi = (int)((int64_t)p.n_layers * (part + 1) >> p.share_log2);
-    float *op = p.out + (int64_t)row * p.total_k + j0;
-    const int width = (int)min((int64_t)VEC, (int64_t)p.total_k - j0);       // tokens of this lane, <= 0 past the row
+    float *op = p.out + (int64_t)row * p.total_k;
+    // A lane past the row's end reads the last token again, so that no load hangs on a branch; the waves inside
+    // the row, almost all of them, load VEC tokens at once.
+    const bool whole = (group + 1) * 64 * VEC <= p.total_k;           // of the wave
 
-    auto load = [&](const float *sp) {
-        vec t = 0.f;
-        if (width == VEC) t = __builtin_nontemporal_load((const vec_any *)sp);
-        else
+    // AHEAD rows in flight: layers, or the heads of a layer, which are added up first.
+    auto sum = [&](auto whole_c) {
+        auto load = [&](const float *sp) {
+            vec t;
+            if constexpr (decltype(whole_c)::value) t = __builtin_nontemporal_load((const vec_any *)(sp + j0));
+            else
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) t[c] = c < width ? sp[c] : 0.f;
-        return t;
-    };
-    vec acc = 0.f;
-    if (p.accumulate && part == 0) acc = load(op);
-    if (width > 0) {
-        const float *sp = p.scores + (int64_t)l_lo * p.layer_stride + (int64_t)h_lo * p.total_k + j0;
-        if (n_h == 1) {
-            int l = l_lo;
-            for (; l + AHEAD <= l_hi; l += AHEAD, sp += AHEAD * p.layer_stride) {
+                for (int c = 0; c < VEC; ++c) t[c] = sp[min(j0 + c, (int64_t)p.total_k - 1)];
+            return t;
+        };
+        // calls add(i, row i), the rows `stride` apart; several loads in flight in the last, incomplete batch too
+        auto each = [&](const float *sp, int n, int64_t stride, auto &&add) {
+            int i0 = 0;
+            for (; i0 + AHEAD <= n; i0 += AHEAD, sp += AHEAD * stride) {
                 vec t[AHEAD];
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) t[i] = load(sp + i * p.layer_stride);
+                for (int i = 0; i < AHEAD; ++i) t[i] = load(sp + i * stride);
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) acc += (p.weights ? p.weights[l + i] : 1.f) * t[i];
+                for (int i = 0; i < AHEAD; ++i) add(i0 + i, t[i]);
             }
-            for (; l < l_hi; ++l, sp += p.layer_stride) acc += (p.weights ? p.weights[l] : 1.f) * load(sp);
+            if constexpr (AHEAD > 1) {
+                const int m = n - i0;
+                vec t[AHEAD - 1];
+#pragma unroll
+                for (int i = 0; i < AHEAD - 1; ++i)
+                    if (i < m) t[i] = load(sp + i * stride);
+#pragma unroll
+                for (int i = 0; i < AHEAD - 1; ++i)
+                    if (i < m) add(i0 + i, t[i]);
+            }
+        };
+        vec acc = 0.f;
+        if (p.accumulate && part == 0) acc = load(op);
+        const float *sp = p.scores + (int64_t)l_lo * p.layer_stride + (int64_t)h_lo * p.total_k;
+        auto weighted = [&](int l, const vec &t) { acc += (p.weights ? p.weights[l] : 1.f) * t; };
+        if (n_h == 1) {
+            each(sp, l_hi - l_lo, p.layer_stride, [&](int i, const vec &t) { weighted(l_lo + i, t); });
         } else {
             for (int l = l_lo; l < l_hi; ++l, sp += p.layer_stride) {
-                const float *hp = sp;
                 vec heads = 0.f;
-                int h = 0;
-                for (; h + AHEAD <= n_h; h += AHEAD, hp += AHEAD * (int64_t)p.total_k) {
-                    vec t[AHEAD];
-#pragma unroll
-                    for (int i = 0; i < AHEAD; ++i) t[i] = load(hp + i * (int64_t)p.total_k);
-#pragma unroll
-                    for (int i = 0; i < AHEAD; ++i) heads += t[i];
-                }
-                for (; h < n_h; ++h, hp += p.total_k) heads += load(hp);
-                acc += (p.weights ? p.weights[l] : 1.f) * heads;
+                each(sp, n_h, p.total_k, [&](int, const vec &t) { heads += t; });
+                weighted(l, heads);
             }
         }
-    }
+        return acc;
+    };
+    vec acc = whole ? sum(std::true_type{}) : sum(std::false_type{});
     if (share > 1) {
-        if (part > 0) part_sum[wave][lane] = acc;
+        if (part > 0) part_sum[64 * wave + lane] = acc;
         __syncthreads();
         if (part > 0) return;
-        for (int w = 1; w < share; ++w) acc += part_sum[wave + w][lane];
+        for (int w = 1; w < share; ++w) acc += part_sum[64 * (wave + w) + lane];
     }
-    if (width == VEC) *(vec_any *)op = acc;
+    if (whole) *(vec_any *)(op + j0) = acc;
     else
 #pragma unroll
         for (int c = 0; c < VEC; ++c)
-            if (c < width) op[c] = acc[c];
+            if (j0 + c < p.total_k) op[j0 + c] = acc[c];
 }
 
 }  // namespace pdd

@@ -855,13 +855,15 @@ pdd_status pdd_aggregate_scores(const float *scores, int32_t n_layers, int32_t n
     // Loads in flight: eight per wave where waves are few; where they fill every compute unit by
     // themselves that queues at the memory: two from 16 waves per compute unit on (32 layers x 8 heads x
     // 131072, 16 waves: 20.4 us against 25.0 with eight and 22.7 with one; x 1048576 into one row 161 against
-    // 206), one from 64 on (per head x 1048576, 128 waves: 184 against 197 with eight and 207 with two).
+    // 206), one from 32 on (32 layers x 2 heads x 1048576, 32 waves: 39.5 us against 43.6 with two; 32 x 8 per head,
+    // 128 waves: 184 against 207 with two and 197 with eight).
     hipStream_t st = (hipStream_t)stream;
-    if (p.share_log2 == 0 && groups(4) >= 64 * cus)      hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 1>), grid, block, 0, st, p);
-    else if (p.share_log2 == 0 && groups(4) >= 16 * cus) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 2>), grid, block, 0, st, p);
-    else if (vec == 4) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 8>), grid, block, 0, st, p);
-    else if (vec == 2) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<2, 8>), grid, block, 0, st, p);
-    else               hipLaunchKernelGGL((pdd::aggregate_scores_kernel<1, 8>), grid, block, 0, st, p);
+    const int smem = p.share_log2 > 0 ? waves * 64 * vec * (int)sizeof(float) : 0;
+    if (p.share_log2 == 0 && groups(4) >= 32 * cus)      hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 1>), grid, block, smem, st, p);
+    else if (p.share_log2 == 0 && groups(4) >= 16 * cus) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 2>), grid, block, smem, st, p);
+    else if (vec == 4) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<4, 8>), grid, block, smem, st, p);
+    else if (vec == 2) hipLaunchKernelGGL((pdd::aggregate_scores_kernel<2, 8>), grid, block, smem, st, p);
+    else               hipLaunchKernelGGL((pdd::aggregate_scores_kernel<1, 8>), grid, block, smem, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(PDD_ERR_HIP, "aggregate launch: %s", hipGetErrorString(e));
     return PDD_OK;
