@@ -22,6 +22,7 @@
 // order, deterministic.
 #pragma once
 #include "attn_fwd.hpp"
+#include "wave_scan.hpp"
 
 namespace pdd {
 
@@ -40,9 +41,10 @@ struct ImpParams {
     // fixed order r = 0, 1, ...
     int32_t n_split;
     float *part;
-    // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave.
+    // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave, whether a
+    // workgroup finds its piece of the keys by a scan over the sequences' lengths.
     uint32_t g_magic;
-    int32_t groups;
+    int32_t groups, scan;
 };
 
 constexpr int kImpWaves = 4;
@@ -245,6 +247,7 @@ void importance_kernel(const ImpParams p)
 // tokens x 32/8 heads, 128 rows: 600 cycles per block and SIMD, 384 of vector issue; 50 -> 42 us), by the
 // first loads on short ones (4096 tokens, 64 rows: 9.1 -> 7.0 us; 5 to 64 tokens behind 700 to 12345 keys
 // x 4 sequences 40 -> 26; 1 token behind 500 to 7900 keys x 8 sequences 25 -> 15.6).
+constexpr int kImpScanMax = 64;         // sequences whose lengths one wave scans
 template <int D>
 constexpr int importance_rows_block_bytes() { return 32 * 2 * D + 32 * (int)sizeof(float); }
 
@@ -258,15 +261,29 @@ __global__ __launch_bounds__(1024) void importance_rows_kernel(const ImpParams p
 
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
-    const int b = bid % p.B;
-    const int kt = bid / p.B;
+    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
+    int b, kt;
+    if (!p.scan) {                                // the last pieces, which may be short, come last
+        b = bid % p.B;
+        kt = bid / p.B;
+    } else {
+        // Sequences of different lengths: workgroup number `bid` takes the bid-th piece that has keys.  (With a
+        // grid of the longest sequence's pieces for each, the ones without keys settle which shader engine the others
+        // go to, because workgroups are dealt out round robin: 8 prompts of 512 to 7900 tokens, 128 rows, kept one in
+        // four of the compute units for half of the work, 66 us; 37 like this.)
+        const int n = lane < p.B ? max(min(p.cu_k[lane + 1], p.total_k) - min(p.cu_k[lane], p.total_k), 0) : 0;
+        const int keys_log2 = 36 - __builtin_clz(waves * p.groups);          // 32 * waves * groups, a power of two
+        const uint32_t own = (uint32_t)(n + (1 << keys_log2) - 1) >> keys_log2, upto = wave_incl_scan(own);
+        const uint64_t after = __ballot(upto > (uint32_t)bid);
+        if (after == 0) return;
+        b = (int)__builtin_ctzll(after);
+        kt = bid - __builtin_amdgcn_readlane((int)(upto - own), b);
+    }
     const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
     const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
     const int nq = qe - qs, nk = ke - ks, delta = nk - nq;
-    const int waves = blockDim.x >> 6;
     const int j_wg0 = kt * waves * p.groups * 32;
     if (j_wg0 >= nk) return;
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5;
     const int W = (nq > 0 && delta >= 0) ? ((p.window < 0 || p.window > nq) ? nq : p.window) : 0;

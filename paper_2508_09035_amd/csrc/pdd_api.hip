@@ -429,12 +429,18 @@ int importance_split(const pdd_attn_desc *d, int window)
 // Whether the importance takes the form with all window rows in LDS, and its launch shape.
 // The rows have to fit the 160 KB of a compute unit (19 blocks of 32 at head_dim 128).  Above 80 KB one
 // 16-wave workgroup runs per compute unit: only for launches that fill the chip's 4096 wave slots with 32-key
-// groups (64 tokens x 4 behind 8192 keys, 64/8 heads 55 -> 51 us; 200 tokens behind 16000, 4/2
-// heads, would take 17 us against 11.4 of the streaming kernel, which divides the rows).  Below,
+// groups (64 tokens x 4 behind 8192 keys, 64/8 heads 59 -> 50 us; 200 tokens behind 16000, 4/2
+// heads, would take 17 us against 11.4 of the streaming kernel, which divides the rows).  A round of such
+// workgroups takes 1.9 times as long with two groups per wave as with one, so the rounds decide: 32768 tokens, 128
+// rows of 32/8 heads (one round or two) 42.3 us with two groups, 46.5 with one, 8 x 5000 (two or three) 72.6 and
+// 63.7, 16 x 1000 (one either way) 34.8 and 25.6; 52, 63 and 32 with the streaming kernel.  Below 80 KB
 // two or more run per compute unit; four waves each while all of them are resident at once (4096
 // tokens, 64 rows: 7.0 us, 8.7 with eight waves), else eight waves, which load the rows half as often,
-// and two groups per wave from 4096 groups on (8 prompts of 512 to 7900 tokens, 64 rows: 38 us with
-// four waves, 30.0 / 29.4 with eight and one / two groups; 34 with the streaming kernel).
+// and two groups per wave from 4096 groups on (8 prompts of 512 to 7900 tokens, 64 rows: 26.5 us with
+// four waves, 24.4 / 23.3 with eight and one / two groups; 35 with the streaming kernel), or four waves where there is
+// one block of rows and so little to load (8 x 5000, 8 heads of head_dim 64, 32 rows: 10.1 us, 11.4 with eight).  Sixteen
+// blocks or more (head_dim 64) for few keys are a long walk, which the streaming kernel divides: 300 tokens 8.7 us
+// against 7.7, 4096 x 16/2 heads 9.2 against 8.2, 3000 x 3 8.7 against 9.4 to 10.3.
 struct ImpRowsPlan { int waves, groups; size_t lds; };            // waves == 0: the form does not apply
 ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
 {
@@ -445,11 +451,16 @@ ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
     const int64_t lds = blocks * (d->head_dim == 128 ? pdd::importance_rows_block_bytes<128>() : pdd::importance_rows_block_bytes<64>());
     if (lds > kLdsBytes) return none;
     const int64_t tasks = (int64_t)(d->total_k / 32 + d->batch) * d->n_kv_heads, slots = 16 * (int64_t)compute_units();
-    const int groups = tasks >= slots ? 2 : 1;
-    if (lds > kLdsBytes / 2) return tasks >= slots ? ImpRowsPlan{16, groups, (size_t)lds} : none;
+    if (lds > kLdsBytes / 2) {
+        if (tasks < slots) return none;
+        const double rounds = (double)d->total_k * d->n_kv_heads / (1024.0 * compute_units());    // with two groups per wave
+        const bool two = 1.9 * std::ceil(rounds - 0.05) <= std::ceil(2.0 * rounds - 0.05);
+        return {16, two ? 2 : 1, (size_t)lds};
+    }
+    if (blocks >= 16 && (int64_t)d->batch * ((d->max_seqlen_k + 31) / 32) * d->n_kv_heads < 2 * compute_units()) return none;
     const int64_t resident = lds > kLdsBytes / 3 ? 2 : lds > kLdsBytes / 4 ? 3 : 4;     // 4-wave workgroups per compute unit
     if (tasks <= 4 * resident * compute_units()) return {4, 1, (size_t)lds};
-    return {8, groups, (size_t)lds};
+    return {blocks == 1 && tasks >= slots ? 4 : 8, tasks >= slots ? 2 : 1, (size_t)lds};
 }
 
 // What the streaming kernel can use, also where the form above runs and needs none: the figure must not
@@ -461,12 +472,17 @@ size_t importance_workspace(const pdd_attn_desc *d, int window)
 }
 
 template <typename Kern>
-pdd_status launch_importance_rows(Kern kern, const pdd::ImpParams &p, const ImpRowsPlan &rows, int max_k, hipStream_t st)
+pdd_status launch_importance_rows(Kern kern, pdd::ImpParams &p, const ImpRowsPlan &rows, int max_k, hipStream_t st)
 {
     const pdd_status s = raise_lds_limit(reinterpret_cast<const void *>(kern), kLdsBytes);
     if (s) return s;
     const int keys = 32 * rows.waves * rows.groups;
-    const int64_t blocks = ((int64_t)max_k + keys - 1) / keys * p.B * p.Hkv;
+    int64_t pieces = ((int64_t)max_k + keys - 1) / keys * p.B;
+    // Sequences of different lengths: only pieces that exist, found by a scan over the lengths (see the kernel; it
+    // costs 0.2 us, so only where the workgroups are not all at once on the chip anyway).
+    p.scan = p.B <= pdd::kImpScanMax && (int64_t)p.B * max_k != p.total_k && pieces * p.Hkv > compute_units();
+    if (p.scan && pieces > p.total_k / keys + p.B) pieces = p.total_k / keys + p.B;
+    const int64_t blocks = pieces * p.Hkv;
     if (blocks > 0x7fffffffLL) return fail(PDD_ERR_INVALID_ARG, "launch grid too large");
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * rows.waves), rows.lds, st, p);
     const hipError_t e = hipGetLastError();

@@ -29,6 +29,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "wave_scan.hpp"
 
 namespace pdd {
 
@@ -87,19 +88,7 @@ __device__ __forceinline__ uint32_t order_key(float x)
 // POOL = true ranks the 1-D pooled scores (see PoolStage);
 // the instantiation for unpooled scores carries none of the pooling code.
 // ---------------------------------------------------------------------------
-constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 21 rounds by thirds, 8 that cut the keys to a quarter
-
-// inclusive prefix sum over the 64 lanes of a wave (DPP row shifts and row broadcasts)
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);   // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);   // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);   // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);   // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
-    return x;
-}
+constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 21 rounds by thirds, 8 that cut the keys to a quarter, 2 after draw_in
 
 // Next value to probe in the threshold search over the bracket [lo, hi] (lo < hi) that holds
 // `inside` keys, of which the `need` largest (1 <= need <= inside) lie at or above the threshold.

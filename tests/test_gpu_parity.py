@@ -397,8 +397,15 @@ def test_importance_with_and_without_scratch(name):
     ([300, 97, 64, 1023], None, 6, 2, 128, 203),                  # 20 blocks: the streaming kernel
     ([1000, 1300], None, 8, 2, 64, 300),                          # 1200 rows of head_dim 64: the streaming kernel
     ([7, 0, 1, 40], [900, 77, 2049, 1500], 6, 2, 128, -1),        # chunks, one without tokens: its keys read zero
-    ([9, 30], [6000, 3100], 16, 16, 64, -1),                      # eight waves, two key groups each
-    ([64], [8161], 128, 16, 128, -1),                             # sixteen waves, two key groups each, 512 rows
+    ([9, 30], [6000, 3100], 16, 16, 64, -1),                      # one block of rows: four waves, two key groups each
+    ([9, 40], [6000, 3100], 16, 16, 64, -1),                      # two: eight waves, two key groups each
+    ([64], [8161], 128, 16, 128, -1),                             # sixteen waves, one key group each, 512 rows
+    ([64], [16320], 128, 16, 128, -1),                            # sixteen waves, two key groups each
+    # sequences of different lengths, whose workgroups look up their pieces: sixteen waves of two groups; four of one
+    ([64, 20, 3], [3, 2500, 9990], 128, 16, 128, -1),
+    ([17, 0, 5, 40], [900, 70, 5000, 1500], 32, 8, 64, -1),
+    ([1] * 63 + [9, 3], list(range(65)), 32, 8, 64, -1),          # 65 sequences: more than are looked up
+    ([300], None, 16, 2, 64, 64),                                 # 16 blocks of rows for few keys: the streaming kernel
 ])
 def test_importance_rows_in_lds(lens, prefix, hq, hkv, d, window):
     """Every launch shape of the importance kernel that holds the window rows in LDS, and the shapes next to
