@@ -171,11 +171,28 @@ __global__ __launch_bounds__(kSelThreads) void select_level_kernel(const SplitSe
         split_sel_digit(p.hist[(LEVEL - 1) & 1] + row0 * (kSplitSelBins / 2), p.group[(LEVEL - 1) & 1] + row0 * kSplitSelGroups,
                         r.chunks, chunk, 11, lane, wave, st);
     }
+    uint32_t bin[4];
+    bool part[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const uint32_t bin = LEVEL == 0 ? key[j] >> 21 : LEVEL == 1 ? key[j] >> 10 & 2047u : key[j] & 1023u;
-        const bool part = x0 + j < r.n && (LEVEL == 0 || key[j] >> (LEVEL == 1 ? 21 : 10) == st.prefix);
-        if (part) atomicAdd(&hist[bin], 1u);
+        bin[j] = LEVEL == 0 ? key[j] >> 21 : LEVEL == 1 ? key[j] >> 10 & 2047u : key[j] & 1023u;
+        part[j] = x0 + j < r.n && (LEVEL == 0 || key[j] >> (LEVEL == 1 ? 21 : 10) == st.prefix);
+    }
+    // Atomics on one address go one after another.  Where the wave's first keys all share a bin, the lanes that have
+    // the common bin add as one (equal scores: 320 rows of 33000 207 -> 115 us, 8 of 131072 32 -> 24).
+    const uint32_t common = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin[0]);
+    if (__ballot(part[0] && bin[0] == common) == ~0ull) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool same = part[j] && bin[j] == common;
+            const uint32_t n = (uint32_t)__popcll(__ballot(same));
+            if (lane == 0) atomicAdd(&hist[common], n);
+            if (part[j] && !same) atomicAdd(&hist[bin[j]], 1u);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (part[j]) atomicAdd(&hist[bin[j]], 1u);
     }
     __syncthreads();
     const uint2 h = ((const uint2 *)hist)[tid];
