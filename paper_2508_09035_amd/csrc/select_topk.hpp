@@ -88,7 +88,7 @@ __device__ __forceinline__ uint32_t order_key(float x)
 // POOL = true ranks the 1-D pooled scores (see PoolStage);
 // the instantiation for unpooled scores carries none of the pooling code.
 // ---------------------------------------------------------------------------
-constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 21 rounds by thirds, 8 that cut the keys to a quarter, 2 after draw_in
+constexpr int kSelMaxProbes = 72;       // a 32-bit bracket needs at most 2 x 21 rounds by thirds, 8 that cut the keys to a quarter
 
 // Next value to probe in the threshold search over the bracket [lo, hi] (lo < hi) that holds
 // `inside` keys, of which the `need` largest (1 <= need <= inside) lie at or above the threshold.
@@ -403,6 +403,7 @@ void select_topk_reg_kernel(const SelParams p)
     //     once at most kSelFinish are left they are ranked directly.
     // Every probed value is > lo > 0, so empty slots never count.
     uint32_t lo = sh_min + 1u, hi = sh_max;                      // lo: back from key - 1 (kk >= 1: the row has a real key)
+    if (kk == n) hi = lo;                                        // everything is kept: T is the minimum, and no tie is cut
     uint32_t c_lo = (uint32_t)n, c_above = 0, pa = 0, pb = 0;
     bool placed = false, interp = true;
     int round = 0;
