@@ -289,6 +289,13 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     const double partial = (double)n_split * per_split * seen * 1e-6 / 4.0;     // written and read back, at 4 TB/s each
     const double split = std::fmax(tiles * 0.8, base * tiles_all * seen / cus * (d64 ? 0.95 : 1.1)) + 8.0 + partial;
     if (split > 0.9 * plain) return none;
+    // A prompt's tiles are full and of very different lengths, two workgroups share most compute units, and there are
+    // as many partial rows as rows: fitted to 97 such launches, within 7 %.  (8/8 heads, head_dim 128, plain against
+    // split: 1500 tokens 26 and 30 us, 2441 39 and 46, 694 + 2020 33 and 43, 4000 63 and 66; 4/2 heads 2441 37 and 29.)
+    if (!chunked) {
+        const double steps = base * tiles_all * seen / cus;
+        if ((d64 ? 7.7 + 0.66 * tiles + 0.24 * steps + 5.2 * partial : 10.5 + 0.79 * tiles + 0.46 * steps + 2.8 * partial) > plain) return none;
+    }
     return {(int)tiles, (int)n_split, (size_t)n_split * per_split};
 }
 
