@@ -250,18 +250,56 @@ def test_strided_views_of_a_packed_qkv_buffer():
     compare_all(wl, dev, label="strided")
 
 
+@pytest.mark.parametrize("layout", ["packed", "head-major"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_split_over_workgroups_in_other_layouts(d, layout):
+    """The key-split form packs the heads of a group into its tiles with the head strides of Q and O: views of one
+    QKV buffer, and head-major tensors, give the bits of the contiguous ones (which the oracle has checked)."""
+    wl = W.make_custom("t", [40, 0, 3], [6000, 70, 2503], 6, 2, d, 0, "1/4", seed=75, chunked=True)
+    dev = DeviceWorkload(wl)
+    assert dev.workspace_bytes >= 2 * wl.total_q * 6 * (d + 1) * 4, "this shape is one that splits its keys"
+    dev.poison()
+    dev.attn(True)
+    torch.cuda.synchronize()
+    want = [x.clone() for x in (dev.o, dev.lse, dev.imp)]
+    if layout == "packed":              # queries and outputs side by side per token, keys and values likewise
+        qo = torch.zeros((wl.total_q, 12, d), dtype=torch.bfloat16, device="cuda")
+        kv = torch.zeros((wl.total_k, 4, d), dtype=torch.bfloat16, device="cuda")
+        qo[:, :6], kv[:, :2], kv[:, 2:] = dev.q, dev.k, dev.v
+        dev.q, dev.o, dev.k, dev.v = qo[:, :6], qo[:, 6:], kv[:, :2], kv[:, 2:]
+    else:
+        dev.q, dev.k, dev.v, dev.o = (x.transpose(0, 1).contiguous().transpose(0, 1) for x in (dev.q, dev.k, dev.v, dev.o))
+    assert not dev.q.is_contiguous() and not dev.o.is_contiguous()
+    dev.o.fill_(float("nan"))
+    dev.lse.fill_(float("nan"))
+    dev.imp.fill_(float("nan"))
+    dev.workspace.fill_(0xFF)
+    dev.attn(True)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(want, (dev.o, dev.lse, dev.imp)))
+
+
 def test_rows_a_mebibyte_apart_close_to_the_4_gib_span_limit():
     """Q, K and V rows 1 MiB apart (views into 3.1 GiB buffers): byte offsets inside the sequence's
     span run up to 3.4 * 2^30, close to what 32-bit buffer offsets can address; same bits as
-    the packed layout.  With the rows 1.25 MiB apart the span passes the limit and the call is
-    refused on the host."""
+    the packed layout, in the key-split form (with scratch) and in the plain one (without).  With the rows
+    1.25 MiB apart the span passes the limit and the call is refused on the host."""
     n, hq, hkv, d = 3000, 4, 2, 128
     wl = W.make_custom("t", [n], None, hq, hkv, d, 64, "1/2", seed=23)
     dev = DeviceWorkload(wl)
-    dev.poison()
-    dev.step()
-    torch.cuda.synchronize()
-    want = [x.clone() for x in (dev.o, dev.lse, dev.imp, dev.idx, dev.mask)]
+
+    def both_forms():
+        got = []
+        for scratch in (True, False):
+            dev.poison()
+            dev.attn(True, use_workspace=scratch)
+            dev.select()
+            torch.cuda.synchronize()
+            got.append([x.clone() for x in (dev.o, dev.lse, dev.imp, dev.idx, dev.mask)])
+        return got
+
+    want = both_forms()
+    assert not torch.equal(want[0][0], want[1][0]), "with scratch this shape splits its keys"
     row = 1 << 19                                            # elements between rows = 1 MiB
     bufs = []
     for name, heads in (("k", hkv), ("v", hkv), ("q", hq)):       # Q too: the importance kernel addresses it like that
@@ -270,12 +308,9 @@ def test_rows_a_mebibyte_apart_close_to_the_4_gib_span_limit():
         view.copy_(getattr(dev, name))
         setattr(dev, name, view)
         bufs.append(big)
-    dev.poison()
-    dev.step()
-    torch.cuda.synchronize()
-    for what, a, b in zip(("O", "lse", "importance", "indices", "mask"), want,
-                          (dev.o, dev.lse, dev.imp, dev.idx, dev.mask)):
-        assert torch.equal(a, b), what
+    for form, a, b in zip(("key split", "plain"), want, both_forms()):
+        for what, x, y in zip(("O", "lse", "importance", "indices", "mask"), a, b):
+            assert torch.equal(x, y), f"{form}: {what}"
     # (3000 + 512) rows x 1 MiB stays below 4 GiB; with rows 1.25 MiB apart it does not
     wrow = row + (row >> 2)
     del bufs
@@ -321,22 +356,38 @@ def test_two_streams_at_once_with_separate_scratch():
             assert torch.equal(a, b), what
 
 
-def test_standalone_importance_equals_fused_and_is_deterministic():
-    wl = W.make_custom("t", [700, 90], None, 8, 2, 128, 64, "1/2", seed=31)
+@pytest.mark.parametrize("lens,heads,window,streams", [([700, 90], (8, 2), 64, False),
+                                                       ([300, 97, 64, 1023], (6, 2), 203, True)])
+def test_standalone_importance_equals_fused_and_is_deterministic(lens, heads, window, streams):
+    """The standalone call against the one behind the attention, with and without scratch: window rows that fit
+    the LDS (which need none), and longer windows in the streaming kernel, whose rows are divided over workgroups
+    where there is scratch."""
+    wl = W.make_custom("t", lens, None, *heads, 128, window, "1/2", seed=31)
     dev = DeviceWorkload(wl)
+    desc, keep = pdd.make_desc(dev.q, dev.k, None, None, dev.cu_q, dev.cu_k, dev.max_q, dev.max_k, wl.scale, wl.window)
+    need = pdd.workspace_bytes(desc, pdd.CALL_TOKEN_IMPORTANCE)
+    del keep
+    assert (need > 0) == streams and dev.workspace_bytes >= need
+    dev.poison()
     dev.step()
     O1, l1, i1, x1, m1 = dev.results()
     imp2 = torch.full_like(dev.imp, float("nan"))
+    if streams:
+        dev.workspace.fill_(0xFF)
     pdd.token_importance(dev.q, dev.k, dev.lse, imp2, dev.cu_q, dev.cu_k, dev.max_q, dev.max_k,
                          wl.scale, wl.window, wl.cu_seqlens_q, wl.cu_seqlens_k, workspace=dev.workspace)
     torch.cuda.synchronize()
     assert np.array_equal(imp2.cpu().numpy(), dev.imp.cpu().numpy())
+    assert not streams or (dev.workspace != 0xFF).any(), "the scratch was not used"
     # without scratch the single-pass form runs: same values up to the order of the fp32 additions
     imp3 = torch.full_like(dev.imp, float("nan"))
     pdd.token_importance(dev.q, dev.k, dev.lse, imp3, dev.cu_q, dev.cu_k, dev.max_q, dev.max_k,
                          wl.scale, wl.window, wl.cu_seqlens_q, wl.cu_seqlens_k)
     torch.cuda.synchronize()
     np.testing.assert_allclose(imp3.cpu().numpy(), dev.imp.cpu().numpy(), rtol=1e-5, atol=1e-12)
+    oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, wl.window)
+    rel_close(imp2.cpu().numpy().astype(np.float64), oI, "importance")
+    rel_close(imp3.cpu().numpy().astype(np.float64), oI, "importance without scratch")
     dev.poison()
     dev.step()
     O2, l2, i2, x2, m2 = dev.results()
