@@ -116,7 +116,9 @@ enum {
  *            query tile are divided over several workgroups that leave 32-bit
  *            partial rows, combined by a second kernel.  All forms are
  *            deterministic; they differ from each
- *            other in the order of the fp32 additions.  The contents are
+ *            other in the order of the fp32 additions, and the key-split form's
+ *            O also in where its probabilities round to bf16 (2e-3 of O, as far
+ *            as either is from the exact result).  The contents are
  *            scratch before and after the call; concurrent calls need separate
  *            workspaces.
  * Requires Nq_b == Nk_b for every sequence when host copies are given (use the
@@ -154,7 +156,8 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * whose longest fills less than 70 % of its query tiles (the second walk costs
  * what full tiles cost) and calls that are given less use the separate
  * importance kernel described above; pdd_workspace_bytes says what the shape
- * will use.  All forms are deterministic and agree to fp32 rounding.
+ * will use.  All forms are deterministic and agree to fp32 rounding (O of the
+ * key-split form to bf16 rounding).
  */
 pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chunk,
                                     const void *k_all, const void *v_all, void *o, float *lse,

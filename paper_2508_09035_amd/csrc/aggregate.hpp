@@ -14,8 +14,8 @@
 // only as aligned as a score is (gfx950 loads 16 bytes from any 4-byte address),
 // so every row length takes the wide form.  A workgroup has four waves at least.
 // 32 layers x 8 heads x 32768 tokens into one row (34 MB, held by the last-level cache):
-// 48 -> 6.6 us (one thread per four tokens walked all 256 scores, 32 workgroups);
-// 32 x 8 x 27090 per head 13.1 -> 8.5 us.  From memory: 1 layer x 8 x 1048576 12.8 us (5.3 TB/s; 22.6 in
+// 48 -> 6.0 us (one thread per four tokens walked all 256 scores, 32 workgroups);
+// 32 x 8 x 27090 per head 13.1 -> 6.1 us (7.7 and 7.6 where every call has other scores).  From memory: 1 layer x 8 x 1048576 12.8 us (5.3 TB/s; 22.6 in
 // workgroups of one wave), 32 x 8 x 1048576 184 per head, 161 into one row (5.8 and 6.7 TB/s).
 #pragma once
 #include <hip/hip_runtime.h>

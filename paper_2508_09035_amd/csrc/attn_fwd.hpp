@@ -25,9 +25,15 @@
 //   long prefix, long prompts with few heads): a tile's 128 rows are (token, head of the KV group)
 //   pairs, so one read of K and V serves the whole group, and a workgroup walks only `split_tiles`
 //   key tiles; attn_combine_kernel joins the pieces.  V tiles are double instead of triple
-//   buffered, so that two workgroups share a compute unit's LDS.  Bound by HBM with few rows
-//   (8 sequences x 1 token, 97 MB of K and V: 102 -> 20 us, 4.9 TB/s of a copy's 5.1), by the
-//   matrix pipe with many (256 tokens behind 8192 keys, 32/8 heads: 122 -> 42 us, 0.83 PFLOP/s).
+//   buffered, so that two workgroups share a compute unit's LDS.  Calls, the join included, where
+//   every one has other inputs / where K and V stay in the last-level cache: 8 sequences x 1 token
+//   (97 MB of K and V) 131 -> 36 / 100 -> 25 us, 256 tokens behind 8192 keys, 32/8 heads
+//   134 -> 59 / 112 -> 50.  With few rows bound by the requests in flight (27 to 31 us of the first,
+//   3.1 to 3.6 TB/s of a copy's 4.9: a tile's rows lie in one wave, which computes while the other
+//   three only request, one V tile ahead), with many by the matrix pipe.
+//   A piece has a softmax reference of its own, so its probabilities round to bf16 at other places
+//   than the plain form's: the outputs of the two differ by 2e-3, and both are 2.3e-3 from the result in 64
+//   bits (34 chunks and prompts; log-sum-exp 5e-8 in both).
 //
 // Data movement and instruction schedule
 //   * K and V tiles (64 keys x 2 D bytes) go from HBM/L2 straight into LDS with
@@ -472,7 +478,8 @@ void attn_fwd_kernel(const AttnParams p)
     // through softmax and PV, the MFMAs of block u+1 are already issued.  Tile t
     // lives in LDS buffer t % 3; at every tile boundary the current block is in sA.
     f32x16 sA = zero16, sB = zero16;
-    if (n_tiles > 0) qk_block(0, sA);   // every wave has rows that see block 0
+    // (a row of the key-split form that sees none of its piece's keys is masked out of it below)
+    if (n_tiles > 0) qk_block(0, sA);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();                    // V tile 0, K tile 1; the next requests overwrite the Q rows
 
@@ -624,7 +631,8 @@ void attn_fwd_kernel(const AttnParams p)
         __syncthreads();
     };
     // The first block: masked where it touches the diagonal, then every row takes its first
-    // reference from it (key 0 is visible to every row).
+    // reference from it: key 0 is visible to every row, except in the key-split form, where the
+    // row may end before the piece and then has no reference, no sums and log-sum-exp -inf.
     int it = 0;
     if (n_tiles > 0) {
         if (31 > wave_lim_min) {

@@ -246,7 +246,8 @@ void importance_kernel(const ImpParams p)
 // with some 0.3 us of work between barriers.)  Bound by the exponentials on long launches (32768
 // tokens x 32/8 heads, 128 rows: 600 cycles per block and SIMD, 384 of vector issue; 50 -> 42 us), by the
 // first loads on short ones (4096 tokens, 64 rows: 9.1 -> 7.0 us; 5 to 64 tokens behind 700 to 12345 keys
-// x 4 sequences 40 -> 26; 1 token behind 500 to 7900 keys x 8 sequences 25 -> 15.6).
+// x 4 sequences 40 -> 19.5; 1 token behind 500 to 7900 keys x 8 sequences 25 -> 10.8, K in the last-level cache;
+// 21.9 and 13.0 where every call has other inputs).
 constexpr int kImpScanMax = 64;         // sequences whose lengths one wave scans
 template <int D>
 constexpr int importance_rows_block_bytes() { return 32 * 2 * D + 32 * (int)sizeof(float); }

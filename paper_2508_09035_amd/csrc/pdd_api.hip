@@ -230,14 +230,18 @@ const char *importance_limits(const pdd_attn_desc *d)
 // (token, head) rows of a KV group into its tiles and cuts the walk into pieces of `tiles` key
 // tiles; it pays with 32-bit partial rows, written once and read back by a second kernel.
 // The choice compares two estimates in microseconds, fitted to kernel times on 256 compute units
-// (plain against split, second kernel included): 1 token x 8 sequences behind 500 to 7900 keys,
-// 32/8 heads, 102 -> 25; 5 to 64 tokens x 4 sequences behind 700 to 12345 keys, 148 -> 42; 200
-// tokens behind 16000, 4/2 heads, 215 -> 30; prompts of 2048 tokens x 1 head 31 -> 18 and of 8192
+// (plain against split, second kernel included, calls repeated on the same inputs): 1 token x 8
+// sequences behind 500 to 7900 keys, 32/8 heads, 100 -> 25; 5 to 64 tokens x 4 sequences behind 700 to
+// 12345 keys, 148 -> 42; 200 tokens behind 16000, 4/2 heads, 209 -> 25 (131 -> 36, 203 -> 54 and 235 -> 26
+// where every call has other inputs); prompts of 2048 tokens x 1 head 31 -> 18 and of 8192
 // x 4/2 heads 117 -> 94; the plain form is better on 128 tokens x 8 behind 4000, 64/8 heads
 // (135 against 153), 256 x 4 behind 8192, 64/8 heads (238 against 291) and prompts that fill the
 // chip (8192 tokens x 8 heads 135 against 165).  One step is one key tile of one workgroup.
+// These batches are even or nearly so.  One long chunk beside short ones is priced as if all were long, and
+// its partial rows are sized for the longest sequence's pieces: such batches may stay whole where the split
+// form would be faster.
 // The scratch of a chunked call stays within the built-in scratch, so that the call without a
-// workspace argument takes the same form.  Depends on the descriptor and the device only.
+// workspace argument takes the same form where it has importance to return.  Depends on the descriptor and the device only.
 SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
 {
     const SplitPlan none = {0, 0, 0};
@@ -257,9 +261,9 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     const double seen = 1.0 - 0.5 * max_q / d->max_seqlen_k;    // share of the keys an average query tile walks
 
     // Key tiles per workgroup: about one workgroup per compute unit, 8 to 24 tiles (fewer and the
-    // start of a workgroup and the partial rows cost more than they spread; decode of the 8
-    // sequences above: 26 us at 8 tiles, 20 at 12, 21 at 16, 26 at 24), evened out over the
-    // longest sequence, and as many more as the scratch asks for.
+    // start of a workgroup and the partial rows cost more than they spread; first kernel for the 8
+    // sequences of one token above, inputs in the last-level cache: 26 us at 8 tiles, 20 at 12, 21 at 16,
+    // 26 at 24), evened out over the longest sequence, and as many more as the scratch asks for.
     const double base = (double)(n_qt * Hkv);
     double T = 24;
     if (cus > base * B) T = std::ceil(tiles_all * base / (cus - base * B));
