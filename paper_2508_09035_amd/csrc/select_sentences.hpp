@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     __shared__ __attribute__((aligned(16))) uint2 fin[kSentFinish];              // key, length
     __shared__ struct { uint32_t bin, tokens, sentences, above, n_above; } place;
     __shared__ uint32_t fin_count, fin_T, fin_above, sh_kept;
+    __shared__ uint2 range[kSentMaxProbes];                       // smallest and largest key that a probe left inside
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,7 +97,10 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     const float *seq = p.scores + (int64_t)g * p.total_k + ks;
     uint8_t *mrow = p.mask ? p.mask + (int64_t)g * p.total_k + ks : nullptr;
 
-    if (tid < kSentMaxProbes) probe_tot[tid] = 0;
+    if (tid < kSentMaxProbes) {
+        probe_tot[tid] = 0;
+        range[tid] = make_uint2(0xffffffffu, 0u);
+    }
     hist[tid] = 0;
     if (tid < kSentFinish) fin[tid] = make_uint2(0, 0);
     if (tid == 0) { fin_count = 0; sh_kept = 0; }
@@ -265,7 +269,15 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
             const unsigned long long t = probe_tot[probe];
             if ((uint32_t)t >= need) { lo = mid; w_lo = (uint32_t)t; n_lo = (uint32_t)(t >> 32); }
             else { hi = mid - 1u; above = (uint32_t)t; n_above = (uint32_t)(t >> 32); }
-            interp = !interp || 4u * (w_lo - above) <= inside;
+            const bool halved = !interp;
+            interp = halved || 4u * (w_lo - above) <= inside;
+            // sentences of one score (2 x 2112 tokens, 845 sentences, most of score 0: 32 -> 10.4 us; 21 by ranks)
+            if (__builtin_expect(halved && w_lo - above == inside && lo < hi, 0)) {
+                uint32_t mn = 0xffffffffu, mx = 0;
+#pragma unroll
+                for (int i = 0; i < kSentOwn; ++i) range_of_key(key[i], lo, hi, mn, mx);
+                narrow_bracket(&range[probe], mn, mx, lane, lo, hi);
+            }
         }
         T = lo;
         if (lo < hi) {

@@ -146,6 +146,24 @@ __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx)
 #undef PDD_MINMAX_STEP
 }
 
+// The bracket [lo, hi] of a threshold search, which holds a key at least, cut to the keys that it holds.  A bisecting
+// probe that cuts nothing has met a run of equal scores, and bisection would close in on it bit by bit, a round for each.
+// First range_of_key for every key of the thread (from mn = 2^32 - 1, mx = 0): keys outside the bracket wrap past
+// those inside, empty slots too.  Then narrow_bracket, with a word pair of this round's own, {2^32 - 1, 0} before.
+__device__ __forceinline__ void range_of_key(uint32_t key, uint32_t lo, uint32_t hi, uint32_t &mn, uint32_t &mx)
+{
+    mn = min(mn, key - lo);
+    mx = max(mx, key - (hi + 1u));
+}
+__device__ __forceinline__ void narrow_bracket(uint2 *range, uint32_t mn, uint32_t mx, int lane, uint32_t &lo, uint32_t &hi)
+{
+    wave_min_max(mn, mx);
+    if (lane == 63) { atomicMin(&range->x, mn); atomicMax(&range->y, mx); }
+    __syncthreads();
+    lo += range->x;
+    hi += 1u + range->y;
+}
+
 // Pooled scores of kSelPoolStep consecutive keys at a time, four per thread.  The scores of a step
 // and the pool_r on either side of it pass through LDS once, 16 bytes per lane (the scores outside
 // the sequence as zero, or as the nearest one inside it where the maximum is taken), those of the
@@ -295,6 +313,7 @@ void select_topk_reg_kernel(const SelParams p)
     __shared__ uint32_t list[QPT > 1 ? kSelList : 1];
     __shared__ uint32_t sh_min, sh_max, list_count, fin_count, fin_T, fin_above, head_tot;
     __shared__ SelPlace place;
+    __shared__ uint2 range[kSelMaxProbes];             // smallest and largest key that round number p left inside
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -320,7 +339,10 @@ void select_topk_reg_kernel(const SelParams p)
     uint8_t *mrow = p.out_mask ? p.out_mask + (int64_t)g * p.total_k + ks : nullptr;
 
     hist[tid] = 0;
-    if (tid < kSelMaxProbes) probe_tot[tid] = 0;
+    if (tid < kSelMaxProbes) {
+        probe_tot[tid] = 0;
+        range[tid] = make_uint2(0xffffffffu, 0u);
+    }
     if (tid < kSelFinish + 4) fin_keys[tid] = 0;
     if (tid == 0) {
         list_count = fin_count = 0;
@@ -410,8 +432,10 @@ void select_topk_reg_kernel(const SelParams p)
     const int shift = max(32 - __builtin_clz((hi - lo) | 1u) - 10, 0);     // kSelBins = 2^10
     // One round: `count` adds this wave's keys >= pa to its first argument and those >= pb to the second.
     // The waves' sums meet in an LDS counter of their own (one fresh counter per round, so none is ever
-    // cleared), two to a word: a count is at most 32768.
-    auto probe = [&](auto &&count) {
+    // cleared), two to a word: a count is at most 32768.  `each` calls its argument with the thread's keys: a round
+    // that cut nothing, by thirds, goes on from the range of the keys inside (five values in 20606 keys 47 -> 17 us, 27 with
+    // one probe a round).
+    auto probe = [&](auto &&count, auto &&each) {
         const uint32_t inside = c_lo - c_above;
         if (!placed) next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
         placed = false;
@@ -429,7 +453,13 @@ void select_topk_reg_kernel(const SelParams p)
             if (tot_a >= (uint32_t)kk) { lo = pa; c_lo = tot_a; }
             else { hi = pa - 1u; c_above = tot_a; }
         }
-        interp = !interp || 4u * (c_lo - c_above) <= inside;
+        const bool thirds = !interp;                             // after interpolation these are tried first
+        interp = thirds || 4u * (c_lo - c_above) <= inside;
+        if (__builtin_expect(thirds && c_lo - c_above == inside && lo < hi, 0)) {
+            uint32_t mn = 0xffffffffu, mx = 0;
+            each([&](uint32_t k) { range_of_key(k, lo, hi, mn, mx); });
+            narrow_bracket(&range[round - 1], mn, mx, lane, lo, hi);
+        }
     };
     constexpr int NL = QPT > 1 ? kSelList / kSelThreads : 5;
     uint32_t lk[NL];                                             // the thread's keys of the second part of the search
@@ -472,6 +502,12 @@ void select_topk_reg_kernel(const SelParams p)
                             lb += key[i][j + 2] >= pb ? 1u : 0u;
                         }
                     }
+                }, [&](auto &&f) {
+                    f(khead);
+#pragma unroll
+                    for (int i = 0; i < QPT; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) f(key[i][j]);
                 });
         }
         if (lo < hi) {                                           // at most kSelList keys lie in [lo, hi]
@@ -530,6 +566,9 @@ void select_topk_reg_kernel(const SelParams p)
                 la += lk[q] >= pa ? 1u : 0u;
                 lb += lk[q] >= pb ? 1u : 0u;
             }
+        }, [&](auto &&f) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) f(lk[q]);
         });
     if (lo < hi) {
         // at most kSelFinish keys lie in [lo, hi]: the (kk - c_above)-th largest of them is T

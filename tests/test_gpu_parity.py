@@ -590,6 +590,35 @@ def test_select_threshold_search_off_its_good_path(n):
         assert np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
 
 
+@pytest.mark.parametrize("n", [300, 4096, 4097, 8192, 20606, 32768])
+def test_select_runs_of_equal_scores(n):
+    """More equal scores than the last step of the search ranks: five values, most of them zero, 24 neighbouring values at
+    doubling distances, the same beside one score far off.  As tokens and, up
+    to 8192, as sentences of one token.  Exact."""
+    rng = np.random.default_rng(n)
+    u = rng.random(n)
+    near = (np.uint32(0x3F000000) + (np.uint32(1) << rng.integers(0, 24, n).astype(np.uint32))).view(np.float32)
+    far = near.copy()
+    far[n // 3] = 1e30
+    rows = np.stack([rng.integers(0, 5, n), np.where(u < 0.9, 0.0, u), near, far]).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cu = np.array([0, n], dtype=np.int32)
+    scores = dev(rows)
+    for k in sorted({1, 2, n // 20, n // 4, n // 2, 3 * n // 4, n - 1, n}):
+        keep = np.array([k], dtype=np.int32)
+        idx = torch.full((len(rows), k), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full(rows.shape, 9, dtype=torch.uint8, device="cuda")
+        pdd.select_topk(scores, dev(cu), n, dev(keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask, None, None, cu)
+        want_idx, want_mask = oracle.select_topk(rows.astype(np.float64), cu, keep)
+        assert np.array_equal(idx.cpu().numpy(), want_idx), f"k = {k}"
+        assert np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
+        if n <= 8192:
+            sent = torch.full(rows.shape, 9, dtype=torch.uint8, device="cuda")
+            pdd.select_sentences(scores, dev(cu), n, dev(cu), dev(np.arange(1, n + 1, dtype=np.int32)), n, dev(keep), pdd.SENT_SUM,
+                                 None, None, sent, None, None, cu)
+            assert np.array_equal(sent.cpu().numpy(), want_mask), f"sentences, k = {k}"
+
+
 @pytest.mark.parametrize("n", [5, 128, 300, 4097, 32768])
 def test_select_key_of_the_lowest_nan(n):
     """A score whose bits are all ones (a buffer filled with 0xFF bytes) ranks below every other value
