@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kSelThreads) void select_sentences_kernel(const Sen
     __shared__ __attribute__((aligned(16))) uint2 fin[kSentFinish];              // key, length
     __shared__ struct { uint32_t bin, tokens, sentences, above, n_above; } place;
     __shared__ uint32_t fin_count, fin_T, fin_above, sh_kept;
-    __shared__ uint2 range[kSentMaxProbes];                       // smallest and largest key that a probe left inside
+    __shared__ uint2 range[kSentMaxProbes];                       // of probe number p, see narrow_bracket
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -313,7 +313,7 @@ void select_topk_reg_kernel(const SelParams p)
     __shared__ uint32_t list[QPT > 1 ? kSelList : 1];
     __shared__ uint32_t sh_min, sh_max, list_count, fin_count, fin_T, fin_above, head_tot;
     __shared__ SelPlace place;
-    __shared__ uint2 range[kSelMaxProbes];             // smallest and largest key that round number p left inside
+    __shared__ uint2 range[kSelMaxProbes];             // of round number p, see narrow_bracket
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
