@@ -128,7 +128,8 @@ constexpr int kSplitVBufs = 2;           // key-split form: V tiles are double b
 template <int D>
 struct AttnSmem {
     static constexpr int TILE = kBN * D * 2;                       // one K or V tile in LDS, bytes
-    static constexpr int BYTES = (2 * kAttnBufs + 1) * TILE;     // + the fourth Q slot of an 8-wave workgroup
+    // + the fourth Q slot of an 8-wave workgroup.  Without it three 4-wave workgroups of head_dim 64 share a compute unit.
+    static constexpr int bytes(int waves) { return (2 * kAttnBufs + (waves > 4 ? 1 : 0)) * TILE; }
     static constexpr int SPLIT_BYTES = (kAttnBufs + kSplitVBufs) * TILE;
     static constexpr int SWEEP_BYTES = (kSweepBufs + 1) * TILE;    // + exchange area
 };
@@ -184,8 +185,14 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(uint32_t lo, uint32_t hi)
     return __builtin_bit_cast(bf16x8, c);
 }
 
+// Waves per SIMD that the registers are held to: two, and three where three 4-wave workgroups share a compute unit (head_dim 64,
+// 141 registers).  Exponentials and other vector work are the larger part of a block there, and with two waves the SIMD waits
+// on both for a fifth of the time (16384 tokens x 32/8 heads 2.23 -> 1.80 M cycles, at a clock that falls from 1.83 to 1.57 GHz).
+constexpr int attn_waves_per_simd(int D, int NWAVES, bool IMP) { return D == 64 && NWAVES == 4 && !IMP ? 3 : 2; }
+
 template <int D, int NWAVES, bool IMP = false, bool SPLIT = false>
-__global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(NWAVES * 64)
+__attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D, NWAVES, IMP), attn_waves_per_simd(D, NWAVES, IMP))))
 void attn_fwd_kernel(const AttnParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only types; the host pass needs the stub only

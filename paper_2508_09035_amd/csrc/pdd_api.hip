@@ -143,7 +143,7 @@ pdd_status launch_attn_t(const pdd::AttnParams &p, int64_t blocks, hipStream_t s
 {
     if (p.imp_part)
         return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW, true>, pdd::AttnSmem<D>::SWEEP_BYTES, NW * 64, p, blocks, st);
-    return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW>, pdd::AttnSmem<D>::BYTES, NW * 64, p, blocks, st);
+    return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW>, pdd::AttnSmem<D>::bytes(NW), NW * 64, p, blocks, st);
 }
 
 int compute_units();
@@ -168,8 +168,7 @@ pdd_status launch_attn_split(const pdd::AttnParams &p, int64_t blocks, hipStream
 
 // Queries per attention workgroup.  8 waves (256 queries, one workgroup per compute unit) halve the
 // K/V traffic into LDS per flop and win wherever the compute units stay evenly busy; 4 waves (128
-// queries: twice as many workgroups of half the rows, which spread more evenly; at head_dim 64
-// two of them also share a compute unit) win on small grids.  Measured on 256 compute units, T = number of 256-query tiles:
+// queries: twice as many workgroups of half the rows, which spread more evenly) win on small grids.  Measured on 256 compute units, T = number of 256-query tiles:
 // chunks behind a prefix at least as long (workgroups of nearly equal length) prefer 8 waves from
 // T = 192 on (1.0 against 0.8 PFLOP/s) and 4 waves at T = 128 (0.87 against 0.76); causal prefill,
 // whose workgroups differ in length by the number of query tiles, needs more than one 8-wave
@@ -185,6 +184,17 @@ int attn_rows_per_workgroup(const pdd_attn_desc *d)
         nw = tiles256 > (even_lengths ? cus / 2 : cus) ? 8 : 4;
     }
     return nw * 32;
+}
+
+// Prompts of head_dim 64 take 4 waves, three workgroups to a compute unit, at every size: against 8 waves, two to a compute
+// unit, 16384 tokens x 32/8 heads 1188 -> 1143 us, 8192 x 64/8 630 -> 597, 3000 + 1111 + 6100 x 32/8 253 -> 236, 8000 + 3 x 300 x 8/8
+// 244 -> 205; only where the 8-wave workgroups just fill the chip once do they stay (3500 x 32/8, 448 of 512 places: 75.4
+// against 77.0).  The chunked call keeps the rule above, by which its importance sweep and its scratch are sized.
+int attn_prefill_rows_per_workgroup(const pdd_attn_desc *d)
+{
+    if (d->head_dim != 64 || g_attn_waves != 0) return attn_rows_per_workgroup(d);
+    const int64_t tiles256 = (int64_t)((d->max_seqlen_q + 255) / 256) * d->batch * d->n_q_heads, slots = 2 * (int64_t)compute_units();
+    return 32 * (8 * tiles256 > 6 * slots && tiles256 <= slots ? 8 : 4);
 }
 
 // Chunked mode can take the token importance from a second sweep inside the
@@ -303,10 +313,11 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     return {(int)tiles, (int)n_split, (size_t)n_split * per_split};
 }
 
+// bm: queries per workgroup of the plain form.
 // imp_part != NULL: sweep_workspace(d) bytes; the importance sweep runs inside
 // the attention kernel and leaves its partial sums there.
 // split_ws != NULL: the key-split form of `plan`, with plan.bytes of scratch.
-pdd_status launch_attn(const pdd_attn_desc *d, const void *q, const void *k, const void *v, void *o, float *lse,
+pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void *k, const void *v, void *o, float *lse,
                        hipStream_t st, float *imp_part = nullptr, const SplitPlan *plan = nullptr,
                        void *split_ws = nullptr)
 {
@@ -325,7 +336,6 @@ pdd_status launch_attn(const pdd_attn_desc *d, const void *q, const void *k, con
     p.total_q = d->total_q;  p.total_k = d->total_k;
     p.scale_log2 = scale_log2(d);
 
-    const int bm = attn_rows_per_workgroup(d);
     const int nw = bm / 32;
     p.n_qtiles = (d->max_seqlen_q + bm - 1) / bm;
     const int64_t blocks = (int64_t)p.n_qtiles * d->batch * d->n_q_heads;
@@ -667,9 +677,9 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
         return fail(PDD_ERR_INVALID_ARG, "window > 0 needs an importance buffer");
     const SplitPlan plan = split_plan(desc, false);
     if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace))
-        s = launch_attn(desc, q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
     else
-        s = launch_attn(desc, q, k, v, o, lse, (hipStream_t)stream);
+        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream);
     if (s) return s;
     if (importance && desc->window > 0)
         return launch_importance(desc, q, k, lse, importance, desc->window, workspace, workspace_bytes,
@@ -686,8 +696,9 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     s = check_ptrs(q_chunk, k_all, v_all, o, lse);
     if (s) return s;
     const SplitPlan plan = split_plan(desc, true);
+    const int bm = attn_rows_per_workgroup(desc);
     if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace)) {
-        s = launch_attn(desc, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
         if (s || !importance) return s;
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,
                                  (hipStream_t)stream);
@@ -696,9 +707,8 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     if (sweep && workspace && workspace_bytes >= sweep) {
         if (reinterpret_cast<uintptr_t>(workspace) & 15u)
             return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
-        s = launch_attn(desc, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, (float *)workspace);
+        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, (float *)workspace);
         if (s) return s;
-        const int bm = attn_rows_per_workgroup(desc);
         const int n_slices = (desc->n_q_heads / desc->n_kv_heads) * ((desc->max_seqlen_q + bm - 1) / bm);
         launch_importance_reduce((const float *)workspace, importance, (int64_t)desc->n_kv_heads * desc->total_k,
                                  n_slices, (hipStream_t)stream);
@@ -706,7 +716,7 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
         if (e != hipSuccess) return fail(PDD_ERR_HIP, "importance reduction launch: %s", hipGetErrorString(e));
         return PDD_OK;
     }
-    s = launch_attn(desc, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream);
+    s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream);
     if (s) return s;
     if (importance)
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,

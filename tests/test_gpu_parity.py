@@ -838,6 +838,27 @@ def test_head_dim_64_longer_prompts_sampled_rows(waves):
     assert swapped == 0
 
 
+@pytest.mark.parametrize("lens", [[700, 1, 513], [1700]])       # 576 and 448 tiles of 256 rows: 4 and 8 waves chosen on 256 units
+def test_head_dim_64_workgroup_choice_gives_the_same_bits(lens):
+    wl = W.make_custom("t", lens, None, 64, 8, 64, 32, "1/4", seed=21)
+    runs = []
+    for waves in (0, 4, 8):
+        dev = DeviceWorkload(wl)
+        dev.poison()
+        pdd.set_option(pdd.OPT_ATTN_WAVES, waves)
+        try:
+            dev.step()
+            runs.append(dev.results())
+        finally:
+            pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
+    for other in runs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(runs[0], other))
+    rows = np.array([0, 1, 127, 128, 255, 256, len(wl.q) - 1])
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+    assert np.abs(runs[0][0][rows] - oO).max() <= O_ATOL
+    rel_close(runs[0][1][:, rows], oL, "lse")
+
+
 def test_c3_ragged_batch_sampled_rows():
     wl = W.make_workload("c3")
     rows = _sample_rows(wl, 48)
