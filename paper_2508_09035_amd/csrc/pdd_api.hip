@@ -372,15 +372,11 @@ void launch_select_reg(const pdd::SelParams &p, dim3 grid, hipStream_t st)
         hipLaunchKernelGGL((pdd::select_topk_reg_kernel<QPT, true>), grid, dim3(pdd::kSelThreads), 0, st, p);
 }
 
-// Chunks of the longest sequence where a selection divides its rows over workgroups, 0 where a row
-// stays in one.  Rows of up to 32768 candidates fit one workgroup's registers: 17.8 us divided against
-// 18.1 in one at 8 x 32768, 17.0 against 14.0 at 8 x 16384, 134 against 40 at 512 x 32768.  Longer
-// ones are read again in every pass of the one workgroup: 65536 19.1 against 117, 131072 20.9 against
-// 225 (8 rows), 153 against 367 (128 rows).  The four launches cost 0.035 us per chunk and so lose where
-// the rows alone keep the chip busy, two to a compute unit: divided against one workgroup per row, 320 rows of
-// 33000 / 50000 / 65536 109 / 151 / 180 against 112 / 167 / 216, 384 rows 126 / 175 / 212 against 114 / 170 / 219,
-// 512 rows 160 / 225 / 276 against 119 / 176 / 227.  Beyond 512 chunks
-// the sums over them would lose; 8192 chunks bound the scratch to 68 MiB.
+// Chunks of 4096 candidates of the longest sequence where a selection divides its rows over workgroups, 0 where
+// a row stays in one.  Longer rows than one workgroup's registers hold, 32768, are read again in every pass of the one
+// workgroup: 8 x 65536 13.3 us divided against 117, 8 x 131072 16.5 against 225.  More than 5/4 of a row per compute unit keep the chip
+// busy by themselves, two to a compute unit (512 x 33000 107 against 121 us), and stay whole for the scratch that they would
+// take; so do rows of more than 512 chunks, whose sums would be long, and 8192 chunks bound the scratch to 68 MiB.
 int select_chunks(int64_t n_heads, int64_t batch, int64_t max_seqlen_k)
 {
     const int64_t chunks = (max_seqlen_k + pdd::kSplitSelChunk - 1) / pdd::kSplitSelChunk;
@@ -388,22 +384,38 @@ int select_chunks(int64_t n_heads, int64_t batch, int64_t max_seqlen_k)
     return 4 * n_heads * batch <= 5 * (int64_t)compute_units() && n_heads * batch * chunks <= 8192 ? (int)chunks : 0;
 }
 
-pdd_status launch_select_split(const pdd::SelParams &s, int chunks, void *workspace, hipStream_t st)
+size_t select_workspace(int64_t n_heads, int64_t batch, int chunks)
+{
+    return (size_t)(n_heads * batch) * (size_t)chunks * pdd::kSplitSelChunkBytes;
+}
+
+template <int QPT>
+void launch_select_split_t(const pdd::SelParams &s, int chunks, void *workspace, hipStream_t st)
 {
     pdd::SplitSelParams p;
-    const int64_t slots = (int64_t)s.n_heads * s.B * chunks;
     p.s = s;
-    p.n_chunks = chunks;
-    p.state = (pdd::SplitSelState *)workspace;
-    p.hist[0] = (uint32_t *)(p.state + slots);
-    p.hist[1] = p.hist[0] + slots * (pdd::kSplitSelBins / 2);
-    p.group[0] = p.hist[1] + slots * (pdd::kSplitSelBins / 2);
-    p.group[1] = p.group[0] + slots * pdd::kSplitSelGroups;
-    const dim3 grid((unsigned)chunks, (unsigned)s.B, (unsigned)s.n_heads), block(pdd::kSelThreads);
-    hipLaunchKernelGGL(pdd::select_level_kernel<0>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(pdd::select_level_kernel<1>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(pdd::select_level_kernel<2>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(pdd::select_finish_kernel, grid, block, 0, st, p);
+    p.n_chunks = (chunks + QPT - 1) / QPT;
+    p.n_units = chunks;
+    const int64_t rows = (int64_t)s.n_heads * s.B;
+    p.list = (uint16_t *)workspace;
+    p.before = p.list + rows * p.n_units * pdd::kSplitSelChunk;
+    p.counts = (pdd::DivCounts *)(p.before + rows * p.n_chunks * pdd::kDivBins);
+    p.row = (uint2 *)(p.counts + rows * p.n_chunks);
+    const dim3 grid((unsigned)p.n_chunks, (unsigned)s.B, (unsigned)s.n_heads), block(pdd::kSelThreads);
+    hipLaunchKernelGGL(pdd::select_bracket_kernel<QPT>, grid, block, 0, st, p);
+    hipLaunchKernelGGL(pdd::select_divided_kernel<QPT>, grid, block, 0, st, p);
+}
+
+// Chunks of 4096 candidates to a workgroup: one while every compute unit gets at most one (8 x 131072 16 us, 17 with
+// two, 21 with four), two up to two of them (32 x 65536 23, 20 and 21), four beyond (32 x 131072 41, 30 and 27), because each
+// workgroup reads the row's sample and what all of its chunks hold.  The latter makes two the better choice for very long rows
+// too (1 x 800000 22.5 and 19.9; 1 x 200000 13.8 and 14.8).
+pdd_status launch_select_split(const pdd::SelParams &s, int chunks, void *workspace, hipStream_t st)
+{
+    const int64_t all = (int64_t)s.n_heads * s.B * chunks, cus = compute_units();
+    if (all <= cus && chunks <= 64) launch_select_split_t<1>(s, chunks, workspace, st);
+    else if (all <= 2 * cus) launch_select_split_t<2>(s, chunks, workspace, st);
+    else launch_select_split_t<4>(s, chunks, workspace, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(PDD_ERR_HIP, "select launch: %s", hipGetErrorString(e));
     return PDD_OK;
@@ -646,8 +658,7 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
 {
     if (!desc || desc->batch < 1 || desc->n_kv_heads < 1) return 0;
     if (which_call == PDD_CALL_SELECT_TOPK)         // the attention fields are not read
-        return (size_t)desc->n_kv_heads * desc->batch *
-               select_chunks(desc->n_kv_heads, desc->batch, desc->max_seqlen_k) * pdd::kSplitSelChunkBytes;
+        return select_workspace(desc->n_kv_heads, desc->batch, select_chunks(desc->n_kv_heads, desc->batch, desc->max_seqlen_k));
     if (desc->n_q_heads < desc->n_kv_heads || desc->total_k < 0) return 0;
     switch (which_call) {
     case PDD_CALL_PREFILL_ATTN:
@@ -794,7 +805,7 @@ pdd_status pdd_select_topk_pooled(const float *scores, int32_t n_heads, int32_t 
     hipStream_t st = (hipStream_t)stream;
     const int chunks = p.pool_r == 0 ? select_chunks(n_heads, batch, max_seqlen_k) : 0;
     if (chunks && workspace && aligned16(workspace) &&
-        workspace_bytes >= (size_t)n_heads * batch * chunks * pdd::kSplitSelChunkBytes)
+        workspace_bytes >= select_workspace(n_heads, batch, chunks))
         return launch_select_split(p, chunks, workspace, st);
     // rows of up to 32768 candidates stay in registers (4096 per step and 1024 threads)
     if (max_seqlen_k <= 4 * pdd::kSelThreads)

@@ -20,8 +20,8 @@
 //    32768 20.0 / 21.3, 512 rows of 32768 42.1 / 47.4; now 6.5 / 6.3, 11.6 / 11.6, 17.0 / 17.2, 36.7 / 37.0.
 //    Histograms of all keys of long rows were slower: 50 cycles per LDS atomic of a wave.  So
 //    were fewer threads with more keys each (256 x 16: 9.7 us at 4096).
-//  * select_topk_kernel (longer rows without a workspace, pooled, or very many of them;
-//    see select_split.hpp for the others): most-significant-first radix select,
+//  * select_topk_kernel (longer rows without a workspace, pooled, or beyond the limits of
+//    select_split.hpp, which has the others): most-significant-first radix select,
 //    8 bits per pass, digits taken from (key - min key) scaled to the row's
 //    range, LDS histograms; the row is re-read from L2 in every pass.
 //

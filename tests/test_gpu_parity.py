@@ -683,6 +683,54 @@ def test_select_rows_divided_over_workgroups(lens, dist):
         assert (ws != 0xFF).any() or not taken.any(), "the scratch was not used"
 
 
+def _sample_of_divided_row(n):
+    """Where a divided row of n candidates is sampled: one place in each of 1024 equal pieces."""
+    i = np.arange(1024, dtype=np.uint64)
+    mix = (i * np.uint64(2654435761)) & np.uint64(0xffffffff)
+    return (((i << np.uint64(16)) | (mix >> np.uint64(16))) * np.uint64(n) >> np.uint64(26)).astype(np.int64)
+
+
+@pytest.mark.parametrize("heads,n,kind", [
+    (1, 40000, "spread"), (40, 40000, "spread"), (64, 40000, "spread"),      # 4096, 8192 and 16384 candidates to a workgroup
+    (1, 300000, "spread"), (3, 1100000, "few"),                              # more than 64 and than 32 workgroups to a row
+    (2, 70000, "octaves"),                                                   # bins wider than 16 bits
+    (1, 70000, "sample above"), (1, 70000, "sample below"),                  # the sample says nothing of the row
+    (1, 300000, "one bin")])                                                 # more keys in the threshold's bin than are listed
+def test_select_divided_rows_off_the_good_path(heads, n, kind):
+    rng = np.random.default_rng(n)
+    s = rng.random((heads, n)) ** 6
+    k = n // 10
+    if kind == "few":
+        s = rng.integers(0, 5, (heads, n)).astype(np.float64)
+    elif kind == "octaves":
+        s, k = np.exp(20 * rng.normal(size=(heads, n))), 40
+    elif kind == "sample above":
+        s[:, _sample_of_divided_row(n)] += 2.0
+    elif kind == "sample below":
+        s[:, _sample_of_divided_row(n)] -= 2.0
+    elif kind == "one bin":
+        s, k = np.where(rng.random((heads, n)) < 0.5, 1.0 + rng.random((heads, n)) * 1e-4, rng.random((heads, n))), n // 2
+    s32 = s.astype(np.float32)
+    cu, k_keep = np.array([0, n], dtype=np.int32), np.array([k], dtype=np.int32)
+    desc = pdd.AttnDesc()
+    desc.batch, desc.n_kv_heads, desc.max_seqlen_k = 1, heads, n
+    need = pdd.workspace_bytes(desc, pdd.CALL_SELECT_TOPK)
+    assert need > 0
+    guard = 4096
+    ws = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    idx = torch.full((heads, k), -7, dtype=torch.int32, device="cuda")
+    mask = torch.full((heads, n), 9, dtype=torch.uint8, device="cuda")
+    pdd.select_topk(dev(s32), dev(cu), n, dev(k_keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask, None, None, cu,
+                    workspace=ws[:need])
+    assert (ws[need:] == 0xA5).all(), "written past the scratch"
+    got, m = idx.cpu().numpy(), mask.cpu().numpy()
+    for h in range(heads):
+        want = np.sort(np.argsort(-s32[h], kind="stable")[:k])           # ties: the lower index
+        assert np.array_equal(got[h], want)
+        assert np.array_equal(np.flatnonzero(m[h]), want)
+
+
 @pytest.mark.parametrize("name", ["c1", "c2", "c3", "c5", "c4"])
 def test_gate_a_oracle_scores_of_every_configuration(name):
     """The oracle's importance of each benchmark configuration, rounded to fp32, through the GPU
