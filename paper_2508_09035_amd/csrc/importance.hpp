@@ -83,9 +83,9 @@ void importance_kernel(const ImpParams p)
 
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
-    const int b = bid % p.B;    bid /= p.B;
-    const int kt = bid % p.n_ktiles;
-    const int split = bid / p.n_ktiles;
+    const int row = bid / p.B, b = (bid + (p.Hkv % kEngines ? row : 0)) % p.B;       // sequences change places, see attn_fwd_kernel
+    const int kt = row % p.n_ktiles;
+    const int split = row / p.n_ktiles;
 
     const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
     const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
