@@ -97,7 +97,21 @@ __device__ __forceinline__ int div_group(int x, uint32_t magic)
 }
 
 constexpr int kBN = 64;  // keys per LDS tile
-constexpr int kEngines = 32;  // 8 XCDs of 4 shader engines
+// Workgroups are dealt out to the chip's 32 shader engines (8 XCDs of 4) in turn.  `heads` of them for a sequence and row of
+// tiles: after how many rows in a row a sequence has had every engine.
+constexpr int kEngines = 32;
+constexpr int rows_per_turn(int heads) { int n = kEngines; while (n > 1 && heads % 2 == 0) { n /= 2; heads /= 2; } return n; }
+// The sequence and the row of workgroup x (heads divided out) of a grid of n_rows rows for each of B sequences: the sequences take
+// turns of `turn` rows, so that each has every engine, rows that do not exist in it or not.  (Changing places from row to
+// row evens out less where a number of rows goes round, but keeps the rows in their order, which is what attn_fwd_kernel wants.)
+__device__ __forceinline__ int sequence_of(int x, int B, int n_rows, int turn, int &row)
+{
+    const int first = x / (turn * B) * turn, rows = min(turn, n_rows - first);
+    x -= first * B;
+    const int b = x / rows;
+    row = first + x - b * rows;
+    return b;
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

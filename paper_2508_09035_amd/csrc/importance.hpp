@@ -33,6 +33,7 @@ struct ImpParams {
     const int32_t *cu_q, *cu_k;
     int64_t q_st, q_sh, k_st, k_sh;
     int32_t B, Hq, Hkv, G, total_q, total_k, n_ktiles;
+    int32_t turn;      // rows_per_turn of the KV heads
     int32_t window;    // < 0: every query is a window query
     float scale_log2;  // softmax scale * log2(e)
     // Row split: the window rows of a workgroup's keys are divided over n_split workgroups; with
@@ -83,7 +84,8 @@ void importance_kernel(const ImpParams p)
 
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
-    const int row = bid / p.B, b = (bid + (p.Hkv % kEngines ? row : 0)) % p.B;       // sequences change places, see attn_fwd_kernel
+    int row;
+    const int b = sequence_of(bid, p.B, p.n_ktiles * p.n_split, p.turn, row);
     const int kt = row % p.n_ktiles;
     const int split = row / p.n_ktiles;
 

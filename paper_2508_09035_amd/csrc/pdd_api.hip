@@ -535,6 +535,7 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.B = d->batch;  p.Hq = d->n_q_heads;  p.Hkv = d->n_kv_heads;  p.G = d->n_q_heads / d->n_kv_heads;
     p.total_q = d->total_q;  p.total_k = d->total_k;
     p.window = window;
+    p.turn = pdd::rows_per_turn(p.Hkv);
     p.scale_log2 = scale_log2(d);
     p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
