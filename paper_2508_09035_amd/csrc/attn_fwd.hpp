@@ -203,11 +203,13 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(uint32_t lo, uint32_t hi)
 // Waves per SIMD that the registers are held to: two, and three where three 4-wave workgroups share a compute unit (head_dim 64,
 // 141 registers).  Exponentials and other vector work are the larger part of a block there, and with two waves the SIMD waits
 // on both for a fifth of the time (16384 tokens x 32/8 heads 2.23 -> 1.80 M cycles, at a clock that falls from 1.83 to 1.57 GHz).
-constexpr int attn_waves_per_simd(int D, int NWAVES, bool IMP) { return D == 64 && NWAVES == 4 && !IMP ? 3 : 2; }
+// The key-split form's workgroups are few to a compute unit and keep to two (6000 tokens x 4/2 heads 57.5 us, 64.7 with three;
+// 16000 x 1 79, 72).
+constexpr int attn_waves_per_simd(int D, int NWAVES, bool IMP, bool SPLIT) { return D == 64 && NWAVES == 4 && !IMP && !SPLIT ? 3 : 2; }
 
 template <int D, int NWAVES, bool IMP = false, bool SPLIT = false>
 __global__ __launch_bounds__(NWAVES * 64)
-__attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D, NWAVES, IMP), attn_waves_per_simd(D, NWAVES, IMP))))
+__attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D, NWAVES, IMP, SPLIT), attn_waves_per_simd(D, NWAVES, IMP, SPLIT))))
 void attn_fwd_kernel(const AttnParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only types; the host pass needs the stub only
