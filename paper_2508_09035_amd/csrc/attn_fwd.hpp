@@ -231,9 +231,10 @@ void attn_fwd_kernel(const AttnParams p)
     // where the number of KV heads divides 8 or is a multiple of 8, all workgroups that share the
     // K and V of a KV head run on the same XCD(s) and find its tiles in that L2; then the query
     // heads of the group, the sequence, and the query tiles from the last (longest) down.  Workgroups are dealt out
-    // to the chip's 32 shader engines in turn, so where the query heads do not go round all of them the sequences
-    // change places from tile to tile: else each keeps to its own engines, and the longest one's work as long as it alone
+    // to the chip's shader engines in turn, so where the query heads do not go round all of them an even number of
+    // sequences change places from tile to tile: else each keeps to its own engines, and the longest one's work as long as it alone
     // (8 prompts of 512 to 7900 tokens x 4/2 heads 312 -> 179 us, 8/8 364 -> 238; 7000 + 300 x 16/2 261 -> 198).
+    // An odd number goes round by itself and loses by it (5 of 600 to 8200 x 16/2 549 us, 582 with it; 8/8 292, 327).
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
     // The key-split form has no query head per workgroup (a tile holds rows of the whole group);
@@ -246,7 +247,7 @@ void attn_fwd_kernel(const AttnParams p)
     } else {
         bid /= p.G;
         const int back = bid / p.B;
-        b = (bid + (p.Hq % kEngines ? back : 0)) % p.B;
+        b = (bid + (p.Hq % kEngines && p.B % 2 == 0 ? back : 0)) % p.B;
         t = p.n_qtiles - 1 - back;
     }
     const int h = g * p.G + hg;
