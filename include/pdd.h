@@ -111,14 +111,16 @@ enum {
  *            importance step divides the window rows of every 256-key slice over
  *            several workgroups that leave partial column sums there, added in a
  *            fixed order afterwards; with less (or NULL) each slice is summed by
- *            one workgroup.  Prompts whose query tiles leave the GPU unevenly
+ *            one workgroup.  Long prompts whose query tiles leave the GPU unevenly
  *            busy also take the key-split attention form there: the keys of a
  *            query tile are divided over several workgroups that leave 32-bit
- *            partial rows, combined by a second kernel.  All forms are
+ *            partial rows, combined by a second kernel.  Short prompts share a
+ *            row tile's keys out over the waves of one workgroup, with or
+ *            without scratch.  All forms are
  *            deterministic; they differ from each
- *            other in the order of the fp32 additions, and the key-split form's
- *            O also in where its probabilities round to bf16 (2e-3 of O, as far
- *            as either is from the exact result).  The contents are
+ *            other in the order of the fp32 additions, and in O
+ *            also in where the probabilities round to bf16 (2e-3 of O, as far
+ *            as any is from the exact result).  The contents are
  *            scratch before and after the call; concurrent calls need separate
  *            workspaces.
  * Requires Nq_b == Nk_b for every sequence when host copies are given (use the
@@ -142,10 +144,11 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * remaining chunk catches up afterwards).  Same formulas as above with
  * delta_b = Nk_b - Nq_b >= 0.  Every chunk query is a window query
  * (desc->window is ignored) when importance is non-NULL.
- * workspace: as for pdd_prefill_attn, with one more form.  (The key-split
- * attention form, which few or short chunks behind a long prefix take, packs the
- * query heads of a group into its tiles; the importance then comes from the
- * separate kernel.)
+ * workspace: as for pdd_prefill_attn, with one more form.  (Few or short
+ * chunks take the attention forms that pack the query heads of a group into a
+ * row tile and, behind a long prefix, divide its keys over workgroups that leave
+ * partial rows in the workspace; the importance then comes from the separate
+ * kernel.)
  * Given pdd_workspace_bytes(desc, PDD_CALL_PREFILL_ATTN_CHUNKED) bytes (one
  * float per query head, tile of 128 or 256 queries and key), the importance is
  * taken inside the attention kernel: once a workgroup knows the log-sum-exp of
@@ -157,7 +160,7 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * what full tiles cost) and calls that are given less use the separate
  * importance kernel described above; pdd_workspace_bytes says what the shape
  * will use.  All forms are deterministic and agree to fp32 rounding (O of the
- * key-split form to bf16 rounding).
+ * forms for few rows to bf16 rounding).
  */
 pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chunk,
                                     const void *k_all, const void *v_all, void *o, float *lse,
@@ -180,7 +183,7 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
  * Without importance (NULL) the call uses no scratch and may overlap with any
  * other; its results are those of pdd_prefill_attn_chunked without a workspace,
  * bit for bit.  (Few or short chunks behind a long prefix are faster there with
- * a workspace: the key-split form.)
+ * a workspace, where their keys are divided.)
  */
 pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const void *q_chunk,
                                             const void *k_all, const void *v_all, void *o,
@@ -376,9 +379,10 @@ pdd_status pdd_pack_mask(const uint8_t *mask, int32_t n_rows, int32_t batch, int
  * has no use for any).  At most the larger of 8 * n_kv_heads * total_k * 4 bytes
  * (partial importance sums), for the chunked call ceil(max_seqlen_q / 128) *
  * n_q_heads * total_k * 4 bytes up to 256 MiB (the in-kernel importance), and
- * for the key-split attention form ceil(max_seqlen_k / 512) * total_q *
- * n_q_heads * (head_dim + 1) * 4 bytes up to 256 MiB (16 MiB in the chunked
- * call), for the selection 8720 bytes per 4096 keys up to 69 MiB: the attention weights
+ * for the attention forms that divide the keys ceil(max_seqlen_k / 512) * total_q *
+ * n_q_heads * (head_dim + 1) * 4 bytes up to 256 MiB (in the chunked call
+ * ceil(max_seqlen_k / 256) + 1 times total_q * n_q_heads * (head_dim + 1) * 4 and
+ * total_q * n_q_heads * 16 bytes up to 16 MiB), for the selection 8720 bytes per 4096 keys up to 69 MiB: the attention weights
  * are not materialised (Section 3.2 "Preliminaries").  The figure depends on
  * the descriptor, on PDD_OPT_ATTN_WAVES and on the number of compute units of
  * the current device only.  A call that is given less runs with a form that

@@ -21,16 +21,12 @@
 //   V^T fragments are read with the same permutation).
 //
 // Key-split form (SPLIT)
-//   For launches that would leave most of the chip or of their tiles idle (few tokens behind a
-//   long prefix, long prompts with few heads): a tile's 128 rows are (token, head of the KV group)
+//   For prompts that would leave most of the chip idle (long ones with few heads; short ones and
+//   chunks take the forms of attn_rows.hpp): a tile's 128 rows are (token, head of the KV group)
 //   pairs, so one read of K and V serves the whole group, and a workgroup walks only `split_tiles`
 //   key tiles; attn_combine_kernel joins the pieces.  V tiles are double instead of triple
-//   buffered, so that two workgroups share a compute unit's LDS.  Calls, the join included, where
-//   every one has other inputs / where K and V stay in the last-level cache: 8 sequences x 1 token
-//   (97 MB of K and V) 131 -> 36 / 100 -> 25 us, 256 tokens behind 8192 keys, 32/8 heads
-//   134 -> 59 / 112 -> 50.  With few rows bound by the requests in flight (27 to 31 us of the first,
-//   3.1 to 3.6 TB/s of a copy's 4.9: a tile's rows lie in one wave, which computes while the other
-//   three only request, one V tile ahead), with many by the matrix pipe.
+//   buffered, so that two workgroups share a compute unit's LDS.  A prompt of 16384 tokens x 1 head
+//   217 -> 96 us, the join included.  Bound by the matrix pipe and the exponentials.
 //   A piece has a softmax reference of its own, so its probabilities round to bf16 at other places
 //   than the plain form's: the outputs of the two differ by 2e-3, and both are 2.3e-3 from the result in 64
 //   bits (34 chunks and prompts; log-sum-exp 5e-8 in both).
@@ -76,6 +72,7 @@ struct AttnParams {
     const int32_t *cu_q, *cu_k;
     int64_t q_st, q_sh, k_st, k_sh, v_st, v_sh, o_st, o_sh;
     int32_t B, Hq, Hkv, G, total_q, total_k, n_qtiles;
+    int32_t turn;      // rows_per_turn of the KV heads (attn_rows_kernel)
     float scale_log2;  // softmax scale * log2(e)
     // Only read by kernels built with the importance sweep: partial column sums
     // [G * n_qtiles][Hkv][total_k], slice hg * n_qtiles + t written by the workgroup of query
@@ -88,6 +85,10 @@ struct AttnParams {
     int32_t split_tiles, n_split;
     uint32_t g_magic;
     float *part_o, *part_l;
+    // Only read by attn_rows_kernel and attn_join_kernel: workgroups per KV head, fewest key tiles for each,
+    // (token, piece) rows that the scratch holds.
+    int32_t workers, min_tiles, part_rows;
+    uint4 *part_of;     // [total_q][Hq]: {first partial row, rows from piece to piece, pieces (1: already final), -}
 };
 
 // x / G for the packed rows of the key-split form, 0 <= x < 2^32 / G

@@ -11,6 +11,7 @@
 #include <cstring>
 
 #include "attn_fwd.hpp"
+#include "attn_rows.hpp"
 #include "importance.hpp"
 #include "select_topk.hpp"
 #include "select_split.hpp"
@@ -151,7 +152,7 @@ int compute_units();
 constexpr int kLdsBytes = 160 * 1024;    // of a compute unit, and the most one workgroup can have
 constexpr int kSplitRows = 128;          // packed (token, head) rows per workgroup of the key-split form
 constexpr size_t kSplitWorkspaceMax = (size_t)256 << 20;
-struct SplitPlan { int tiles, n_split; size_t bytes; };        // tiles == 0: the form does not apply
+struct SplitPlan { int tiles, n_split; size_t bytes; double us; };        // tiles == 0: the form does not apply; us: its estimate
 
 template <int D>
 pdd_status launch_attn_split(const pdd::AttnParams &p, int64_t blocks, hipStream_t st)
@@ -221,8 +222,6 @@ void launch_importance_reduce(const float *part, float *imp, int64_t n, int n_sp
                        part, imp, n, n_split);
 }
 
-size_t importance_workspace(const pdd_attn_desc *d, int window);
-
 // What keeps the importance kernel from taking this shape (32-bit byte offsets inside one
 // sequence's Q rows and inside the log-sum-exp tensor), or NULL
 const char *importance_limits(const pdd_attn_desc *d)
@@ -233,37 +232,48 @@ const char *importance_limits(const pdd_attn_desc *d)
     return nullptr;
 }
 
-// Whether and how the keys of a call are split over workgroups (attn_fwd_kernel's SPLIT form).
-// The plain form gives a workgroup all keys of 128 or 256 queries of one head, so a call lasts at
-// least as long as its longest sequence's walk over the key tiles, however few workgroups there
-// are, and a chunk of few tokens leaves most rows of every tile empty.  The split form packs the
-// (token, head) rows of a KV group into its tiles and cuts the walk into pieces of `tiles` key
-// tiles; it pays with 32-bit partial rows, written once and read back by a second kernel.
-// The choice compares two estimates in microseconds, fitted to kernel times on 256 compute units
-// (plain against split, second kernel included, calls repeated on the same inputs): 1 token x 8
-// sequences behind 500 to 7900 keys, 32/8 heads, 100 -> 25; 5 to 64 tokens x 4 sequences behind 700 to
-// 12345 keys, 148 -> 42; 200 tokens behind 16000, 4/2 heads, 209 -> 25 (131 -> 36, 203 -> 54 and 235 -> 26
-// where every call has other inputs); prompts of 2048 tokens x 1 head 31 -> 18 and of 8192
-// x 4/2 heads 117 -> 94; the plain form is better on 128 tokens x 8 behind 4000, 64/8 heads
-// (135 against 153), 256 x 4 behind 8192, 64/8 heads (238 against 291) and prompts that fill the
-// chip (8192 tokens x 8 heads 135 against 165).  One step is one key tile of one workgroup.
-// These batches are even or nearly so.  One long chunk beside short ones is priced as if all were long, and
-// its partial rows are sized for the longest sequence's pieces: such batches may stay whole where the split
-// form would be faster.
-// The scratch of a chunked call stays within the built-in scratch, so that the call without a
-// workspace argument takes the same form where it has importance to return.  Depends on the descriptor and the device only.
-SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
+// What a call's attention costs in the plain form, in microseconds, from the sizes alone.  Fitted on 256 compute units to the
+// times of 1400 chunks and prompts (inputs of their own in every call), half of them within 5 %, nine in ten within 20; a launch
+// lasts as long as its longest sequence's walk over the key tiles or as its tiles take the whole chip.
+// (Uneven batches are priced as if the longest query sequence met all keys.)
+double plain_attention_us(const pdd_attn_desc *d, int bm)
 {
-    const SplitPlan none = {0, 0, 0};
+    const double cus = (double)compute_units(), max_q = d->max_seqlen_q;
+    const int64_t n_qt = (d->max_seqlen_q + bm - 1) / bm, tiles_max = (d->max_seqlen_k + pdd::kBN - 1) / pdd::kBN;
+    const double fill = max_q / (double)(n_qt * bm), seen = 1.0 - 0.5 * max_q / d->max_seqlen_k;
+    const double work = (double)n_qt * d->n_q_heads * ((double)d->total_k / pdd::kBN + 0.5 * d->batch) * seen / cus;
+    const double us = bm == 256 ? std::fmax(tiles_max * (0.75 + 0.5 * fill), work * (0.75 + 1.05 * fill))
+                                : std::fmax((double)tiles_max, work) * (0.75 + 0.15 * fill);
+    return 5.0 + (d->head_dim == 64 ? 0.68 : 0.95) * us;
+}
+
+// Whether the sizes are inside what every form but the plain one can take: the kernels divide a row by G with one 32-bit
+// multiplication and address up to 128 rows of Q with 32-bit byte offsets.
+bool packed_rows_fit(const pdd_attn_desc *d)
+{
     // (the scratch query comes here with whatever its caller's descriptor holds)
     if (g_attn_waves != 0 || d->total_q <= 0 || d->total_k <= 0 || d->max_seqlen_q <= 0 || d->max_seqlen_k <= 0 ||
         (d->head_dim != 64 && d->head_dim != 128) || d->n_q_heads % d->n_kv_heads)
-        return none;
+        return false;
+    const int64_t G = d->n_q_heads / d->n_kv_heads, max_q = d->max_seqlen_q;
+    if (G > 65535 || max_q * G >= (1LL << 31) || max_q * G * G >= (1LL << 32)) return false;
+    return d->q_stride_tok < (1LL << 23) && G * d->q_stride_head < (1LL << 30);
+}
+
+// Whether and how the keys of a prompt are split over workgroups (attn_fwd_kernel's SPLIT form).
+// The plain form gives a workgroup all keys of 128 or 256 queries of one head, so a call lasts at
+// least as long as its longest sequence's walk over the key tiles, however few workgroups there
+// are.  The split form packs the (token, head) rows of a KV group into its tiles and cuts the walk into pieces of `tiles` key
+// tiles; it pays with 32-bit partial rows, written once and read back by a second kernel.
+// The choice compares estimates in microseconds, fitted to kernel times on 256 compute units: prompts of 2048
+// tokens x 1 head 31 -> 18 and of 8192 x 4/2 heads 117 -> 94; the plain form is better on prompts that fill the
+// chip (8192 tokens x 8 heads 135 against 165).  One step is one key tile of one workgroup.
+// Depends on the descriptor and the device only.
+SplitPlan split_plan(const pdd_attn_desc *d)
+{
+    const SplitPlan none = {0, 0, 0, 0.0};
+    if (!packed_rows_fit(d)) return none;
     const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q;
-    // the kernel divides a row by G with one 32-bit multiplication, addresses 32 rows of Q with
-    // 32-bit byte offsets
-    if (G > 65535 || max_q * G >= (1LL << 31) || max_q * G * G >= (1LL << 32)) return none;
-    if (d->q_stride_tok >= (1LL << 25) || G * d->q_stride_head >= (1LL << 30)) return none;
     const double cus = (double)compute_units();
     const int64_t n_qt = (max_q * G + kSplitRows - 1) / kSplitRows;
     const int64_t tiles_max = (d->max_seqlen_k + pdd::kBN - 1) / pdd::kBN;
@@ -271,26 +281,21 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     const double seen = 1.0 - 0.5 * max_q / d->max_seqlen_k;    // share of the keys an average query tile walks
 
     // Key tiles per workgroup: about one workgroup per compute unit, 8 to 24 tiles (fewer and the
-    // start of a workgroup and the partial rows cost more than they spread; first kernel for the 8
-    // sequences of one token above, inputs in the last-level cache: 26 us at 8 tiles, 20 at 12, 21 at 16,
-    // 26 at 24), evened out over the longest sequence, and as many more as the scratch asks for.
+    // start of a workgroup and the partial rows cost more than they spread), evened out over the longest sequence, and
+    // as many more as the scratch asks for.
     const double base = (double)(n_qt * Hkv);
     double T = 24;
     if (cus > base * B) T = std::ceil(tiles_all * base / (cus - base * B));
     T = T < 8 ? 8 : T > 24 ? 24 : T;
     if ((double)d->total_q * d->n_q_heads > (double)kSplitWorkspaceMax) return none;
     const size_t per_split = (size_t)d->total_q * d->n_q_heads * (d->head_dim + 1) * sizeof(float);
-    const size_t room = (chunked ? (size_t)PDD_STATIC_SCRATCH_BYTES : kSplitWorkspaceMax) / per_split;
+    const size_t room = kSplitWorkspaceMax / per_split;
     int64_t n_split = (tiles_max + (int64_t)T - 1) / (int64_t)T;
     if (n_split > (int64_t)room) n_split = (int64_t)room;
     if (n_split < 2) return none;
     const int64_t tiles = (tiles_max + n_split - 1) / n_split;
     n_split = (tiles_max + tiles - 1) / tiles;
     if ((double)n_split * base * B >= 2147483647.0) return none;
-    if (chunked) {      // the importance kernel has to be able to follow (the sweep has wider limits)
-        if (importance_workspace(d, -1) > PDD_STATIC_SCRATCH_BYTES) return none;
-        if (importance_limits(d)) return none;
-    }
 
     const int bm = attn_rows_per_workgroup(d);
     const int64_t n_qt_plain = (max_q + bm - 1) / bm;
@@ -306,20 +311,127 @@ SplitPlan split_plan(const pdd_attn_desc *d, bool chunked)
     // A prompt's tiles are full and of very different lengths, two workgroups share most compute units, and there are
     // as many partial rows as rows: fitted to 97 such launches, within 7 %.  (8/8 heads, head_dim 128, plain against
     // split: 1500 tokens 26 and 30 us, 2441 39 and 46, 694 + 2020 33 and 43, 4000 63 and 66; 4/2 heads 2441 37 and 29.)
-    if (!chunked) {
-        const double steps = base * tiles_all * seen / cus;
-        if ((d64 ? 7.7 + 0.66 * tiles + 0.24 * steps + 5.2 * partial : 10.5 + 0.79 * tiles + 0.46 * steps + 2.8 * partial) > plain) return none;
+    const double steps = base * tiles_all * seen / cus;
+    const double us = d64 ? 7.7 + 0.66 * tiles + 0.24 * steps + 5.2 * partial : 10.5 + 0.79 * tiles + 0.46 * steps + 2.8 * partial;
+    if (us > plain) return none;
+    return {(int)tiles, (int)n_split, (size_t)n_split * per_split, us};
+}
+
+size_t importance_workspace(const pdd_attn_desc *d, int window);
+
+// The form of attn_rows.hpp that a call takes: row groups per workgroup (0: none, the plain form or split_plan's), workgroups
+// per KV head and partial rows where the keys are divided (workers == 0: they are not).
+//   * Whole (RG = 1): a workgroup per tile of 32 packed rows walks all of its keys, eight blocks at a time.
+//   * Divided (RG = 1 or 4): pieces of the key tiles over about one workgroup per compute unit and a second kernel
+//     that joins them; RG = 4 reads K and V once for 128 rows.
+// The choice compares estimates in microseconds with the plain form's, fitted like those (median error 3 to 5 % for whole
+// prompts, 7 to 15 % else), and wants a tenth off the plain time.  Attention alone, plain or split as before | whole | RG = 1 | RG = 4:
+// 512 tokens x 1/1 head of 64 9.6 | 6.3 us, 2000 x 8/8 of 128 31 | 21; 1 token behind 1126 keys, 4/2 heads of 128 17.3 | 9.7 |
+// 11.3 | 12.7, 8 x 1 behind 512 to 7900, 32/8 heads 32.1 | 85 | 26 | 28; 5 to 64 tokens x 4 behind 700 to 12345, 32/8 heads 54 | - | 77 |
+// 41.5; 7 chunks of 3 to 230 behind 200 to 12700, 16/2 heads 88 | - | 79 | 48; 256 behind 8192, 64/8 heads (243 plain) 240 | - | 190 | 172.
+// (Beyond 100 us the whole form was not once the better one in 250 launches: K and V come once per 32 rows.)
+// The divided forms' scratch of a chunked call stays within the built-in scratch, so that the call without a workspace
+// argument takes the same form where it has importance to return.  Depends on the descriptor and the device only.
+constexpr int kWholeTiles = 45;
+struct RowsPlan { int rg; int64_t workers; int min_tiles; int64_t part_rows; size_t bytes; };
+
+RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, bool scratch)
+{
+    RowsPlan best = {0, 0, 0, 0, 0};
+    if (!packed_rows_fit(d)) return best;
+    const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q, total_q = d->total_q;
+    if (chunked) {      // the importance kernel has to be able to follow (the sweep has wider limits)
+        if (importance_workspace(d, -1) > PDD_STATIC_SCRATCH_BYTES || importance_limits(d)) return best;
     }
-    return {(int)tiles, (int)n_split, (size_t)n_split * per_split};
+    const double cus = (double)compute_units();
+    const bool d64 = d->head_dim == 64;
+    const double tiles_max = (double)((d->max_seqlen_k + pdd::kBN - 1) / pdd::kBN);
+    const double tiles_mean = ((double)d->total_k / pdd::kBN + 0.5 * B) / B, seen = 1.0 - 0.5 * max_q / d->max_seqlen_k;
+    auto row_tiles = [&](int rg) {      // of all sequences
+        return std::fmin((double)total_q * G / (32 * rg) + 0.5 * B, (double)((max_q * G + 32 * rg - 1) / (32 * rg)) * B);
+    };
+    double us = 0.9 * plain_attention_us(d, chunked ? attn_rows_per_workgroup(d) : attn_prefill_rows_per_workgroup(d));
+    if (!chunked && scratch) {
+        // A prompt that the key-split form would take keeps to it beyond kWholeTiles: its walks are long enough to be worth the
+        // division that the caller gave scratch for (whole against split: 1500 to 2500 tokens 0.67 of its time, 3000 to 4000
+        // 0.72, 6000 to 9000 0.90, beyond 1.03).
+        const SplitPlan split = split_plan(d);
+        if (split.tiles && tiles_max > kWholeTiles) return best;
+        if (split.tiles) us = std::fmin(us, 0.85 * split.us);
+    }
+    {
+        // rounds of the longest walk against what all of them take the chip; a prompt's long row tiles meet long keys
+        const double rt = row_tiles(1), walk = std::ceil(tiles_max / 4.0) * (chunked ? (d64 ? 0.73 : 1.33) : (d64 ? 0.615 : 0.97));
+        const double tiles = rt * Hkv * seen * (chunked ? 0.4 * tiles_mean + 0.6 * tiles_max : tiles_max) / cus;
+        const double over = std::fmax(rt * Hkv / cus - 1.0, 0.0);
+        const double all = chunked ? (d64 ? 0.18 * tiles + 3.0 * over : 0.30 * tiles + 4.1 * over) : (d64 ? 0.142 * tiles + 2.14 * over : 0.26 * tiles + 5.55 * over);
+        const double est = (chunked ? (d64 ? 4.6 : 5.0) : (d64 ? 5.1 : 6.75)) + std::fmax(walk, all) + 0.3 * std::fmin(walk, all);
+        const int64_t blocks = (max_q * G + 31) / 32 * B * Hkv;
+        if (est < std::fmin(us, 100.0) && blocks <= 0x7fffffffLL) {
+            us = est;
+            best = {1, 0, 0, 0, 0};
+        }
+    }
+    if (!chunked || !scratch) return best;
+    for (int rg = 1; rg <= 4; rg += 3) {
+        // about one workgroup per compute unit, more where the row tiles alone are half as many
+        const int64_t per_head = compute_units() / Hkv > 1 ? compute_units() / Hkv : 1, rows = 32 * rg;
+        const int64_t by_rows = total_q * G / rows + B, by_longest = (max_q * G + rows - 1) / rows * B, pairs = by_rows < by_longest ? by_rows : by_longest;
+        const int64_t workers = pairs <= per_head / 2 ? per_head : per_head + pairs;
+        const int64_t row_bytes = (int64_t)d->n_q_heads * (d->head_dim + 1) * (int64_t)sizeof(float);
+        const int64_t table = total_q * d->n_q_heads * (int64_t)sizeof(uint4);
+        const int64_t room = ((int64_t)PDD_STATIC_SCRATCH_BYTES - table) / row_bytes;
+        if (workers * Hkv > 0x7fffffffLL || room < total_q + (total_q + 3) / 4) continue;
+        if ((double)(total_q > pairs ? total_q : pairs) * tiles_max >= 2147483648.0) continue;      // work_per's sums
+        const int min_tiles = rg == 1 ? 8 : 4;
+        // key tiles of a piece as the kernel will find them (work_per)
+        const double rt = row_tiles(rg), tiles = rt * seen * (rg == 1 ? 0.3 * tiles_mean + 0.7 * tiles_max : 0.7 * tiles_mean + 0.3 * tiles_max);
+        double per = std::ceil(rt * tiles_mean / std::fmax((double)workers - rt, 1.0));
+        per = std::fmin(std::fmax(std::fmax(per, total_q * tiles_max / (double)(room - total_q)), (double)min_tiles), tiles_max);
+        const double all = tiles * Hkv / cus;
+        const double est = rg == 1 ? (d64 ? 10.7 + 0.024 * std::ceil(per / 4.0) + 0.20 * all : 12.2 + 0.42 * std::ceil(per / 4.0) + 0.30 * all)
+                                   : (d64 ? 11.7 + 0.053 * per + 0.61 * all : 15.1 + 0.85 * all);
+        if (est < 0.95 * us) {
+            us = est;
+            // what the pieces can take at most: each sequence one more than `min_tiles` goes into its key tiles
+            const int64_t most = total_q * (((int64_t)tiles_max + min_tiles - 1) / min_tiles + 1), part_rows = most < room ? most : room;
+            best = {rg, workers, min_tiles, part_rows, (size_t)(part_rows * row_bytes + table)};
+        }
+    }
+    return best;
+}
+
+template <int D, int RG>
+pdd_status launch_attn_rows(const RowsPlan &plan, pdd::AttnParams &p, int64_t max_q, void *scratch, hipStream_t st)
+{
+    p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
+    if (plan.workers == 0) {
+        p.n_qtiles = (int)((max_q * p.G + 32 * RG - 1) / (32 * RG));
+        p.turn = pdd::rows_per_turn(p.Hkv);
+        return launch_attn_kernel(pdd::attn_rows_kernel<D, RG, false>, pdd::RowsSmem<D, RG>::BYTES, 64 * pdd::kRowsWaves, p,
+                                  (int64_t)p.n_qtiles * p.B * p.Hkv, st);
+    }
+    p.workers = (int)plan.workers;  p.min_tiles = plan.min_tiles;  p.part_rows = (int)plan.part_rows;
+    p.part_of = (uint4 *)scratch;
+    p.part_o = (float *)(p.part_of + (int64_t)p.total_q * p.Hq);
+    p.part_l = p.part_o + plan.part_rows * p.Hq * D;
+    const pdd_status s = launch_attn_kernel(pdd::attn_rows_kernel<D, RG, true>, pdd::RowsSmem<D, RG>::BYTES, 64 * pdd::kRowsWaves, p,
+                                            plan.workers * p.Hkv, st);
+    if (s) return s;
+    const int64_t n = ((int64_t)p.total_q * p.Hq + 3) / 4;       // one wave per (token, head)
+    hipLaunchKernelGGL(pdd::attn_join_kernel<D>, dim3((unsigned)n), dim3(256), 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(PDD_ERR_HIP, "attention join launch: %s", hipGetErrorString(e));
+    return PDD_OK;
 }
 
 // bm: queries per workgroup of the plain form.
 // imp_part != NULL: sweep_workspace(d) bytes; the importance sweep runs inside
 // the attention kernel and leaves its partial sums there.
-// split_ws != NULL: the key-split form of `plan`, with plan.bytes of scratch.
+// plan, rows != NULL: the key-split form or that of attn_rows.hpp, with plan->bytes or rows->bytes of scratch.
 pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void *k, const void *v, void *o, float *lse,
                        hipStream_t st, float *imp_part = nullptr, const SplitPlan *plan = nullptr,
-                       void *split_ws = nullptr)
+                       const RowsPlan *rows = nullptr, void *scratch = nullptr)
 {
     if (d->total_q == 0) return PDD_OK;
     pdd::AttnParams p;
@@ -334,6 +446,7 @@ pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void
     p.o_st = d->o_stride_tok;  p.o_sh = d->o_stride_head;
     p.B = d->batch;  p.Hq = d->n_q_heads;  p.Hkv = d->n_kv_heads;  p.G = d->n_q_heads / d->n_kv_heads;
     p.total_q = d->total_q;  p.total_k = d->total_k;
+    p.turn = 1;
     p.scale_log2 = scale_log2(d);
 
     const int nw = bm / 32;
@@ -349,11 +462,16 @@ pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void
         if ((int64_t)d->q_stride_tok * 2 * 32 >= (1LL << 32))
             return fail(PDD_ERR_UNSUPPORTED, "32 rows of Q must span less than 4 GiB");
     }
-    if (split_ws) {
+    if (rows) {
+        if (d->head_dim == 128)
+            return rows->rg == 1 ? launch_attn_rows<128, 1>(*rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<128, 4>(*rows, p, d->max_seqlen_q, scratch, st);
+        return rows->rg == 1 ? launch_attn_rows<64, 1>(*rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<64, 4>(*rows, p, d->max_seqlen_q, scratch, st);
+    }
+    if (plan) {
         p.split_tiles = plan->tiles;  p.n_split = plan->n_split;
         p.n_qtiles = (int)(((int64_t)d->max_seqlen_q * p.G + kSplitRows - 1) / kSplitRows);
         p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
-        p.part_o = (float *)split_ws;
+        p.part_o = (float *)scratch;
         p.part_l = p.part_o + (size_t)plan->n_split * d->total_q * d->n_q_heads * d->head_dim;
         const int64_t n = (int64_t)p.n_qtiles * d->batch * d->n_kv_heads * plan->n_split;
         return d->head_dim == 128 ? launch_attn_split<128>(p, n, st) : launch_attn_split<64>(p, n, st);
@@ -591,14 +709,21 @@ size_t plain_chunked_workspace(const pdd_attn_desc *d)
     return sweep ? sweep : importance_workspace(d, -1);
 }
 
-// The same with the key-split form where that applies: its partial rows, and after them, in the
+// The same with the form of attn_rows.hpp where that applies: its partial rows, and after them, in the
 // same place, the partial sums of the importance kernel.
 size_t chunked_workspace(const pdd_attn_desc *d)
 {
-    const size_t split = split_plan(d, true).bytes;
-    if (!split) return plain_chunked_workspace(d);
+    const RowsPlan rows = rows_plan(d, true, true);
+    if (!rows.rg) return plain_chunked_workspace(d);
     const size_t imp = importance_workspace(d, -1);
-    return split > imp ? split : imp;
+    return rows.bytes > imp ? rows.bytes : imp;
+}
+
+// The plan of rows_plan for the scratch that a call is given.
+RowsPlan rows_plan_with(const pdd_attn_desc *d, bool chunked, const void *workspace, size_t workspace_bytes)
+{
+    const RowsPlan rows = rows_plan(d, chunked, true);
+    return rows.bytes == 0 || (workspace && workspace_bytes >= rows.bytes && aligned16(workspace)) ? rows : rows_plan(d, chunked, false);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device.
@@ -665,7 +790,7 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
     case PDD_CALL_PREFILL_ATTN:
     {
         const size_t imp = desc->window > 0 ? importance_workspace(desc, desc->window) : 0;
-        const size_t split = split_plan(desc, false).bytes;
+        const size_t split = split_plan(desc).bytes;      // (also where a form of attn_rows.hpp needs none)
         return split > imp ? split : imp;
     }
     case PDD_CALL_PREFILL_ATTN_CHUNKED:
@@ -687,9 +812,14 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
     if (s) return s;
     if (desc->window > 0 && !importance)
         return fail(PDD_ERR_INVALID_ARG, "window > 0 needs an importance buffer");
-    const SplitPlan plan = split_plan(desc, false);
-    if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace))
-        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+    // (a prompt's rows plan takes no scratch; without scratch for the key-split form it is compared with the plain form alone)
+    const SplitPlan plan = split_plan(desc);
+    const bool room = plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace);
+    const RowsPlan rows = rows_plan(desc, false, room);
+    if (rows.rg)
+        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows);
+    else if (room)
+        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, nullptr, workspace);
     else
         s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream);
     if (s) return s;
@@ -707,10 +837,9 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     if (s) return s;
     s = check_ptrs(q_chunk, k_all, v_all, o, lse);
     if (s) return s;
-    const SplitPlan plan = split_plan(desc, true);
     const int bm = attn_rows_per_workgroup(desc);
-    if (plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace)) {
-        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, &plan, workspace);
+    if (const RowsPlan rows = rows_plan_with(desc, true, workspace, workspace_bytes); rows.rg) {
+        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows, workspace);
         if (s || !importance) return s;
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,
                                  (hipStream_t)stream);
@@ -748,7 +877,7 @@ pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const voi
     if (plain > PDD_STATIC_SCRATCH_BYTES)
         return fail(PDD_ERR_WORKSPACE, "this shape wants %zu bytes of scratch, the built-in scratch holds %u "
                     "(use pdd_prefill_attn_chunked with a workspace)", plain, (unsigned)PDD_STATIC_SCRATCH_BYTES);
-    // (the key-split form never wants more than the built-in scratch)
+    // (the forms of attn_rows.hpp never want more than the built-in scratch)
     const size_t need = chunked_workspace(desc);
     void *ws = nullptr;
     if (need > 0) {

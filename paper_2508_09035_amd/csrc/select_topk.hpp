@@ -107,25 +107,6 @@ __device__ __forceinline__ uint32_t next_probe(uint32_t lo, uint32_t hi, uint32_
     return hi - min(down, span - 1u);
 }
 
-// the same over N independent values per lane, one step over all of them at a time: consecutive
-// instructions are independent, so none of them waits for the DPP hazard of its predecessor
-template <int N>
-__device__ __forceinline__ void wave_incl_scan_n(uint32_t (&x)[N])
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x111, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x112, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x114, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x118, 0xf, 0xf, true);
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x142, 0xa, 0xf, false);
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x143, 0xc, 0xf, false);
-}
-
 // minimum / maximum over the 64 lanes of a wave, valid in lane 63 (same DPP pattern as the scan)
 __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx)
 {

@@ -279,6 +279,57 @@ def test_keys_split_over_workgroups_in_other_layouts(d, layout):
     assert all(torch.equal(a, b) for a, b in zip(want, (dev.o, dev.lse, dev.imp)))
 
 
+_ROWS_SHAPES = {        # (new tokens, keys or None for prefill, query heads, KV heads, partial rows in scratch)
+    # a workgroup to a tile of 32 rows: around a row tile, a block and a key tile; no keys shared by two heads
+    "whole prompts": ([1, 31, 32, 33, 64, 65, 500], None, 1, 1, False),
+    "whole, group 3": ([1, 33, 40, 0, 11], [200, 33, 300, 7, 65], 6, 2, False),
+    # keys divided, 32 rows: more sequences than lanes, an empty one; more heads in a group than rows in a tile
+    "many short": ([1] * 69 + [0, 1], [400 + 37 * i for i in range(69)] + [90, 6000], 6, 2, True),
+    "group 48": ([3, 1], [4003, 2500], 48, 1, True),
+    # keys divided, 128 rows: around a row tile (at head_dim 64 the second one takes 32 rows); more sequences than lanes
+    "chunks": ([43, 0, 1, 85, 300], [3043, 70, 4001, 5085, 3300], 12, 2, True),
+    "mha": ([32, 33, 31, 129, 127, 128], [5032, 4033, 6031, 6128, 3000, 6144], 8, 8, True),
+    "many chunks": ([6] * 66 + [0, 43], [300 + 30 * i for i in range(66)] + [50, 4000], 36, 1, True),
+}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", list(_ROWS_SHAPES))
+def test_few_rows_over_many_keys(name, d):
+    """The attention forms that share a row tile's keys out over the waves of a workgroup, and over workgroups,
+    against the oracle on every row with the scratch full of NaN patterns; then the same bits from views with
+    strides, without the host's copy of the lengths."""
+    lens_q, lens_k, hq, hkv, divided = _ROWS_SHAPES[name]
+    window = 16 if lens_k is None else 0
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, d, window, "1/4", seed=720 + d, chunked=lens_k is not None)
+    dev = DeviceWorkload(wl)
+    row_bytes = wl.total_q * hq * (d + 1) * 4
+    assert (dev.workspace_bytes >= row_bytes + row_bytes // 4) == divided, "this shape is one that takes the form"
+    bits = []
+    for views in (False, True):
+        if views:
+            qo = torch.zeros((wl.total_q, 2 * hq, d), dtype=torch.bfloat16, device="cuda")
+            kv = torch.zeros((wl.total_k, 2 * hkv, d), dtype=torch.bfloat16, device="cuda")
+            qo[:, :hq], kv[:, :hkv], kv[:, hkv:] = dev.q, dev.k, dev.v
+            dev.q, dev.o, dev.k, dev.v = qo[:, :hq], qo[:, hq:], kv[:, :hkv], kv[:, hkv:]
+        dev.o.fill_(float("nan"))
+        dev.lse.fill_(float("nan"))
+        dev.imp.fill_(float("nan"))
+        if dev.workspace is not None:
+            dev.workspace.fill_(0xFF)
+        dev.attn(True, host_cu=not views)
+        torch.cuda.synchronize()
+        bits.append([x.clone() for x in (dev.o, dev.lse, dev.imp)])
+        if not views:
+            O, lse, imp = dev.results()[:3]
+            assert not divided or (dev.workspace.view(torch.int32) != -1).any(), "the scratch was not used"
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale)
+    assert np.abs(O - oO).max() <= O_ATOL
+    rel_close(lse, oL, "lse")
+    rel_close(imp, oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, window or -1), "importance")
+    assert all(torch.equal(a, b) for a, b in zip(*bits))
+
+
 def test_rows_a_mebibyte_apart_close_to_the_4_gib_span_limit():
     """Q, K and V rows 1 MiB apart (views into 3.1 GiB buffers): byte offsets inside the sequence's
     span run up to 3.4 * 2^30, close to what 32-bit buffer offsets can address; same bits as
