@@ -155,15 +155,10 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 
     if (mine != 0) atomicAdd(&hist[0][(mine - bottom) >> width0], 1u);
     // wave 0 looks for the upper edge, wave 1 for the lower one
     auto look = [&](const uint32_t *h, int want) {
-        uint32_t bin[16], incl, most = 0;
-        const uint32_t total = hist_total(h, lane, bin, incl);
-        int run = (int)(total - incl);
-#pragma unroll
-        for (int e = 15; e >= 0; --e) {
-            if (run < want && want <= run + (int)bin[e]) place[wave] = {16u * lane + e, bin[e], (uint32_t)run};
-            run += (int)bin[e];
-            most = max(most, bin[e]);
-        }
+        uint32_t sum, over, most;
+        hist_total(h, lane, sum, over, most);
+        const SelBin at = hist_find(h, lane, sum, over, want);
+        if (lane == 0 && at.bin >= 0) place[wave] = {(uint32_t)at.bin, at.own, at.above};
         return most;
     };
     __syncthreads();

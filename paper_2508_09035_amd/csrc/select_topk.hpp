@@ -7,17 +7,22 @@
 // order-preserving uint32 keys.  Two kernels:
 //
 //  * select_topk_reg_kernel<QPT> (rows of up to 4096 * QPT <= 32768 candidates):
-//    every thread keeps its 4 QPT keys in registers for the whole kernel.  The k-th
-//    largest key is found in a few rounds of two probes on the key value: one round = two
-//    compares per key, wave ballots counted on the scalar unit and lane counts on the
-//    vector unit, one LDS counter.  A histogram (of a sample, where the row is long)
-//    places the first bracket, and the keys left in it move to LDS early, because a
-//    round costs by its instructions: 16 cycles each with four waves per SIMD.  The row is
+//    every thread keeps its 4 QPT keys in registers for the whole kernel.  A histogram (of a
+//    sample, where the row is long) places a bracket around the k-th largest key; one pass over the
+//    keys counts those inside and above it and one moves those inside to LDS, where a few rounds of two probes
+//    on the key value find it (one round = two compares per key, one LDS counter).  Passes are
+//    few because each costs by its instructions, 16 cycles each with four waves per SIMD.  The row is
 //    not read again.  The kept indices are written in ascending order from
 //    prefix counts, with a 16 * QPT-entry scan across waves.
 //    By single interpolated or bisecting probes from the row's range on (8 to 11, 27 with many
 //    ties) 8 rows took, scores spread over octaves / log-normal: 4096 9.5 / 10.5 us, 16384 13.6 / 16.2,
-//    32768 20.0 / 21.3, 512 rows of 32768 42.1 / 47.4; now 6.5 / 6.3, 11.6 / 11.6, 17.0 / 17.2, 36.7 / 37.0.
+//    32768 20.0 / 21.3, 512 rows of 32768 42.1 / 47.4; with all keys' range, two probes a round over all keys and loads behind
+//    branches 6.5 / 6.3, 11.6 / 11.6, 17.0 / 17.2, 36.7 / 37.0.  With the sample's own range, requested ahead of the row and
+//    placed while that is on its way (uniform scores to the sixth power, kept 1/10 to 1/2, before -> now): 8 rows of 4096 6.5 -> 5.8 us, 16384
+//    12.3 -> 11.2, 32768 16.7 -> 14.1, 512 rows of 32768 34.3 -> 29.8, 512 of 4000 9.6 -> 8.6.  Rows of few different
+//    scores, or of scores that hardly change from key to key, which the sample misjudges, take up to 1.2 times as long.
+//    Bound by the latency of some ten steps where the rows are few; 512 rows read 67 MB and write 23 (18.5 us) before and after the
+//    passes, with all rows at the same point at once.
 //    Histograms of all keys of long rows were slower: 50 cycles per LDS atomic of a wave.  So
 //    were fewer threads with more keys each (256 x 16: 9.7 us at 4096).
 //  * select_topk_kernel (longer rows without a workspace, pooled, or beyond the limits of
@@ -49,6 +54,7 @@ struct SelParams {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelFinish = 128;   // keys left in the bracket that are ranked directly
+constexpr uint32_t kSelRun = 64;  // keys of the sample in one bin that may be a run of equal scores
 constexpr int kSelList = 4 * kSelThreads;     // keys left in the bracket that move to four per thread
 constexpr int kSelBins = 1024;    // of the histograms that place the bracket, one bin per thread
 constexpr int kSelRegCap = 32 * 1024;  // rows up to this many candidates stay in registers
@@ -183,11 +189,11 @@ struct PoolStage {
     }
 
     // the thread's four pooled scores of keys first + 4 tid .. + 3
-    __device__ __forceinline__ void step(const float *seq, int nk, int first, bool is_first, bool more, int tid, float (&out)[4])
+    __device__ __forceinline__ void step(const float *seq, int nk, int first, int number, bool more, int tid, float (&out)[4])
     {
-        __shared__ __attribute__((aligned(16))) float stage[kSelPoolStep + 2 * kSelPoolMax];
-        if (is_first) request(seq, nk, first, tid);
-        else __syncthreads();                                    // the last step's reads are done
+        __shared__ __attribute__((aligned(16))) float stages[2][kSelPoolStep + 2 * kSelPoolMax];     // in turn: one barrier a step
+        float *const stage = stages[number & 1];
+        if (number == 0) request(seq, nk, first, tid);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int at = q * kSelPoolStep + 4 * tid;
@@ -253,32 +259,36 @@ __device__ __forceinline__ void next_pair(uint32_t lo, uint32_t hi, uint32_t ins
     b = hi - min((uint32_t)fminf(fmaxf(down - dev, 0.f) * per_key, 4294967040.f), hi - a);
 }
 
-// Wave 0's part of a histogram step over kSelBins bins: the bins in which the keys of rank r0 and r1
-// (from the top) lie, the keys above the first of them, and its own.  Untouched where there is no such rank.
-struct SelPlace { int32_t bin[2]; uint32_t above, own; };
-__device__ __forceinline__ uint32_t hist_total(const uint32_t *hist, int lane, uint32_t (&bin)[16], uint32_t &incl)
+// Wave 0's part of a histogram step over kSelBins bins, of which lane l looks after the 16 from 16 l on: the keys in
+// the lane's bins, in those above them and in its fullest, and the bin with the key of a given rank from the top, the keys above that bin and in it.
+struct SelBin { int bin; uint32_t above, own; };              // bin < 0: there is no such rank
+__device__ __forceinline__ uint32_t hist_total(const uint32_t *hist, int lane, uint32_t &sum, uint32_t &above, uint32_t &most)
 {
-    uint32_t sum = 0;                                            // lane: 16 consecutive bins
+    sum = most = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint4 t = ((const uint4 *)hist)[4 * lane + q];
-        bin[4 * q] = t.x;  bin[4 * q + 1] = t.y;  bin[4 * q + 2] = t.z;  bin[4 * q + 3] = t.w;
+        const uint4 t = ((const uint4 *)hist)[4 * lane + ((q + lane) & 3)];     // turned, so that no two lanes meet in a bank
         sum += (t.x + t.y) + (t.z + t.w);
+        most = max(max(most, max(t.x, t.y)), max(t.z, t.w));
     }
-    incl = wave_incl_scan(sum);
-    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    const uint32_t incl = wave_incl_scan(sum), total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    above = total - incl;
+    return total;
 }
-__device__ __forceinline__ void hist_place(const uint32_t (&bin)[16], uint32_t total, uint32_t incl, int lane, int r0, int r1,
-                                           SelPlace *out)
+__device__ __forceinline__ SelBin hist_find(const uint32_t *hist, int lane, uint32_t sum, uint32_t above, int rank)
 {
-    int run = (int)(total - incl);
-#pragma unroll
-    for (int e = 15; e >= 0; --e) {
-        const int up = run + (int)bin[e];
-        if (run < r0 && r0 <= up) { out->bin[0] = 16 * lane + e; out->above = (uint32_t)run; out->own = bin[e]; }
-        if (run < r1 && r1 <= up) out->bin[1] = 16 * lane + e;
-        run = up;
-    }
+    const uint64_t at = __ballot((int)above < rank && rank <= (int)(above + sum));
+    const int l = at ? (int)__builtin_ctzll(at) : 0;
+    const uint32_t own = hist[16 * l + 15 - (lane & 15)];     // each row of 16 lanes: the lane's bins from the top
+    uint32_t before = own;
+    before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x111, 0xf, 0xf, true);
+    before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x112, 0xf, 0xf, true);
+    before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x114, 0xf, 0xf, true);
+    before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x118, 0xf, 0xf, true);
+    before += (uint32_t)__builtin_amdgcn_readlane((int)above, l) - own;
+    const uint64_t in = __ballot((int)before < rank && rank <= (int)(before + own));
+    const int e = in ? (int)__builtin_ctzll(in) : 0;
+    return {at ? 16 * l + 15 - e : -1, (uint32_t)__builtin_amdgcn_readlane((int)before, e), (uint32_t)__builtin_amdgcn_readlane((int)own, e)};
 }
 
 // At most 64 vector registers, so that two workgroups (8 waves per SIMD) share a compute unit: the
@@ -292,9 +302,11 @@ void select_topk_reg_kernel(const SelParams p)
     __shared__ uint32_t probe_tot[kSelMaxProbes];      // counts of pair number p, summed over the waves
     __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins], fin_keys[kSelFinish + 4];
     __shared__ uint32_t list[QPT > 1 ? kSelList : 1];
-    __shared__ uint32_t sh_min, sh_max, list_count, fin_count, fin_T, fin_above, head_tot;
-    __shared__ SelPlace place;
-    __shared__ uint2 range[kSelMaxProbes];             // of round number p, see narrow_bracket
+    __shared__ unsigned long long list_tot[2];         // keys inside a bracket | keys above it << 32
+    __shared__ uint32_t sh_min, sh_max, fin_count, head_tot;
+    __shared__ uint4 place;                            // lower and upper end of a bracket, keys above it and in it
+    __shared__ struct { uint32_t T, above, upto; } fin;
+    __shared__ uint2 range[kSelMaxProbes + 3];         // of round number p (and of two other steps), see narrow_bracket
 
     const int b = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -319,18 +331,41 @@ void select_topk_reg_kernel(const SelParams p)
     int32_t *out = p.out_idx + (int64_t)g * p.total_keep + keep0;
     uint8_t *mrow = p.out_mask ? p.out_mask + (int64_t)g * p.total_k + ks : nullptr;
 
-    hist[tid] = 0;
-    if (tid < kSelMaxProbes) {
-        probe_tot[tid] = 0;
-        range[tid] = make_uint2(0xffffffffu, 0u);
+    // ---- everything that is read is requested here: a sample of a long row first, then the row.  Buffer loads, which
+    // return zero outside the range: a branch around a load would wait for it.
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const bool has_head = tid < nhead;
+    const float *qbase = seq + c0 + nhead;                       // 16-byte aligned (unpooled)
+    const int n_quads = nq_el / 4;                               // whole ones
+    auto first_of = [&](int i) { return 4 * (i * kSelThreads + 64 * wave_u); };    // the wave's first index of a step
+    uint32_t sample = 0, head = 0;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 quad[QPT];
+    // QPT = 8: two steps at a time, else a wave waits to issue its loads while the chip's are queued (512 rows of 32768)
+    constexpr int kEarly = QPT > 4 ? 3 : QPT > 2 ? 2 : QPT;
+    const auto quads = __builtin_amdgcn_make_buffer_rsrc((void *)qbase, 0, 16 * n_quads, 0x00020000);
+    auto request = [&](int from, int to) {
+#pragma unroll
+        for (int i = from; i < to; ++i) quad[i] = __builtin_amdgcn_raw_buffer_load_b128(quads, 16 * (i * kSelThreads + tid), 0, 0);
+    };
+    if constexpr (!POOL) {
+        const auto row = __builtin_amdgcn_make_buffer_rsrc((void *)(seq + c0), 0, 4 * n, 0x00020000);
+        // two lanes to each of 512 places spread over the row, so that a part of its lines holds it and it is there early
+        if constexpr (QPT > 1)
+            sample = __builtin_amdgcn_raw_buffer_load_b32(row, n > kSelList ? 4 * (((tid >> 1) * n >> 9) + 4 * (tid & 1)) : -4, 0, 0);
+        head = __builtin_amdgcn_raw_buffer_load_b32(row, has_head ? 4 * tid : -4, 0, 0);
+        request(0, kEarly);
     }
+
+    hist[tid] = 0;
+    if (tid < kSelMaxProbes + 3) range[tid] = make_uint2(0xffffffffu, 0u);
+    if (tid < kSelMaxProbes) probe_tot[tid] = 0;
     if (tid < kSelFinish + 4) fin_keys[tid] = 0;
     if (tid == 0) {
-        list_count = fin_count = 0;
+        list_tot[0] = list_tot[1] = 0;
+        fin_count = 0;
         sh_min = 0xffffffffu;
         sh_max = 0;
-        place.bin[0] = kSelBins - 1;
-        place.bin[1] = 0;
     }
     __syncthreads();
     if (p.pooled_out) {
@@ -352,66 +387,108 @@ void select_topk_reg_kernel(const SelParams p)
         return;
     }
 
+    uint32_t lo = 1u, hi = 0xffffffffu, c_lo = (uint32_t)n, c_above = 0;       // see the threshold search
+    constexpr bool kLong = QPT > 1;                              // the instantiation takes rows beyond kSelList
+    const bool is_long = kLong && n > kSelList;
+    // ---- long rows: a histogram of some 1024 keys places the first bracket.  It encloses the threshold but for some three
+    // standard deviations of its rank in the sample, and is made while the row is on its way.
+    auto place_sample = [&](uint32_t k) {                        // k = 0: the thread has none
+        uint32_t mn = k - 1u, mx = k;
+        wave_min_max(mn, mx);
+        if (lane == 63) { atomicMin(&sh_min, mn); atomicMax(&sh_max, mx); }
+        if constexpr (!POOL && kEarly < QPT) request(kEarly, 2 * kEarly);
+        __syncthreads();
+        const uint32_t first = sh_min + 1u;
+        const int shift = max(32 - __builtin_clz((sh_max - first) | 1u) - 10, 0);      // kSelBins = 2^10
+        if (k != 0 && first < sh_max) atomicAdd(&hist[(k - first) >> shift], 1u);
+        if constexpr (!POOL && kEarly < QPT) request(2 * kEarly, QPT);
+        if (first == sh_max) {                                   // one value (1024 atomics on one bin take 2.5 us)
+            lo = hi = first;
+            return;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            uint32_t sum, above, most;
+            const uint32_t m = hist_total(hist, lane, sum, above, most);
+            const float share = (float)kk * __builtin_amdgcn_rcpf((float)n), rank = share * (float)m;
+            const float dev = 3.f * __builtin_amdgcn_sqrtf(rank * fmaxf(1.f - share, 0.f)) + 1.f;
+            const SelBin up = hist_find(hist, lane, sum, above, (int)(rank - dev));
+            const SelBin down = hist_find(hist, lane, sum, above, (int)(rank + dev) + 1);
+            // no such rank: the bracket is open there
+            const uint32_t end = ((uint32_t)max(up.bin, 0) << shift) + ((1u << shift) - 1u);
+            if (lane == 0) place = make_uint4(down.bin < 0 ? 1u : first + ((uint32_t)down.bin << shift),
+                                              up.bin < 0 || end > 0xffffffffu - first ? 0xffffffffu : first + end,
+                                              up.bin == down.bin ? up.own : 0u, 0u);
+        }
+        __syncthreads();
+        lo = place.x;
+        hi = place.y;
+        if (place.z > kSelRun) {                                 // scores that are equal?  Then the bracket is the one value
+            uint32_t mn = 0xffffffffu, mx = 0, from = lo, to = hi;
+            range_of_key(k, lo, hi, mn, mx);
+            narrow_bracket(&range[kSelMaxProbes], mn, mx, lane, from, to);
+            if (from == to) lo = hi = from;
+        }
+    };
+    if constexpr (kLong && !POOL) {
+        if (is_long && kk > 1 && kk < n) place_sample(order_key(__uint_as_float(sample)));
+        else if constexpr (kEarly < QPT) request(kEarly, QPT);
+    }
+
     // ---- keys into registers.  Slots outside the row hold key 0, which is below the key of
-    // every finite score.
-    const bool has_head = tid < nhead;
-    const uint32_t khead = has_head ? order_key(seq[c0 + tid]) : 0u;
-    const float *qbase = seq + c0 + nhead;                       // 16-byte aligned (unpooled)
+    // every score.
+    const uint32_t khead = has_head ? order_key(__uint_as_float(head)) : 0u;      // (POOL: none)
     uint32_t key[QPT][4];
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     PoolStage pool(p);
 #pragma unroll
     for (int i = 0; i < QPT; ++i) {
-        const int xw = 4 * (i * kSelThreads + 64 * wave_u);      // the wave's first index of this step
+        const int xw = first_of(i);
         if constexpr (POOL) {
             if (i * kSelPoolStep < n) {                          // the same in every thread
                 float pooled[4];
-                pool.step(seq, nk, c0 + i * kSelPoolStep, i == 0, (i + 1) * kSelPoolStep < n, tid, pooled);
+                pool.step(seq, nk, c0 + i * kSelPoolStep, i, (i + 1) * kSelPoolStep < n, tid, pooled);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) key[i][j] = (xw + 4 * lane + j < n) ? order_key(pooled[j]) : 0u;
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) key[i][j] = 0u;
             }
-        } else if (xw + 255 < nq_el) {                           // all of its 64 quads lie inside the row
-            const float4 t = *(const float4 *)(qbase + xw + 4 * lane);
-            key[i][0] = order_key(t.x);  key[i][1] = order_key(t.y);
-            key[i][2] = order_key(t.z);  key[i][3] = order_key(t.w);
-        } else {
-            const int x0 = xw + 4 * lane;
+        } else if (xw + 255 < nq_el) {                           // all of the wave's 64 quads lie inside the row
 #pragma unroll
-            for (int j = 0; j < 4; ++j) key[i][j] = (x0 + j < nq_el) ? order_key(qbase[x0 + j]) : 0u;
+            for (int j = 0; j < 4; ++j) key[i][j] = order_key(__uint_as_float(quad[i][j]));
+        } else {
+            const int left = nq_el - (xw + 4 * lane);
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(quad[i][j]);
+            if (left > 0 && left < 4)                            // the row's last quad, one at most
+                for (int j = 0; j < left; ++j) v[j] = qbase[xw + 4 * lane + j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) key[i][j] = j < left ? order_key(v[j]) : 0u;
         }
     }
-    // row range over the real keys: an empty slot (key 0) wraps to the largest value under key - 1
-    // and so never is the minimum
-    uint32_t kmin = khead - 1u, kmax = khead;
+    if constexpr (kLong && POOL) {
+        if (is_long && kk > 1 && kk < n) {
+            uint32_t k = key[0][0];
 #pragma unroll
-    for (int i = 0; i < QPT; ++i) {
-        kmin = min(kmin, min(min(key[i][0] - 1u, key[i][1] - 1u), min(key[i][2] - 1u, key[i][3] - 1u)));
-        kmax = max(kmax, max(max(key[i][0], key[i][1]), max(key[i][2], key[i][3])));
+            for (int o = 1; o < QPT; ++o) k = (tid & (QPT - 1)) == o ? key[o][0] : k;
+            place_sample(k);
+        }
     }
-    wave_min_max(kmin, kmax);
-    if (lane == 63) { atomicMin(&sh_min, kmin); atomicMax(&sh_max, kmax); }
-    __syncthreads();
 
-    // ---- threshold search: largest T in the row's range with count(key >= T) >= kk, over the bracket [lo, hi] with
-    // c_lo = count(key >= lo) >= kk > c_above = count(key > hi), in rounds of two probes (see next_pair).
-    // A round costs the workgroup some thousand cycles with few keys per thread, twice that with 32, so
+    // ---- threshold search: the largest T with count(key >= T) >= kk, over the bracket [lo, hi] with
+    // c_lo = count(key >= lo) >= kk > c_above = count(key > hi).
+    // A step over all keys costs the workgroup by its instructions, four wavefronts to a SIMD, so
     //   * rows of up to 4096 candidates count all of them into bins over the row's range and go on in
     //     the bin that holds the threshold;
-    //   * longer rows do so with about 1024 keys, spread over the row, which gives two bins that enclose
-    //     the threshold but for some three standard deviations of its rank: the first pair of probes;
-    //   * once at most 4096 keys are left inside the bracket, these move to LDS and four to a thread, and
-    //     once at most kSelFinish are left they are ranked directly.
+    //   * longer rows count the keys inside the sample's bracket and above it, and where the threshold is inside and
+    //     at most 4096 keys are, these move to LDS and four to a thread; else rounds of two probes (see next_pair)
+    //     over all keys come between;
+    //   * two probes a round go on over those, and once at most kSelFinish are left they are ranked directly.
     // Every probed value is > lo > 0, so empty slots never count.
-    uint32_t lo = sh_min + 1u, hi = sh_max;                      // lo: back from key - 1 (kk >= 1: the row has a real key)
-    if (kk == n) hi = lo;                                        // everything is kept: T is the minimum, and no tie is cut
-    if (kk == 1) lo = hi;                                        // T is the maximum (8 x 681 6.0 -> 3.7 us)
-    uint32_t c_lo = (uint32_t)n, c_above = 0, pa = 0, pb = 0;
-    bool placed = false, interp = true;
+    uint32_t pa = 0, pb = 0;
+    bool interp = true;
     int round = 0;
-    const int shift = max(32 - __builtin_clz((hi - lo) | 1u) - 10, 0);     // kSelBins = 2^10
     // One round: `count` adds this wave's keys >= pa to its first argument and those >= pb to the second.
     // The waves' sums meet in an LDS counter of their own (one fresh counter per round, so none is ever
     // cleared), two to a word: a count is at most 32768.  `each` calls its argument with the thread's keys: a round
@@ -419,8 +496,7 @@ void select_topk_reg_kernel(const SelParams p)
     // one probe a round).
     auto probe = [&](auto &&count, auto &&each) {
         const uint32_t inside = c_lo - c_above;
-        if (!placed) next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
-        placed = false;
+        next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
         uint32_t ca = 0, cb = 0, la = 0, lb = 0;                 // of the wave; of the lane
         count(ca, cb, la, lb);
         const uint32_t both = (ca | cb << 16) + (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(la | lb << 16), 63);
@@ -443,33 +519,71 @@ void select_topk_reg_kernel(const SelParams p)
             narrow_bracket(&range[round - 1], mn, mx, lane, lo, hi);
         }
     };
-    constexpr int NL = QPT > 1 ? kSelList / kSelThreads : 5;
+    auto all_keys = [&](auto &&f) {
+        f(khead);
+#pragma unroll
+        for (int i = 0; i < QPT; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f(key[i][j]);
+    };
+    constexpr int NL = kSelList / kSelThreads + 1;
     uint32_t lk[NL];                                             // the thread's keys of the second part of the search
     uint32_t list_above = 0;                                     // keys above all of those
-    if constexpr (QPT > 1) {
-        if (lo < hi && n > kSelList) {
-            uint32_t k = key[0][0];
+    if (kk == n || (is_long && kk == 1)) {
+        if (kk == n) hi = lo;                                    // everything is kept: below or at the minimum, and no tie is cut
+        else {                                                   // T is the maximum
+            uint32_t mn = 0xffffffffu, mx = 0;
+            all_keys([&](uint32_t k) { mx = max(mx, k); });
+            wave_min_max(mn, mx);
+            if (lane == 63) atomicMax(&sh_max, mx);
+            __syncthreads();
+            lo = hi = sh_max;
+        }
+    } else if (is_long) {
+        // the keys inside [lo, hi], a bit for each, and the number above
+        uint32_t in = 0, at = 0;
+        bool head_in = false;
+        auto divide = [&](unsigned long long *tot) {
+            uint32_t from = 0, over = 0;                         // key[i][j] >= lo and > hi: bit 4 i + j
 #pragma unroll
-            for (int o = 1; o < QPT; ++o) k = (tid & (QPT - 1)) == o ? key[o][0] : k;
-            if (k != 0) atomicAdd(&hist[(k - lo) >> shift], 1u);
+            for (int i = QPT - 1; i >= 0; --i)
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {                   // empty slots hold key 0 < lo
+                    from = 2u * from + (key[i][j] >= lo ? 1u : 0u);
+                    over = 2u * over + (key[i][j] > hi ? 1u : 0u);
+                }
+            in = from & ~over;
+            head_in = khead >= lo && khead <= hi;
+            const uint32_t la = (uint32_t)__popc(over) + (khead > hi ? 1u : 0u);
+            const uint32_t c = (uint32_t)__popc(in) + (head_in ? 1u : 0u);
+            const uint32_t incl = wave_incl_scan(c | la << 16), all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            uint32_t before = 0;
+            if (lane == 0) before = (uint32_t)atomicAdd(tot, (unsigned long long)(all & 0xffffu) | (unsigned long long)(all >> 16) << 32);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)before) + (incl & 0xffffu) - c;
             __syncthreads();
-            if (wave == 0) {
-                uint32_t bin[16], incl;
-                const uint32_t m = hist_total(hist, lane, bin, incl);
-                const float share = (float)kk * __builtin_amdgcn_rcpf((float)n), rank = share * (float)m;
-                const float dev = 3.f * __builtin_amdgcn_sqrtf(rank * fmaxf(1.f - share, 0.f)) + 1.f;
-                hist_place(bin, m, incl, lane, (int)(rank - dev), (int)(rank + dev) + 1, &place);
+            c_above = (uint32_t)(*tot >> 32);
+            c_lo = c_above + (uint32_t)*tot;
+        };
+        divide(&list_tot[0]);
+        const bool inside = c_above < (uint32_t)kk && (uint32_t)kk <= c_lo;
+        bool fits = inside && lo < hi && c_lo - c_above <= (uint32_t)kSelList;
+        if (__builtin_expect(!fits && !(inside && lo == hi), 0)) {
+            if (c_above >= (uint32_t)kk) {                       // the threshold is above the bracket
+                lo = hi + 1u;
+                hi = 0xffffffffu;
+                c_lo = c_above;
+                c_above = 0;
+            } else if ((uint32_t)kk > c_lo) {                    // below it
+                hi = lo - 1u;
+                lo = 1u;
+                c_above = c_lo;
+                c_lo = (uint32_t)n;
             }
-            __syncthreads();
-            // upper edge of the one bin, lower edge of the other; the row's ends where there is none
-            pb = lo + (place.bin[0] == kSelBins - 1 ? hi - lo : min((uint32_t)(place.bin[0] + 1) << shift, hi - lo));
-            pa = min(lo + max((uint32_t)place.bin[1] << shift, 1u), pb);
-            placed = true;
-            // Half of the comparisons are counted with a ballot and a scalar population count, half per
-            // lane on the vector unit with one wave sum at the end.  The 16 waves of the workgroup (and
-            // a second workgroup on the same compute unit) share one scalar unit: all on it, the probes
-            // queue there (512 rows of 32768, single probes: 1.87 TB/s); all on the vector unit is slower
-            // again (2.17 TB/s); the split reaches 2.29 TB/s.
+            uint32_t mn = 0xffffffffu, mx = 0;
+            all_keys([&](uint32_t k) { range_of_key(k, lo, hi, mn, mx); });
+            narrow_bracket(&range[kSelMaxProbes + 2], mn, mx, lane, lo, hi);
+            // Half of the comparisons are counted with a ballot and a scalar population count, half per lane on the vector unit
+            // with one wave sum at the end: all on the scalar unit, which the waves share, the probes queue there.
             while (lo < hi && c_lo - c_above > (uint32_t)kSelList)
                 probe([&](uint32_t &ca, uint32_t &cb, uint32_t &la, uint32_t &lb) {
                     ca = (uint32_t)__popcll(__ballot(khead >= pa));
@@ -484,60 +598,66 @@ void select_topk_reg_kernel(const SelParams p)
                             lb += key[i][j + 2] >= pb ? 1u : 0u;
                         }
                     }
-                }, [&](auto &&f) {
-                    f(khead);
-#pragma unroll
-                    for (int i = 0; i < QPT; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) f(key[i][j]);
-                });
+                }, all_keys);
+            fits = lo < hi;
+            if (fits) divide(&list_tot[1]);
         }
-        if (lo < hi) {                                           // at most kSelList keys lie in [lo, hi]
-            const uint32_t width = hi - lo;                      // empty slots, key 0 < lo, wrap past it
-            uint32_t c = khead - lo <= width ? 1u : 0u;
-#pragma unroll
-            for (int i = 0; i < QPT; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) c += key[i][j] - lo <= width ? 1u : 0u;
-            const uint32_t incl = wave_incl_scan(c);
-            uint32_t at = 0;
-            if (lane == 63 && incl > 0) at = atomicAdd(&list_count, incl);
-            uint32_t *dst = list + (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - c;
-            if (khead - lo <= width) *dst++ = khead;
-            // compared again against a copy of lo the compiler cannot relate to the first (see Tc below)
-            uint32_t lc = lo;
-            asm volatile("" : "+v"(lc));
+        if (fits) {
+            uint32_t *dst = list + at;
+            if (head_in) *dst++ = khead;
 #pragma unroll
             for (int i = 0; i < QPT; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (key[i][j] - lc <= width) *dst++ = key[i][j];
+                    if (in >> (4 * i + j) & 1u) *dst++ = key[i][j];
             list_above = c_above;
             __syncthreads();
 #pragma unroll
             for (int q = 0; q < NL; ++q) lk[q] = q * kSelThreads + tid < (int)(c_lo - c_above) ? list[q * kSelThreads + tid] : 0u;
+            if (lo == 1u || hi == 0xffffffffu) {                 // an open end: probes are placed by the bracket's width
+                uint32_t mn = 0xffffffffu, mx = 0;
+#pragma unroll
+                for (int q = 0; q < NL; ++q) range_of_key(lk[q], lo, hi, mn, mx);
+                narrow_bracket(&range[kSelMaxProbes + 1], mn, mx, lane, lo, hi);
+            }
         }
     } else {
+        // the row's keys are all in lk (key 0 wraps to the largest value under key - 1 and so never is the minimum)
+        uint32_t mn = khead - 1u, mx = khead;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lk[j] = key[0][j];
-        lk[4] = khead;
-    }
-    if (lo < hi && n > kSelFinish && n <= kSelList) {            // the row's keys are all in lk
-#pragma unroll
-        for (int q = 0; q < NL; ++q)
-            if (lk[q] != 0) atomicAdd(&hist[(lk[q] - lo) >> shift], 1u);
-        __syncthreads();
-        if (wave == 0) {
-            uint32_t bin[16], incl;
-            const uint32_t m = hist_total(hist, lane, bin, incl);
-            hist_place(bin, m, incl, lane, kk, 0, &place);
+        for (int j = 0; j < 4; ++j) {
+            lk[j] = key[0][j];
+            mn = min(mn, lk[j] - 1u);
+            mx = max(mx, lk[j]);
         }
+        lk[4] = khead;
+        wave_min_max(mn, mx);
+        if (lane == 63) { atomicMin(&sh_min, mn); atomicMax(&sh_max, mx); }
         __syncthreads();
-        const uint32_t first = (uint32_t)place.bin[0] << shift;
-        hi = lo + min(first + ((1u << shift) - 1u), hi - lo);
-        lo += first;
-        c_above = place.above;
-        c_lo = place.above + place.own;
+        lo = sh_min + 1u;                                        // back from key - 1 (the row has a real key)
+        hi = sh_max;
+        if (kk == 1) {
+            c_lo = 0;                                            // (not known)
+            lo = hi;                                             // T is the maximum (8 x 681 6.0 -> 3.7 us)
+        } else if (lo < hi && n > kSelFinish) {
+            const int shift = max(32 - __builtin_clz(hi - lo) - 10, 0);     // kSelBins = 2^10
+#pragma unroll
+            for (int q = 0; q < NL; ++q)
+                if (lk[q] != 0) atomicAdd(&hist[(lk[q] - lo) >> shift], 1u);
+            __syncthreads();
+            if (wave == 0) {
+                uint32_t sum, above, most;
+                hist_total(hist, lane, sum, above, most);
+                const SelBin at = hist_find(hist, lane, sum, above, kk);
+                const uint32_t first = (uint32_t)at.bin << shift;
+                if (lane == 0) place = make_uint4(lo + first, lo + min(first + ((1u << shift) - 1u), hi - lo), at.above, at.own);
+            }
+            __syncthreads();
+            lo = place.x;
+            hi = place.y;
+            c_above = place.z;
+            c_lo = place.z + place.w;
+        }
     }
     while (lo < hi && c_lo - c_above > (uint32_t)kSelFinish)
         probe([&](uint32_t &ca, uint32_t &, uint32_t &la, uint32_t &lb) {
@@ -580,15 +700,19 @@ void select_topk_reg_kernel(const SelParams p)
         above = both & 0xffffu;
         upto = both >> 16;
         const uint32_t r = (uint32_t)kk - c_above;               // 1 <= r <= m
-        if (tid / PER < m && above < r && r <= upto) { fin_T = mine; fin_above = c_above + above; }      // equal keys only
+        if (tid / PER < m && above < r && r <= upto) { fin.T = mine; fin.above = c_above + above; fin.upto = c_above + upto; }    // equal keys only
         __syncthreads();
-        lo = fin_T;
-        c_above = fin_above;
+        lo = fin.T;
+        c_above = fin.above;
+        c_lo = fin.upto;
     }
     const uint32_t T = lo;
     const int krem = kk - (int)c_above;     // ties at T to keep (>= 1), lowest index first
 
-    // ---- counts of keys > T and == T in index order: the head, then (i major, lane, j)
+    // ---- counts in index order: the head, then (i major, lane, j).  Common case: count(key >= T) = kk, every key equal to T is
+    // kept (no tie is cut, e.g. T is unique), and a key is selected iff it is >= T.  Else the keys > T and == T are
+    // counted apart, and of the latter the first krem kept.
+    const bool all_ties = kk == n || c_lo == (uint32_t)kk;
     const uint32_t c_head = (has_head && khead > T ? 1u : 0u) | (has_head && khead == T ? 0x10000u : 0u);
     uint32_t pre_head = 0;                  // wave 0: exclusive prefix over the head lanes
     if (wave == 0) {
@@ -596,21 +720,39 @@ void select_topk_reg_kernel(const SelParams p)
         pre_head = incl - c_head;
         if (lane == 63) head_tot = incl;
     }
-    uint32_t pre[QPT];                      // prefix inside the wave, packed gt | eq << 16
+    uint32_t pre[QPT];                      // prefix inside the wave: >= T, or packed gt | eq << 16
+    uint32_t kept = 0;                      // all_ties: key[i][j] >= T at bit 4 i + j
+    if (all_ties) {
 #pragma unroll
-    for (int i = 0; i < QPT; ++i) {
-        uint32_t c = 0;
+        for (int i = QPT - 1; i >= 0; --i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {                  // empty slots hold key 0 < kmin <= T
-            c += key[i][j] > T ? 1u : 0u;
-            c += key[i][j] == T ? 0x10000u : 0u;
+            for (int j = 3; j >= 0; --j) kept = 2u * kept + (key[i][j] >= T ? 1u : 0u);       // empty slots hold key 0 < T
+        constexpr int NW = (QPT + 1) / 2;                        // two steps to a word: a wave's step has 256 keys
+        uint32_t own[NW], incl[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            own[w] = (uint32_t)__popc(kept >> (8 * w) & 15u) | (2 * w + 1 < QPT ? (uint32_t)__popc(kept >> (8 * w + 4) & 15u) << 16 : 0u);
+            incl[w] = own[w];
         }
-        pre[i] = c;
-    }
-    {
+        wave_incl_scan_n(incl);
+#pragma unroll
+        for (int i = 0; i < QPT; ++i) {
+            const uint32_t upto = i & 1 ? incl[i >> 1] >> 16 : incl[i >> 1] & 0xffffu;
+            pre[i] = upto - (i & 1 ? own[i >> 1] >> 16 : own[i >> 1] & 0xffffu);
+            if (lane == 63) cnt[i * kSelWaves + wave] = upto;
+        }
+    } else {
         uint32_t incl[QPT];
 #pragma unroll
-        for (int i = 0; i < QPT; ++i) incl[i] = pre[i];
+        for (int i = 0; i < QPT; ++i) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                c += key[i][j] > T ? 1u : 0u;
+                c += key[i][j] == T ? 0x10000u : 0u;
+            }
+            pre[i] = incl[i] = c;
+        }
         wave_incl_scan_n(incl);
 #pragma unroll
         for (int i = 0; i < QPT; ++i) {
@@ -622,21 +764,20 @@ void select_topk_reg_kernel(const SelParams p)
     // every wave scans the (step, wave) totals itself (at most 128 of them, two per lane) and picks
     // the offsets of its own QPT steps: no further barrier
     constexpr int NC = kSelWaves * QPT;
-    uint32_t step_off[QPT];                 // keys > T | == T << 16 before this wave's part of step i
-    uint32_t eq_total;
+    uint32_t step_off[QPT];                 // the same before this wave's part of step i
     {
+        const uint32_t ahead = all_ties ? (head_tot & 0xffffu) + (head_tot >> 16) : head_tot;
         uint32_t v[2] = {lane < NC ? cnt[lane] : 0u, 64 + lane < NC ? cnt[64 + lane] : 0u};
         uint32_t sc[2] = {v[0], v[1]};
         wave_incl_scan_n(sc);
         const uint32_t tot0 = (uint32_t)__builtin_amdgcn_readlane((int)sc[0], 63);
-        const uint32_t ex0 = sc[0] - v[0] + head_tot, ex1 = sc[1] - v[1] + tot0 + head_tot;
+        const uint32_t ex0 = sc[0] - v[0] + ahead, ex1 = sc[1] - v[1] + tot0 + ahead;
 #pragma unroll
         for (int i = 0; i < QPT; ++i) {
             const int e = i * kSelWaves + wave_u;
             step_off[i] = e < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)ex0, e)
                                  : (uint32_t)__builtin_amdgcn_readlane((int)ex1, e - 64);
         }
-        eq_total = (head_tot + tot0 + (uint32_t)__builtin_amdgcn_readlane((int)sc[1], 63)) >> 16;
     }
 
     // ---- stable compaction
@@ -646,9 +787,6 @@ void select_topk_reg_kernel(const SelParams p)
         if (sel) out[gt_before + min(eq_before, krem)] = c0 + tid;
         if (mrow) mrow[c0 + tid] = sel ? 1 : 0;
     }
-    // Common case: every key equal to T is kept (no tie is cut, e.g. T is unique).  A key is then
-    // selected iff it is >= T and its slot is the count of such keys before it.
-    const bool ties_all_kept = (int)eq_total <= krem;
     // the quads' mask bytes go out as one 4-byte store where the mask tensor is aligned like that
     const bool mask_dwords = mrow && (((uint32_t)(uintptr_t)(mrow + c0 + nhead)) & 3u) == 0;
     // The comparisons of the counting pass are made again here, against a copy of T the compiler
@@ -661,15 +799,15 @@ void select_topk_reg_kernel(const SelParams p)
         const int x0 = 4 * (i * kSelThreads + tid);
         const uint32_t before = step_off[i] + pre[i];
         uint32_t mbytes = 0;
-        if (ties_all_kept) {
-            int pos = (int)(before & 0xffffu) + (int)(before >> 16);
+        if (all_ties) {
+            uint32_t pos = 4u * before;                          // in bytes
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool sel = key[i][j] >= Tc;                             // never true for an empty slot
-                if (sel) out[pos] = c0 + nhead + x0 + j;
-                pos += sel ? 1 : 0;
-                mbytes |= sel ? (1u << (8 * j)) : 0u;
+                const bool sel = key[i][j] >= Tc;
+                if (sel) *(int32_t *)((uint8_t *)out + pos) = c0 + nhead + x0 + j;
+                pos += sel ? 4u : 0u;
             }
+            mbytes = (kept >> (4 * i) & 15u) * 0x00204081u & 0x01010101u;     // bit j to byte j
         } else {
             int gt_before = (int)(before & 0xffffu), eq_before = (int)(before >> 16);
 #pragma unroll

@@ -817,6 +817,31 @@ def test_select_exact_in_every_register_variant(n):
     _select_case(s, lens, [n // 4, 1, 5], cand=([7, 0, 1], [n - 5, 1, n // 3 - 1]))
 
 
+@pytest.mark.parametrize("kind", ["above", "below", "equal", "one bin", "one bin, many"])
+@pytest.mark.parametrize("n", [4097, 8193, 20606, 32767, 32768])
+def test_select_register_rows_that_their_sample_misjudges(n, kind):
+    """Rows of 4097 to 32768 keys bracket the threshold by 1024 of their scores.  Here those say nothing about
+    the others: all above or below them, all equal, or in one bin of the histogram with many keys that differ."""
+    rng = np.random.default_rng(n)
+    tid = np.arange(1024)
+    at = (tid // 2) * n // 512 + 4 * (tid % 2)
+    s = rng.random((3, n))
+    if kind == "above":
+        s[:, at] += 2.0
+    elif kind == "below":
+        s[:, at] -= 2.0
+    elif kind == "equal":
+        s[:, at] = 0.5
+    elif kind == "one bin":
+        s = 1.0 + s * 1e-4
+        s[:, at[::7]] = 1e30
+    else:
+        s = np.where(rng.random((3, n)) < 0.5, 1.0 + s * 1e-4, s)
+    s = s.astype(np.float32).astype(np.float64)
+    for k in (1, 2, n // 100, n // 4, n // 2, n - 1, n):
+        _select_case(s, [n], [k], rel_tie=-1)
+
+
 def _score_row(rng, kind, n):
     """Score distributions that stress the threshold search: its probes interpolate on the key value."""
     if kind == 0:
