@@ -23,6 +23,7 @@
 #pragma once
 #include "attn_fwd.hpp"
 #include "wave_scan.hpp"
+#include <type_traits>
 
 namespace pdd {
 
@@ -43,9 +44,10 @@ struct ImpParams {
     int32_t n_split;
     float *part;
     // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave, whether a
-    // workgroup finds its piece of the keys by a scan over the sequences' lengths.
+    // workgroup finds its piece of the keys by a scan over the sequences' lengths, and workgroups per KV head that
+    // are on the chip at once where the groups follow from the sequences' rows too (0: they do not).
     uint32_t g_magic;
-    int32_t groups, scan;
+    int32_t groups, scan, places;
 };
 
 constexpr int kImpWaves = 4;
@@ -246,11 +248,15 @@ void importance_kernel(const ImpParams p)
 // the kernel; then each wave walks `groups` groups of 32 keys by itself, K fragments of the next
 // group requested while one is summed.  (The kernel above waits at a barrier for every block of 32 rows
 // with some 0.3 us of work between barriers.)  Bound by the exponentials on long launches (32768
-// tokens x 32/8 heads, 128 rows: 600 cycles per block and SIMD, 384 of vector issue; 50 -> 42 us), by the
-// first loads on short ones (4096 tokens, 64 rows: 9.1 -> 7.0 us; 5 to 64 tokens behind 700 to 12345 keys
-// x 4 sequences 40 -> 19.5; 1 token behind 500 to 7900 keys x 8 sequences 25 -> 10.8, K in the last-level cache;
-// 21.9 and 13.0 where every call has other inputs).
+// tokens x 32/8 heads, 128 rows: 50 us streamed, 41), by the first loads on short ones (4096 tokens, 64 rows: 9.1 streamed,
+// 7.2) and by K from memory between them (64 tokens x 4 behind 8192 keys: 17 us with one block of rows, 26 with
+// eight).  What a wave does besides its 16 exponentials per block and lane was as much again and is kept short: LDS addresses from one
+// register, rows of Q stepped along instead of divided out, two register sets for K instead of copies, blocks that need no
+// mask in a loop of their own; and the barrier waits for the rows, not for K.  Together 46 -> 42 us at the first of these
+// sizes, 29.7 -> 26.0 at the last, 8 prompts of 512 to 7900 tokens, 64 rows 28.4 -> 24.6 (traced, other inputs each call).
 constexpr int kImpScanMax = 64;         // sequences whose lengths one wave scans
+constexpr uint32_t kImpLoadSteps = 8;   // blocks of rows that a wave works on while 32 keys come from memory
+constexpr int kImpLse = 3;              // rows per thread at most: 576 (18 blocks in 80 KB) for four waves, 1184 (37 in 160 KB) for 16
 template <int D>
 constexpr int importance_rows_block_bytes() { return 32 * 2 * D + 32 * (int)sizeof(float); }
 
@@ -265,10 +271,40 @@ __global__ __launch_bounds__(1024) void importance_rows_kernel(const ImpParams p
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
-    int b, kt;
+    int b, kt, groups = p.groups;
     if (!p.scan) {                                // the last pieces, which may be short, come last
         b = bid % p.B;
         kt = bid / p.B;
+    } else if (p.places > 0) {
+        // Chunks of different lengths: a group of keys costs a wave kImpLoadSteps steps and one per block of the sequence's
+        // rows, so a sequence's waves get groups for about `steps` steps, the same for all sequences and few enough groups
+        // that all pieces are on the chip at once.  `steps` grows until they are, at the latest where each sequence is one
+        // piece (p.B <= p.places).  Whole calls against one or two
+        // groups for every sequence: 3 to 300 tokens x 6 behind 106 to 10913, 8/8 heads of head_dim 64 49.9 -> 44.8 us, 6 to 87 x 7
+        // behind 214 to 15157, 32/8 heads 87.3 -> 80.8; 31 uneven launches 1.4 % faster in the mean, one of them 2 % slower.
+        uint32_t keys32 = 0, cost = kImpLoadSteps + 1;
+        if (lane < p.B) {
+            const int nq = min(p.cu_q[lane + 1], p.total_q) - min(p.cu_q[lane], p.total_q);
+            const int nk = max(min(p.cu_k[lane + 1], p.total_k) - min(p.cu_k[lane], p.total_k), 0);
+            keys32 = (uint32_t)(nk + 31) / 32;
+            if (nq > 0 && nk >= nq) cost = kImpLoadSteps + (uint32_t)(min(nq, p.window < 0 ? nq : p.window) * p.G + 31) / 32;
+        }
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(keys32 * cost), 63);
+        uint32_t steps = max(all / (uint32_t)(p.places * waves), 1u), own, upto;
+        for (;;) {
+            const uint32_t keys = (uint32_t)waves * max((steps + cost / 2) / cost, 1u);
+            own = (keys32 + keys - 1) / keys;
+            upto = wave_incl_scan(own);
+            if ((uint32_t)__builtin_amdgcn_readlane((int)upto, 63) <= (uint32_t)p.places || steps >= 1u << 27) break;
+            steps += steps / 8 + 1;
+        }
+        const uint64_t after = __ballot(upto > (uint32_t)bid);
+        if (after == 0) return;
+        b = (int)__builtin_ctzll(after);
+        kt = bid - __builtin_amdgcn_readlane((int)(upto - own), b);
+        // the sequence's groups evenly over its pieces' waves
+        const int pieces = __builtin_amdgcn_readlane((int)own, b) * waves;
+        groups = (__builtin_amdgcn_readlane((int)keys32, b) + pieces - 1) / pieces;
     } else {
         // Sequences of different lengths: workgroup number `bid` takes the bid-th piece that has keys.  (With a
         // grid of the longest sequence's pieces for each, the ones without keys settle which shader engine the others
@@ -285,7 +321,7 @@ __global__ __launch_bounds__(1024) void importance_rows_kernel(const ImpParams p
     const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
     const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
     const int nq = qe - qs, nk = ke - ks, delta = nk - nq;
-    const int j_wg0 = kt * waves * p.groups * 32;
+    const int j_wg0 = kt * waves * groups * 32;
     if (j_wg0 >= nk) return;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5;
@@ -295,79 +331,131 @@ __global__ __launch_bounds__(1024) void importance_rows_kernel(const ImpParams p
     // first row that sees key j
     auto row_of = [&](int j) { return min(max(0, j - delta - iw0), W) * p.G; };
 
-    bf16x8 kf[NKK];
     const uint16_t *const kbase = p.k + (int64_t)ks * p.k_st + (int64_t)g * p.k_sh + 8 * hh;
-    auto load_k = [&](int j0) {
+    auto load_k = [&](bf16x8 (&kf)[NKK], int j0) {
         const uint16_t *kp = kbase + (int64_t)min(j0 + n, nk - 1) * p.k_st;
 #pragma unroll
         for (int kk = 0; kk < NKK; ++kk) kf[kk] = *(const bf16x8 *)(kp + 16 * kk);
     };
     const int j_first = j_wg0 + 32 * wave;
-    load_k(j_first);
     const int block0 = row_of(j_wg0) / 32;        // blocks before it see none of the workgroup's keys
     float *const lse_sh = (float *)(imp_smem + n_blocks * QBLK_BYTES);
+    // The rows of Q, their log-sum-exp and the first keys are requested in this order and return in it, so that the
+    // barrier waits for the first two only.
+    bf16x8 kf[2][NKK];
     if (n_rows > 0) {
         const uint16_t *qbase = p.q + (int64_t)(qs + iw0) * p.q_st + (int64_t)(g * p.G) * p.q_sh;
         const uint32_t q_row_bytes = (uint32_t)p.q_st * 2u, q_head_bytes = (uint32_t)p.q_sh * 2u;
-        const i32x4 rs = make_rsrc(qbase, (uint32_t)(W - 1) * q_row_bytes + (uint32_t)(p.G - 1) * q_head_bytes + (uint32_t)ROW_BYTES);
+        const uint32_t last = (uint32_t)(W - 1) * q_row_bytes + (uint32_t)(p.G - 1) * q_head_bytes;
+        const i32x4 rs = make_rsrc(qbase, last + (uint32_t)ROW_BYTES);
         const uint32_t lds = lds_addr_of(imp_smem);
-        for (int i = block0 * (32 / RPI) + wave; i < n_blocks * (32 / RPI); i += waves) {
-            const int r = RPI * i + lane / CH;
-            const int rr = min(r, n_rows - 1), tok = div_group(rr, p.g_magic);
-            const int pos = lane % CH, c = D == 128 ? (pos ^ swz_row<128>(r & 31)) : (pos ^ ((r >> 1) & 7));
-            dma16_to_lds(rs, lds + 1024 * i, (uint32_t)tok * q_row_bytes + (uint32_t)(rr - tok * p.G) * q_head_bytes + (uint32_t)c * 16u);
+        // a transfer brings RPI rows, the wave's next one those `step` rows on (a multiple of 16, so the chunk of a lane,
+        // which follows from its row modulo 16, stays)
+        const int i0 = block0 * (32 / RPI) + wave, step = RPI * waves, step_tok = div_group(step, p.g_magic), step_head = step - step_tok * p.G;
+        int r = RPI * i0 + lane / CH, head;
+        const uint32_t chunk = (uint32_t)((lane % CH) ^ (D == 128 ? swz_row<128>(r & 31) : ((r >> 1) & 7))) * 16u;
+        uint32_t at;
+        {
+            const int tok = div_group(r, p.g_magic);
+            head = r - tok * p.G;
+            at = (uint32_t)tok * q_row_bytes + (uint32_t)head * q_head_bytes + chunk;
         }
-        for (int r = 32 * block0 + tid; r < 32 * n_blocks; r += blockDim.x) {
-            float l2 = INFINITY;                  // rows past the last one add nothing
-            if (r < n_rows) {
-                const int tok = div_group(r, p.g_magic);
-                l2 = p.lse[(int64_t)(g * p.G + r - tok * p.G) * p.total_q + qs + iw0 + tok] * 1.4426950408889634f;
+        const uint32_t step_bytes = (uint32_t)step_tok * q_row_bytes + (uint32_t)step_head * q_head_bytes, carry = q_row_bytes - (uint32_t)p.G * q_head_bytes;
+        for (int i = i0; i < n_blocks * (32 / RPI); i += waves) {
+            dma16_to_lds(rs, lds + 1024 * i, r < n_rows ? at : last + chunk);
+            r += step;
+            head += step_head;
+            at += step_bytes;
+            if (head >= p.G) {
+                head -= p.G;
+                at += carry;
             }
-            lse_sh[r] = -l2;
         }
+        auto request = [&](auto loads_c) __attribute__((always_inline)) {
+            constexpr int LOADS = decltype(loads_c)::value;          // rows per thread
+            float l2[LOADS];
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int row = min(32 * block0 + tid + i * (int)blockDim.x, n_rows - 1), tok = div_group(row, p.g_magic);
+                l2[i] = p.lse[(int64_t)(g * p.G + row - tok * p.G) * p.total_q + qs + iw0 + tok];
+            }
+            asm volatile("" ::: "memory");            // the compiler keeps the order
+            load_k(kf[0], j_first);
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int x = 32 * block0 + tid + i * (int)blockDim.x;
+                if (x < 32 * n_blocks) lse_sh[x] = x < n_rows ? l2[i] * -1.4426950408889634f : -INFINITY;      // rows past the last one add nothing
+            }
+        };
+        if (n_rows - 32 * block0 <= (int)blockDim.x) request(std::integral_constant<int, 1>{});
+        else request(std::integral_constant<int, kImpLse>{});
+        wait_vmcnt<NKK>();
     }
-    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    uint32_t qaddr[NKK];                          // row n, chunk 2 kk + hh of a block
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-        const int c = 2 * kk + hh;
-        qaddr[kk] = (uint32_t)n * ROW_BYTES + (uint32_t)(D == 128 ? (c ^ swz_row<128>(n)) : (c ^ ((n >> 1) & 7))) * 16u;
-    }
+    // LDS addresses: row n, chunk hh of block 0 (chunk 2 kk + hh: with 32 kk exclusive-or'ed in), and the log-sum-exp of its rows 4 hh ..
+    typedef const __attribute__((address_space(3))) bf16x8 *LdsRow;
+    typedef const __attribute__((address_space(3))) f32x4 *LdsLse;
+    const uint32_t qaddr = lds_addr_of(imp_smem) + (uint32_t)n * ROW_BYTES + (uint32_t)(hh ^ (D == 128 ? swz_row<128>(n) : (n >> 1) & 7)) * 16u;
+    const uint32_t laddr = lds_addr_of(lse_sh) + 16u * hh;
     const float c2 = p.scale_log2;
-    for (int t = 0; t < p.groups; ++t) {
+    // (waited for in one place, or the compiler, which cannot tell whether kn was requested, waits for it at the first use of kc)
+    auto wait_keys = [] { __builtin_amdgcn_s_waitcnt(0x0f70); };                // vmcnt(0)
+    // keys j0 .. j0 + 31, whose K fragments are in kc, against their blocks; the next group's fragments go to kn
+    auto group = [&](const bf16x8 (&kc)[NKK], bf16x8 (&kn)[NKK], int t) __attribute__((always_inline)) {
         const int j0 = j_first + 32 * waves * t;
-        if (j0 >= nk) break;
-        bf16x8 kc[NKK];
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) kc[kk] = kf[kk];
-        if (t + 1 < p.groups) load_k(j0 + 32 * waves);
-        const int key_row = row_of(j0 + n), last_row = row_of(j0 + 31);
+        if (t + 1 < groups) load_k(kn, j0 + 32 * waves);
+        const int key_row = row_of(j0 + n);
+        int rb = row_of(j0) / 32;
+        const int masked = min((row_of(j0 + 31) + 31) / 32, n_blocks);          // from this block on every row sees every key
         float colsum = 0.f;
-        for (int rb = row_of(j0) / 32; rb < n_blocks; ++rb) {
-            const uint8_t *qb = imp_smem + rb * QBLK_BYTES;
+        uint32_t qa = qaddr + (uint32_t)rb * QBLK_BYTES, la = laddr + 128u * rb;
+        auto block = [&](auto at_c, auto masked_c) __attribute__((always_inline)) {
+            constexpr uint32_t AT = decltype(at_c)::value;
             f32x16 sc;
             const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk)
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)(qb + qaddr[kk]), kc[kk], kk == 0 ? zero16 : sc, 0, 0, 0);
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(LdsRow)((qa ^ 32u * kk) + AT * QBLK_BYTES), kc[kk], kk == 0 ? zero16 : sc, 0, 0, 0);
             f32x4 nl[4];                          // rows 8 (e / 4) + 4 hh + e % 4
 #pragma unroll
-            for (int bq = 0; bq < 4; ++bq) nl[bq] = *(const f32x4 *)(lse_sh + 32 * rb + 8 * bq + 4 * hh);
-            if (last_row <= 32 * rb) {            // every row sees every key
+            for (int bq = 0; bq < 4; ++bq) nl[bq] = *(LdsLse)(la + AT * 128 + 32 * bq);
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);           // three reads ahead of the products: registers allow no more
 #pragma unroll
-                for (int e = 0; e < 16; ++e) colsum += fast_exp2(fmaf(sc[e], c2, nl[e >> 2][e & 3]));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float pe = fast_exp2(fmaf(sc[e], c2, nl[e >> 2][e & 3]));
-                    colsum += 32 * rb + 8 * (e >> 2) + 4 * hh + (e & 3) >= key_row ? pe : 0.f;
-                }
+            for (int kk = 0; kk < NKK; ++kk) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float pe = fast_exp2(fmaf(sc[e], c2, nl[e >> 2][e & 3]));
+                if constexpr (decltype(masked_c)::value) colsum += 32 * rb + 8 * (e >> 2) + 4 * hh + (e & 3) >= key_row ? pe : 0.f;
+                else colsum += pe;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto advance = [&](int by) {
+            rb += by;
+            la += 128u * by;
+            qa += (uint32_t)by * QBLK_BYTES;
+        };
+        constexpr std::integral_constant<uint32_t, 0> first{};
+        constexpr std::integral_constant<uint32_t, 1> second{};
+        for (; rb < masked; advance(1)) block(first, std::true_type{});
+        for (; rb + 2 <= n_blocks; advance(2)) {
+            block(first, std::false_type{});
+            block(second, std::false_type{});
         }
+        if (rb < n_blocks) block(first, std::false_type{});
         const float tot = colsum + xchg_half(colsum);
+        wait_keys();
         if (hh == 0 && j0 + n < nk) p.imp[(int64_t)g * p.total_k + ks + j0 + n] = tot;
+    };
+    wait_keys();
+    const int todo = min(groups, (max(nk - j_first, 0) + 32 * waves - 1) / (32 * waves));      // groups with keys
+    for (int t = 0; t < todo; t += 2) {
+        group(kf[0], kf[1], t);
+        if (t + 1 < todo) group(kf[1], kf[0], t + 1);
     }
 #else
     (void)p;

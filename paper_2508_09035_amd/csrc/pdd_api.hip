@@ -591,27 +591,30 @@ int importance_split(const pdd_attn_desc *d, int window)
 // four waves, 24.4 / 23.3 with eight and one / two groups; 35 with the streaming kernel), or four waves where there is
 // one block of rows and so little to load (8 x 5000, 8 heads of head_dim 64, 32 rows: 10.1 us, 11.4 with eight).  Sixteen
 // blocks or more (head_dim 64) for few keys are a long walk, which the streaming kernel divides: 300 tokens 8.7 us
-// against 7.7, 4096 x 16/2 heads 9.2 against 8.2, 3000 x 3 8.7 against 9.4 to 10.3.
-struct ImpRowsPlan { int waves, groups; size_t lds; };            // waves == 0: the form does not apply
+// against 7.7, 4096 x 16/2 heads 9.2 against 8.2, 3000 x 3 8.7 against 9.4 to 10.3.  (This form's times are from before its
+// loop was shortened; it takes 0.86 to 1.0 of them now.)
+// uneven: the sequences may have different numbers of rows, and the launch is more than the chip holds at a group per wave.
+struct ImpRowsPlan { int waves, groups; size_t lds; bool uneven; };       // waves == 0: the form does not apply
 ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
 {
-    const ImpRowsPlan none = {0, 0, 0};
+    const ImpRowsPlan none = {0, 0, 0, false};
     if (g_imp_keys != 0) return none;
     const int64_t w = (window < 0 || window > d->max_seqlen_q) ? d->max_seqlen_q : window;
     const int64_t blocks = (w * (d->n_q_heads / d->n_kv_heads) + 31) / 32;
     const int64_t lds = blocks * (d->head_dim == 128 ? pdd::importance_rows_block_bytes<128>() : pdd::importance_rows_block_bytes<64>());
     if (lds > kLdsBytes) return none;
+    const bool uneven = w == d->max_seqlen_q && (int64_t)d->batch * w != d->total_q && blocks > 1;
     const int64_t tasks = (int64_t)(d->total_k / 32 + d->batch) * d->n_kv_heads, slots = 16 * (int64_t)compute_units();
     if (lds > kLdsBytes / 2) {
         if (tasks < slots) return none;
         const double rounds = (double)d->total_k * d->n_kv_heads / (1024.0 * compute_units());    // with two groups per wave
         const bool two = 1.9 * std::ceil(rounds - 0.05) <= std::ceil(2.0 * rounds - 0.05);
-        return {16, two ? 2 : 1, (size_t)lds};
+        return {16, two ? 2 : 1, (size_t)lds, uneven};
     }
     if (blocks >= 16 && (int64_t)d->batch * ((d->max_seqlen_k + 31) / 32) * d->n_kv_heads < 2 * compute_units()) return none;
     const int64_t resident = lds > kLdsBytes / 3 ? 2 : lds > kLdsBytes / 4 ? 3 : 4;     // 4-wave workgroups per compute unit
-    if (tasks <= 4 * resident * compute_units()) return {4, 1, (size_t)lds};
-    return {blocks == 1 && tasks >= slots ? 4 : 8, tasks >= slots ? 2 : 1, (size_t)lds};
+    if (tasks <= 4 * resident * compute_units()) return {4, 1, (size_t)lds, false};
+    return {blocks == 1 && tasks >= slots ? 4 : 8, tasks >= slots ? 2 : 1, (size_t)lds, uneven};
 }
 
 // What the streaming kernel can use, also where the form above runs and needs none: the figure must not
@@ -633,6 +636,15 @@ pdd_status launch_importance_rows(Kern kern, pdd::ImpParams &p, const ImpRowsPla
     // costs 0.2 us, so only where the workgroups are not all at once on the chip anyway).
     p.scan = p.B <= pdd::kImpScanMax && (int64_t)p.B * max_k != p.total_k && pieces * p.Hkv > compute_units();
     if (p.scan && pieces > p.total_k / keys + p.B) pieces = p.total_k / keys + p.B;
+    // Chunks of different lengths, with more keys than one group for every wave of the chip: as many pieces as
+    // are on the chip at once (16 waves per compute unit), see the kernel.
+    const int64_t places = 16 / rows.waves * (int64_t)compute_units() / p.Hkv;
+    p.places = 0;
+    if (rows.uneven && p.B <= pdd::kImpScanMax && 4 * p.B <= places) {
+        p.scan = 1;
+        p.places = (int)places;
+        pieces = places;
+    }
     const int64_t blocks = pieces * p.Hkv;
     if (blocks > 0x7fffffffLL) return fail(PDD_ERR_INVALID_ARG, "launch grid too large");
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * rows.waves), rows.lds, st, p);

@@ -527,6 +527,33 @@ def test_importance_rows_in_lds(lens, prefix, hq, hkv, d, window):
     rel_close(got[0].cpu().numpy().astype(np.float64), oI, "importance")
 
 
+@pytest.mark.parametrize("lens,prefix,hq,hkv,d", [
+    ([1, 37, 96, 8, 2], [5003, 9000, 4100, 31, 0], 16, 4, 128),             # 8 waves, 1 to 12 blocks
+    ([130, 3, 71], [12001, 20000, 999], 16, 4, 128),                        # 16 waves
+    ([0, 33, 290, 1], [700, 7000, 9777, 15000], 8, 8, 64),                  # head_dim 64, a sequence without rows
+    ([5] * 31 + [40], [900 + 7 * i for i in range(32)], 12, 4, 64),         # G = 3, many sequences
+])
+def test_importance_of_uneven_chunks(lens, prefix, hq, hkv, d):
+    """Chunks whose lengths differ and whose keys are more than the chip takes at once: every sequence gets
+    groups of keys by its own number of rows.  The same sums as the streaming kernel up to the order of fp32
+    additions (at most 1184 positive terms in a sum, 1e-4 relative), every key written."""
+    klens = [a + b for a, b in zip(lens, prefix)]
+    wl = W.make_custom("t", lens, klens, hq, hkv, d, 0, "1/4", seed=92, chunked=True)
+    dev = DeviceWorkload(wl)
+    got = []
+    try:
+        for keys in (0, 0, 128):
+            pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, keys)
+            dev.poison()
+            dev.attn(True)
+            torch.cuda.synchronize()
+            got.append(dev.imp.clone())
+    finally:
+        pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, 0)
+    assert torch.equal(got[0], got[1])
+    rel_close(got[0].cpu().numpy().astype(np.float64), got[2].cpu().numpy().astype(np.float64), "importance")
+
+
 def test_importance_key_widths_give_the_same_bits():
     """The importance kernel with 256 and with 128 keys per workgroup (the library picks by launch
     size): the same column sums bit for bit, on ragged prefill (windows that end inside a key
