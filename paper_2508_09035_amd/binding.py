@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -44,6 +45,11 @@ class AttnDesc(ctypes.Structure):
     ]
 
 
+# AttnDesc's layout: filling 22 fields of a ctypes structure takes 1.2 us, packing them 0.5
+_DESC = struct.Struct("@8i4P8qfi")
+assert _DESC.size == ctypes.sizeof(AttnDesc)
+
+
 def library_path() -> str:
     return _LIB_PATH
 
@@ -68,6 +74,14 @@ def load_library():
     lib.pdd_prefill_attn_chunked_noalloc.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp]
     lib.pdd_token_importance.restype = ctypes.c_int
     lib.pdd_token_importance.argtypes = [dp, vp, vp, vp, vp, vp, sz, vp]
+    # the same entry points once more (a function object of its own for each lookup by item), for packed descriptors
+    packed = {}
+    for name in ("pdd_prefill_attn", "pdd_prefill_attn_chunked", "pdd_prefill_attn_chunked_noalloc",
+                 "pdd_token_importance"):
+        packed[name] = fn = lib[name]
+        fn.restype = ctypes.c_int
+        fn.argtypes = [vp, *getattr(lib, name).argtypes[1:]]
+    lib.packed = packed
     lib.pdd_select_topk.restype = ctypes.c_int
     lib.pdd_select_topk.argtypes = [vp, i32, i32, i32, vp, vp, i32, vp, vp, vp, vp, i32, vp, vp,
                                     vp, sz, vp]
@@ -117,8 +131,9 @@ def _ptr(t) -> Optional[int]:
 # The calls below spend about as long on the host as the smallest of them on the GPU, so the
 # marshalling takes the short ways: the current stream's handle without a Stream object (1.5 -> 0.3
 # us) where this torch has the function that its own generated code calls for it, a host array's
-# address without numpy's ctypes view (1.2 -> 0.3 us), a descriptor filled by its constructor (8 -> 3 us).
-_np = _current_device = _raw_stream = None
+# address without numpy's ctypes view (1.2 -> 0.3 us), a descriptor that is packed instead of filled field by field (2.5 -> 1.2
+# us for its call's tensors, their strides read once for the descriptor and the check).
+_np = _int32 = _current_device = _raw_stream = None
 
 
 def _load_torch() -> None:
@@ -136,9 +151,10 @@ def _stream() -> Optional[int]:
 
 
 def _numpy():
-    global _np
+    global _np, _int32
     if _np is None:
         import numpy
+        _int32 = numpy.dtype(numpy.int32)
         _np = numpy
     return _np
 
@@ -148,6 +164,11 @@ def _host_i32(a):
     if a is None:
         return None, None
     np = _np or _numpy()
+    if type(a) is np.ndarray and a.dtype is _int32:
+        try:                                                       # a contiguous, writable array that is not empty
+            return a, ctypes.addressof(ctypes.c_int32.from_buffer(a))
+        except (TypeError, ValueError, BufferError):
+            pass
     arr = np.ascontiguousarray(a, dtype=np.int32)
     if arr.flags.writeable and arr.size:
         return arr, ctypes.addressof(ctypes.c_int32.from_buffer(arr))
@@ -171,6 +192,35 @@ def make_desc(q, k, v, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q: int, max_seq
     return d, (qh, kh)
 
 
+_NOT_ON_GPU = "tensors must live on the GPU with a contiguous last axis"
+
+
+def _packed_desc(q, k, v, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k, softmax_scale,
+                 window, cu_seqlens_q_host, cu_seqlens_k_host):
+    """Check the tensors of an attention call and describe them as make_desc does.  Returns (what to pass as the
+    descriptor, keepalive)."""
+    sq, sk = q.stride(), k.stride()
+    sv = (0, 0, 1) if v is None else v.stride()
+    so = (0, 0, 1) if o is None else o.stride()
+    if not (q.is_cuda and k.is_cuda and sq[-1] == 1 and sk[-1] == 1 and sv[-1] == 1 and so[-1] == 1
+            and (v is None or v.is_cuda) and (o is None or o.is_cuda)):
+        raise ValueError(_NOT_ON_GPU)
+    _check_tensors(lse, importance)
+    try:
+        qh, qh_addr = _host_i32(cu_seqlens_q_host)
+        kh, kh_addr = _host_i32(cu_seqlens_k_host)
+        total_q, n_q_heads, head_dim = q.shape[:3]
+        total_k, n_kv_heads = k.shape[:2]
+        return _DESC.pack(cu_seqlens_q.numel() - 1, n_q_heads, n_kv_heads, head_dim, total_q, total_k,
+                          int(max_seqlen_q), int(max_seqlen_k), cu_seqlens_q.data_ptr(), cu_seqlens_k.data_ptr(),
+                          qh_addr or 0, kh_addr or 0, sq[0], sq[1], sk[0], sk[1], sv[0], sv[1], so[0], so[1],
+                          float(softmax_scale), int(window)), (qh, kh)
+    except (struct.error, OverflowError, IndexError):              # a value beyond its field
+        desc, keep = make_desc(q, k, v, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k, softmax_scale,
+                               window, cu_seqlens_q_host, cu_seqlens_k_host)
+        return ctypes.byref(desc), (desc, keep)
+
+
 def workspace_bytes(desc: AttnDesc, which_call: int) -> int:
     return int(load_library().pdd_workspace_bytes(ctypes.byref(desc), which_call))
 
@@ -178,7 +228,7 @@ def workspace_bytes(desc: AttnDesc, which_call: int) -> int:
 def _check_tensors(*ts):
     for t in ts:
         if t is not None and (not t.is_cuda or t.stride(-1) != 1):
-            raise ValueError("tensors must live on the GPU with a contiguous last axis")
+            raise ValueError(_NOT_ON_GPU)
 
 
 def prefill_attn(q, k, v, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
@@ -186,11 +236,10 @@ def prefill_attn(q, k, v, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_se
                  cu_seqlens_k_host=None, workspace=None):
     """pdd_prefill_attn: writes o (bf16), lse (fp32 [Hq,total_q]) and, when
     window > 0, importance (fp32 [Hkv,total_k])."""
-    _check_tensors(q, k, v, o, lse, importance)
-    desc, keep = make_desc(q, k, v, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k,
-                           softmax_scale, window, cu_seqlens_q_host, cu_seqlens_k_host)
-    _check(load_library().pdd_prefill_attn(
-        ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(importance),
+    desc, keep = _packed_desc(q, k, v, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k,
+                              softmax_scale, window, cu_seqlens_q_host, cu_seqlens_k_host)
+    _check(load_library().packed["pdd_prefill_attn"](
+        desc, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(importance),
         _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(),
         _stream()))
     del keep
@@ -200,11 +249,10 @@ def prefill_attn_chunked(q_chunk, k_all, v_all, o, lse, importance, cu_seqlens_q
                          max_seqlen_q, max_seqlen_k, softmax_scale=0.0, cu_seqlens_q_host=None,
                          cu_seqlens_k_host=None, workspace=None):
     """pdd_prefill_attn_chunked: new query chunk vs KV prefix + chunk."""
-    _check_tensors(q_chunk, k_all, v_all, o, lse, importance)
-    desc, keep = make_desc(q_chunk, k_all, v_all, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
-                           max_seqlen_k, softmax_scale, 0, cu_seqlens_q_host, cu_seqlens_k_host)
-    _check(load_library().pdd_prefill_attn_chunked(
-        ctypes.byref(desc), _ptr(q_chunk), _ptr(k_all), _ptr(v_all), _ptr(o), _ptr(lse),
+    desc, keep = _packed_desc(q_chunk, k_all, v_all, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
+                              max_seqlen_k, softmax_scale, 0, cu_seqlens_q_host, cu_seqlens_k_host)
+    _check(load_library().packed["pdd_prefill_attn_chunked"](
+        desc, _ptr(q_chunk), _ptr(k_all), _ptr(v_all), _ptr(o), _ptr(lse),
         _ptr(importance), _ptr(workspace),
         0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
     del keep
@@ -214,11 +262,10 @@ def prefill_attn_chunked_noalloc(q_chunk, k_all, v_all, o, lse, importance, cu_s
                                  max_seqlen_q, max_seqlen_k, softmax_scale=0.0, cu_seqlens_q_host=None,
                                  cu_seqlens_k_host=None):
     """pdd_prefill_attn_chunked_noalloc: the chunked call on the library's built-in scratch."""
-    _check_tensors(q_chunk, k_all, v_all, o, lse, importance)
-    desc, keep = make_desc(q_chunk, k_all, v_all, o, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
-                           max_seqlen_k, softmax_scale, 0, cu_seqlens_q_host, cu_seqlens_k_host)
-    _check(load_library().pdd_prefill_attn_chunked_noalloc(
-        ctypes.byref(desc), _ptr(q_chunk), _ptr(k_all), _ptr(v_all), _ptr(o), _ptr(lse),
+    desc, keep = _packed_desc(q_chunk, k_all, v_all, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
+                              max_seqlen_k, softmax_scale, 0, cu_seqlens_q_host, cu_seqlens_k_host)
+    _check(load_library().packed["pdd_prefill_attn_chunked_noalloc"](
+        desc, _ptr(q_chunk), _ptr(k_all), _ptr(v_all), _ptr(o), _ptr(lse),
         _ptr(importance), _stream()))
     del keep
 
@@ -227,12 +274,10 @@ def token_importance(q, k, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seql
                      max_seqlen_k, softmax_scale=0.0, window=-1, cu_seqlens_q_host=None,
                      cu_seqlens_k_host=None, workspace=None):
     """pdd_token_importance: importance from precomputed lse."""
-    _check_tensors(q, k, lse, importance)
-    desc, keep = make_desc(q, k, None, None, cu_seqlens_q, cu_seqlens_k, max_seqlen_q,
-                           max_seqlen_k, softmax_scale, window, cu_seqlens_q_host,
-                           cu_seqlens_k_host)
-    _check(load_library().pdd_token_importance(
-        ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(lse), _ptr(importance), _ptr(workspace),
+    desc, keep = _packed_desc(q, k, None, None, lse, importance, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k,
+                              softmax_scale, window, cu_seqlens_q_host, cu_seqlens_k_host)
+    _check(load_library().packed["pdd_token_importance"](
+        desc, _ptr(q), _ptr(k), _ptr(lse), _ptr(importance), _ptr(workspace),
         0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
     del keep
 
