@@ -43,11 +43,11 @@ struct ImpParams {
     // fixed order r = 0, 1, ...
     int32_t n_split;
     float *part;
-    // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave, whether a
-    // workgroup finds its piece of the keys by a scan over the sequences' lengths, and workgroups per KV head that
-    // are on the chip at once where the groups follow from the sequences' rows too (0: they do not).
+    int32_t scan;      // whether a workgroup finds its piece of the keys among the sequences' lengths
+    // Only read by importance_rows_kernel: ceil(2^32 / G) (0 where G = 1), 32-key groups per wave, and workgroups per KV
+    // head that are on the chip at once where the groups follow from the sequences' rows too (0: they do not).
     uint32_t g_magic;
-    int32_t groups, scan, places;
+    int32_t groups, places;
 };
 
 constexpr int kImpWaves = 4;
@@ -86,18 +86,39 @@ void importance_kernel(const ImpParams p)
 
     int bid = blockIdx.x;
     const int g = bid % p.Hkv;  bid /= p.Hkv;
-    int row;
-    const int b = sequence_of(bid, p.B, p.n_ktiles * p.n_split, p.turn, row);
-    const int kt = row % p.n_ktiles;
-    const int split = row / p.n_ktiles;
+    constexpr int WKEYS = 32 * KG;               // keys per wave
+    const int tid = threadIdx.x, lane = tid & 63;
+    int b, row, tiles = p.n_ktiles;
+    if (!p.scan) {
+        b = sequence_of(bid, p.B, p.n_ktiles * p.n_split, p.turn, row);
+    } else {
+        // Sequences of different lengths: only slices that exist, those of the sequence with the most window rows, whose walks
+        // are the longest, first.  (With a grid of the longest sequence's slices for each, the empty ones held places that the
+        // others waited for, and a long walk could start last: 4 to 279 new tokens x 4 behind 1468 to 15431 keys, 32/8 heads, whole call
+        // 109.5 -> 88.2 us, 3 to 363 x 8 behind 141 to 12509, 16/2 heads 95.1 -> 83.5.  A launch of few slices pays 0.5 us for it.)
+        const int nq = lane < p.B ? min(p.cu_q[lane + 1], p.total_q) - min(p.cu_q[lane], p.total_q) : 0;
+        const int nk = lane < p.B ? max(min(p.cu_k[lane + 1], p.total_k) - min(p.cu_k[lane], p.total_k), 0) : 0;
+        const int walk = nq > 0 && nk >= nq ? min(nq, p.window < 0 ? nq : p.window) : 0;
+        const int slices = (nk + WKEYS * kImpWaves - 1) / (WKEYS * kImpWaves), own = slices * p.n_split;
+        int before = 0;
+        for (int x = 0; x < p.B; ++x) {
+            const int other = __builtin_amdgcn_readlane(walk, x);
+            before += other > walk || (other == walk && x < lane) ? __builtin_amdgcn_readlane(own, x) : 0;
+        }
+        const uint64_t at = __ballot(bid >= before && bid < before + own);
+        if (at == 0) return;
+        b = (int)__builtin_ctzll(at);
+        row = bid - __builtin_amdgcn_readlane(before, b);
+        tiles = __builtin_amdgcn_readlane(slices, b);
+    }
+    const int kt = row % tiles;
+    const int split = row / tiles;
 
     const int qs = min(p.cu_q[b], p.total_q), qe = min(p.cu_q[b + 1], p.total_q);
     const int ks = min(p.cu_k[b], p.total_k), ke = min(p.cu_k[b + 1], p.total_k);
     const int nq = qe - qs, nk = ke - ks;
-    constexpr int WKEYS = 32 * KG;               // keys per wave
     const int j_wg0 = kt * (WKEYS * kImpWaves);
     if (j_wg0 >= nk) return;
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5;
     const int delta = nk - nq;

@@ -571,9 +571,31 @@ int importance_split(const pdd_attn_desc *d, int window)
         const double rounds = (double)((wgs * r + slots - 1) / slots);
         return rounds * ((double)((items + r - 1) / r) + 6.0) + (r > 1 ? 3.0 : 0.0);
     };
-    int best = 1;
-    for (int r = 2; r <= 8 && items / r >= 4; ++r)
-        if (cost(r) < (best == 1 ? 0.85 * cost(1) : cost(best))) best = r;
+    const bool even = (int64_t)d->batch * d->max_seqlen_k == d->total_k && (w < d->max_seqlen_q || (int64_t)d->batch * w == d->total_q);
+    // Sequences of different lengths: the longest walk over the row blocks, or what all slices take of the chip's places at
+    // the mean window (only slices with keys are launched).  By the rule above, which takes every sequence for the longest
+    // one, the walks stayed whole: 1 to 383 tokens x 6 behind 314 to 10880 keys, 16/2 heads 105 us, 68 divided; 6 to 315 x 7 behind
+    // 117 to 2169, 32/8 heads 58.9 and 48.0; 277 tokens and seven sequences of few, where the long walk has few keys, 82.5 and 83.9.
+    const double mean_rows = std::fmin((double)w, (double)d->total_q / d->batch);
+    const double mean_items = (double)(d->n_q_heads / d->n_kv_heads) * std::fmax(mean_rows / 32.0, 1.0);
+    const int64_t by_keys = d->total_k / pdd::kImpBK + d->batch, by_longest = n_ktiles * d->batch;
+    const double real_wgs = (double)(by_keys < by_longest ? by_keys : by_longest) * d->n_kv_heads;
+    auto cost_uneven = [&](int r) {
+        return std::fmax((double)((items + r - 1) / r) + 6.0, real_wgs * r / slots * (mean_items / r + 6.0)) + (r > 1 ? 3.0 : 0.0);
+    };
+    auto best_of = [&](auto &&cost) {
+        int best = 1;
+        for (int r = 2; r <= 8 && items / r >= 4; ++r)
+            if (cost(r) < (best == 1 ? 0.85 * cost(1) : cost(best))) best = r;
+        return best;
+    };
+    int best = best_of(cost);
+    if (!even) {
+        // (the built-in scratch holds what the even rule would ask for or this)
+        const int64_t bytes = (int64_t)d->n_kv_heads * d->total_k * (int64_t)sizeof(float), fits = bytes > 0 ? PDD_STATIC_SCRATCH_BYTES / bytes : 8;
+        const int uneven = best_of(cost_uneven);
+        best = uneven <= best || uneven <= fits ? uneven : best > fits ? best : (int)fits;
+    }
     return best;
 }
 
@@ -667,7 +689,6 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.window = window;
     p.turn = pdd::rows_per_turn(p.Hkv);
     p.scale_log2 = scale_log2(d);
-    p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
     // the row split needs room for its partial sums; without it the single-pass form runs.  Scratch that
     // it could not use for its address is refused whichever form runs.
@@ -684,7 +705,6 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     }
     p.n_split = split ? importance_split(d, window) : 1;
     p.part = split ? (float *)workspace : nullptr;
-    int64_t blocks = (int64_t)p.n_ktiles * d->batch * d->n_kv_heads * p.n_split;
     // Up to four workgroups per compute unit the launch runs with half the keys per workgroup
     // (one 32-key group per wave instead of two): the same blocks of rows per workgroup at half
     // the work per block, and a workgroup's time is mostly its chain of blocks.  Measured against
@@ -692,12 +712,15 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     // the batch of 8 mixed prompts (768 -> 1536), equal on the 32k-token prompt (1024 -> 2048);
     // beyond that the wide form re-reads the window rows half as often.  Same bits either way.
     // (Counted in workgroups that have keys: the grid is sized for the longest sequence.)
+    // sequences of different lengths: only slices that exist, see the kernel
+    p.scan = p.B <= pdd::kImpScanMax && (int64_t)p.B * d->max_seqlen_k != p.total_k;
     const int64_t working = (int64_t)d->total_k / pdd::kImpBK * d->n_kv_heads * p.n_split;
     const bool narrow = g_imp_keys ? g_imp_keys == pdd::kImpBK / 2 : working <= 4 * (int64_t)compute_units();
-    if (narrow) {
-        p.n_ktiles = (d->max_seqlen_k + pdd::kImpBK / 2 - 1) / (pdd::kImpBK / 2);
-        blocks = (int64_t)p.n_ktiles * d->batch * d->n_kv_heads * p.n_split;
-    }
+    const int keys = narrow ? pdd::kImpBK / 2 : pdd::kImpBK;
+    p.n_ktiles = (d->max_seqlen_k + keys - 1) / keys;
+    int64_t slices = (int64_t)p.n_ktiles * d->batch;
+    if (p.scan && slices > p.total_k / keys + p.B) slices = p.total_k / keys + p.B;
+    const int64_t blocks = slices * d->n_kv_heads * p.n_split;
     if (blocks > 0x7fffffffLL) return fail(PDD_ERR_INVALID_ARG, "launch grid too large");
     const dim3 grid((unsigned)blocks), block(pdd::kImpWaves * 64);
     if (d->head_dim == 128) {

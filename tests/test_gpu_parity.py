@@ -507,6 +507,9 @@ def test_importance_with_and_without_scratch(name):
     ([64, 20, 3], [3, 2500, 9990], 128, 16, 128, -1),
     ([17, 0, 5, 40], [900, 70, 5000, 1500], 32, 8, 64, -1),
     ([1] * 63 + [9, 3], list(range(65)), 32, 8, 64, -1),          # 65 sequences: more than are looked up
+    # the streaming kernel over sequences of different lengths: slices looked up, rows divided; 65 sequences: not looked up
+    ([3, 200, 0, 31], [4000, 500, 100, 77], 16, 4, 128, -1),
+    ([2] * 62 + [170, 0, 9], list(range(65)), 16, 2, 128, -1),
     ([300], None, 16, 2, 64, 64),                                 # 16 blocks of rows for few keys: the streaming kernel
 ])
 def test_importance_rows_in_lds(lens, prefix, hq, hkv, d, window):
