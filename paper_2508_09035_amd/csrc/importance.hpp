@@ -277,7 +277,7 @@ void importance_kernel(const ImpParams p)
 // sizes, 29.7 -> 26.0 at the last, 8 prompts of 512 to 7900 tokens, 64 rows 28.4 -> 24.6 (traced, other inputs each call).
 constexpr int kImpScanMax = 64;         // sequences whose lengths one wave scans
 constexpr uint32_t kImpLoadSteps = 8;   // blocks of rows that a wave works on while 32 keys come from memory
-constexpr int kImpLse = 3;              // rows per thread at most: 576 (18 blocks in 80 KB) for four waves, 1184 (37 in 160 KB) for 16
+constexpr int kImpLse = 3;              // rows per thread at most: 608 (19 blocks of head_dim 64 in 80 KB) for four waves, 1216 (38 in 160 KB) for 16
 template <int D>
 constexpr int importance_rows_block_bytes() { return 32 * 2 * D + 32 * (int)sizeof(float); }
 

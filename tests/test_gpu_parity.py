@@ -539,7 +539,7 @@ def test_importance_rows_in_lds(lens, prefix, hq, hkv, d, window):
 def test_importance_of_uneven_chunks(lens, prefix, hq, hkv, d):
     """Chunks whose lengths differ and whose keys are more than the chip takes at once: every sequence gets
     groups of keys by its own number of rows.  The same sums as the streaming kernel up to the order of fp32
-    additions (at most 1184 positive terms in a sum, 1e-4 relative), every key written."""
+    additions (at most 1216 positive terms in a sum, 1e-4 relative), every key written."""
     klens = [a + b for a, b in zip(lens, prefix)]
     wl = W.make_custom("t", lens, klens, hq, hkv, d, 0, "1/4", seed=92, chunked=True)
     dev = DeviceWorkload(wl)
