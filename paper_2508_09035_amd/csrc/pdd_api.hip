@@ -566,7 +566,7 @@ int importance_split(const pdd_attn_desc *d, int window)
     const int64_t n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     const int64_t wgs = n_ktiles * d->batch * d->n_kv_heads;
     const int w = (window < 0 || window > d->max_seqlen_q) ? d->max_seqlen_q : window;
-    const int64_t items = (int64_t)(d->n_q_heads / d->n_kv_heads) * ((w + 31) / 32);
+    const int64_t items = (int64_t)(d->n_q_heads / d->n_kv_heads) * ((w + 31) / 32);        // at whole blocks of a head
     auto cost = [&](int r) {
         const double rounds = (double)((wgs * r + slots - 1) / slots);
         return rounds * ((double)((items + r - 1) / r) + 6.0) + (r > 1 ? 3.0 : 0.0);
@@ -577,23 +577,24 @@ int importance_split(const pdd_attn_desc *d, int window)
     // one, the walks stayed whole: 1 to 383 tokens x 6 behind 314 to 10880 keys, 16/2 heads 105 us, 68 divided; 6 to 315 x 7 behind
     // 117 to 2169, 32/8 heads 58.9 and 48.0; 277 tokens and seven sequences of few, where the long walk has few keys, 82.5 and 83.9.
     const double mean_rows = std::fmin((double)w, (double)d->total_q / d->batch);
-    const double mean_items = (double)(d->n_q_heads / d->n_kv_heads) * std::fmax(mean_rows / 32.0, 1.0);
+    const int64_t longest = ((int64_t)(d->n_q_heads / d->n_kv_heads) * w + 31) / 32;
+    const double mean_items = std::fmax((double)(d->n_q_heads / d->n_kv_heads) * mean_rows / 32.0, 1.0);
     const int64_t by_keys = d->total_k / pdd::kImpBK + d->batch, by_longest = n_ktiles * d->batch;
     const double real_wgs = (double)(by_keys < by_longest ? by_keys : by_longest) * d->n_kv_heads;
     auto cost_uneven = [&](int r) {
-        return std::fmax((double)((items + r - 1) / r) + 6.0, real_wgs * r / slots * (mean_items / r + 6.0)) + (r > 1 ? 3.0 : 0.0);
+        return std::fmax((double)((longest + r - 1) / r) + 6.0, real_wgs * r / slots * (mean_items / r + 6.0)) + (r > 1 ? 3.0 : 0.0);
     };
-    auto best_of = [&](auto &&cost) {
+    auto best_of = [&](auto &&cost, int64_t blocks) {
         int best = 1;
-        for (int r = 2; r <= 8 && items / r >= 4; ++r)
+        for (int r = 2; r <= 8 && blocks / r >= 4; ++r)
             if (cost(r) < (best == 1 ? 0.85 * cost(1) : cost(best))) best = r;
         return best;
     };
-    int best = best_of(cost);
+    int best = best_of(cost, items);
     if (!even) {
         // (the built-in scratch holds what the even rule would ask for or this)
         const int64_t bytes = (int64_t)d->n_kv_heads * d->total_k * (int64_t)sizeof(float), fits = bytes > 0 ? PDD_STATIC_SCRATCH_BYTES / bytes : 8;
-        const int uneven = best_of(cost_uneven);
+        const int uneven = best_of(cost_uneven, longest);
         best = uneven <= best || uneven <= fits ? uneven : best > fits ? best : (int)fits;
     }
     return best;
@@ -687,6 +688,7 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.B = d->batch;  p.Hq = d->n_q_heads;  p.Hkv = d->n_kv_heads;  p.G = d->n_q_heads / d->n_kv_heads;
     p.total_q = d->total_q;  p.total_k = d->total_k;
     p.window = window;
+    p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
     p.turn = pdd::rows_per_turn(p.Hkv);
     p.scale_log2 = scale_log2(d);
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
@@ -696,7 +698,6 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     const bool split = need > 0 && workspace && workspace_bytes >= need;
     if (split && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
     if (const ImpRowsPlan rows = importance_rows(d, window); rows.waves) {
-        p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
         p.groups = rows.groups;
         // the LDS is sized from max_seqlen_q; a longer sequence of the device array keeps to it
         if (window < 0 || window > d->max_seqlen_q) p.window = d->max_seqlen_q;
