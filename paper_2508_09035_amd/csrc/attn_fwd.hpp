@@ -451,7 +451,9 @@ void attn_fwd_kernel(const AttnParams p)
     auto renew = [&](float t_max, f32x16 &blk) {
         const bool up = t_max > thr;
         const float shift = up ? t_max : 0.f;
-        const float alpha = fast_exp2(-shift);
+        // Only a first reference moves down, and then there is nothing to rescale: 2^-shift, which is infinite for scores
+        // below -128, would make NaN of the zeros.
+        const float alpha = fast_exp2(-fmaxf(shift, 0.f));
 #pragma unroll
         for (int i = 0; i < 4; ++i) l_part[i] *= alpha;
 #pragma unroll

@@ -227,7 +227,8 @@ void attn_rows_kernel(const AttnParams p)
         auto renew = [&](float t_max, f32x16 &x) {                    // where a row exceeds its threshold (see attn_fwd_kernel)
             if (!__any(t_max > thr)) return;
             const bool up = t_max > thr;
-            const float shift = up ? t_max : 0.f, alpha = fast_exp2(-shift);
+            const float shift = up ? t_max : 0.f;
+            const float alpha = fast_exp2(-fmaxf(shift, 0.f));        // (a first reference rescales nothing)
 #pragma unroll
             for (int q = 0; q < 4; ++q) l_part[q] *= alpha;
 #pragma unroll

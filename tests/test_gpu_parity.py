@@ -330,6 +330,51 @@ def test_few_rows_over_many_keys(name, d):
     assert all(torch.equal(a, b) for a, b in zip(*bits))
 
 
+_LOW_SHAPES = {         # (new tokens, keys or None for prefill, query heads, KV heads, waves, scratch)
+    "whole prompt": ([70, 500], None, 1, 1, 0, False),
+    "whole chunk": ([1, 40], [200, 300], 4, 2, 0, False),
+    "divided, 32 rows": ([1] * 8, [600 + 777 * i for i in range(8)], 32, 8, 0, True),
+    "divided, 128 rows": ([43, 85, 300], [3043, 5085, 3300], 12, 2, 0, True),
+    "key split": ([6000], None, 2, 1, 0, True),
+    "plain, 4 waves": ([70, 500], None, 2, 1, 4, False),
+    "plain, 8 waves": ([70, 500], None, 2, 1, 8, False),
+    "sweep": ([256, 200], [1256, 900], 4, 2, 8, True),
+}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", list(_LOW_SHAPES))
+def test_logits_far_below_zero(name, d):
+    """Keys that stand against every query: scaled logits near -150, where e^-logit is beyond fp32 before a row has a
+    reference.  All keys; keys 32 to 63 alone; all but a sequence's last one.  Every form, against the oracle."""
+    lens_q, lens_k, hq, hkv, waves, scratch = _LOW_SHAPES[name]
+    window = 32 if lens_k is None else 0
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, d, window, "1/4", seed=760 + d, chunked=lens_k is not None)
+    c = np.sqrt(150.0 / wl.scale / d)                             # of each of the d components
+    wl.q = W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.q) * 0.5 + np.float32(c))
+    ordinary = W.bf16_bits_to_f32(wl.k) * 0.5
+    local = np.concatenate([np.arange(n) for n in wl.seqlens_k])
+    last = np.concatenate([np.arange(n) == n - 1 for n in wl.seqlens_k])
+    rows = np.unique(np.concatenate([np.r_[b, min(b + 40, e - 1), max(b, e - 33):e]
+                                     for b, e in zip(wl.cu_seqlens_q[:-1], wl.cu_seqlens_q[1:])]))
+    try:
+        pdd.set_option(pdd.OPT_ATTN_WAVES, waves)
+        for which, low in (("all", local >= 0), ("a block", (local >= 32) & (local < 64)), ("all but the last", ~last)):
+            wl.k = W.f32_to_bf16_bits(ordinary - np.float32(c) * low[:, None, None])
+            dev = DeviceWorkload(wl)
+            dev.poison()
+            dev.attn(True, use_workspace=scratch)
+            O, lse, imp = dev.results()[:3]
+            oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+            oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, window or -1)
+            assert np.isfinite(O).all() and np.isfinite(lse).all() and np.isfinite(imp).all(), which
+            assert np.abs(O[rows] - oO).max() <= O_ATOL, which
+            rel_close(lse[:, rows], oL, which + " lse")
+            rel_close(imp, oI, which + " importance")
+    finally:
+        pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
+
+
 def test_rows_a_mebibyte_apart_close_to_the_4_gib_span_limit():
     """Q, K and V rows 1 MiB apart (views into 3.1 GiB buffers): byte offsets inside the sequence's
     span run up to 3.4 * 2^30, close to what 32-bit buffer offsets can address; same bits as
