@@ -440,6 +440,15 @@ void attn_rows_kernel(const AttnParams p)
         run(s, rt, 0, s.key_tiles, true, 0);
     } else {
         WorkSeq seqs = work_seq<ROWS>(p, lane);
+        if (bid == 0) {
+            // Tokens before the first sequence or behind the last one, if there are any, are left alone: final for attn_join_kernel,
+            // which would take what the scratch held for their entry.  (Asked there, by every row, a decoding step takes 0.4 us more.)
+            const int begin = min(max(p.cu_q[0], 0), p.total_q), end = min(max(p.cu_q[p.B], begin), p.total_q);
+            for (int x = tid; x < (p.total_q - end + begin) * p.G; x += kRowsWaves * 64) {
+                const int t = x / p.G, tok = t < begin ? t : t - begin + end;
+                p.part_of[(int64_t)tok * p.Hq + g * p.G + x - t * p.G] = make_uint4(0u, 0u, 1u, 0u);
+            }
+        }
         const uint32_t per = work_per<ROWS>(p, seqs, lane);
         WorkPlace before = {0, 0};
         for (int b0 = 0; b0 < p.B; b0 += 64) {
@@ -491,7 +500,7 @@ __global__ __launch_bounds__(256) void attn_join_kernel(const AttnParams p)
     const uint32_t first = __builtin_amdgcn_readfirstlane(of.x), stride = __builtin_amdgcn_readfirstlane(of.y);
     const int pieces = __builtin_amdgcn_readfirstlane(of.z);
     if (pieces == 1) return;                          // the first kernel's result is final
-    // (a token of no sequence has no entry)
+    // (lengths that are none have no entries)
     if (pieces < 0 || pieces > p.workers || first + (uint64_t)max(pieces - 1, 0) * stride >= (uint64_t)p.part_rows * p.Hq) return;
     const int sub = lane / LPR, c = lane % LPR;
     const float *pl = p.part_l + first, *po = p.part_o + (uint64_t)first * D + 4 * c;

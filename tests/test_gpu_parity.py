@@ -330,6 +330,31 @@ def test_few_rows_over_many_keys(name, d):
     assert all(torch.equal(a, b) for a, b in zip(*bits))
 
 
+@pytest.mark.parametrize("d,name", [(128, "chunks"), (64, "many short")])
+def test_tokens_of_no_sequence_keep_their_outputs(d, name):
+    """Lengths on the device that begin behind the first tokens and end before the last ones, on the scratch of a call
+    whose lengths covered all: the outputs of tokens outside stay as they are, the others are the earlier call's."""
+    lens_q, lens_k, hq, hkv, _ = _ROWS_SHAPES[name]
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, d, 0, "1/4", seed=740 + d, chunked=True)
+    dev = DeviceWorkload(wl)
+    dev.attn(False)
+    torch.cuda.synchronize()
+    want = dev.o.clone(), dev.lse.clone()
+    first, end = lens_q[0], wl.total_q - lens_q[-1]
+    for cu, lens in ((dev.cu_q, lens_q), (dev.cu_k, lens_k)):
+        cu[0] = lens[0]                                           # the first sequence is empty
+        cu[-1] -= lens[-1]                                        # and so is the last one
+    dev.o.fill_(7.0)
+    dev.lse.fill_(7.0)
+    dev.attn(False, host_cu=False)
+    torch.cuda.synchronize()
+    for rest in (slice(0, first), slice(end, None)):
+        assert (dev.o[rest] == 7.0).all() and (dev.lse[:, rest] == 7.0).all()
+    # (the pieces may be others, whose probabilities round to bf16 at other places)
+    assert (dev.o[first:end].float() - want[0][first:end].float()).abs().max() <= O_ATOL
+    assert torch.allclose(dev.lse[:, first:end], want[1][:, first:end], rtol=REL)
+
+
 _LOW_SHAPES = {         # (new tokens, keys or None for prefill, query heads, KV heads, waves, scratch)
     "whole prompt": ([70, 500], None, 1, 1, 0, False),
     "whole chunk": ([1, 40], [200, 300], 4, 2, 0, False),
