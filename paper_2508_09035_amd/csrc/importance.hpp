@@ -173,9 +173,12 @@ void importance_kernel(const ImpParams p)
             qrow_l[ci] = r;
             qvoff[ci] = (uint32_t)c * 16u;
         }
-        // Blocks are requested and worked on in order, so a lane's rows are stepped along by 32: one division each here,
-        // none per block.  Rows past the last one are the last one again.
-        const int row0 = 32 * (rb_first + item0), step_tok = div_group(32, p.g_magic), step_head = 32 - step_tok * p.G;
+        // Blocks are requested and worked on in order, so a lane's rows are stepped along by 32: one division for the first
+        // of them here, none per block.  Rows past the last one are the last one again.  (There are up to 2^30 rows, and
+        // div_group is exact below 2^32 / G only: it takes the rows from the first token's on, 62 at most where G <= 31.)
+        const int row0 = 32 * (rb_first + item0), tok0 = row0 / p.G, head0 = row0 - tok0 * p.G;
+        auto token_of = [&](int r) { return tok0 + (p.G > 31 ? (head0 + r >= p.G ? 1 : 0) : div_group(head0 + r, p.g_magic)); };
+        const int step_tok = div_group(32, p.g_magic), step_head = 32 - step_tok * p.G;
         const uint32_t q_head_bytes = (uint32_t)p.q_sh * 2u;
         const uint32_t q_step = (uint32_t)step_tok * q_row_bytes + (uint32_t)step_head * q_head_bytes, q_carry = q_row_bytes - (uint32_t)p.G * q_head_bytes;
         const uint32_t q_last = (uint32_t)(nq - 1) * q_row_bytes + (uint32_t)(g * p.G + p.G - 1) * q_head_bytes;
@@ -186,12 +189,12 @@ void importance_kernel(const ImpParams p)
         int q_head[NLD], l_head;
 #pragma unroll
         for (int ci = 0; ci < NLD; ++ci) {
-            const int tok = div_group(row0 + qrow_l[ci], p.g_magic);
+            const int tok = token_of(qrow_l[ci]);
             q_head[ci] = row0 + qrow_l[ci] - tok * p.G;
             q_at[ci] = (uint32_t)(iw0 + tok) * q_row_bytes + (uint32_t)(g * p.G + q_head[ci]) * q_head_bytes;
         }
         {
-            const int tok = div_group(row0 + n, p.g_magic);
+            const int tok = token_of(n);
             l_head = row0 + n - tok * p.G;
             l_at = (uint32_t)(g * p.G + l_head) * l_head_bytes + (uint32_t)(qs + iw0 + tok) * 4u;
         }

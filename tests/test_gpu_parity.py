@@ -627,6 +627,23 @@ def test_importance_of_uneven_chunks(lens, prefix, hq, hkv, d):
     rel_close(got[0].cpu().numpy().astype(np.float64), got[2].cpu().numpy().astype(np.float64), "importance")
 
 
+def test_importance_of_a_very_large_group():
+    """39676 query heads on one KV head: a (token, head) row number times the group's size passes 2^32, and the
+    divided walks over the rows begin in the last heads of a token."""
+    wl = W.make_custom("t", [9], [136], 39676, 1, 64, 0, "1/4", seed=93, gain=1.5, chunked=True)
+    dev = DeviceWorkload(wl)
+    desc, keep = pdd.make_desc(dev.q, dev.k, None, None, dev.cu_q, dev.cu_k, 9, 136, wl.scale, -1)
+    nbytes = pdd.workspace_bytes(desc, pdd.CALL_TOKEN_IMPORTANCE)
+    assert nbytes >= 2 * 136 * 4, "the rows are divided"
+    dev.imp.fill_(float("nan"))
+    lse = torch.from_numpy(oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale)[1]).float().cuda()
+    pdd.token_importance(dev.q, dev.k, lse, dev.imp, dev.cu_q, dev.cu_k, 9, 136, wl.scale, -1,
+                         workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, -1)
+    rel_close(dev.imp.cpu().numpy().astype(np.float64), oI, "importance")
+    del keep
+
+
 def test_importance_key_widths_give_the_same_bits():
     """The importance kernel with 256 and with 128 keys per workgroup (the library picks by launch
     size): the same column sums bit for bit, on ragged prefill (windows that end inside a key
