@@ -560,44 +560,55 @@ int compute_units()
 // for a gain above 15 % (measured: 246 -> 220 us on 4 x 8448 keys x 64 heads x 256 rows, nothing
 // on the 32k-token prompt with its 128 window rows).  It depends only on the descriptor and the
 // device.
-int importance_split(const pdd_attn_desc *d, int window)
+template <typename Cost>
+int best_importance_split(Cost &&cost, int64_t blocks)
+{
+    int best = 1;
+    for (int r = 2; r <= 8 && blocks / r >= 4; ++r)
+        if (cost(r) < (best == 1 ? 0.85 * cost(1) : cost(best))) best = r;
+    return best;
+}
+
+// every sequence taken for the longest one
+int importance_split_even(const pdd_attn_desc *d, int window)
 {
     const int64_t slots = 3 * (int64_t)compute_units();
     const int64_t n_ktiles = (d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK;
     const int64_t wgs = n_ktiles * d->batch * d->n_kv_heads;
     const int w = (window < 0 || window > d->max_seqlen_q) ? d->max_seqlen_q : window;
     const int64_t items = (int64_t)(d->n_q_heads / d->n_kv_heads) * ((w + 31) / 32);        // at whole blocks of a head
-    auto cost = [&](int r) {
+    return best_importance_split([&](int r) {
         const double rounds = (double)((wgs * r + slots - 1) / slots);
         return rounds * ((double)((items + r - 1) / r) + 6.0) + (r > 1 ? 3.0 : 0.0);
-    };
-    const bool even = (int64_t)d->batch * d->max_seqlen_k == d->total_k && (w < d->max_seqlen_q || (int64_t)d->batch * w == d->total_q);
+    }, items);
+}
+
+int importance_split(const pdd_attn_desc *d, int window)
+{
+    const int even = importance_split_even(d, window);
+    const int w = (window < 0 || window > d->max_seqlen_q) ? d->max_seqlen_q : window;
+    if ((int64_t)d->batch * d->max_seqlen_k == d->total_k && (w < d->max_seqlen_q || (int64_t)d->batch * w == d->total_q)) return even;
     // Sequences of different lengths: the longest walk over the row blocks, or what all slices take of the chip's places at
-    // the mean window (only slices with keys are launched).  By the rule above, which takes every sequence for the longest
-    // one, the walks stayed whole: 1 to 383 tokens x 6 behind 314 to 10880 keys, 16/2 heads 105 us, 68 divided; 6 to 315 x 7 behind
+    // the mean window (only slices with keys are launched).  By the rule above the walks stayed whole: 1 to 383 tokens x 6 behind
+    // 314 to 10880 keys, 16/2 heads 105 us, 68 divided; 6 to 315 x 7 behind
     // 117 to 2169, 32/8 heads 58.9 and 48.0; 277 tokens and seven sequences of few, where the long walk has few keys, 82.5 and 83.9.
-    const double mean_rows = std::fmin((double)w, (double)d->total_q / d->batch);
+    const double group = (double)(d->n_q_heads / d->n_kv_heads), slots = 3.0 * compute_units();
+    const double mean_items = std::fmax(group * std::fmin((double)w, (double)d->total_q / d->batch) / 32.0, 1.0);
     const int64_t longest = ((int64_t)(d->n_q_heads / d->n_kv_heads) * w + 31) / 32;
-    const double mean_items = std::fmax((double)(d->n_q_heads / d->n_kv_heads) * mean_rows / 32.0, 1.0);
-    const int64_t by_keys = d->total_k / pdd::kImpBK + d->batch, by_longest = n_ktiles * d->batch;
+    const int64_t by_keys = d->total_k / pdd::kImpBK + d->batch, by_longest = (int64_t)((d->max_seqlen_k + pdd::kImpBK - 1) / pdd::kImpBK) * d->batch;
     const double real_wgs = (double)(by_keys < by_longest ? by_keys : by_longest) * d->n_kv_heads;
-    auto cost_uneven = [&](int r) {
+    const int uneven = best_importance_split([&](int r) {
         return std::fmax((double)((longest + r - 1) / r) + 6.0, real_wgs * r / slots * (mean_items / r + 6.0)) + (r > 1 ? 3.0 : 0.0);
-    };
-    auto best_of = [&](auto &&cost, int64_t blocks) {
-        int best = 1;
-        for (int r = 2; r <= 8 && blocks / r >= 4; ++r)
-            if (cost(r) < (best == 1 ? 0.85 * cost(1) : cost(best))) best = r;
-        return best;
-    };
-    int best = best_of(cost, items);
-    if (!even) {
-        // (the built-in scratch holds what the even rule would ask for or this)
-        const int64_t bytes = (int64_t)d->n_kv_heads * d->total_k * (int64_t)sizeof(float), fits = bytes > 0 ? PDD_STATIC_SCRATCH_BYTES / bytes : 8;
-        const int uneven = best_of(cost_uneven, longest);
-        best = uneven <= best || uneven <= fits ? uneven : best > fits ? best : (int)fits;
-    }
-    return best;
+    }, longest);
+    // (the built-in scratch holds what the rule above would ask for or this)
+    const int64_t bytes = (int64_t)d->n_kv_heads * d->total_k * (int64_t)sizeof(float), fits = bytes > 0 ? PDD_STATIC_SCRATCH_BYTES / bytes : 8;
+    return uneven <= even || uneven <= fits ? uneven : even > fits ? even : (int)fits;
+}
+
+// scratch for the partial sums of that many workgroups to a slice
+size_t importance_split_bytes(const pdd_attn_desc *d, int r)
+{
+    return r > 1 ? (size_t)r * d->n_kv_heads * (size_t)d->total_k * sizeof(float) : 0;
 }
 
 // Whether the importance takes the form with all window rows in LDS, and its launch shape.
@@ -644,8 +655,7 @@ ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
 // change with PDD_OPT_IMPORTANCE_KEYS, which a caller may set after sizing the scratch.
 size_t importance_workspace(const pdd_attn_desc *d, int window)
 {
-    const int r = importance_split(d, window);
-    return r > 1 ? (size_t)r * d->n_kv_heads * (size_t)d->total_k * sizeof(float) : 0;
+    return importance_split_bytes(d, importance_split(d, window));
 }
 
 template <typename Kern>
@@ -692,11 +702,17 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
     p.turn = pdd::rows_per_turn(p.Hkv);
     p.scale_log2 = scale_log2(d);
     if (const char *beyond = importance_limits(d)) return fail(PDD_ERR_UNSUPPORTED, "%s", beyond);
-    // the row split needs room for its partial sums; without it the single-pass form runs.  Scratch that
-    // it could not use for its address is refused whichever form runs.
-    const size_t need = importance_workspace(d, window);
-    const bool split = need > 0 && workspace && workspace_bytes >= need;
-    if (split && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
+    // The row split needs room for its partial sums; where there is less, the rule for even lengths may fit, else the
+    // single-pass form runs.  Scratch that has room for that rule's sums but not its alignment is refused whichever form runs;
+    // other misaligned scratch is left unused.
+    const int even = importance_split_even(d, window);
+    const bool aligned = aligned16(workspace);
+    if (even > 1 && workspace && workspace_bytes >= importance_split_bytes(d, even) && !aligned)
+        return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
+    const size_t room = workspace && aligned ? workspace_bytes : 0;
+    p.n_split = importance_split(d, window);
+    if (importance_split_bytes(d, p.n_split) > room) p.n_split = importance_split_bytes(d, even) > room ? 1 : even;
+    const bool split = p.n_split > 1;
     if (const ImpRowsPlan rows = importance_rows(d, window); rows.waves) {
         p.groups = rows.groups;
         // the LDS is sized from max_seqlen_q; a longer sequence of the device array keeps to it
@@ -704,7 +720,6 @@ pdd_status launch_importance(const pdd_attn_desc *d, const void *q, const void *
         return d->head_dim == 128 ? launch_importance_rows(pdd::importance_rows_kernel<128>, p, rows, d->max_seqlen_k, st)
                                   : launch_importance_rows(pdd::importance_rows_kernel<64>, p, rows, d->max_seqlen_k, st);
     }
-    p.n_split = split ? importance_split(d, window) : 1;
     p.part = split ? (float *)workspace : nullptr;
     // Up to four workgroups per compute unit the launch runs with half the keys per workgroup
     // (one 32-key group per wave instead of two): the same blocks of rows per workgroup at half
@@ -909,7 +924,7 @@ pdd_status pdd_prefill_attn_chunked_noalloc(const pdd_attn_desc *desc, const voi
     if (s) return s;
     // Attention alone needs no scratch, so it takes none of the shared one: such calls may overlap.
     if (!importance) return pdd_prefill_attn_chunked(desc, q_chunk, k_all, v_all, o, lse, nullptr, nullptr, 0, stream);
-    const size_t plain = plain_chunked_workspace(desc);
+    const size_t sweep = sweep_workspace(desc), plain = sweep ? sweep : importance_split_bytes(desc, importance_split_even(desc, -1));
     if (plain > PDD_STATIC_SCRATCH_BYTES)
         return fail(PDD_ERR_WORKSPACE, "this shape wants %zu bytes of scratch, the built-in scratch holds %u "
                     "(use pdd_prefill_attn_chunked with a workspace)", plain, (unsigned)PDD_STATIC_SCRATCH_BYTES);

@@ -644,6 +644,45 @@ def test_importance_of_a_very_large_group():
     del keep
 
 
+@pytest.mark.parametrize("lens,klens,hq,hkv,planes", [
+    ([130, 1, 1, 1, 1], [130, 1, 32, 301, 2501], 32, 8, 1),      # divided for its uneven lengths alone
+    ([3, 1, 3, 1, 130], [3, 32, 303, 2501, 130], 16, 4, 3),      # by three if all were as long as the longest; by four as they are
+])
+def test_importance_scratch_too_small_or_misaligned(lens, klens, hq, hkv, planes):
+    """Scratch that holds what lengths all alike would take is used, or refused if it is misaligned; scratch that only
+    the uneven lengths make use of is not refused."""
+    wl = W.make_custom("t", lens, klens, hq, hkv, 128, 0, "1/4", seed=94, chunked=True)
+    dev = DeviceWorkload(wl)
+    dev.attn(False)
+    desc, keep = pdd.make_desc(dev.q, dev.k, None, None, dev.cu_q, dev.cu_k, dev.max_q, dev.max_k, wl.scale, -1)
+    need, plane = pdd.workspace_bytes(desc, pdd.CALL_TOKEN_IMPORTANCE), hkv * wl.total_k * 4
+    assert need == 4 * plane
+    buf = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+
+    def run(scratch):
+        dev.imp.fill_(float("nan"))
+        buf.fill_(0xFF)
+        pdd.token_importance(dev.q, dev.k, dev.lse, dev.imp, dev.cu_q, dev.cu_k, dev.max_q, dev.max_k, wl.scale, -1,
+                             workspace=scratch)
+        torch.cuda.synchronize()
+        return dev.imp.clone(), bool((buf != 0xFF).any())
+
+    whole, _ = run(None)
+    oI = oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, -1)
+    for size, used in ((need, True), (need - 1, planes > 1), (planes * plane, planes > 1), (planes * plane - 1, False)):
+        got, wrote = run(buf[:size])
+        assert wrote == used, size
+        assert torch.equal(got, whole) or used
+        rel_close(got.cpu().numpy().astype(np.float64), oI, f"importance, {size} bytes")
+        if planes > 1 and size >= planes * plane:
+            with pytest.raises(pdd.PddError, match="aligned"):
+                run(buf[8:8 + size])
+        else:
+            got, wrote = run(buf[8:8 + size])
+            assert torch.equal(got, whole) and not wrote
+    del keep
+
+
 def test_importance_key_widths_give_the_same_bits():
     """The importance kernel with 256 and with 128 keys per workgroup (the library picks by launch
     size): the same column sums bit for bit, on ragged prefill (windows that end inside a key
