@@ -888,6 +888,10 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     if (s) return s;
     s = check_ptrs(q_chunk, k_all, v_all, o, lse);
     if (s) return s;
+    // Scratch that has room for the sweep but not its alignment is refused whichever form runs.
+    const size_t sweep = importance ? sweep_workspace(desc) : 0;
+    const bool sweeps = sweep && workspace && workspace_bytes >= sweep;
+    if (sweeps && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
     const int bm = attn_rows_per_workgroup(desc);
     if (const RowsPlan rows = rows_plan_with(desc, true, workspace, workspace_bytes); rows.rg) {
         s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows, workspace);
@@ -895,10 +899,7 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,
                                  (hipStream_t)stream);
     }
-    const size_t sweep = importance ? sweep_workspace(desc) : 0;
-    if (sweep && workspace && workspace_bytes >= sweep) {
-        if (reinterpret_cast<uintptr_t>(workspace) & 15u)
-            return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
+    if (sweeps) {
         s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, (float *)workspace);
         if (s) return s;
         const int n_slices = (desc->n_q_heads / desc->n_kv_heads) * ((desc->max_seqlen_q + bm - 1) / bm);

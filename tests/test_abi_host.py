@@ -363,6 +363,19 @@ def test_misaligned_scratch_is_refused_for_short_windows_too():
     assert rc == -3 and "aligned" in lib.pdd_last_error().decode()
 
 
+def test_misaligned_scratch_is_refused_for_the_sweep_whichever_form_runs():
+    """Three chunks whose longest fills its query tiles: with aligned scratch their keys are divided, without scratch
+    they take the plain form, and with scratch that holds the sweep, off a 16-byte boundary, the call is refused."""
+    lib = pdd.load_library()
+    d = good_desc()
+    d.batch, d.n_q_heads, d.n_kv_heads, d.head_dim = 3, 16, 2, 64
+    d.total_q, d.max_seqlen_q, d.total_k, d.max_seqlen_k = 1295, 1293, 6341, 2654
+    sweep = 16 * 6 * 6341 * 4                           # per query head, tile of 256 queries, and key
+    rc = lib.pdd_prefill_attn_chunked(ctypes.byref(d), 0x10000, 0x20000, 0x30000, 0x40000, 0x50000, 0x60000,
+                                      0x70008, 2 * sweep, None)
+    assert rc == -3 and "aligned" in lib.pdd_last_error().decode()
+
+
 def test_noalloc_rejects_shapes_beyond_its_scratch():
     """The allocation-free chunked entry point refuses, on the host, a shape whose scratch
     would not fit its built-in 16 MiB array: nothing is launched."""
