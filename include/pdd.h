@@ -147,8 +147,8 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * workspace: as for pdd_prefill_attn, with one more form.  (Few or short
  * chunks take the attention forms that pack the query heads of a group into a
  * row tile and, behind a long prefix, divide its keys over workgroups that leave
- * partial rows in the workspace; the importance then comes from the separate
- * kernel.)
+ * partial rows in the workspace, into fewer pieces where it is smaller than
+ * pdd_workspace_bytes says; the importance then comes from the separate kernel.)
  * Given pdd_workspace_bytes(desc, PDD_CALL_PREFILL_ATTN_CHUNKED) bytes (one
  * float per query head, tile of 128 or 256 queries and key), the importance is
  * taken inside the attention kernel: once a workgroup knows the log-sum-exp of

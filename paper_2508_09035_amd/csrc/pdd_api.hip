@@ -331,11 +331,12 @@ size_t importance_workspace(const pdd_attn_desc *d, int window);
 // 41.5; 7 chunks of 3 to 230 behind 200 to 12700, 16/2 heads 88 | - | 79 | 48; 256 behind 8192, 64/8 heads (243 plain) 240 | - | 190 | 172.
 // (Beyond 100 us the whole form was not once the better one in 250 launches: K and V come once per 32 rows.)
 // The divided forms' scratch of a chunked call stays within the built-in scratch, so that the call without a workspace
-// argument takes the same form where it has importance to return.  Depends on the descriptor and the device only.
+// argument takes the same form where it has importance to return.  Depends on the descriptor, the device and `scratch`, the
+// bytes that there are (a prompt: 0 where the key-split form has no room).
 constexpr int kWholeTiles = 45;
 struct RowsPlan { int rg; int64_t workers; int min_tiles; int64_t part_rows; size_t bytes; };
 
-RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, bool scratch)
+RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
 {
     RowsPlan best = {0, 0, 0, 0, 0};
     if (!packed_rows_fit(d)) return best;
@@ -373,6 +374,7 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, bool scratch)
         }
     }
     if (!chunked || !scratch) return best;
+    const int64_t scratch_bytes = scratch < PDD_STATIC_SCRATCH_BYTES ? (int64_t)scratch : (int64_t)PDD_STATIC_SCRATCH_BYTES;
     for (int rg = 1; rg <= 4; rg += 3) {
         // about one workgroup per compute unit, more where the row tiles alone are half as many
         const int64_t per_head = compute_units() / Hkv > 1 ? compute_units() / Hkv : 1, rows = 32 * rg;
@@ -380,7 +382,7 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, bool scratch)
         const int64_t workers = pairs <= per_head / 2 ? per_head : per_head + pairs;
         const int64_t row_bytes = (int64_t)d->n_q_heads * (d->head_dim + 1) * (int64_t)sizeof(float);
         const int64_t table = total_q * d->n_q_heads * (int64_t)sizeof(uint4);
-        const int64_t room = ((int64_t)PDD_STATIC_SCRATCH_BYTES - table) / row_bytes;
+        const int64_t room = (scratch_bytes - table) / row_bytes;
         if (workers * Hkv > 0x7fffffffLL || room < total_q + (total_q + 3) / 4) continue;
         if ((double)(total_q > pairs ? total_q : pairs) * tiles_max >= 2147483648.0) continue;      // work_per's sums
         const int min_tiles = rg == 1 ? 8 : 4;
@@ -764,17 +766,19 @@ size_t plain_chunked_workspace(const pdd_attn_desc *d)
 // same place, the partial sums of the importance kernel.
 size_t chunked_workspace(const pdd_attn_desc *d)
 {
-    const RowsPlan rows = rows_plan(d, true, true);
+    const RowsPlan rows = rows_plan(d, true, PDD_STATIC_SCRATCH_BYTES);
     if (!rows.rg) return plain_chunked_workspace(d);
     const size_t imp = importance_workspace(d, -1);
     return rows.bytes > imp ? rows.bytes : imp;
 }
 
-// The plan of rows_plan for the scratch that a call is given.
-RowsPlan rows_plan_with(const pdd_attn_desc *d, bool chunked, const void *workspace, size_t workspace_bytes)
+// The plan of rows_plan for the scratch that a chunked call is given.  Scratch that is too small for the plan it would take
+// with all that it asks for still divides the keys, into fewer pieces.
+RowsPlan rows_plan_with(const pdd_attn_desc *d, const void *workspace, size_t workspace_bytes)
 {
-    const RowsPlan rows = rows_plan(d, chunked, true);
-    return rows.bytes == 0 || (workspace && workspace_bytes >= rows.bytes && aligned16(workspace)) ? rows : rows_plan(d, chunked, false);
+    if (!workspace || !aligned16(workspace)) return rows_plan(d, true, 0);
+    const RowsPlan rows = rows_plan(d, true, PDD_STATIC_SCRATCH_BYTES);
+    return workspace_bytes >= rows.bytes ? rows : rows_plan(d, true, workspace_bytes);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device.
@@ -866,7 +870,7 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
     // (a prompt's rows plan takes no scratch; without scratch for the key-split form it is compared with the plain form alone)
     const SplitPlan plan = split_plan(desc);
     const bool room = plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace);
-    const RowsPlan rows = rows_plan(desc, false, room);
+    const RowsPlan rows = rows_plan(desc, false, room ? workspace_bytes : 0);
     if (rows.rg)
         s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows);
     else if (room)
@@ -893,7 +897,7 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     const bool sweeps = sweep && workspace && workspace_bytes >= sweep;
     if (sweeps && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
     const int bm = attn_rows_per_workgroup(desc);
-    if (const RowsPlan rows = rows_plan_with(desc, true, workspace, workspace_bytes); rows.rg) {
+    if (const RowsPlan rows = rows_plan_with(desc, workspace, workspace_bytes); rows.rg) {
         s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows, workspace);
         if (s || !importance) return s;
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,

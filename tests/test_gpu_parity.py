@@ -330,6 +330,34 @@ def test_few_rows_over_many_keys(name, d):
     assert all(torch.equal(a, b) for a, b in zip(*bits))
 
 
+@pytest.mark.parametrize("d,name", [(128, "chunks"), (64, "many short"), (64, "mha")])
+def test_keys_divided_over_less_scratch(d, name):
+    """Scratch smaller than the call asks for: the keys are divided into fewer pieces, down to room for 5/4 partial rows
+    for every row beside the table of the rows' pieces; the bytes behind it are left alone."""
+    lens_q, lens_k, hq, hkv, _ = _ROWS_SHAPES[name]
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, d, 0, "1/4", seed=750 + d, chunked=True)
+    dev = DeviceWorkload(wl)
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale)
+    table, row = wl.total_q * hq * 16, hq * (d + 1) * 4
+    least = table + row * (wl.total_q + (wl.total_q + 3) // 4)
+    assert least < dev.workspace_bytes // 2
+    dev.attn(False, use_workspace=False)
+    torch.cuda.synchronize()
+    plain = dev.o.clone()
+    for size in (dev.workspace_bytes, dev.workspace_bytes - 4, dev.workspace_bytes // 2 // 16 * 16 + 8, least, least - 4):
+        dev.poison()
+        dev.workspace.fill_(0xFF)
+        dev.attn(False, use_workspace=size)
+        O, lse = dev.results()[:2]
+        assert np.abs(O - oO).max() <= O_ATOL, size
+        rel_close(lse, oL, f"lse, {size} bytes")
+        assert (dev.workspace[size:] == 0xFF).all()
+        if size >= dev.workspace_bytes // 2:
+            assert (dev.workspace[:size] != 0xFF).any(), size
+        if size < least:
+            assert torch.equal(dev.o, plain)
+
+
 @pytest.mark.parametrize("d,name", [(128, "chunks"), (64, "many short")])
 def test_tokens_of_no_sequence_keep_their_outputs(d, name):
     """Lengths on the device that begin behind the first tokens and end before the last ones, on the scratch of a call
