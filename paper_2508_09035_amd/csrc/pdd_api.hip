@@ -248,8 +248,8 @@ double plain_attention_us(const pdd_attn_desc *d, int bm)
 }
 
 // Whether the sizes are inside what every form but the plain one can take: the kernels divide a row by G with one 32-bit
-// multiplication and address up to 128 rows of Q with 32-bit byte offsets.
-bool packed_rows_fit(const pdd_attn_desc *d)
+// multiplication and address `rows` rows of Q, 32 or 128, with 32-bit byte offsets.
+bool packed_rows_fit(const pdd_attn_desc *d, int rows)
 {
     // (the scratch query comes here with whatever its caller's descriptor holds)
     if (g_attn_waves != 0 || d->total_q <= 0 || d->total_k <= 0 || d->max_seqlen_q <= 0 || d->max_seqlen_k <= 0 ||
@@ -257,7 +257,7 @@ bool packed_rows_fit(const pdd_attn_desc *d)
         return false;
     const int64_t G = d->n_q_heads / d->n_kv_heads, max_q = d->max_seqlen_q;
     if (G > 65535 || max_q * G >= (1LL << 31) || max_q * G * G >= (1LL << 32)) return false;
-    return d->q_stride_tok < (1LL << 23) && G * d->q_stride_head < (1LL << 30);
+    return rows * d->q_stride_tok < (1LL << 30) && G * d->q_stride_head < (1LL << 30);
 }
 
 // Whether and how the keys of a prompt are split over workgroups (attn_fwd_kernel's SPLIT form).
@@ -272,7 +272,7 @@ bool packed_rows_fit(const pdd_attn_desc *d)
 SplitPlan split_plan(const pdd_attn_desc *d)
 {
     const SplitPlan none = {0, 0, 0, 0.0};
-    if (!packed_rows_fit(d)) return none;
+    if (!packed_rows_fit(d, 32)) return none;
     const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q;
     const double cus = (double)compute_units();
     const int64_t n_qt = (max_q * G + kSplitRows - 1) / kSplitRows;
@@ -339,7 +339,7 @@ struct RowsPlan { int rg; int64_t workers; int min_tiles; int64_t part_rows; siz
 RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
 {
     RowsPlan best = {0, 0, 0, 0, 0};
-    if (!packed_rows_fit(d)) return best;
+    if (!packed_rows_fit(d, 32)) return best;
     const int64_t G = d->n_q_heads / d->n_kv_heads, Hkv = d->n_kv_heads, B = d->batch, max_q = d->max_seqlen_q, total_q = d->total_q;
     if (chunked) {      // the importance kernel has to be able to follow (the sweep has wider limits)
         if (importance_workspace(d, -1) > PDD_STATIC_SCRATCH_BYTES || importance_limits(d)) return best;
@@ -376,6 +376,7 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
     if (!chunked || !scratch) return best;
     const int64_t scratch_bytes = scratch < PDD_STATIC_SCRATCH_BYTES ? (int64_t)scratch : (int64_t)PDD_STATIC_SCRATCH_BYTES;
     for (int rg = 1; rg <= 4; rg += 3) {
+        if (!packed_rows_fit(d, 32 * rg)) continue;
         // about one workgroup per compute unit, more where the row tiles alone are half as many
         const int64_t per_head = compute_units() / Hkv > 1 ? compute_units() / Hkv : 1, rows = 32 * rg;
         const int64_t by_rows = total_q * G / rows + B, by_longest = (max_q * G + rows - 1) / rows * B, pairs = by_rows < by_longest ? by_rows : by_longest;

@@ -428,6 +428,32 @@ def test_logits_far_below_zero(name, d):
         pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
 
 
+@pytest.mark.parametrize("lens_q,lens_k,hq,hkv,scratch", [
+    ([3000], None, 1, 1, True),                              # key split: 32 rows per wave
+    ([40, 200], None, 2, 2, False),                          # whole, 32 rows
+    ([40], [4000], 4, 2, True),                              # divided, 32 rows
+])
+def test_query_rows_sixteen_mebibytes_apart(lens_q, lens_k, hq, hkv, scratch):
+    """Q rows 2^23 elements apart are beyond what 128 rows can address with 32 bits, not what 32 rows can: the forms
+    that address 32 take them, with the bits of the packed layout and not those of the plain form."""
+    wl = W.make_custom("t", lens_q, lens_k, hq, hkv, 64, 0, "1/4", seed=24, chunked=lens_k is not None)
+    dev = DeviceWorkload(wl)
+    packed, far = dev.q, torch.empty_strided((wl.total_q, hq, 64), (1 << 23, 64, 1), dtype=torch.bfloat16, device="cuda")
+    far.copy_(packed)
+    got = []
+    try:
+        for dev.q, waves in ((packed, 4), (packed, 0), (far, 0)):
+            pdd.set_option(pdd.OPT_ATTN_WAVES, waves)
+            dev.poison()
+            dev.attn(False, use_workspace=scratch)
+            torch.cuda.synchronize()
+            got.append((dev.o.clone(), dev.lse.clone()))
+    finally:
+        pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
+    assert not torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[1][0], got[2][0]) and torch.equal(got[1][1], got[2][1])
+
+
 def test_rows_a_mebibyte_apart_close_to_the_4_gib_span_limit():
     """Q, K and V rows 1 MiB apart (views into 3.1 GiB buffers): byte offsets inside the sequence's
     span run up to 3.4 * 2^30, close to what 32-bit buffer offsets can address; same bits as
