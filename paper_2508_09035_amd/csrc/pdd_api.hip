@@ -108,6 +108,8 @@ float scale_log2(const pdd_attn_desc *d)
     return s * 1.4426950408889634f;
 }
 
+constexpr int kLdsBytes = 160 * 1024;    // of a compute unit, and the most one workgroup can have
+
 // The dynamic-LDS limit of a kernel is raised once per (kernel, device), not on every launch.
 pdd_status raise_lds_limit(const void *kern, int bytes)
 {
@@ -131,7 +133,7 @@ template <typename Kern>
 pdd_status launch_attn_kernel(Kern kern, int smem, int threads, const pdd::AttnParams &p, int64_t blocks,
                               hipStream_t st)
 {
-    const pdd_status s = raise_lds_limit(reinterpret_cast<const void *>(kern), smem);
+    const pdd_status s = raise_lds_limit(reinterpret_cast<const void *>(kern), kLdsBytes);      // (launches differ in what they take)
     if (s) return s;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), smem, st, p);
     const hipError_t e = hipGetLastError();
@@ -139,17 +141,17 @@ pdd_status launch_attn_kernel(Kern kern, int smem, int threads, const pdd::AttnP
     return PDD_OK;
 }
 
+// spread: with the LDS of an 8-wave workgroup, so that no more than two share a compute unit
 template <int D, int NW>
-pdd_status launch_attn_t(const pdd::AttnParams &p, int64_t blocks, hipStream_t st)
+pdd_status launch_attn_t(const pdd::AttnParams &p, int64_t blocks, bool spread, hipStream_t st)
 {
     if (p.imp_part)
         return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW, true>, pdd::AttnSmem<D>::SWEEP_BYTES, NW * 64, p, blocks, st);
-    return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW>, pdd::AttnSmem<D>::bytes(NW), NW * 64, p, blocks, st);
+    return launch_attn_kernel(pdd::attn_fwd_kernel<D, NW>, pdd::AttnSmem<D>::bytes(spread ? 8 : NW), NW * 64, p, blocks, st);
 }
 
 int compute_units();
 
-constexpr int kLdsBytes = 160 * 1024;    // of a compute unit, and the most one workgroup can have
 constexpr int kSplitRows = 128;          // packed (token, head) rows per workgroup of the key-split form
 constexpr size_t kSplitWorkspaceMax = (size_t)256 << 20;
 struct SplitPlan { int tiles, n_split; size_t bytes; double us; };        // tiles == 0: the form does not apply; us: its estimate
@@ -187,7 +189,7 @@ int attn_rows_per_workgroup(const pdd_attn_desc *d)
     return nw * 32;
 }
 
-// Prompts of head_dim 64 take 4 waves, three workgroups to a compute unit, at every size: against 8 waves, two to a compute
+// Prompts of head_dim 64 take 4 waves at every size: against 8 waves, two to a compute
 // unit, 16384 tokens x 32/8 heads 1188 -> 1143 us, 8192 x 64/8 630 -> 597, 3000 + 1111 + 6100 x 32/8 253 -> 236, 8000 + 3 x 300 x 8/8
 // 244 -> 205; only where the 8-wave workgroups just fill the chip once do they stay (3500 x 32/8, 448 of 512 places: 75.4
 // against 77.0).  The chunked call keeps the rule above, by which its importance sweep and its scratch are sized.
@@ -196,6 +198,17 @@ int attn_prefill_rows_per_workgroup(const pdd_attn_desc *d)
     if (d->head_dim != 64 || g_attn_waves != 0) return attn_rows_per_workgroup(d);
     const int64_t tiles256 = (int64_t)((d->max_seqlen_q + 255) / 256) * d->batch * d->n_q_heads, slots = 2 * (int64_t)compute_units();
     return 32 * (8 * tiles256 > 6 * slots && tiles256 <= slots ? 8 : 4);
+}
+
+// Whether all query tiles of a call take the chip longer than the longest walk over the keys takes one of them; the sequences but
+// the longest are taken for equally long.  Then three 4-wave workgroups of head_dim 64 share a compute unit (266 launches 1.04 to
+// 1.19 times as fast as 8 waves).  Else no more than two: a long walk is the slower for two neighbours (1456 + 704 + 663 + 615 + 632 + 770 +
+// 3482 + 5753 x 4/2 heads 87 us by threes, 71 by twos and 82 with 8 waves; 574 + 1335 + 7269 + 253 + 801 x 16/2 152, 139 and 139; 440 such prompts 1.04 times
+// as fast by twos as by threes, 0.93 to 1.43, break even where both times are alike).
+bool tiles_fill_the_chip(const pdd_attn_desc *d)
+{
+    const double cus = (double)compute_units(), longest = d->max_seqlen_q, others = d->batch - 1.0, mean = others > 0 ? (d->total_q - longest) / others : 0.0;
+    return d->n_q_heads * (longest * longest + others * mean * mean) >= 512.0 * cus * longest;      // tiles of 256 rows, half their walk
 }
 
 // Chunked mode can take the token importance from a second sweep inside the
@@ -480,8 +493,8 @@ pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void
         return d->head_dim == 128 ? launch_attn_split<128>(p, n, st) : launch_attn_split<64>(p, n, st);
     }
     if (d->head_dim == 128)
-        return nw == 8 ? launch_attn_t<128, 8>(p, blocks, st) : launch_attn_t<128, 4>(p, blocks, st);
-    return nw == 8 ? launch_attn_t<64, 8>(p, blocks, st) : launch_attn_t<64, 4>(p, blocks, st);
+        return nw == 8 ? launch_attn_t<128, 8>(p, blocks, false, st) : launch_attn_t<128, 4>(p, blocks, false, st);
+    return nw == 8 ? launch_attn_t<64, 8>(p, blocks, false, st) : launch_attn_t<64, 4>(p, blocks, !tiles_fill_the_chip(d), st);
 }
 
 template <int QPT>
