@@ -310,7 +310,7 @@ SplitPlan split_plan(const pdd_attn_desc *d)
     n_split = (tiles_max + tiles - 1) / tiles;
     if ((double)n_split * base * B >= 2147483647.0) return none;
 
-    const int bm = attn_rows_per_workgroup(d);
+    const int bm = attn_prefill_rows_per_workgroup(d);
     const int64_t n_qt_plain = (max_q + bm - 1) / bm;
     const double fill = (double)max_q / (double)(n_qt_plain * bm);      // rows in use of the plain form's tiles
     const double work = (double)n_qt_plain * d->n_q_heads * tiles_all * seen / cus;

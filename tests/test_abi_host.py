@@ -329,6 +329,20 @@ def test_prompts_that_would_lose_by_splitting_their_keys_do_not():
         assert (lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_PREFILL_ATTN) > 0) == splits, (heads, kv, lens)
 
 
+def test_head_dim_64_prompts_are_priced_in_the_form_that_would_run():
+    """Keys are not split where the 4-wave workgroups that head_dim 64 takes are faster (the split was 1.03 to 1.5
+    times slower on these); one long prompt of two heads still splits them."""
+    lib = pdd.load_library()
+    d = good_desc()
+    d.head_dim, d.window = 64, 0
+    for heads, kv, lens, splits in ((8, 8, [357, 5137], False), (8, 8, [951, 4561], False),
+                                    (4, 2, [2864, 521, 596, 1545, 4420], False), (2, 1, [6000], True)):
+        d.batch, d.n_q_heads, d.n_kv_heads = len(lens), heads, kv
+        d.total_q = d.total_k = sum(lens)
+        d.max_seqlen_q = d.max_seqlen_k = max(lens)
+        assert (lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_PREFILL_ATTN) > 0) == splits, (heads, kv, lens)
+
+
 def test_workspace_figure_does_not_depend_on_the_importance_option():
     """Scratch sized under one setting of PDD_OPT_IMPORTANCE_KEYS serves a call under another one, for
     windows that the default setting sums without scratch too."""
