@@ -377,12 +377,15 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
         // rounds of the longest walk against what all of them take the chip; a prompt's long row tiles meet long keys
         const double rt = row_tiles(1), walk = std::ceil(tiles_max / 4.0) * (chunked ? (d64 ? 0.73 : 1.33) : (d64 ? 0.615 : 0.97));
         const double tiles = rt * Hkv * seen * (chunked ? 0.4 * tiles_mean + 0.6 * tiles_max : tiles_max) / cus;
-        const double over = std::fmax(rt * Hkv / cus - 1.0, 0.0);
+        // (chunks of head_dim 128: whole rounds, because a workgroup has its compute unit to itself, and the unit waits for workgroups without
+        // a row tile too, 1.5 us each for the first few: 24 to 257 new tokens x 7, 32/8 heads, 20.7 us, plain 14.7; 143 + 8 + 3 x 64/8 12.1 and 8.7)
+        const int64_t blocks = (max_q * G + 31) / 32 * B * Hkv;
+        const double per_cu = rt * Hkv / cus, over = std::fmax((chunked && !d64 && per_cu < 3.0 ? std::ceil(per_cu - 0.03) : per_cu) - 1.0, 0.0);
+        const double empty = chunked && !d64 ? std::fmin(1.5 * std::fmax((double)blocks / cus - per_cu - 0.5, 0.0), 3.0) : 0.0;
         const double all = chunked ? (d64 ? 0.18 * tiles + 3.0 * over : 0.30 * tiles + 4.1 * over) : (d64 ? 0.142 * tiles + 2.14 * over : 0.26 * tiles + 5.55 * over);
         const double est = (chunked ? (d64 ? 4.6 : 5.0) : (d64 ? 5.1 : 6.75)) + std::fmax(walk, all) + 0.3 * std::fmin(walk, all);
-        const int64_t blocks = (max_q * G + 31) / 32 * B * Hkv;
-        if (est < std::fmin(us, 100.0) && blocks <= 0x7fffffffLL) {
-            us = est;
+        if (est + empty < us && est < 100.0 && blocks <= 0x7fffffffLL) {
+            us = est + empty;
             best = {1, 0, 0, 0, 0};
         }
     }
@@ -390,10 +393,17 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
     const int64_t scratch_bytes = scratch < PDD_STATIC_SCRATCH_BYTES ? (int64_t)scratch : (int64_t)PDD_STATIC_SCRATCH_BYTES;
     for (int rg = 1; rg <= 4; rg += 3) {
         if (!packed_rows_fit(d, 32 * rg)) continue;
-        // about one workgroup per compute unit, more where the row tiles alone are half as many
         const int64_t per_head = compute_units() / Hkv > 1 ? compute_units() / Hkv : 1, rows = 32 * rg;
         const int64_t by_rows = total_q * G / rows + B, by_longest = (max_q * G + rows - 1) / rows * B, pairs = by_rows < by_longest ? by_rows : by_longest;
-        const int64_t workers = pairs <= per_head / 2 ? per_head : per_head + pairs;
+        // Workgroups for the pieces.  Few (sequence, row tile) pairs: what is on the chip at once, one to a compute unit (one token x 8 and the like).
+        // Each pair has up to a piece more than its share, so many of them at one round's share run into a second round: then
+        // three rounds of smaller pieces where each sequence is one row tile (41 x 2 tokens behind 113 to 14497 keys, 8/8 heads of 64 83.7 -> 71.7 us,
+        // 19 such launches of 31 and more 1.07 to 1.19 times as fast), two workgroups to a compute unit at head_dim 64 (341 + 10 + 56 + 20 + 1 + 58 behind
+        // 268 to 15973, 32/8 heads 108 -> 89; 73 launches 1.05, 0.94 to 1.31; at shares of fewer than 16 key tiles 0.97), one round up to 0.7 pairs at head_dim 128 with 32 rows (17 launches 1.05).
+        int64_t workers = per_head + pairs;
+        if (2 * pairs <= per_head || (rg == 1 && !d64 && max_q * G > rows && 10 * pairs <= 7 * per_head)) workers = per_head;
+        else if (max_q * G <= rows && pairs <= 2 * per_head) workers = 3 * per_head;
+        else if (max_q * G > rows && d64 && 10 * pairs <= 9 * per_head && row_tiles(rg) * tiles_mean >= 16.0 * per_head) workers = 2 * per_head;
         const int64_t row_bytes = (int64_t)d->n_q_heads * (d->head_dim + 1) * (int64_t)sizeof(float);
         const int64_t table = total_q * d->n_q_heads * (int64_t)sizeof(uint4);
         const int64_t room = (scratch_bytes - table) / row_bytes;
