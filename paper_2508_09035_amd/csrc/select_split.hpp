@@ -12,8 +12,10 @@
 //   select_divided_kernel   The chunks' counts give the threshold's class and bin, the bin's keys (some
 //                           tens) are ranked, and the chunk's indices and mask written.
 // Where the histogram has a bin of many keys, the edges' bins are divided anew: a value that many keys share
-// becomes an edge, whose equals are counted and never listed.  Where the threshold lies outside the edges all the same
-// (one row in a hundred thousand) or its bin holds more than kDivListMax keys, every workgroup searches the row by itself.
+// becomes an edge, whose equals are counted and never listed.  A bin of more than kDivListMax keys (a value between the
+// edges that a twentieth of a long row shares) is read where it lies: if its smallest and largest key are one, that is the
+// threshold, else its digits give it.  Where the threshold lies outside the edges all the same (one row in a hundred
+// thousand), every workgroup searches the row by itself.
 // Bound by the latency of its steps (loads, scans, barriers, launches) up to some 10 rows, by
 // instruction issue beyond.  By a radix search of three digits, a launch for each and one for the output, 8 rows of
 // 131072 candidates took 21.7 us, 16 of 400000 81, 128 of 131072 162; now 16.5, 37.6 and 79 (k = 10 %).  Of the first
@@ -30,7 +32,7 @@ constexpr int kDivSample = kSelThreads;               // keys of the sample, one
 constexpr uint32_t kDivBinMany = 24;                  // keys of the sample in one of its 1024 bins that are no even spread
 constexpr int kDivBins = 256;                         // of the keys between the edges
 constexpr int kDivGroups = kSelThreads / 32;          // half waves of a workgroup
-constexpr int kDivListMax = 12 * kSelThreads;         // keys of one bin that a workgroup ranks
+constexpr int kDivListMax = 12 * kSelThreads;         // keys of one bin that a workgroup ranks in LDS
 
 // What a workgroup leaves in the workspace: its keys above the upper edge `hi`, equal to it, strictly between
 // the edges, equal to the lower one `lo` (0 where lo == hi), 16384 at most.
@@ -326,19 +328,19 @@ __device__ __forceinline__ uint32_t list_key_of_rank(const uint32_t *list, int m
     return fin_T;
 }
 
-// The same threshold without a bracket: the row's keys by four digits of eight bits, read anew for each.
-__device__ __forceinline__ uint32_t row_key_of_rank(const SelRow &r, uint32_t rank, int tid, int lane, int wave)
+// The same threshold without a bracket: keys by four digits of eight bits, read anew for each.  `each` calls its
+// argument with (key, whether the lane has one), all lanes of a wave together.
+template <typename Each>
+__device__ __forceinline__ uint32_t any_key_of_rank(Each &&each, uint32_t rank, int tid, int lane, int wave)
 {
     __shared__ uint32_t hist[256], sh_bin, sh_rank;
     uint32_t prefix = 0;
     for (int shift = 24; shift >= 0; shift -= 8) {
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
-#pragma unroll 4
-        for (int x0 = 0; x0 < r.n; x0 += kSelThreads) {
-            const int x = x0 + tid;
-            const uint32_t k = x < r.n ? order_key(r.cand[x]) : 0u, bin = k >> shift & 255u;
-            const bool part = x < r.n && (shift == 24 || k >> (shift + 8) == prefix);
+        each([&](uint32_t k, bool has) {
+            const uint32_t bin = k >> shift & 255u;
+            const bool part = has && (shift == 24 || k >> (shift + 8) == prefix);
             const uint64_t parts = __ballot(part);
             if (parts) {                                         // the lanes of the first one's bin add as one
                 const int first = __ffsll((unsigned long long)parts) - 1;
@@ -347,7 +349,7 @@ __device__ __forceinline__ uint32_t row_key_of_rank(const SelRow &r, uint32_t ra
                 if (lane == first) atomicAdd(&hist[common], (uint32_t)__popcll(same));
                 if (part && bin != common) atomicAdd(&hist[bin], 1u);
             }
-        }
+        });
         __syncthreads();
         if (wave == 0) {
             const uint4 h = make_uint4(hist[4 * lane], hist[4 * lane + 1], hist[4 * lane + 2], hist[4 * lane + 3]);
@@ -371,7 +373,8 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 
 {
     __shared__ __attribute__((aligned(16))) uint32_t bin_part[kSelWaves][kDivBins], bin_sum[kDivBins], list[kDivListMax];
     __shared__ uint2 bin_own[kDivGroups];              // keys of the bin and of higher ones in a chunk
-    __shared__ uint32_t step_own[kSelWaves * QPT], list_above, list_before;
+    __shared__ uint32_t step_own[kSelWaves * QPT], list_above, list_before, row_count[3];
+    __shared__ uint2 heavy;                            // smallest and largest key of a bin
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = blockIdx.x;
     const SelRow r = split_sel_row<QPT>(p.s, p.n_units);
@@ -459,7 +462,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 
         const uint4 t = *(const uint4 *)&bin_sum[4 * lane];
         const uint32_t next = (uint32_t)__shfl_down((int)t.x, 1, 64), s[5] = {t.x, t.y, t.z, t.w, lane == 63 ? all[2] : next};
         const uint32_t want = kk - all[0] - all[1];
-        uint32_t bin = 0, over = 0;
+        uint32_t bin = 0, over = 0, upto = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint64_t hit = __ballot(all[2] - s[e + 1] < want && want <= all[2] - s[e]);
@@ -467,57 +470,74 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 
                 const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)hit) - 1);
                 bin = (uint32_t)(4 * l + e);
                 over = all[2] - (uint32_t)__builtin_amdgcn_readlane((int)s[e + 1], l);
+                upto = all[2] - (uint32_t)__builtin_amdgcn_readlane((int)s[e], l);
             }
         }
         const bool by_value = div_by_value(bin, (int)binning.y);
         const uint32_t low = binning.x + (bin << binning.y);
-        // its keys from all chunks, in the order of the chunks, a half wave per chunk and kDivGroups of them at a time
-        uint32_t total = 0, own_at = 0, higher = 0;              // `higher`: keys of the chunks before in higher bins
-        for (int c0 = 0; c0 < r.chunks; c0 += kDivGroups) {
-            const int c = c0 + group;
-            uint32_t b0 = 0, n = 0;
-            if (c0 > 0) {
-                starts = make_uint4(0, 0, 0, 0);
-                group_between = 0;
-                if (c < r.chunks) {
-                    starts = *(const uint4 *)(before + c * kDivBins + 8 * l32);
-                    group_between = counts[c].between;
+        above = all[0] + all[1] + over;
+        // AHEAD keys of a chunk's part of the bin, on from number x < n, requested together (the workspace goes on behind the last list)
+        constexpr int AHEAD = QPT > 2 ? 4 : 8;
+        typedef uint16_t Ahead __attribute__((ext_vector_type(AHEAD), aligned(2)));
+        const auto keys_at = [&](const uint16_t *src, int c, uint32_t x, uint32_t n, uint32_t (&k)[AHEAD]) __attribute__((always_inline)) {
+            const Ahead at = *(const Ahead *)(src + x);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) k[u] = by_value ? low + at[u] : order_key(r.cand[c * (kSplitSelChunk * QPT) + (x + u < n ? at[u] : 0)]);
+        };
+        if (__builtin_expect(upto - over <= (uint32_t)kDivListMax, 1)) {
+            // its keys from all chunks, in the order of the chunks, a half wave per chunk and kDivGroups of them at a time
+            uint32_t total = 0, own_at = 0, higher = 0;              // `higher`: keys of the chunks before in higher bins
+            for (int c0 = 0; c0 < r.chunks; c0 += kDivGroups) {
+                const int c = c0 + group;
+                uint32_t b0 = 0, n = 0;
+                if (c0 > 0) {
+                    starts = make_uint4(0, 0, 0, 0);
+                    group_between = 0;
+                    if (c < r.chunks) {
+                        starts = *(const uint4 *)(before + c * kDivBins + 8 * l32);
+                        group_between = counts[c].between;
+                    }
                 }
+                const auto start_of = [&](uint32_t x) {
+                    const uint32_t pair = (x & 7u) < 2 ? starts.x : (x & 7u) < 4 ? starts.y : (x & 7u) < 6 ? starts.z : starts.w;
+                    return (uint32_t)__shfl((int)(x & 1u ? pair >> 16 : pair & 0xffffu), (int)(x >> 3), 32);
+                };
+                b0 = start_of(bin);
+                const uint32_t b1 = bin + 1 < kDivBins ? start_of(bin + 1) : group_between;
+                n = b1 - b0;
+                const uint16_t *src = p.list + (r.row * p.n_units + c * QPT) * kSplitSelChunk + b0;
+                const auto key_at = [&](uint32_t x) {
+                    return by_value ? low + src[x] : order_key(r.cand[c * (kSplitSelChunk * QPT) + src[x]]);
+                };
+                const uint32_t first = l32 < (int)n ? key_at(l32) : 0u;
+                if (c0 > 0) __syncthreads();                         // the last round's reads are done
+                if (l32 == 0) bin_own[group] = make_uint2(n, group_between - b1);
+                __syncthreads();
+                const uint2 mine = lane < kDivGroups ? bin_own[lane] : make_uint2(0u, 0u);
+                uint32_t sc[2] = {mine.x, mine.y};
+                wave_incl_scan_n(sc);
+                if (chunk > c0) {
+                    const int l = min(chunk - c0, kDivGroups) - 1;
+                    own_at = total + (uint32_t)__builtin_amdgcn_readlane((int)sc[0], l);
+                    higher += (uint32_t)__builtin_amdgcn_readlane((int)sc[1], l);
+                }
+                const uint32_t to = total + (uint32_t)__shfl((int)sc[0], group, 64) - n;
+                if (l32 < (int)n) list[to + l32] = first;
+                if (__builtin_expect(__any(n > 32), 0)) {
+                    for (uint32_t x = l32 + 32; x < min(n, 128u); x += 32) list[to + x] = key_at(x);
+                    for (uint32_t x = 128 + AHEAD * l32; x < n; x += 32 * AHEAD) {
+                        uint32_t k[AHEAD];
+                        keys_at(src, c, x, n, k);
+#pragma unroll
+                        for (int u = 0; u < AHEAD; ++u)
+                            if (x + u < n) list[to + x + u] = k[u];
+                    }
+                }
+                total += (uint32_t)__builtin_amdgcn_readlane((int)sc[0], 63);
             }
-            const auto start_of = [&](uint32_t x) {
-                const uint32_t pair = (x & 7u) < 2 ? starts.x : (x & 7u) < 4 ? starts.y : (x & 7u) < 6 ? starts.z : starts.w;
-                return (uint32_t)__shfl((int)(x & 1u ? pair >> 16 : pair & 0xffffu), (int)(x >> 3), 32);
-            };
-            b0 = start_of(bin);
-            const uint32_t b1 = bin + 1 < kDivBins ? start_of(bin + 1) : group_between;
-            n = b1 - b0;
-            const uint16_t *src = p.list + (r.row * p.n_units + c * QPT) * kSplitSelChunk + b0;
-            const auto key_at = [&](uint32_t x) {
-                return by_value ? low + src[x] : order_key(r.cand[c * (kSplitSelChunk * QPT) + src[x]]);
-            };
-            const uint32_t first = l32 < (int)n ? key_at(l32) : 0u;
-            if (c0 > 0) __syncthreads();                         // the last round's reads are done
-            if (l32 == 0) bin_own[group] = make_uint2(n, group_between - b1);
             __syncthreads();
-            const uint2 mine = lane < kDivGroups ? bin_own[lane] : make_uint2(0u, 0u);
-            uint32_t sc[2] = {mine.x, mine.y};
-            wave_incl_scan_n(sc);
-            if (chunk > c0) {
-                const int l = min(chunk - c0, kDivGroups) - 1;
-                own_at = total + (uint32_t)__builtin_amdgcn_readlane((int)sc[0], l);
-                higher += (uint32_t)__builtin_amdgcn_readlane((int)sc[1], l);
-            }
-            const uint32_t to = total + (uint32_t)__shfl((int)sc[0], group, 64) - n;
-            if (l32 < (int)n && to + l32 < (uint32_t)kDivListMax) list[to + l32] = first;
-            for (uint32_t x = l32 + 32; x < n; x += 32)
-                if (to + x < (uint32_t)kDivListMax) list[to + x] = key_at(x);
-            total += (uint32_t)__builtin_amdgcn_readlane((int)sc[0], 63);
-        }
-        __syncthreads();
-        found = total <= (uint32_t)kDivListMax;
-        if (found) {
             T = list_key_of_rank(list, (int)total, want - over, tid, lane);
-            uint32_t sc[2] = {0u, 0u};                           // of the bin: keys above T in the row; above it | at it << 16 before this chunk
+            uint32_t sc[2] = {0u, 0u};                               // of the bin: keys above T in the row; above it | at it << 16 before this chunk
             for (int x = tid; x < (int)total; x += kSelThreads) {
                 const uint32_t k = list[x];
                 sc[0] += k > T ? 1u : 0u;
@@ -531,14 +551,79 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(8, 
                 }
             }
             listed = true;
-            above = all[0] + all[1] + over;
             gt_before = pre[0] + pre[1] + higher;
+        } else {
+            // Too many for LDS: most often they are one value, else the rank is found by digits, the keys read where they are.
+            // (8 rows of 131072 of seven values, k = half: 20.9 us, by a search of the row in every workgroup 82.8; one of
+            // 500000, a millionth apart: 39 against 730.  The code beside the path above costs that 0.2 us of 14.)
+            const auto bin_keys = [&](auto &&f) __attribute__((always_inline)) {
+                for (int c0 = 0; c0 < r.chunks; c0 += kDivGroups) {
+                    const int c = c0 + group;
+                    uint32_t b0 = 0, n = 0;
+                    if (c < r.chunks) {
+                        b0 = before[c * kDivBins + bin];
+                        n = (bin + 1 < kDivBins ? (uint32_t)before[c * kDivBins + bin + 1] : (uint32_t)counts[c].between) - b0;
+                    }
+                    const uint16_t *src = p.list + (r.row * p.n_units + c * QPT) * kSplitSelChunk + b0;
+                    for (uint32_t x = AHEAD * l32; __any(x < n); x += 32 * AHEAD) {
+                        uint32_t k[AHEAD] = {};
+                        if (x < n) keys_at(src, c, x, n, k);
+#pragma unroll
+                        for (int u = 0; u < AHEAD; ++u) f(k[u], x + u < n, c < chunk);
+                    }
+                }
+            };
+            if (tid == 0) heavy = make_uint2(0xffffffffu, 0u);
+            if (tid < 3) row_count[tid] = 0;
+            __syncthreads();
+            uint32_t mn = 0xffffffffu, mx = 0;
+            bin_keys([&](uint32_t k, bool has, bool) { mn = min(mn, has ? k : 0xffffffffu); mx = max(mx, has ? k : 0u); });
+            wave_min_max(mn, mx);
+            if (lane == 63) { atomicMin(&heavy.x, mn); atomicMax(&heavy.y, mx); }
+            // what the chunks before hold of the bin and of higher ones, every wave for itself
+            uint32_t own_at = 0;
+            gt_before = pre[0] + pre[1];
+            for (int c = lane; c - lane < chunk; c += 64) {
+                uint32_t sc[2] = {0u, 0u};
+                if (c < chunk) {
+                    const uint32_t all_c = counts[c].between, b1 = bin + 1 < kDivBins ? before[c * kDivBins + bin + 1] : all_c;
+                    sc[0] = b1 - before[c * kDivBins + bin];
+                    sc[1] = all_c - b1;
+                }
+                wave_incl_scan_n(sc);
+                own_at += (uint32_t)__builtin_amdgcn_readlane((int)sc[0], 63);
+                gt_before += (uint32_t)__builtin_amdgcn_readlane((int)sc[1], 63);
+            }
+            __syncthreads();
+            T = heavy.x;
+            eq_before = own_at;
+            if (heavy.x != heavy.y) {                            // the same in every thread
+                T = any_key_of_rank([&](auto &&f) { bin_keys([&](uint32_t k, bool has, bool) { f(k, has); }); }, want - over, tid, lane, wave);
+                uint32_t sc[3] = {0u, 0u, 0u};                   // of the bin: keys above T in the row, above it and at it before this chunk
+                bin_keys([&](uint32_t k, bool has, bool earlier) {
+                    sc[0] += has && k > T ? 1u : 0u;
+                    sc[1] += has && earlier && k > T ? 1u : 0u;
+                    sc[2] += has && earlier && k == T ? 1u : 0u;
+                });
+                wave_incl_scan_n(sc);
+                if (lane == 63)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) atomicAdd(&row_count[e], sc[e]);
+                __syncthreads();
+                above += row_count[0];
+                gt_before += row_count[1];
+                eq_before = row_count[2];
+            }
+#pragma unroll
+            for (int i = 0; i < QPT; ++i) split_sel_keys(r, (chunk * QPT + i) * kSplitSelChunk + 4 * tid, key[i]);     // (not held through all that)
         }
     }
-    if (!found) {                                                // the same in every thread
-        __shared__ uint32_t row_count[3];
+    if (__builtin_expect(!found, 0)) {                           // the same in every thread
         __syncthreads();
-        T = row_key_of_rank(r, kk, tid, lane, wave);
+        T = any_key_of_rank([&](auto &&f) {
+#pragma unroll 4
+            for (int x0 = 0; x0 < r.n; x0 += kSelThreads) f(x0 + tid < r.n ? order_key(r.cand[x0 + tid]) : 0u, x0 + tid < r.n);
+        }, kk, tid, lane, wave);
         if (tid < 3) row_count[tid] = 0;
         __syncthreads();
         uint32_t c[3] = {};

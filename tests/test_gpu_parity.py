@@ -992,6 +992,45 @@ def test_select_divided_rows_off_the_good_path(heads, n, kind):
         assert np.array_equal(np.flatnonzero(m[h]), want)
 
 
+@pytest.mark.parametrize("heads,n,values", [
+    (8, 131072, 7), (40, 40000, 7), (1, 600000, 7),          # the threshold's value is neither edge: 18700, 5700 and 86000 keys of a bin
+    (2, 400000, "pair"),                                     # two neighbouring values, 40000 keys of a bin that are not one value
+    (1, 900000, "pair, few bits"), (1, 300000, "octaves"),   # bins of one value each; the outermost bins, of many
+])
+@pytest.mark.parametrize("at", [0.5, 0.47])
+def test_select_divided_rows_with_more_keys_in_a_bin_than_lds_holds(heads, n, values, at):
+    """Rows of few values, or of two common ones among many, kept to about the middle: the threshold's bin holds more
+    keys than a workgroup lists in LDS (or, in the shortest row, many)."""
+    rng = np.random.default_rng(n)
+    u = rng.random((heads, n))
+    if values == 7:
+        s = np.floor(7 * u) / 7 + 0.1
+    elif values == "octaves":
+        s = np.where(u < 0.4, 1.0 + u, np.where(u < 0.6, np.exp2(np.floor(200 * rng.random((heads, n)) - 100)), -1.0 - u))
+        s[u < 0.4] += 2.0 ** 101
+    else:
+        a = np.float32(0.55)
+        b = np.nextafter(a, np.float32(1))
+        s = np.where(u < 0.45, 0.5 * u, np.where(u < 0.5, a, np.where(u < 0.55, b, 0.6 + (u - 0.55) * (1e3 if values == "pair" else 1e-3))))
+    s32 = s.astype(np.float32)
+    k = int(at * n)
+    cu, k_keep = np.array([0, n], dtype=np.int32), np.array([k], dtype=np.int32)
+    desc = pdd.AttnDesc()
+    desc.batch, desc.n_kv_heads, desc.max_seqlen_k = 1, heads, n
+    need = pdd.workspace_bytes(desc, pdd.CALL_SELECT_TOPK)
+    assert need > 0
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    idx = torch.full((heads, k), -7, dtype=torch.int32, device="cuda")
+    mask = torch.full((heads, n), 9, dtype=torch.uint8, device="cuda")
+    pdd.select_topk(dev(s32), dev(cu), n, dev(k_keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask, None, None, cu, workspace=ws)
+    got, m = idx.cpu().numpy(), mask.cpu().numpy()
+    for h in range(heads):
+        want = np.sort(np.argsort(-s32[h], kind="stable")[:k])           # ties: the lower index
+        assert np.array_equal(got[h], want)
+        assert np.array_equal(np.flatnonzero(m[h]), want)
+
+
 @pytest.mark.parametrize("name", ["c1", "c2", "c3", "c5", "c4"])
 def test_gate_a_oracle_scores_of_every_configuration(name):
     """The oracle's importance of each benchmark configuration, rounded to fp32, through the GPU
