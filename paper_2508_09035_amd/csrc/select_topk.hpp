@@ -19,8 +19,9 @@
 //    32768 20.0 / 21.3, 512 rows of 32768 42.1 / 47.4; with all keys' range, two probes a round over all keys and loads behind
 //    branches 6.5 / 6.3, 11.6 / 11.6, 17.0 / 17.2, 36.7 / 37.0.  With the sample's own range, requested ahead of the row and
 //    placed while that is on its way (uniform scores to the sixth power, kept 1/10 to 1/2, before -> now): 8 rows of 4096 6.5 -> 5.8 us, 16384
-//    12.3 -> 11.2, 32768 16.7 -> 14.1, 512 rows of 32768 34.3 -> 29.8, 512 of 4000 9.6 -> 8.6.  Rows of few different
-//    scores, or of scores that hardly change from key to key, which the sample misjudges, take up to 1.2 times as long.
+//    12.3 -> 11.2, 32768 16.7 -> 14.1, 512 rows of 32768 34.3 -> 29.8, 512 of 4000 9.6 -> 8.6.  Rows of few
+//    different scores, which the sample misjudges, take 0.8 to 1.3 times as long (8 of 32768, k = 1/10 / half: one value 9.4 / 11.2 -> 10.2 / 12.0,
+//    two 12.6 / 13.8 -> 11.9 / 15.5, seven 12.7 / 19.1 -> 12.7 / 14.9, nine zeros in ten 18.3 / 14.9 -> 20.2 / 14.3).
 //    Bound by the latency of some ten steps where the rows are few; 512 rows read 67 MB and write 23 (18.5 us) before and after the
 //    passes, with all rows at the same point at once.
 //    Histograms of all keys of long rows were slower: 50 cycles per LDS atomic of a wave.  So
@@ -493,10 +494,13 @@ void select_topk_reg_kernel(const SelParams p)
     // The waves' sums meet in an LDS counter of their own (one fresh counter per round, so none is ever
     // cleared), two to a word: a count is at most 32768.  `each` calls its argument with the thread's keys: a round
     // that cut nothing, by thirds, goes on from the range of the keys inside (five values in 20606 keys 47 -> 17 us, 27 with
-    // one probe a round).
-    auto probe = [&](auto &&count, auto &&each) {
+    // one probe a round).  A round for which `at_ends` holds asks for the keys at the bracket's two ends alone.
+    auto probe = [&](auto &&count, auto &&each, auto &&at_ends) {
         const uint32_t inside = c_lo - c_above;
-        next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
+        if (at_ends()) {
+            pa = lo + 1u;
+            pb = hi;
+        } else next_pair(lo, hi, inside, (uint32_t)kk - c_above, interp, pa, pb);
         uint32_t ca = 0, cb = 0, la = 0, lb = 0;                 // of the wave; of the lane
         count(ca, cb, la, lb);
         const uint32_t both = (ca | cb << 16) + (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(la | lb << 16), 63);
@@ -598,7 +602,10 @@ void select_topk_reg_kernel(const SelParams p)
                             lb += key[i][j + 2] >= pb ? 1u : 0u;
                         }
                     }
-                }, all_keys);
+                }, all_keys, [&] {                               // twice what a sample of many values leaves inside: a few share them
+                    // (8 rows of 32768, k = half, of two values 18.9 -> 15.5 us, of seven 18.3 -> 14.9; 512 rows 40.4 -> 34.6, 35.2 -> 31.0)
+                    return round == 0 && 4u * (c_lo - c_above) > (uint32_t)n;
+                });
             fits = lo < hi;
             if (fits) divide(&list_tot[1]);
         }
@@ -671,7 +678,7 @@ void select_topk_reg_kernel(const SelParams p)
         }, [&](auto &&f) {
 #pragma unroll
             for (int q = 0; q < NL; ++q) f(lk[q]);
-        });
+        }, [] { return false; });
     if (lo < hi) {
         // at most kSelFinish keys lie in [lo, hi]: the (kk - c_above)-th largest of them is T
         const uint32_t width = hi - lo;

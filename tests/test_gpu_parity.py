@@ -880,6 +880,32 @@ def test_select_runs_of_equal_scores(n):
             assert np.array_equal(sent.cpu().numpy(), want_mask), f"sentences, k = {k}"
 
 
+@pytest.mark.parametrize("n,pool", [(4097, 0), (6001, 0), (8192, 2), (16384, 0), (20606, 2), (32768, 0)])
+def test_select_long_rows_of_two_and_three_scores(n, pool):
+    """Two scores, alone and with a rare one between, above or below, kept to one less than the higher ones, to all of
+    them and to one more, to the rare ones and past them.  With and without pooling by the maximum; exact."""
+    rng = np.random.default_rng(n)
+    at, rare = rng.random(n), rng.random(n) < 0.01
+    row = lambda low, high, other: np.where(rare, other, np.where(at < (0.05 if pool else 0.45), high, low))
+    rows = np.stack([row(-2, 3, 3), row(-2, 3, 0.5), row(-2, 3, 7), row(-2, 3, -5), row(0, 1e-45, 0)]).astype(np.float32)
+    ranked = oracle.pool_scores(rows.astype(np.float64), np.array([0, n]), 2 * pool + 1, "max") if pool else rows
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cu = np.array([0, n], dtype=np.int32)
+    counts = {int((r >= v).sum()) for r in ranked for v in np.unique(r)}
+    for k in sorted({min(max(c + d, 1), n) for c in counts for d in (-1, 0, 1)}):
+        keep = np.array([k], dtype=np.int32)
+        idx = torch.full((len(rows), k), -7, dtype=torch.int32, device="cuda")
+        mask = torch.full(rows.shape, 9, dtype=torch.uint8, device="cuda")
+        args = (dev(rows), dev(cu), n, dev(keep), dev(np.array([0, k], dtype=np.int32)), k, idx, mask)
+        if pool:
+            pdd.select_topk_pooled(*args, 2 * pool + 1, pdd.POOL_MAX, None, None, None, cu)
+        else:
+            pdd.select_topk(*args, None, None, cu)
+        want_idx, want_mask = oracle.select_topk(ranked, cu, keep)
+        assert np.array_equal(idx.cpu().numpy(), want_idx), f"k = {k}"
+        assert np.array_equal(mask.cpu().numpy(), want_mask), f"k = {k}"
+
+
 @pytest.mark.parametrize("n", [5, 128, 300, 4097, 32768])
 def test_select_key_of_the_lowest_nan(n):
     """A score whose bits are all ones (a buffer filled with 0xFF bytes) ranks below every other value
