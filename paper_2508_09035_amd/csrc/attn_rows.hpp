@@ -97,6 +97,7 @@ template <int D, int RG, bool DIVIDED>
 __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && RG == 1 ? 4 : 2, D == 64 && RG == 1 ? 4 : 2)))
 void attn_rows_kernel(const AttnParams p)
 {
+    static_assert(DIVIDED || RG == 1, "whole key ranges: one row group to a workgroup");
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int ROWB = 2 * D, CH = D / 8, RPI = 1024 / ROWB;
     constexpr int KG = kRowsWaves / RG, ROWS = 32 * RG, SLOTS = RowsSmem<D, RG>::SLOTS;

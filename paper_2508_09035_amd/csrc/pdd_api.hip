@@ -431,12 +431,13 @@ template <int D, int RG>
 pdd_status launch_attn_rows(const RowsPlan &plan, pdd::AttnParams &p, int64_t max_q, void *scratch, hipStream_t st)
 {
     p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
-    if (plan.workers == 0) {
-        p.n_qtiles = (int)((max_q * p.G + 32 * RG - 1) / (32 * RG));
-        p.turn = pdd::rows_per_turn(p.Hkv);
-        return launch_attn_kernel(pdd::attn_rows_kernel<D, RG, false>, pdd::RowsSmem<D, RG>::BYTES, 64 * pdd::kRowsWaves, p,
-                                  (int64_t)p.n_qtiles * p.B * p.Hkv, st);
-    }
+    if constexpr (RG == 1)                                       // the whole form has 32 rows to a workgroup
+        if (plan.workers == 0) {
+            p.n_qtiles = (int)((max_q * p.G + 31) / 32);
+            p.turn = pdd::rows_per_turn(p.Hkv);
+            return launch_attn_kernel(pdd::attn_rows_kernel<D, 1, false>, pdd::RowsSmem<D, 1>::BYTES, 64 * pdd::kRowsWaves, p,
+                                      (int64_t)p.n_qtiles * p.B * p.Hkv, st);
+        }
     p.workers = (int)plan.workers;  p.min_tiles = plan.min_tiles;  p.part_rows = (int)plan.part_rows;
     p.part_of = (uint4 *)scratch;
     p.part_o = (float *)(p.part_of + (int64_t)p.total_q * p.Hq);
