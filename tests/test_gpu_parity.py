@@ -328,6 +328,15 @@ def test_few_rows_over_many_keys(name, d):
     rel_close(lse, oL, "lse")
     rel_close(imp, oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, window or -1), "importance")
     assert all(torch.equal(a, b) for a, b in zip(*bits))
+    if not divided:                     # the form whose waves walk all keys of their own rows rounds elsewhere
+        try:
+            pdd.set_option(pdd.OPT_ATTN_WAVES, 4)
+            dev.attn(True)
+            torch.cuda.synchronize()
+        finally:
+            pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
+        assert not torch.equal(dev.o, bits[1][0]), "this shape is one that takes the form"
+        assert np.abs(dev.results()[0] - oO).max() <= O_ATOL
 
 
 @pytest.mark.parametrize("d,name", [(128, "chunks"), (64, "many short"), (64, "mha")])
@@ -679,6 +688,7 @@ def test_importance_of_uneven_chunks(lens, prefix, hq, hkv, d):
         pdd.set_option(pdd.OPT_IMPORTANCE_KEYS, 0)
     assert torch.equal(got[0], got[1])
     rel_close(got[0].cpu().numpy().astype(np.float64), got[2].cpu().numpy().astype(np.float64), "importance")
+    rel_close(got[0].cpu().numpy().astype(np.float64), oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, -1), "against the oracle")
 
 
 def test_importance_of_a_very_large_group():
