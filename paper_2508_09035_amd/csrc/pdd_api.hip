@@ -417,6 +417,12 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
         const double all = tiles * Hkv / cus;
         const double est = rg == 1 ? (d64 ? 10.7 + 0.024 * std::ceil(per / 4.0) + 0.20 * all : 12.2 + 0.42 * std::ceil(per / 4.0) + 0.30 * all)
                                    : (d64 ? 11.7 + 0.053 * per + 0.61 * all : 15.1 + 0.85 * all);
+        // Where no cache nearer than the memory's own holds the keys and values, each tile of 32 rows reads them anew, at some
+        // 9 TB/s: 128 rows are compared with that (67 tokens x 6 behind 13418, 8/8 heads of 64, 97 us, 72 with smaller pieces, in 128 rows 45;
+        // 97 launches that this decides 1.31 times as fast, 0.89 to 1.97; from 64 to 80 MB 20 took 0.71 to 1.7).
+        const double tile_mb = 2.0 * pdd::kBN * d->head_dim * 2e-6;
+        if (rg == 4 && best.rg == 1 && max_q * G > 32 && tile_mb * tiles_mean * B * Hkv > 80.0)
+            us = std::fmax(us, 5.0 + row_tiles(1) * tiles_mean * seen * Hkv * tile_mb / 9.0);
         if (est < 0.95 * us) {
             us = est;
             // what the pieces can take at most: each sequence one more than `min_tiles` goes into its key tiles

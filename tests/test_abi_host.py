@@ -343,6 +343,19 @@ def test_head_dim_64_prompts_are_priced_in_the_form_that_would_run():
         assert (lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_PREFILL_ATTN) > 0) == splits, (heads, kv, lens)
 
 
+def test_chunks_over_more_keys_than_caches_hold_take_128_rows():
+    """Equal chunks of a few row tiles over 80 MB of keys and values are divided in tiles of 128 rows, which ask for the
+    partial rows of pieces of 4 key tiles; behind fewer keys tiles of 32 rows walk them whole, without scratch."""
+    lib = pdd.load_library()
+    d = good_desc()
+    d.head_dim, d.n_q_heads, d.n_kv_heads, d.batch = 64, 32, 8, 7
+    d.total_q, d.max_seqlen_q = 7 * 34, 34
+    for keys, rows_128 in ((5738, True), (1738, False)):
+        d.total_k, d.max_seqlen_k = 7 * keys, keys
+        row_bytes = d.total_q * 32 * (64 + 1) * 4
+        assert (lib.pdd_workspace_bytes(ctypes.byref(d), pdd.CALL_PREFILL_ATTN_CHUNKED) >= row_bytes + row_bytes // 4) == rows_128, keys
+
+
 def test_workspace_figure_does_not_depend_on_the_importance_option():
     """Scratch sized under one setting of PDD_OPT_IMPORTANCE_KEYS serves a call under another one, for
     windows that the default setting sums without scratch too."""
