@@ -647,19 +647,19 @@ size_t importance_split_bytes(const pdd_attn_desc *d, int r)
 // Whether the importance takes the form with all window rows in LDS, and its launch shape.
 // The rows have to fit the 160 KB of a compute unit (19 blocks of 32 at head_dim 128).  Above 80 KB one
 // 16-wave workgroup runs per compute unit: only for launches that fill the chip's 4096 wave slots with 32-key
-// groups (64 tokens x 4 behind 8192 keys, 64/8 heads 59 -> 50 us; 200 tokens behind 16000, 4/2
-// heads, would take 17 us against 11.4 of the streaming kernel, which divides the rows).  A round of such
-// workgroups takes 1.9 times as long with two groups per wave as with one, so the rounds decide: 32768 tokens, 128
-// rows of 32/8 heads (one round or two) 42.3 us with two groups, 46.5 with one, 8 x 5000 (two or three) 72.6 and
-// 63.7, 16 x 1000 (one either way) 34.8 and 25.6; 52, 63 and 32 with the streaming kernel.  Below 80 KB
+// groups (64 tokens x 4 behind 8192 keys, 64/8 heads 46 us, 57 with the streaming kernel; 200 tokens behind 16000, 4/2
+// heads, would take 15.3 us against 12.3 of the streaming kernel, which divides the rows).  A round of such
+// workgroups takes 1.9 times as long with two groups per wave as with one, so the rounds decide: 32768 tokens, window of
+// 128, 32/8 heads (one round or two) 38.2 us with two groups, 42.1 with one, 8 x 5000 (two or three) 64 and
+// 61.5, 16 x 1000 (one either way) 29.3 and 22.1; 51.5, 59.5 and 27.0 with the streaming kernel.  Below 80 KB
 // two or more run per compute unit; four waves each while all of them are resident at once (4096
-// tokens, 64 rows: 7.0 us, 8.7 with eight waves), else eight waves, which load the rows half as often,
-// and two groups per wave from 4096 groups on (8 prompts of 512 to 7900 tokens, 64 rows: 26.5 us with
-// four waves, 24.4 / 23.3 with eight and one / two groups; 35 with the streaming kernel), or four waves where there is
-// one block of rows and so little to load (8 x 5000, 8 heads of head_dim 64, 32 rows: 10.1 us, 11.4 with eight).  Sixteen
-// blocks or more (head_dim 64) for few keys are a long walk, which the streaming kernel divides: 300 tokens 8.7 us
-// against 7.7, 4096 x 16/2 heads 9.2 against 8.2, 3000 x 3 8.7 against 9.4 to 10.3.  (This form's times are from before its
-// loop was shortened; it takes 0.86 to 1.0 of them now.)
+// tokens, window of 64: 7.0 us, 8.5 with eight waves), else eight waves, which load the rows half as often,
+// and two groups per wave from 4096 groups on (8 prompts of 512 to 7900 tokens, window of 64: 21.6 us with
+// four waves, 17.7 / 19.4 with eight and one / two groups, the second the better one when the line was drawn; 27 with the
+// streaming kernel), or four waves where there is one block of rows and so little to load (8 x 5000, 8 heads of head_dim 64,
+// window of 32: 9.6 us, 11.6 with eight).  Sixteen blocks or more (head_dim 64) for few keys are a long walk, which the
+// streaming kernel divides (300 tokens 7.6 us, 4096 x 16/2 heads 7.8; this form takes 7.0 and 7.3 since its loop was
+// shortened, 8.7 and 9.2 before).
 // uneven: the sequences may have different numbers of rows, and the launch is more than the chip holds at a group per wave.
 struct ImpRowsPlan { int waves, groups; size_t lds; bool uneven; };       // waves == 0: the form does not apply
 ImpRowsPlan importance_rows(const pdd_attn_desc *d, int window)
