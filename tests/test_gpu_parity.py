@@ -352,6 +352,34 @@ def test_wide_attention_far_from_its_first_reference(logit, v_exponent, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rise,late", [(10.9, range(32, 2400)), (16.0, range(40, 41))])
+def test_wide_attention_with_values_near_the_largest(rise, late, d):
+    """Values of 2^107 (2^113 at one key), and scores that rise by so much (log2) over the first block at many keys or at one:
+    such probabilities times such values, not divided by their sum yet, are beyond fp32, though every part of the sum is small."""
+    wl = W.make_custom("t", [2400, 300], None, 64, 8, d, 0, "1/4", seed=3)
+    c = np.sqrt(rise * np.log(2.0) / wl.scale / d)
+    at = np.isin(np.arange(wl.total_k), list(late))
+    wl.q = W.f32_to_bf16_bits(np.full(wl.q.shape, c, dtype=np.float32))
+    wl.k = W.f32_to_bf16_bits(np.broadcast_to(np.float32(c) * at[:, None, None], wl.k.shape))
+    v = np.full(wl.total_k, 2.0 ** 107)
+    if len(late) == 1:
+        v[late[0]] = 2.0 ** 113
+    wl.v = W.f32_to_bf16_bits(np.broadcast_to(v[:, None, None], wl.v.shape))
+    dev = DeviceWorkload(wl)
+    dev.poison()
+    dev.attn(False, use_workspace=False)
+    O = dev.results()[0]
+    assert np.isfinite(O).all()
+    # all rows of a sequence that see the same number of such keys are averages of the same values; bf16 of O, and of q, k and
+    # the probabilities in the second case's weights
+    score = np.float64(W.bf16_bits_to_f32(W.f32_to_bf16_bits(np.array([c], np.float32)))[0]) ** 2 * d * wl.scale
+    w = np.where(at, np.exp(score), 1.0)
+    for b, e in ((0, 2400), (2400, 2700)):
+        want = np.cumsum(w[b:e] * v[b:e]) / np.cumsum(w[b:e])
+        assert np.abs(O[b:e] / want[:, None, None] - 1.0).max() <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_wide_attention_with_a_nan_key(d):
     """A key of NaN spoils the rows that see it (NaN outputs, log-sum-exp -infinity) and no others."""
     wl = W.make_custom("t", [2400, 300], None, 64, 8, d, 0, "1/4", seed=77)
