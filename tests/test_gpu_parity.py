@@ -380,6 +380,30 @@ def test_wide_attention_with_values_near_the_largest(rise, late, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens_q,lens_k", [([2400, 300], None), ([300, 2048], [4300, 5000])])
+def test_wide_attention_without_a_score_in_the_first_block(lens_q, lens_k, d):
+    """The first 32 keys' products with every query leave fp32 (scores of -inf); the others lie near -150.  Rows that see one of
+    those are as if the first 32 keys did not exist."""
+    wl = W.make_custom("t", lens_q, lens_k, 64, 8, d, 0, "1/4", seed=5, chunked=lens_k is not None)
+    first = np.zeros(wl.total_k, dtype=bool)
+    for b in wl.cu_seqlens_k[:-1]:
+        first[b:b + 32] = True
+    wl.q = W.f32_to_bf16_bits(np.full(wl.q.shape, 2.0 ** 60, dtype=np.float32))
+    k = -2.0 ** -60 * (150.0 / (wl.scale * d) + 0.1 * W.bf16_bits_to_f32(wl.k).astype(np.float64))
+    wl.k = W.f32_to_bf16_bits(np.where(first[:, None, None], -2.0 ** 70, k).astype(np.float32))
+    dev = DeviceWorkload(wl)
+    dev.poison()
+    dev.attn(False, use_workspace=False)
+    O, lse = dev.results()[:2]
+    rows = _wide_rows(wl)
+    at, seq = rows - wl.cu_seqlens_q[np.searchsorted(wl.cu_seqlens_q, rows, "right") - 1], np.searchsorted(wl.cu_seqlens_q, rows, "right") - 1
+    rows = rows[at + (wl.seqlens_k - wl.seqlens_q)[seq] >= 32]
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+    assert np.abs(O[rows] - oO).max() <= O_ATOL
+    rel_close(lse[:, rows], oL, "lse")
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_wide_attention_with_a_nan_key(d):
     """A key of NaN spoils the rows that see it (NaN outputs, log-sum-exp -infinity) and no others."""
     wl = W.make_custom("t", [2400, 300], None, 64, 8, d, 0, "1/4", seed=77)
