@@ -391,6 +391,23 @@ pdd_status pdd_pack_mask(const uint8_t *mask, int32_t n_rows, int32_t batch, int
 size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call);
 
 /*
+ * The attention form that a call with this descriptor takes (host only, no GPU work): which_call
+ * PDD_CALL_PREFILL_ATTN or PDD_CALL_PREFILL_ATTN_CHUNKED, importance != 0 where the chunked call has
+ * importance to return, workspace_bytes of aligned scratch (0: none).  Depends on what the calls themselves
+ * go by: descriptor, scratch, PDD_OPT_ATTN_WAVES and the device's compute units.  A negative pdd_status
+ * where the call would refuse the descriptor.
+ */
+enum {
+    PDD_ATTN_4_WAVES = 0,        /* 128 queries of one head to a workgroup         */
+    PDD_ATTN_8_WAVES = 1,        /* 256                                            */
+    PDD_ATTN_4_WAVES_LISTED = 2, /* 128, only the query tiles that exist           */
+    PDD_ATTN_WIDE = 3,           /* 256, 64 queries to a wave                      */
+    PDD_ATTN_SPLIT = 4,          /* keys divided over workgroups (prompts)         */
+    PDD_ATTN_ROWS = 5            /* few rows: keys shared out over waves           */
+};
+int pdd_attn_form(const pdd_attn_desc *desc, int which_call, int importance, size_t workspace_bytes);
+
+/*
  * Tuning knobs (process-wide, not thread-safe against concurrent launches).
  *   PDD_OPT_ATTN_WAVES: wavefronts per attention workgroup, 4 (128 queries) or
  *   8 (256 queries); 0 = chosen per problem (default).

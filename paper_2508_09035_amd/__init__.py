@@ -28,6 +28,13 @@ from .binding import (
     aggregate_scores,
     choose_r_L,
     workspace_bytes,
+    attn_form,
+    ATTN_4_WAVES,
+    ATTN_8_WAVES,
+    ATTN_4_WAVES_LISTED,
+    ATTN_WIDE,
+    ATTN_SPLIT,
+    ATTN_ROWS,
     AttnDesc,
     make_desc,
     OPT_ATTN_WAVES,
@@ -41,5 +48,5 @@ from .binding import (
 __all__ = [
     "PddError", "library_path", "load_library", "version", "set_option", "prefill_attn",
     "prefill_attn_chunked", "prefill_attn_chunked_noalloc", "token_importance", "select_topk", "select_topk_pooled", "POOL_NONE", "POOL_MAX", "POOL_AVG", "select_sentences", "SENT_SUM", "SENT_MEAN", "pack_mask", "pack_mask_layout", "aggregate_scores", "choose_r_L", "workspace_bytes", "AttnDesc",
-    "make_desc", "OPT_ATTN_WAVES", "OPT_IMPORTANCE_KEYS",
+    "attn_form", "ATTN_4_WAVES", "ATTN_8_WAVES", "ATTN_4_WAVES_LISTED", "ATTN_WIDE", "ATTN_SPLIT", "ATTN_ROWS", "make_desc", "OPT_ATTN_WAVES", "OPT_IMPORTANCE_KEYS",
 ]

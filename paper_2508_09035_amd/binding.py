@@ -14,6 +14,7 @@ _lib = None
 
 OPT_ATTN_WAVES = 0
 OPT_IMPORTANCE_KEYS = 1
+(ATTN_4_WAVES, ATTN_8_WAVES, ATTN_4_WAVES_LISTED, ATTN_WIDE, ATTN_SPLIT, ATTN_ROWS) = range(6)
 CALL_PREFILL_ATTN, CALL_PREFILL_ATTN_CHUNKED, CALL_TOKEN_IMPORTANCE, CALL_SELECT_TOPK = 0, 1, 2, 3
 
 
@@ -102,6 +103,8 @@ def load_library():
     lib.pdd_pack_mask.argtypes = [vp, i32, i32, i32, vp, vp, i32, vp, i32, vp, vp]
     lib.pdd_workspace_bytes.restype = sz
     lib.pdd_workspace_bytes.argtypes = [dp, ctypes.c_int]
+    lib.pdd_attn_form.restype = ctypes.c_int
+    lib.pdd_attn_form.argtypes = [dp, ctypes.c_int, ctypes.c_int, sz]
     lib.pdd_last_error.restype = ctypes.c_char_p
     lib.pdd_version.restype = ctypes.c_char_p
     lib.pdd_set_option.restype = ctypes.c_int
@@ -223,6 +226,14 @@ def _packed_desc(q, k, v, o, lse, importance, cu_seqlens_q, cu_seqlens_k, max_se
 
 def workspace_bytes(desc: AttnDesc, which_call: int) -> int:
     return int(load_library().pdd_workspace_bytes(ctypes.byref(desc), which_call))
+
+
+def attn_form(desc: AttnDesc, which_call: int, importance: bool = True, workspace_bytes: int = 0) -> int:
+    """The ATTN_* form that a call with this descriptor and that much scratch takes."""
+    form = int(load_library().pdd_attn_form(ctypes.byref(desc), which_call, int(importance), workspace_bytes))
+    if form < 0:
+        _check(form)
+    return form
 
 
 def _check_tensors(*ts):

@@ -254,6 +254,14 @@ bool takes_wide(const pdd_attn_desc *d, int bm)
     return bm == 128 && fill_of_the_chip(d) >= 1.1;
 }
 
+// The plain form of a call whose tiles would have bm queries: `sweeps` with the importance sweep.
+int plain_form(const pdd_attn_desc *d, int bm, bool sweeps)
+{
+    if (takes_wide(d, bm) && (!sweeps || d->head_dim == 128)) return PDD_ATTN_WIDE;
+    if (bm == 256) return PDD_ATTN_8_WAVES;
+    return !sweeps && d->head_dim == 128 && lists_tiles(d) ? PDD_ATTN_4_WAVES_LISTED : PDD_ATTN_4_WAVES;
+}
+
 // Chunked mode can take the token importance from a second sweep inside the
 // attention kernel (every query of the call is a window query there).  Its partial sums need one
 // float per (query head, query tile, key); 0 = this shape does not use the sweep.
@@ -501,13 +509,15 @@ pdd_status launch_attn_rows(const RowsPlan &plan, pdd::AttnParams &p, int64_t ma
     return PDD_OK;
 }
 
-// bm: queries per workgroup of the plain form.
+// The attention form of a call.  bm: queries per workgroup of the plain forms but the wide one; split, rows: the plans of
+// PDD_ATTN_SPLIT and PDD_ATTN_ROWS.
+struct AttnForm { int kind, bm; SplitPlan split; RowsPlan rows; };
+
 // imp_part != NULL: sweep_workspace(d) bytes; the importance sweep runs inside
 // the attention kernel and leaves its partial sums there.
-// plan, rows != NULL: the key-split form or that of attn_rows.hpp, with plan->bytes or rows->bytes of scratch.
-pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void *k, const void *v, void *o, float *lse,
-                       hipStream_t st, float *imp_part = nullptr, const SplitPlan *plan = nullptr,
-                       const RowsPlan *rows = nullptr, void *scratch = nullptr)
+// scratch: split.bytes or rows.bytes of a form that divides the keys.
+pdd_status launch_attn(const pdd_attn_desc *d, const AttnForm &form, const void *q, const void *k, const void *v, void *o, float *lse,
+                       hipStream_t st, float *imp_part, void *scratch)
 {
     if (d->total_q == 0) return PDD_OK;
     pdd::AttnParams p;
@@ -525,14 +535,12 @@ pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void
     p.turn = 1;
     p.scale_log2 = scale_log2(d);
 
-    const int nw = bm / 32;
-    const bool wide = !plan && !rows && takes_wide(d, bm) && (!imp_part || d->head_dim == 128);
-    if (wide) bm = pdd::kWideRows;
+    const int bm = form.kind == PDD_ATTN_WIDE ? pdd::kWideRows : form.bm, nw = bm / 32;
     p.n_qtiles = (d->max_seqlen_q + bm - 1) / bm;
     int64_t blocks = (int64_t)p.n_qtiles * d->batch * d->n_q_heads;
     if (blocks > 0x7fffffffLL) return fail(PDD_ERR_INVALID_ARG, "launch grid too large");
     p.listed = 0;
-    if (!imp_part && !plan && !rows && d->head_dim == 128 && bm == 128 && lists_tiles(d)) {
+    if (form.kind == PDD_ATTN_4_WAVES_LISTED) {
         p.listed = (d->max_seqlen_k > d->max_seqlen_q ? d->max_seqlen_k : d->max_seqlen_q) / bm + 1;
         blocks = existing_tiles(d, bm) * d->n_q_heads;
     }
@@ -545,21 +553,22 @@ pdd_status launch_attn(const pdd_attn_desc *d, int bm, const void *q, const void
         if ((int64_t)d->q_stride_tok * 2 * 32 >= (1LL << 32))
             return fail(PDD_ERR_UNSUPPORTED, "32 rows of Q must span less than 4 GiB");
     }
-    if (rows) {
+    if (form.kind == PDD_ATTN_ROWS) {
+        const RowsPlan &rows = form.rows;
         if (d->head_dim == 128)
-            return rows->rg == 1 ? launch_attn_rows<128, 1>(*rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<128, 4>(*rows, p, d->max_seqlen_q, scratch, st);
-        return rows->rg == 1 ? launch_attn_rows<64, 1>(*rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<64, 4>(*rows, p, d->max_seqlen_q, scratch, st);
+            return rows.rg == 1 ? launch_attn_rows<128, 1>(rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<128, 4>(rows, p, d->max_seqlen_q, scratch, st);
+        return rows.rg == 1 ? launch_attn_rows<64, 1>(rows, p, d->max_seqlen_q, scratch, st) : launch_attn_rows<64, 4>(rows, p, d->max_seqlen_q, scratch, st);
     }
-    if (plan) {
-        p.split_tiles = plan->tiles;  p.n_split = plan->n_split;
+    if (form.kind == PDD_ATTN_SPLIT) {
+        p.split_tiles = form.split.tiles;  p.n_split = form.split.n_split;
         p.n_qtiles = (int)(((int64_t)d->max_seqlen_q * p.G + kSplitRows - 1) / kSplitRows);
         p.g_magic = p.G > 1 ? (uint32_t)(((1ull << 32) + p.G - 1) / p.G) : 0u;
         p.part_o = (float *)scratch;
-        p.part_l = p.part_o + (size_t)plan->n_split * d->total_q * d->n_q_heads * d->head_dim;
-        const int64_t n = (int64_t)p.n_qtiles * d->batch * d->n_kv_heads * plan->n_split;
+        p.part_l = p.part_o + (size_t)form.split.n_split * d->total_q * d->n_q_heads * d->head_dim;
+        const int64_t n = (int64_t)p.n_qtiles * d->batch * d->n_kv_heads * form.split.n_split;
         return d->head_dim == 128 ? launch_attn_split<128>(p, n, st) : launch_attn_split<64>(p, n, st);
     }
-    if (wide) {
+    if (form.kind == PDD_ATTN_WIDE) {
         if (imp_part)
             return launch_attn_kernel(pdd::attn_wide_kernel<128, true>, pdd::WideSmem<128>::BYTES, 64 * pdd::kWideWaves, p, blocks, st);
         if (d->head_dim == 128)
@@ -869,6 +878,24 @@ RowsPlan rows_plan_with(const pdd_attn_desc *d, const void *workspace, size_t wo
     return workspace_bytes >= rows.bytes ? rows : rows_plan(d, true, workspace_bytes);
 }
 
+// The forms that the two calls take for their scratch.
+AttnForm prefill_form(const pdd_attn_desc *d, const void *workspace, size_t workspace_bytes)
+{
+    // (a prompt's rows plan takes no scratch; without scratch for the key-split form it is compared with the plain form alone)
+    AttnForm f = {0, attn_prefill_rows_per_workgroup(d), split_plan(d), {}};
+    const bool room = f.split.tiles && workspace && workspace_bytes >= f.split.bytes && aligned16(workspace);
+    f.rows = rows_plan(d, false, room ? workspace_bytes : 0);
+    f.kind = f.rows.rg ? PDD_ATTN_ROWS : room ? PDD_ATTN_SPLIT : plain_form(d, f.bm, false);
+    return f;
+}
+// sweeps: there is importance to return, and scratch for the sweep
+AttnForm chunk_form(const pdd_attn_desc *d, bool sweeps, const void *workspace, size_t workspace_bytes)
+{
+    AttnForm f = {0, attn_rows_per_workgroup(d), {}, rows_plan_with(d, workspace, workspace_bytes)};
+    f.kind = f.rows.rg ? PDD_ATTN_ROWS : plain_form(d, f.bm, sweeps);
+    return f;
+}
+
 // Device address of this GPU's copy of `scratch`, looked up once per device.
 pdd_status static_scratch(void **out)
 {
@@ -945,6 +972,20 @@ size_t pdd_workspace_bytes(const pdd_attn_desc *desc, int which_call)
     }
 }
 
+int pdd_attn_form(const pdd_attn_desc *desc, int which_call, int importance, size_t workspace_bytes)
+{
+    if (which_call != PDD_CALL_PREFILL_ATTN && which_call != PDD_CALL_PREFILL_ATTN_CHUNKED) {
+        fail(PDD_ERR_INVALID_ARG, "pdd_attn_form: not an attention call: %d", which_call);
+        return PDD_ERR_INVALID_ARG;
+    }
+    const bool chunked = which_call == PDD_CALL_PREFILL_ATTN_CHUNKED;
+    if (const pdd_status s = check_desc(desc, chunked ? MODE_CHUNKED : MODE_PREFILL)) return s;
+    const void *scratch = workspace_bytes ? reinterpret_cast<const void *>(uintptr_t(16)) : nullptr;      // (not followed)
+    if (!chunked) return prefill_form(desc, scratch, workspace_bytes).kind;
+    const size_t sweep = importance ? sweep_workspace(desc) : 0;
+    return chunk_form(desc, sweep && workspace_bytes >= sweep, scratch, workspace_bytes).kind;
+}
+
 pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void *k, const void *v, void *o,
                             float *lse, float *importance, void *workspace, size_t workspace_bytes,
                             pdd_stream stream)
@@ -955,16 +996,7 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
     if (s) return s;
     if (desc->window > 0 && !importance)
         return fail(PDD_ERR_INVALID_ARG, "window > 0 needs an importance buffer");
-    // (a prompt's rows plan takes no scratch; without scratch for the key-split form it is compared with the plain form alone)
-    const SplitPlan plan = split_plan(desc);
-    const bool room = plan.tiles && workspace && workspace_bytes >= plan.bytes && aligned16(workspace);
-    const RowsPlan rows = rows_plan(desc, false, room ? workspace_bytes : 0);
-    if (rows.rg)
-        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows);
-    else if (room)
-        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream, nullptr, &plan, nullptr, workspace);
-    else
-        s = launch_attn(desc, attn_prefill_rows_per_workgroup(desc), q, k, v, o, lse, (hipStream_t)stream);
+    s = launch_attn(desc, prefill_form(desc, workspace, workspace_bytes), q, k, v, o, lse, (hipStream_t)stream, nullptr, workspace);
     if (s) return s;
     if (importance && desc->window > 0)
         return launch_importance(desc, q, k, lse, importance, desc->window, workspace, workspace_bytes,
@@ -984,24 +1016,18 @@ pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chu
     const size_t sweep = importance ? sweep_workspace(desc) : 0;
     const bool sweeps = sweep && workspace && workspace_bytes >= sweep;
     if (sweeps && !aligned16(workspace)) return fail(PDD_ERR_WORKSPACE, "workspace must be 16-byte aligned");
-    const int bm = attn_rows_per_workgroup(desc);
-    if (const RowsPlan rows = rows_plan_with(desc, workspace, workspace_bytes); rows.rg) {
-        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, nullptr, &rows, workspace);
-        if (s || !importance) return s;
-        return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,
-                                 (hipStream_t)stream);
-    }
-    if (sweeps) {
-        s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, (float *)workspace);
+    const AttnForm form = chunk_form(desc, sweeps, workspace, workspace_bytes);
+    if (sweeps && form.kind != PDD_ATTN_ROWS) {
+        s = launch_attn(desc, form, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, (float *)workspace, nullptr);
         if (s) return s;
-        const int n_slices = (desc->n_q_heads / desc->n_kv_heads) * ((desc->max_seqlen_q + bm - 1) / bm);
+        const int n_slices = (desc->n_q_heads / desc->n_kv_heads) * ((desc->max_seqlen_q + form.bm - 1) / form.bm);
         launch_importance_reduce((const float *)workspace, importance, (int64_t)desc->n_kv_heads * desc->total_k,
                                  n_slices, (hipStream_t)stream);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(PDD_ERR_HIP, "importance reduction launch: %s", hipGetErrorString(e));
         return PDD_OK;
     }
-    s = launch_attn(desc, bm, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream);
+    s = launch_attn(desc, form, q_chunk, k_all, v_all, o, lse, (hipStream_t)stream, nullptr, workspace);
     if (s) return s;
     if (importance)
         return launch_importance(desc, q_chunk, k_all, lse, importance, -1, workspace, workspace_bytes,

@@ -70,6 +70,16 @@ class DeviceWorkload:
                              self.max_q, self.max_k, wl.scale,
                              wl.window if with_importance else 0, hq, hk, workspace=ws)
 
+    def attn_form(self, with_importance=True, use_workspace=True):
+        """The attention form (ATTN_*) that attn() with these arguments takes."""
+        wl = self.wl
+        desc, keep = pdd.make_desc(self.q, self.k, self.v, self.o, self.cu_q, self.cu_k, self.max_q, self.max_k, wl.scale,
+                                   wl.window if with_importance else 0)
+        call = pdd.CALL_PREFILL_ATTN_CHUNKED if wl.chunked else pdd.CALL_PREFILL_ATTN
+        form = pdd.attn_form(desc, call, with_importance, self.workspace_bytes if use_workspace else 0)
+        del keep
+        return form
+
     def select(self, scores=None):
         wl = self.wl
         pdd.select_topk(self.imp if scores is None else scores, self.cu_k, self.max_k,

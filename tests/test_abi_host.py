@@ -126,6 +126,37 @@ def test_importance_and_select_validation():
     assert pdd.workspace_bytes(good_desc(), 0) < 64 * 64 * 4     # never O(N^2)
 
 
+def attn_desc(new, keys, hq, hkv, d, window=0):
+    """A call's descriptor, contiguous tensors."""
+    desc = AttnDesc()
+    desc.batch, desc.n_q_heads, desc.n_kv_heads, desc.head_dim = len(new), hq, hkv, d
+    desc.total_q, desc.total_k, desc.max_seqlen_q, desc.max_seqlen_k = sum(new), sum(keys), max(new), max(keys)
+    desc.cu_seqlens_q = desc.cu_seqlens_k = 0x1000
+    for f in ("q", "k", "v", "o"):
+        setattr(desc, f + "_stride_tok", (hq if f in "qo" else hkv) * d)
+        setattr(desc, f + "_stride_head", d)
+    desc.window = window
+    return desc
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,form", [
+    # head_dim 128: 8 waves from more than a 256-query tile to a compute unit on; 36 key tiles or more: 64 queries to a wave
+    ([2048], 32, 8, 128, "ATTN_4_WAVES"), ([2049], 32, 8, 128, "ATTN_8_WAVES"),
+    ([2240], 32, 8, 128, "ATTN_8_WAVES"), ([2304], 32, 8, 128, "ATTN_WIDE"),
+    # uneven: tiles by their mean number at most 1.3 to a compute unit, a fifth of the longest one's for each empty
+    ([4924, 1160], 12, 2, 128, "ATTN_4_WAVES_LISTED"), ([4200, 900], 16, 8, 128, "ATTN_WIDE"),
+    ([4000, 900], 16, 8, 128, "ATTN_4_WAVES_LISTED"), ([2600, 2300], 16, 8, 128, "ATTN_WIDE"),
+    ([1000] + [300] * 15, 8, 8, 128, "ATTN_4_WAVES_LISTED"), ([1000] + [300] * 16, 8, 8, 128, "ATTN_8_WAVES"),
+    # ... and from 0.6875 of a tile to a compute unit on where the longest walk has 36 key tiles
+    ([7726, 1060, 1060, 1060, 1060], 4, 2, 128, "ATTN_4_WAVES_LISTED"), ([7726, 700, 700, 700, 700], 4, 2, 128, "ATTN_WIDE"),
+    # head_dim 64: 64 queries to a wave where the tiles take the chip a tenth longer than the longest walk takes one
+    ([2300], 64, 8, 64, "ATTN_WIDE"), ([2240], 64, 8, 64, "ATTN_4_WAVES"), ([3500], 32, 8, 64, "ATTN_8_WAVES"),
+])
+def test_attention_form_of_prompts(lens, hq, hkv, d, form):
+    """Both sides of the lines between the plain forms, without scratch, on 256 compute units."""
+    assert pdd.attn_form(attn_desc(lens, lens, hq, hkv, d), pdd.CALL_PREFILL_ATTN) == getattr(pdd, form)
+
+
 def test_choose_r_L_against_exhaustive_search():
     """Host-only entry point: the closed form must agree with the oracle's search of program P."""
     import oracle

@@ -245,8 +245,9 @@ def test_tiles_listed_longest_first(lens_q, lens_k):
     dev = DeviceWorkload(wl)
     got = []
     try:
-        for waves in (4, 8):
+        for waves, form in ((4, pdd.ATTN_4_WAVES_LISTED), (8, pdd.ATTN_8_WAVES)):
             pdd.set_option(pdd.OPT_ATTN_WAVES, waves)
+            assert dev.attn_form(False, use_workspace=False) == form
             dev.poison()
             dev.attn(False, use_workspace=False)
             torch.cuda.synchronize()
@@ -255,6 +256,22 @@ def test_tiles_listed_longest_first(lens_q, lens_k):
         pdd.set_option(pdd.OPT_ATTN_WAVES, 0)
     assert torch.isfinite(got[0][0].float()).all() and torch.isfinite(got[0][1]).all()
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("lens,hq,hkv", [([4000, 900], 16, 8), ([3308, 4000, 5809, 1320, 269], 4, 2)])
+def test_tiles_listed_where_the_rule_says_so(lens, hq, hkv):
+    """Uneven prompts that the library itself lists the tiles of: rows at the ends of tiles against the oracle."""
+    wl = W.make_custom("t", lens, None, hq, hkv, 128, 0, "1/4", seed=881)
+    dev = DeviceWorkload(wl)
+    assert dev.attn_form(False, use_workspace=False) == pdd.ATTN_4_WAVES_LISTED
+    dev.poison()
+    dev.attn(False, use_workspace=False)
+    O, lse = dev.results()[:2]
+    assert np.isfinite(O).all() and np.isfinite(lse).all()
+    rows = _wide_rows(wl)
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+    assert np.abs(O[rows] - oO).max() <= O_ATOL
+    rel_close(lse[:, rows], oL, "lse")
 
 
 def _wide_rows(wl):
@@ -275,8 +292,9 @@ def test_wide_attention(name):
     dev = DeviceWorkload(wl)
     got = []
     try:
-        for waves in (0, 8):
+        for waves, form in ((0, pdd.ATTN_WIDE), (8, pdd.ATTN_8_WAVES)):
             pdd.set_option(pdd.OPT_ATTN_WAVES, waves)
+            assert dev.attn_form(False, use_workspace=False) == form
             dev.poison()
             dev.attn(False, use_workspace=False)
             torch.cuda.synchronize()
@@ -304,6 +322,7 @@ def test_wide_attention_with_the_importance_sweep(lens_q, lens_k, hq):
     dev = DeviceWorkload(wl)
     slices = hq // 8 * ((max(lens_q) + 255) // 256)
     assert dev.workspace_bytes == slices * 8 * wl.total_k * 4, "this shape is one that sweeps"
+    assert dev.attn_form() == pdd.ATTN_WIDE
     runs = []
     for _ in range(2):
         dev.poison()
@@ -334,6 +353,7 @@ def test_wide_attention_far_from_its_first_reference(logit, v_exponent, d):
     wl.k = W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.k) * 0.5 + np.float32(np.sign(logit) * c) * at[:, None, None])
     wl.v = W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.v) * np.float32(2.0 ** v_exponent))
     dev = DeviceWorkload(wl)
+    assert dev.attn_form(False, use_workspace=False) == pdd.ATTN_WIDE
     dev.poison()
     dev.attn(False, use_workspace=False)
     O, lse = dev.results()[:2]
@@ -366,6 +386,7 @@ def test_wide_attention_with_values_near_the_largest(rise, late, d):
         v[late[0]] = 2.0 ** 113
     wl.v = W.f32_to_bf16_bits(np.broadcast_to(v[:, None, None], wl.v.shape))
     dev = DeviceWorkload(wl)
+    assert dev.attn_form(False, use_workspace=False) == pdd.ATTN_WIDE
     dev.poison()
     dev.attn(False, use_workspace=False)
     O = dev.results()[0]
@@ -392,6 +413,7 @@ def test_wide_attention_without_a_score_in_the_first_block(lens_q, lens_k, d):
     k = -2.0 ** -60 * (150.0 / (wl.scale * d) + 0.1 * W.bf16_bits_to_f32(wl.k).astype(np.float64))
     wl.k = W.f32_to_bf16_bits(np.where(first[:, None, None], -2.0 ** 70, k).astype(np.float32))
     dev = DeviceWorkload(wl)
+    assert (dev.attn_form(False, use_workspace=False) == pdd.ATTN_WIDE) == (lens_k is None or d == 128)
     dev.poison()
     dev.attn(False, use_workspace=False)
     O, lse = dev.results()[:2]
@@ -408,6 +430,7 @@ def test_wide_attention_with_a_nan_key(d):
     """A key of NaN spoils the rows that see it (NaN outputs, log-sum-exp -infinity) and no others."""
     wl = W.make_custom("t", [2400, 300], None, 64, 8, d, 0, "1/4", seed=77)
     dev = DeviceWorkload(wl)
+    assert dev.attn_form(False, use_workspace=False) == pdd.ATTN_WIDE
     dev.attn(False, use_workspace=False)
     torch.cuda.synchronize()
     clean = (dev.o.float(), dev.lse.clone())
