@@ -296,10 +296,11 @@ const char *importance_limits(const pdd_attn_desc *d)
     return nullptr;
 }
 
-// What a call's attention costs in the plain form, in microseconds, from the sizes alone.  Fitted on 256 compute units to the
+// What a chunk's attention costs in the plain form, in microseconds, from the sizes alone.  Fitted on 256 compute units to the
 // times of 1400 chunks and prompts (inputs of their own in every call), half of them within 5 %, nine in ten within 20; a launch
 // lasts as long as its longest sequence's walk over the key tiles or as its tiles take the whole chip.
-// (Uneven batches are priced as if the longest query sequence met all keys.)
+// (Uneven batches are priced as if the longest query sequence met all keys; the 400 chunks that take attn_wide_kernel have 0.74 to 1.2
+// of it, half of them 0.87 to 1.15.)
 double plain_attention_us(const pdd_attn_desc *d, int bm)
 {
     const double cus = (double)compute_units(), max_q = d->max_seqlen_q;
@@ -309,6 +310,40 @@ double plain_attention_us(const pdd_attn_desc *d, int bm)
     const double us = bm == 256 ? std::fmax(tiles_max * (0.75 + 0.5 * fill), work * (0.75 + 1.05 * fill))
                                 : std::fmax((double)tiles_max, work) * (0.75 + 0.15 * fill);
     return 5.0 + (d->head_dim == 64 ? 0.68 : 0.95) * us;
+}
+
+// `of` a sequence's tokens, summed over a prompt batch whose sequences but the longest are taken for equally long, for a compute unit.
+template <typename F>
+double per_compute_unit(const pdd_attn_desc *d, F of)
+{
+    const double longest = d->max_seqlen_q, others = d->batch - 1.0, mean = others > 0 ? (d->total_q - longest) / others : 0.0;
+    return (of(longest) + (mean > 0 ? others * of(mean) : 0.0)) / compute_units();
+}
+double with_part(double a, double b, double share) { return std::fmax(a, b) + share * std::fmin(a, b); }
+
+// What a prompt batch's attention costs in the plain form that it would run in, in microseconds, from the sizes alone: the longest
+// walk in key tiles, and the key tiles that all tiles walk for a compute unit.  Fitted on 256 compute units to 6000 prompt batches of 1
+// to 8 sequences of 200 to 16384 tokens, every form on those that it is chosen for: half of them within 1 to 5 %, nine in ten within 4
+// to 20 (attn_wide_kernel up to 250 us; beyond, the clock decides and no other form is near).
+double plain_prompt_us(const pdd_attn_desc *d)
+{
+    struct Price { double base, walk, all, less; };      // [head_dim 64][4 waves, 8 waves, 4 waves listed, wide]
+    static const Price prices[2][4] = {{{6.87, 0.771, 0.955, 0.244}, {9.05, 1.31, 1.88, 0.0}, {7.55, 0.766, 1.01, 0.244}, {10.1, 0.968, 1.56, 0.273}},
+                                       {{6.02, 0.585, 0.498, 0.377}, {7.52, 0.764, 0.829, 0.334}, {}, {14.6, 1.18, 0.846, 0.223}}};
+    const int form = plain_form(d, attn_prefill_rows_per_workgroup(d), false);
+    const Price &p = prices[d->head_dim == 64][form];
+    const double bm = form == PDD_ATTN_8_WAVES || form == PDD_ATTN_WIDE ? 256.0 : 128.0, walk = (d->max_seqlen_q + pdd::kBN - 1) / pdd::kBN;
+    const double all = d->n_q_heads * per_compute_unit(d, [&](double n) {
+        const double t = std::ceil(n / bm);
+        return t * (n / pdd::kBN + 0.5) - 0.5 * t * (t - 1.0) * bm / pdd::kBN;
+    });
+    return p.base + with_part(p.walk * walk, p.all * all, p.less);
+}
+
+// Key tiles that a prompt batch's tiles of `rows` packed (token, head of the group) rows walk, for a compute unit.
+double packed_prompt_walks(const pdd_attn_desc *d, int rows)
+{
+    return d->n_q_heads * per_compute_unit(d, [&](double n) { return n / rows * (n / pdd::kBN + 1.0) / 2.0; });
 }
 
 // Whether the sizes are inside what every form but the plain one can take: the kernels divide a row by G with one 32-bit
@@ -329,9 +364,9 @@ bool packed_rows_fit(const pdd_attn_desc *d, int rows)
 // least as long as its longest sequence's walk over the key tiles, however few workgroups there
 // are.  The split form packs the (token, head) rows of a KV group into its tiles and cuts the walk into pieces of `tiles` key
 // tiles; it pays with 32-bit partial rows, written once and read back by a second kernel.
-// The choice compares estimates in microseconds, fitted to kernel times on 256 compute units: prompts of 2048
-// tokens x 1 head 31 -> 18 and of 8192 x 4/2 heads 117 -> 94; the plain form is better on prompts that fill the
-// chip (8192 tokens x 8 heads 135 against 165).  One step is one key tile of one workgroup.
+// The choice compares estimates in microseconds, fitted to times on 256 compute units of 3700 prompt batches that could be split (half
+// of them within 8 %), with plain_prompt_us: 2048 tokens x 1 head 31 -> 18 and 8192 x 4/2 heads 117 -> 94; the plain form is better on
+// prompts that fill the chip (8192 tokens x 8 heads 135 against 165).
 // Depends on the descriptor and the device only.
 SplitPlan split_plan(const pdd_attn_desc *d)
 {
@@ -361,23 +396,13 @@ SplitPlan split_plan(const pdd_attn_desc *d)
     n_split = (tiles_max + tiles - 1) / tiles;
     if ((double)n_split * base * B >= 2147483647.0) return none;
 
-    const int bm = attn_prefill_rows_per_workgroup(d);
-    const int64_t n_qt_plain = (max_q + bm - 1) / bm;
-    const double fill = (double)max_q / (double)(n_qt_plain * bm);      // rows in use of the plain form's tiles
-    const double work = (double)n_qt_plain * d->n_q_heads * tiles_all * seen / cus;
-    const bool d64 = d->head_dim == 64;        // half the bytes and matrix work, the same exponentials
-    const double plain = (d64 ? 0.75 : 1.0) *
-        (bm == 256 ? std::fmax(tiles_max * (0.75 + 0.5 * fill), work * (0.75 + 1.05 * fill))
-                   : std::fmax((double)tiles_max, work) * (0.75 + 0.15 * fill));
     const double partial = (double)n_split * per_split * seen * 1e-6 / 4.0;     // written and read back, at 4 TB/s each
-    const double split = std::fmax(tiles * 0.8, base * tiles_all * seen / cus * (d64 ? 0.95 : 1.1)) + 8.0 + partial;
-    if (split > 0.9 * plain) return none;
-    // A prompt's tiles are full and of very different lengths, two workgroups share most compute units, and there are
-    // as many partial rows as rows: fitted to 97 such launches, within 7 %.  (8/8 heads, head_dim 128, plain against
+    const double all = packed_prompt_walks(d, kSplitRows);
+    // As long as its pieces, or as the chip takes for all of them.  (8/8 heads, head_dim 128, plain against
     // split: 1500 tokens 26 and 30 us, 2441 39 and 46, 694 + 2020 33 and 43, 4000 63 and 66; 4/2 heads 2441 37 and 29.)
-    const double steps = base * tiles_all * seen / cus;
-    const double us = d64 ? 7.7 + 0.66 * tiles + 0.24 * steps + 5.2 * partial : 10.5 + 0.79 * tiles + 0.46 * steps + 2.8 * partial;
-    if (us > plain) return none;
+    const double us = d->head_dim == 64 ? std::fmax(9.1 + 0.627 * tiles + 0.228 * all + 5.95 * partial, 0.668 * all + 2.72 * partial)
+                                        : std::fmax(11.4 + 0.635 * tiles + 0.55 * all + 3.48 * partial, 14.7 + 1.11 * all + 0.988 * partial);
+    if (us > 0.97 * plain_prompt_us(d)) return none;
     return {(int)tiles, (int)n_split, (size_t)n_split * per_split, us};
 }
 
@@ -388,8 +413,8 @@ size_t importance_workspace(const pdd_attn_desc *d, int window);
 //   * Whole (RG = 1): a workgroup per tile of 32 packed rows walks all of its keys, eight blocks at a time.
 //   * Divided (RG = 1 or 4): pieces of the key tiles over about one workgroup per compute unit and a second kernel
 //     that joins them; RG = 4 reads K and V once for 128 rows.
-// The choice compares estimates in microseconds with the plain form's, fitted like those (median error 3 to 5 % for whole
-// prompts, 7 to 15 % else), and wants a tenth off the plain time.  Attention alone, plain or split as before | whole | RG = 1 | RG = 4:
+// The choice compares estimates in microseconds with the plain form's, fitted like those (half of the whole prompts within 4 %, else
+// a median error of 7 to 15 %), and wants some of the plain time off.  Attention alone, plain or split as before | whole | RG = 1 | RG = 4:
 // 512 tokens x 1/1 head of 64 9.6 | 6.3 us, 2000 x 8/8 of 128 31 | 21; 1 token behind 1126 keys, 4/2 heads of 128 17.3 | 9.7 |
 // 11.3 | 12.7, 8 x 1 behind 512 to 7900, 32/8 heads 32.1 | 85 | 26 | 28; 5 to 64 tokens x 4 behind 700 to 12345, 32/8 heads 54 | - | 77 |
 // 41.5; 7 chunks of 3 to 230 behind 200 to 12700, 16/2 heads 88 | - | 79 | 48; 256 behind 8192, 64/8 heads (243 plain) 240 | - | 190 | 172.
@@ -415,26 +440,31 @@ RowsPlan rows_plan(const pdd_attn_desc *d, bool chunked, size_t scratch)
     auto row_tiles = [&](int rg) {      // of all sequences
         return std::fmin((double)total_q * G / (32 * rg) + 0.5 * B, (double)((max_q * G + 32 * rg - 1) / (32 * rg)) * B);
     };
-    double us = 0.9 * plain_attention_us(d, chunked ? attn_rows_per_workgroup(d) : attn_prefill_rows_per_workgroup(d));
-    if (!chunked && scratch) {
-        // A prompt that the key-split form would take keeps to it beyond kWholeTiles: its walks are long enough to be worth the
-        // division that the caller gave scratch for (whole against split: 1500 to 2500 tokens 0.67 of its time, 3000 to 4000
-        // 0.72, 6000 to 9000 0.90, beyond 1.03).
-        const SplitPlan split = split_plan(d);
-        if (split.tiles && tiles_max > kWholeTiles) return best;
-        if (split.tiles) us = std::fmin(us, 0.85 * split.us);
-    }
+    const double plain = chunked ? plain_attention_us(d, attn_rows_per_workgroup(d)) : plain_prompt_us(d), share = chunked || d64 ? 0.9 : 0.95;
+    double us = share * plain;
+    if (!chunked && scratch)
+        if (const SplitPlan split = split_plan(d); split.tiles) {
+            // A prompt that the key-split form takes a tenth off keeps to it beyond kWholeTiles, where the whole form waits for keys that no
+            // cache holds (1/1 head of 128, whole and split with keys from memory: 6350 tokens 47.6 and 37.2 us, 3350 + 300 30.0 and 25.9).
+            if (tiles_max > kWholeTiles && split.us < 0.9 * plain) return best;
+            us = std::fmin(us, share * split.us);
+        }
     {
-        // rounds of the longest walk against what all of them take the chip; a prompt's long row tiles meet long keys
-        const double rt = row_tiles(1), walk = std::ceil(tiles_max / 4.0) * (chunked ? (d64 ? 0.73 : 1.33) : (d64 ? 0.615 : 0.97));
-        const double tiles = rt * Hkv * seen * (chunked ? 0.4 * tiles_mean + 0.6 * tiles_max : tiles_max) / cus;
-        // (chunks of head_dim 128: whole rounds, because a workgroup has its compute unit to itself, and the unit waits for workgroups without
-        // a row tile too, 1.5 us each for the first few: 24 to 257 new tokens x 7, 32/8 heads, 20.7 us, plain 14.7; 143 + 8 + 3 x 64/8 12.1 and 8.7)
+        // rounds of the longest walk, what all walks take the chip, and a start for each workgroup behind the first of a compute unit
+        const double rounds = std::ceil(tiles_max / 4.0);
         const int64_t blocks = (max_q * G + 31) / 32 * B * Hkv;
-        const double per_cu = rt * Hkv / cus, over = std::fmax((chunked && !d64 && per_cu < 3.0 ? std::ceil(per_cu - 0.03) : per_cu) - 1.0, 0.0);
-        const double empty = chunked && !d64 ? std::fmin(1.5 * std::fmax((double)blocks / cus - per_cu - 0.5, 0.0), 3.0) : 0.0;
-        const double all = chunked ? (d64 ? 0.18 * tiles + 3.0 * over : 0.30 * tiles + 4.1 * over) : (d64 ? 0.142 * tiles + 2.14 * over : 0.26 * tiles + 5.55 * over);
-        const double est = (chunked ? (d64 ? 4.6 : 5.0) : (d64 ? 5.1 : 6.75)) + std::fmax(walk, all) + 0.3 * std::fmin(walk, all);
+        double est, empty = 0.0;
+        if (chunked) {
+            const double rt = row_tiles(1), tiles = rt * Hkv * seen * (0.4 * tiles_mean + 0.6 * tiles_max) / cus, per_cu = rt * Hkv / cus;
+            // (head_dim 128: whole rounds, because a workgroup has its compute unit to itself, and the unit waits for workgroups without
+            // a row tile too, 1.5 us each for the first few: 24 to 257 new tokens x 7, 32/8 heads, 20.7 us, plain 14.7; 143 + 8 + 3 x 64/8 12.1 and 8.7)
+            const double over = std::fmax((!d64 && per_cu < 3.0 ? std::ceil(per_cu - 0.03) : per_cu) - 1.0, 0.0);
+            if (!d64) empty = std::fmin(1.5 * std::fmax((double)blocks / cus - per_cu - 0.5, 0.0), 3.0);
+            est = d64 ? 4.6 + with_part(0.73 * rounds, 0.18 * tiles + 3.0 * over, 0.3) : 5.0 + with_part(1.33 * rounds, 0.30 * tiles + 4.1 * over, 0.3);
+        } else {
+            const double all = packed_prompt_walks(d, 32), over = std::fmax(((double)total_q * G / 32 + 0.5 * B) * Hkv / cus - 1.0, 0.0);
+            est = d64 ? 6.09 + with_part(0.518 * rounds, 0.142 * all + 1.97 * over, 0.738) : 7.67 + with_part(0.674 * rounds, 0.205 * all + 5.77 * over, 1.2);
+        }
         if (est + empty < us && est < 100.0 && blocks <= 0x7fffffffLL) {
             us = est + empty;
             best = {1, 0, 0, 0, 0};

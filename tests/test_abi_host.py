@@ -157,6 +157,22 @@ def test_attention_form_of_prompts(lens, hq, hkv, d, form):
     assert pdd.attn_form(attn_desc(lens, lens, hq, hkv, d), pdd.CALL_PREFILL_ATTN) == getattr(pdd, form)
 
 
+@pytest.mark.parametrize("lens,hq,hkv,d,form", [
+    # times in us of the plain form that would run | key-split | whole
+    ([1326, 8163], 4, 2, 128, "ATTN_SPLIT"), ([7343, 3000], 4, 2, 128, "ATTN_SPLIT"),          # listed 115 | 100, 108 | 98
+    ([2626, 475], 8, 8, 128, "ATTN_ROWS"), ([313, 5355], 8, 8, 128, "ATTN_4_WAVES_LISTED"),     # listed 42.5 | 44.5 | 37.5, 77 | 87
+    ([11930], 4, 2, 64, "ATTN_SPLIT"), ([4000], 8, 8, 128, "ATTN_4_WAVES"),                    # 4 waves 139 | 122, 63 | 66
+    ([2441], 8, 8, 128, "ATTN_ROWS"), ([6350], 1, 1, 128, "ATTN_SPLIT"), # 39 | 46 | 33, from memory 92 | 37 | 48
+    ([4096], 32, 8, 128, "ATTN_WIDE"),
+])
+def test_prompts_are_priced_in_the_form_that_would_run(lens, hq, hkv, d, form):
+    """The plain form's price is that of the plain form that the call would take (only the tiles that exist, where those
+    are listed; 64 queries to a wave), with the scratch that the library asks for and on 256 compute units."""
+    desc = attn_desc(lens, lens, hq, hkv, d)
+    scratch = pdd.workspace_bytes(desc, pdd.CALL_PREFILL_ATTN)
+    assert pdd.attn_form(desc, pdd.CALL_PREFILL_ATTN, False, scratch) == getattr(pdd, form)
+
+
 def test_choose_r_L_against_exhaustive_search():
     """Host-only entry point: the closed form must agree with the oracle's search of program P."""
     import oracle

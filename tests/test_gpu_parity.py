@@ -194,6 +194,23 @@ def test_keys_split_over_workgroups(name, d):
     assert all(torch.equal(a, b) for a, b in zip(bits, (dev.o, dev.lse, dev.imp)))
 
 
+@pytest.mark.parametrize("lens,d", [([4000, 130], 128), ([16000, 100], 64)])
+def test_prompts_with_their_keys_split(lens, d):
+    """Prompts of the key-split form, whose pieces end at the diagonal: rows at the ends of tiles against the oracle."""
+    wl = W.make_custom("t", lens, None, 1, 1, d, 0, "1/4", seed=705 + d)
+    dev = DeviceWorkload(wl)
+    assert dev.attn_form(False) == pdd.ATTN_SPLIT
+    dev.poison()
+    dev.workspace.fill_(0xFF)
+    dev.attn(False)
+    O, lse = dev.results()[:2]
+    assert np.isfinite(O).all() and np.isfinite(lse).all()
+    rows = _wide_rows(wl)
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+    assert np.abs(O[rows] - oO).max() <= O_ATOL
+    rel_close(lse[:, rows], oL, "lse")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_keys_split_over_workgroups_with_a_nan_key(d):
     """A key of NaN, which no caller should pass, spoils the same rows in the same way whichever form runs: every
