@@ -356,6 +356,57 @@ def test_wide_attention_with_the_importance_sweep(lens_q, lens_k, hq):
     assert np.isfinite(O).all() and np.isfinite(lse).all() and np.isfinite(imp).all()
 
 
+def test_wide_attention_far_from_its_first_reference_with_the_importance_sweep():
+    """The second walk, with a reference that follows the maxima, before the sweep; waves and groups without rows among them.
+    One sequence of three rises by 150 behind its first 32 keys."""
+    wl = W.make_custom("t", [256, 200, 97], [4700, 3001, 5000], 64, 8, 128, 0, "1/4", seed=861, chunked=True)
+    c = np.float32(np.sqrt(150.0 / wl.scale / 128))
+    at_q, at_k = np.zeros((wl.total_q, 1, 1), np.float32), np.zeros((wl.total_k, 1, 1), np.float32)
+    at_q[wl.cu_seqlens_q[1]:wl.cu_seqlens_q[2]] = 1
+    at_k[wl.cu_seqlens_k[1] + 32:wl.cu_seqlens_k[2]] = 1
+    wl.q = W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.q) * 0.5 + c * at_q)
+    wl.k = W.f32_to_bf16_bits(W.bf16_bits_to_f32(wl.k) * 0.5 + c * at_k)
+    dev = DeviceWorkload(wl)
+    assert dev.attn_form() == pdd.ATTN_WIDE
+    dev.poison()
+    dev.workspace.fill_(0xFF)
+    dev.attn(True)
+    O, lse, imp = dev.results()[:3]
+    assert np.isfinite(O).all() and np.isfinite(lse).all() and np.isfinite(imp).all()
+    rel_close(imp, oracle.importance(wl.q, wl.k, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, -1), "importance")
+    rows = _wide_rows(wl)
+    oO, oL = oracle.attention(wl.q, wl.k, wl.v, wl.cu_seqlens_q, wl.cu_seqlens_k, wl.scale, rows=rows)
+    assert np.abs(O[rows] - oO).max() <= O_ATOL
+    rel_close(lse[:, rows], oL, "lse")
+
+
+@pytest.mark.parametrize("layout", ["packed", "head-major"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_wide_attention_in_other_layouts(d, layout):
+    """Views of one QKV buffer and head-major tensors give the bits of the contiguous ones (which the oracle has checked);
+    what lies beside the outputs stays."""
+    hq, hkv = (64, 8) if d == 64 else (32, 8)
+    wl = W.make_custom("t", [2497, 300], None, hq, hkv, d, 0, "1/4", seed=76)
+    dev = DeviceWorkload(wl)
+    assert dev.attn_form(False) == pdd.ATTN_WIDE
+    dev.poison()
+    dev.attn(False)
+    torch.cuda.synchronize()
+    want = [x.clone() for x in (dev.o, dev.lse)]
+    beside = torch.zeros((wl.total_q, 2 * hq, d), dtype=torch.bfloat16, device="cuda")
+    if layout == "packed":
+        qkv = torch.cat((dev.q, dev.k, dev.v), 1)
+        dev.q, dev.k, dev.v, dev.o = qkv[:, :hq], qkv[:, hq:hq + hkv], qkv[:, hq + hkv:], beside[:, hq:]
+    else:
+        dev.q, dev.k, dev.v, dev.o = (x.transpose(0, 1).contiguous().transpose(0, 1) for x in (dev.q, dev.k, dev.v, dev.o))
+    assert not dev.q.is_contiguous() and not dev.o.is_contiguous() and dev.attn_form(False) == pdd.ATTN_WIDE
+    dev.o.fill_(float("nan"))
+    dev.lse.fill_(float("nan"))
+    dev.attn(False)
+    torch.cuda.synchronize()
+    assert torch.equal(dev.o, want[0]) and torch.equal(dev.lse, want[1]) and not beside[:, :hq].any()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("logit,v_exponent", [(150.0, 0), (-150.0, 0), (55.0, 0), (55.0, 100)])
 def test_wide_attention_far_from_its_first_reference(logit, v_exponent, d):
@@ -1521,10 +1572,13 @@ def test_head_dim_64_longer_prompts_sampled_rows(waves):
     assert swapped == 0
 
 
-# 4 waves, two workgroups to a compute unit, and 8 waves on 256 units (576 and 448 tiles of 256 rows); 4 waves, three to a unit
-@pytest.mark.parametrize("lens", [[700, 1, 513], [1700], [1700, 1, 1690]])
-def test_head_dim_64_workgroup_choice_gives_the_same_bits(lens):
+# On 256 compute units: 4 waves, two workgroups to a unit, and 8 waves (576 and 448 tiles of 256 rows); 64 queries to a wave; 4 waves,
+# three to a unit (all tiles take the chip as long as the longest walk takes one)
+@pytest.mark.parametrize("lens,form", [([700, 1, 513], pdd.ATTN_4_WAVES), ([1700], pdd.ATTN_8_WAVES), ([1700, 1, 1690], pdd.ATTN_WIDE),
+                                       ([2100], pdd.ATTN_4_WAVES)])
+def test_head_dim_64_workgroup_choice_gives_the_same_bits(lens, form):
     wl = W.make_custom("t", lens, None, 64, 8, 64, 32, "1/4", seed=21)
+    assert DeviceWorkload(wl).attn_form() == form
     runs = []
     for waves in (0, 4, 8):
         dev = DeviceWorkload(wl)
