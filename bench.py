@@ -30,7 +30,7 @@ OTHERS = ("c1", "c2", "c3", "c5")
 # scaled by the same counter's reading for a 1 GiB device copy; see profiles/).  Valid only for the
 # kernel sources with this digest: once they change the figure is reported as null.
 KERNEL_SOURCES = ("attn_fwd.hpp", "attn_wide.hpp")
-TRAFFIC = {"c4": {"bytes": 1.688e9, "sources_sha256": "75770336deb8ba22c5616e0ffeb4213fc705ba5772000498a2d2e7cae190c296"}}
+TRAFFIC = {"c4": {"bytes": 1.688e9, "sources_sha256": "afa03a21771c1c55c95d8d70c4d43d1a2e3ad540c9291b9d44990b12f0edd02d"}}
 
 O_ATOL, REL = 2e-2, 1e-3       # the parity bar: O max-abs, log-sum-exp / importance relative
 
@@ -260,8 +260,7 @@ def run_config(name, args, budget_gflop, with_cpu_baseline):
                     "select+compaction": round(ms_select, 4)},
         "select_GBps": round(sel_bytes / (ms_select * 1e-3) / 1e9, 2),
         "roofline": {"bound": "mfma",
-                     # (the short prompt takes the form whose waves share a row tile's keys)
-                     "kernel": "attn_fwd_kernel" if args.waves != 0 else "attn_rows_kernel" if wl.name == "c1" else "attn_wide_kernel",
+                     "kernel": {pdd.ATTN_WIDE: "attn_wide_kernel", pdd.ATTN_ROWS: "attn_rows_kernel"}.get(dev.attn_form(False), "attn_fwd_kernel"),
                      "achieved": round(tflops_attn, 2), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(tflops_attn / PEAK_BF16_TFLOPS, 4),
                      "traffic": traffic,

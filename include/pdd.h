@@ -120,7 +120,10 @@ enum {
  *            deterministic; they differ from each
  *            other in the order of the fp32 additions, and in O
  *            also in where the probabilities round to bf16 (2e-3 of O, as far
- *            as any is from the exact result).  The contents are
+ *            as any is from the exact result).  Launches that fill the GPU
+ *            refer a row's exponentials to its first 32 keys; a tile of 256
+ *            queries in which a row's logits rise 69 and more above those is
+ *            walked twice (time, not exactness).  The contents are
  *            scratch before and after the call; concurrent calls need separate
  *            workspaces.
  * Requires Nq_b == Nk_b for every sequence when host copies are given (use the
@@ -160,7 +163,8 @@ pdd_status pdd_prefill_attn(const pdd_attn_desc *desc, const void *q, const void
  * what full tiles cost) and calls that are given less use the separate
  * importance kernel described above; pdd_workspace_bytes says what the shape
  * will use.  All forms are deterministic and agree to fp32 rounding (O of the
- * forms for few rows to bf16 rounding).
+ * forms for few rows, and of the one for launches that fill the GPU where logits
+ * rise 5 and more above a row's first 32, to bf16 rounding).
  */
 pdd_status pdd_prefill_attn_chunked(const pdd_attn_desc *desc, const void *q_chunk,
                                     const void *k_all, const void *v_all, void *o, float *lse,
@@ -410,7 +414,9 @@ int pdd_attn_form(const pdd_attn_desc *desc, int which_call, int importance, siz
 /*
  * Tuning knobs (process-wide, not thread-safe against concurrent launches).
  *   PDD_OPT_ATTN_WAVES: wavefronts per attention workgroup, 4 (128 queries) or
- *   8 (256 queries); 0 = chosen per problem (default).
+ *   8 (256 queries); 0 = chosen per problem (default).  Another value than 0 also
+ *   turns off every other attention form (64 queries to a wave, keys divided or
+ *   shared out).
  *   PDD_OPT_IMPORTANCE_KEYS: keys per workgroup of the importance kernel, 128
  *   or 256: the two give the same bits; 0 = chosen per problem (default), which
  *   for windows of few rows is a kernel with all of them in LDS, whose sums are

@@ -240,6 +240,8 @@ __device__ __forceinline__ bf16x8 lds_read_tr8(uint32_t lo, uint32_t hi)
 // Waves per SIMD that the registers are held to: two, and three where three 4-wave workgroups share a compute unit (head_dim 64,
 // 141 registers).  Exponentials and other vector work are the larger part of a block there, and with two waves the SIMD waits
 // on both for a fifth of the time (16384 tokens x 32/8 heads 2.23 -> 1.80 M cycles, at a clock that falls from 1.83 to 1.57 GHz).
+// (Prompts that long take 64 queries to a wave by now; three share a unit where all tiles take the chip at most a tenth longer
+// than the longest walk takes one, and where 4 waves are asked for.)
 // The key-split form's workgroups are few to a compute unit and keep to two (6000 tokens x 4/2 heads 57.5 us, 64.7 with three;
 // 16000 x 1 79, 72).
 constexpr int attn_waves_per_simd(int D, int NWAVES, bool IMP, bool SPLIT) { return D == 64 && NWAVES == 4 && !IMP && !SPLIT ? 3 : 2; }

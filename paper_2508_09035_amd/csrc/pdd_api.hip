@@ -192,8 +192,8 @@ int attn_rows_per_workgroup(const pdd_attn_desc *d)
 
 // Query tiles that exist in a batch, at most, and whether the grid of 4-wave workgroups lists them (tile_of), longest walks first,
 // instead of holding the longest sequence's tiles for each sequence: where a fifth of those at least would be empty.  (The place of the empty
-// ones settles which shader engines the others go to: 653 + 6936 tokens x 8/8 heads 188 us, listed 116.  Launches of many larger
-// workgroups even out by themselves and lose half a per cent by the search.)
+// ones settles which shader engines the others go to: 653 + 6936 tokens x 8/8 heads 4 waves 188 us, 8 waves 124, 4 waves listed 116.
+// Launches of many larger workgroups even out by themselves and lose half a per cent by the search.)
 int64_t existing_tiles(const pdd_attn_desc *d, int bm) { return (d->total_q + (int64_t)d->batch * (bm - 1)) / bm; }
 bool lists_tiles(const pdd_attn_desc *d)
 {
@@ -206,7 +206,7 @@ bool lists_tiles(const pdd_attn_desc *d)
 // 380 + 2136 x 16/2 heads 49.9 | 41 us, 240 3308 + 4000 + 5809 + 1320 + 269 x 4/2 114 | 95, 333 7879 + 7 x 263 to 4548 x 4/2 157 | 127, 396
 // 4924 + 1160 x 16/2 117 | 131, 479 4895 + 4 x 292 to 4048 x 8/8 122 | 146).  Below 0.69 of a tile to a compute unit one long walk decides, in
 // which attn_wide_kernel is the faster (200 7726 + 4 x 464 to 2132 x 4/2 111 | 115).
-// Of head_dim 64: 4 waves at every size: against 8 waves, two to a compute
+// Of head_dim 64: 4 waves at every size (the largest go on to 64 queries to a wave, takes_wide): against 8 waves, two to a compute
 // unit, 16384 tokens x 32/8 heads 1188 -> 1143 us, 8192 x 64/8 630 -> 597, 3000 + 1111 + 6100 x 32/8 253 -> 236, 8000 + 3 x 300 x 8/8
 // 244 -> 205; only where the 8-wave workgroups just fill the chip once do they stay (3500 x 32/8, 448 of 512 places: 75.4
 // against 77.0).  The chunked call keeps the rule above, by which its importance sweep and its scratch are sized.
@@ -224,7 +224,7 @@ int attn_prefill_rows_per_workgroup(const pdd_attn_desc *d)
 
 // Whether all query tiles of a call take the chip longer than the longest walk over the keys takes one of them; the sequences but
 // the longest are taken for equally long.  Then three 4-wave workgroups of head_dim 64 share a compute unit (266 launches 1.04 to
-// 1.19 times as fast as 8 waves).  Else no more than two: a long walk is the slower for two neighbours (1456 + 704 + 663 + 615 + 632 + 770 +
+// 1.19 times as fast as 8 waves; from a tenth longer on 64 queries to a wave).  Else no more than two: a long walk is the slower for two neighbours (1456 + 704 + 663 + 615 + 632 + 770 +
 // 3482 + 5753 x 4/2 heads 87 us by threes, 71 by twos and 82 with 8 waves; 574 + 1335 + 7269 + 253 + 801 x 16/2 152, 139 and 139; 440 such prompts 1.04 times
 // as fast by twos as by threes, 0.93 to 1.43, break even where both times are alike).
 double fill_of_the_chip(const pdd_attn_desc *d)
@@ -236,14 +236,15 @@ bool tiles_fill_the_chip(const pdd_attn_desc *d) { return fill_of_the_chip(d) >=
 
 // Launches that take attn_wide_kernel, 64 queries to a wave (bm: queries per workgroup of the other forms).
 //   * head_dim 128: where the 8-wave workgroups were chosen and the longest walk (behind longer prefixes: the mean one) has 36
-//     tiles or more.  A workgroup spends more cycles outside its loop than one of attn_fwd_kernel and 10 % fewer in it
-//     (8 waves | wide: 1611 tokens x 64/8 heads 55.1 | 56.2 us, 2324 x 64/8 101.4 | 99.4, 2429 x 32/8 65.4 | 63.0, 5807 x 32/8 258 | 241,
-//     12487 x 32/8 1063 | 979; 92 + 73 + 427 + 377 behind 2919 + 539 + 628 + 678, 32/8 heads 45.5 | 47.8, 403 x 4 behind 2598 76.3 | 75.0,
-//     881 behind 15130, 64/8 389 | 360; with the importance sweep 4 x 256 behind 8192, 64/8 377 | 357, 8 x 800 behind 10510, 32/8 1816 | 1626).
+//     tiles or more.  A workgroup spends more cycles outside its loop than one of attn_fwd_kernel and 8 % fewer in it
+//     (8 waves | wide: 2414 tokens x 64/8 heads 102.8 | 103.0 us, 2413 x 32/8 60.9 | 60.0, 2959 x 32/8 79.4 | 76.0, 2346 + 1560 x 32/8 72.4 | 73.9,
+//     30 such prompts of 2300 to 3300 tokens 1.01 in the mean, 0.98 to 1.05; 403 x 4 behind 2598, 32/8 heads 77.7 | 76.5, 512 x 3 behind 3500
+//     94.7 | 91.7, 64/8 187.9 | 179.0; below, with 2 % less in the loop than now: 1611 tokens x 64/8 55.1 | 56.2).
 //   * Prompts of head_dim 64 that took 4 waves: where the tiles take the chip a tenth longer than the longest walk takes one, by the measure of
 //     tiles_fill_the_chip.  Two of these workgroups share a compute unit where three of 128 queries do otherwise (4 waves | wide, that
-//     measure in front: 0.90 1848 x 64/8 43.2 | 44.5, 0.99 8104 x 16/2 153 | 160, 1.20 2457 x 64/8 69.5 | 65.0, 1.54 4 of 3158 x 16/2
-//     100 | 90.4, 3.4 13885 x 32/8 786 | 698).
+//     measure in front: 0.90 1848 x 64/8 43.2 | 44.5, 0.99 8104 x 16/2 153 | 160, 1.19 2438 x 64/8 67.8 | 66.4, 1.41 2878 x 64/8 85.3 | 79.5,
+//     1.61 6597 x 32/8 197.8 | 183.1.  One long sequence among short ones loses up to there: 1.11 3490 + 616 + 1965 + 734 x 32/8 89 | 101,
+//     1.38 5603 + 599 x 32/8 144 | 152; 34 drawn batches from 1.1 to 1.7 1.01 in the mean, 0.88 to 1.08).
 bool takes_wide(const pdd_attn_desc *d, int bm)
 {
     if (g_attn_waves != 0) return false;
